@@ -55,7 +55,7 @@ namespace {
 
 constexpr int kMaxRank = 64;
 constexpr int kMaxHeads = 64;
-constexpr int kMaxGenericD = 16000;   // the plain path keeps one fp32 row of length d in LDS
+constexpr int kMaxGenericD = 16000;   // the plain path's draft-type calls keep one fp32 row of length d in LDS
 
 int check_desc(const cp_head_desc *ds)
 {

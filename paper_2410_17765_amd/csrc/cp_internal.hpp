@@ -48,6 +48,30 @@ __device__ __forceinline__ float wave_max(float v)
     return v;
 }
 
+// Cross-lane steps of the row statistics, as data-parallel-primitive moves (no LDS traffic):
+// quad swaps, mirror inside 8 and inside 16 lanes give every lane of a 16-lane row the row's value.
+template <int CTRL, int ROW_MASK = 0xF>
+__device__ __forceinline__ float dpp_move(float old, float v)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(v), CTRL, ROW_MASK, 0xF, false));
+}
+__device__ __forceinline__ float row16_max(float v)
+{
+    v = fmaxf(v, dpp_move<0xB1>(v, v));    // lane ^ 1
+    v = fmaxf(v, dpp_move<0x4E>(v, v));    // lane ^ 2
+    v = fmaxf(v, dpp_move<0x141>(v, v));   // mirror within 8
+    v = fmaxf(v, dpp_move<0x140>(v, v));   // mirror within 16
+    return v;
+}
+__device__ __forceinline__ float row16_sum(float v)
+{
+    v += dpp_move<0xB1>(v, v);
+    v += dpp_move<0x4E>(v, v);
+    v += dpp_move<0x141>(v, v);
+    v += dpp_move<0x140>(v, v);
+    return v;
+}
+
 // ---------------------------------------------------------------- host-side layout
 inline size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
 
@@ -106,18 +130,20 @@ int generic_draft(const cp_head_desc &ds, const void *H, const void *W, const vo
 
 // Pieces of the plain path that the fine-tuning loss builds on.  generic_fwd_rows runs the per-row part of the
 // training loss's forward pass (gate, y, lse, C) into ctx / ws laid out as for generic_loss_fwd;
-// generic_logits_rows writes the fp32 logits of the rows [m0, m0 + Mc) to z[Mc, V]; generic_bwd_from_dz runs the
-// training loss's backward pass below the logit gradients, which `fn` produces one chunk of
-// generic_bwd_chunk_rows() rows (a multiple of r) at a time.  ws is laid out as for generic_loss_bwd.
+// generic_logits_rows writes the fp32 logits of the rows [m0, m0 + Mc) to z[Mc, ldz], zero from column V on;
+// generic_bwd_from_dz runs the training loss's backward pass below the logit gradients, which `fn` produces (rows of
+// generic_dz_row() floats, zero from column V on) one chunk of generic_bwd_chunk_rows() rows (a multiple of r) at a
+// time.  ws is laid out as for generic_loss_bwd.
 struct GenericFwdBuffers {
     float *lse, *w, *gamma, *Y, *logw, *C;
 };
 int generic_fwd_rows(const cp_head_desc &ds, const void *H, const void *W, const void *U, const void *G,
                      const int32_t *X, void *ctx, void *ws, GenericFwdBuffers *out, hipStream_t st);
-void generic_logits_rows(const cp_head_desc &ds, const void *U, const float *Y, size_t m0, size_t Mc, float *z,
+void generic_logits_rows(const cp_head_desc &ds, const void *U, const float *Y, size_t m0, size_t Mc, float *z, long ldz,
                          hipStream_t st);
 size_t generic_bwd_chunk_rows(const cp_head_desc &ds);
-typedef void (*GenericDzLaunch)(void *user, size_t m0, size_t Mc, float *dZ, hipStream_t st);
+long generic_dz_row(const cp_head_desc &ds);
+typedef void (*GenericDzLaunch)(void *user, size_t m0, size_t Mc, float *dZ, long ldz, hipStream_t st);
 int generic_bwd_from_dz(const cp_head_desc &ds, const void *H, const void *W, const void *U, const void *G,
                         const float *Y, const float *dg, float *dH, float *dW, float *dU, float *dG, void *ws,
                         GenericDzLaunch fn, void *user, hipStream_t st);

@@ -722,11 +722,11 @@ int mfma_distill_bwd(const cp_head_desc &ds, const void *H, const void *W, const
 // ------------------------------------------------------------------------------------------
 constexpr int kMaxRank = 64;
 
-// One block per token g = g0 + blockIdx.x of the chunk whose logits are zc[(gi r + a), V]:
+// One block per token g = g0 + blockIdx.x of the chunk whose logits are zc[(gi r + a), ldz]:
 // SK[g r + a] = {S_a, KL} with S_a = sum_v p^c[v] rho_a[v], KL = sum_v p^c[v] (log p^c[v] - log p^d[v]).
 // Lane a of every wavefront accumulates S_a (r <= 64).
 template <typename TT>
-__global__ void __launch_bounds__(kBlock) k_distill_kl_plain(int V, int r, size_t g0, const float *__restrict__ zc,
+__global__ void __launch_bounds__(kBlock) k_distill_kl_plain(int V, long ldz, int r, size_t g0, const float *__restrict__ zc,
                                                              const float2 *__restrict__ rowa, const TT *__restrict__ TZ,
                                                              const float *__restrict__ tlse, float2 *__restrict__ SK)
 {
@@ -740,7 +740,7 @@ __global__ void __launch_bounds__(kBlock) k_distill_kl_plain(int V, int r, size_
     }
     __syncthreads();
     const float tl = tlse[g];
-    const float *zrow = zc + gi * r * (size_t)V;
+    const float *zrow = zc + gi * r * (size_t)ldz;
     const TT *trow = TZ + g * (size_t)V;
     float Sacc = 0.f, kl = 0.f;
     // every lane of a wavefront runs the same number of rounds, so that the sums over lanes see all of them
@@ -749,15 +749,15 @@ __global__ void __launch_bounds__(kBlock) k_distill_kl_plain(int V, int r, size_
         const bool cv = v < V;
         const int vc = cv ? v : V - 1;
         float mx = -INFINITY;
-        for (int a = 0; a < r; ++a) mx = fmaxf(mx, zrow[(size_t)a * V + vc] - lse_s[a] + lq_s[a]);
+        for (int a = 0; a < r; ++a) mx = fmaxf(mx, zrow[(size_t)a * ldz + vc] - lse_s[a] + lq_s[a]);
         float sum = 0.f;
-        for (int a = 0; a < r; ++a) sum += expf(zrow[(size_t)a * V + vc] - lse_s[a] + lq_s[a] - mx);
+        for (int a = 0; a < r; ++a) sum += expf(zrow[(size_t)a * ldz + vc] - lse_s[a] + lq_s[a] - mx);
         const float lm = mx + logf(sum);
         const float lpc = ld_f32(trow, (size_t)vc) - tl;
         const float pc = cv ? expf(lpc) : 0.f;
         kl += pc * (lpc - lm);
         for (int a = 0; a < r; ++a) {
-            const float s = wave_sum(pc * expf(zrow[(size_t)a * V + vc] - lse_s[a] + lq_s[a] - lm));
+            const float s = wave_sum(pc * expf(zrow[(size_t)a * ldz + vc] - lse_s[a] + lq_s[a] - lm));
             if (lane == a) Sacc += s;
         }
     }
@@ -775,7 +775,7 @@ __global__ void __launch_bounds__(kBlock) k_distill_kl_plain(int V, int r, size_
 // One block per token of the chunk: the chunk's logits in dZ become, in place,
 // dz = c1 P - c3 p^c rho + c2 1[v = x] (every entry is read and written by the same thread).
 template <typename TT>
-__global__ void __launch_bounds__(kBlock) k_distill_dz_plain(int V, int r, size_t g0, float *__restrict__ dZ,
+__global__ void __launch_bounds__(kBlock) k_distill_dz_plain(int V, long ldz, int r, size_t g0, float *__restrict__ dZ,
                                                              const float4 *__restrict__ rowinfo,
                                                              const float4 *__restrict__ grp, const TT *__restrict__ TZ)
 {
@@ -786,24 +786,24 @@ __global__ void __launch_bounds__(kBlock) k_distill_dz_plain(int V, int r, size_
     const float4 gv = grp[g];
     const float tl = gv.x, c3 = gv.y;
     const int x = __float_as_int(gv.z);
-    float *zrow = dZ + gi * r * (size_t)V;
+    float *zrow = dZ + gi * r * (size_t)ldz;
     const TT *trow = TZ + g * (size_t)V;
     for (int v = threadIdx.x; v < V; v += kBlock) {
         float mx = -INFINITY;
-        for (int a = 0; a < r; ++a) mx = fmaxf(mx, zrow[(size_t)a * V + v] - ri_s[a].x + ri_s[a].y);
+        for (int a = 0; a < r; ++a) mx = fmaxf(mx, zrow[(size_t)a * ldz + v] - ri_s[a].x + ri_s[a].y);
         float sum = 0.f;
-        for (int a = 0; a < r; ++a) sum += expf(zrow[(size_t)a * V + v] - ri_s[a].x + ri_s[a].y - mx);
+        for (int a = 0; a < r; ++a) sum += expf(zrow[(size_t)a * ldz + v] - ri_s[a].x + ri_s[a].y - mx);
         const float lm = mx + logf(sum);
         const float lpc = ld_f32(trow, (size_t)v) - tl;
         for (int a = 0; a < r; ++a) {
             const float4 ri = ri_s[a];
-            const float lP = zrow[(size_t)a * V + v] - ri.x;
-            zrow[(size_t)a * V + v] = ri.z * expf(lP) - c3 * expf(lpc + lP + ri.y - lm) + (v == x ? ri.w : 0.f);
+            const float lP = zrow[(size_t)a * ldz + v] - ri.x;
+            zrow[(size_t)a * ldz + v] = ri.z * expf(lP) - c3 * expf(lpc + lP + ri.y - lm) + (v == x ? ri.w : 0.f);
         }
     }
 }
 
-// forward workspace: the plain training loss's, then {rhox [M], ce [T n], SK [M] float2, zc [chunk, V]}
+// forward workspace: the plain training loss's, then {rhox [M], ce [T n], SK [M] float2, zc [chunk, ldz]}
 struct PlainFwdWs {
     size_t rhox, ce, SK, zc, total;
 };
@@ -816,7 +816,7 @@ PlainFwdWs plain_fwd_ws(const cp_head_desc &ds)
     f.rhox = take(M * 4);
     f.ce = take(Tn * 4);
     f.SK = take(M * 8);
-    f.zc = take(generic_bwd_chunk_rows(ds) * ds.V * 4);
+    f.zc = take(generic_bwd_chunk_rows(ds) * generic_dz_row(ds) * 4);
     f.total = off;
     return f;
 }
@@ -853,10 +853,11 @@ int plain_distill_fwd(const cp_head_desc &ds, const void *H, const void *W, cons
     k_distill_weights<kMaxRank><<<blocks_for(T, kBlock), kBlock, 0, st>>>(T, ds.n, ds.r, fb.logw, fb.C, fb.lse, X, rowa,
                                                                           rhox, ce);
     const size_t chunk = generic_bwd_chunk_rows(ds);
+    const long ldz = generic_dz_row(ds);
     for (size_t m0 = 0; m0 < M; m0 += chunk) {
         const size_t Mc = (M - m0 < chunk) ? M - m0 : chunk;
-        generic_logits_rows(ds, U, fb.Y, m0, Mc, zc, st);
-        k_distill_kl_plain<TT><<<(unsigned)(Mc / ds.r), kBlock, 0, st>>>(ds.V, ds.r, m0 / ds.r, zc, rowa, TZ, tlse, SK);
+        generic_logits_rows(ds, U, fb.Y, m0, Mc, zc, ldz, st);
+        k_distill_kl_plain<TT><<<(unsigned)(Mc / ds.r), kBlock, 0, st>>>(ds.V, ldz, ds.r, m0 / ds.r, zc, rowa, TZ, tlse, SK);
     }
     k_distill_finish<kMaxRank><<<blocks_for(T, kBlock), kBlock, 0, st>>>(T, ds.n, ds.r, beta, disc, X, rowa, rhox, ce, SK,
                                                                          loss, c1, c2, c3, dgsum);
@@ -872,12 +873,12 @@ struct PlainDzArgs {
     const float4 *rowinfo, *grp;
 };
 template <typename TT>
-void plain_dz_launch(void *user, size_t m0, size_t Mc, float *dZ, hipStream_t st)
+void plain_dz_launch(void *user, size_t m0, size_t Mc, float *dZ, long ldz, hipStream_t st)
 {
     const PlainDzArgs<TT> *a = static_cast<const PlainDzArgs<TT> *>(user);
     const cp_head_desc &ds = *a->ds;
-    generic_logits_rows(ds, a->U, a->Y, m0, Mc, dZ, st);
-    k_distill_dz_plain<TT><<<(unsigned)(Mc / ds.r), kBlock, 0, st>>>(ds.V, ds.r, m0 / ds.r, dZ, a->rowinfo, a->grp, a->TZ);
+    generic_logits_rows(ds, a->U, a->Y, m0, Mc, dZ, ldz, st);
+    k_distill_dz_plain<TT><<<(unsigned)(Mc / ds.r), kBlock, 0, st>>>(ds.V, ldz, ds.r, m0 / ds.r, dZ, a->rowinfo, a->grp, a->TZ);
 }
 
 template <typename TT>

@@ -1,12 +1,13 @@
-// Plain fp32 path of the CP head: correct for every shape and storage type, no
-// tiling.  It serves fp32 storage and shapes the matrix-core path does not take,
-// and its per-position bookkeeping kernels (gate, mixture, expert draw) are
-// shared with that path.  One thread block per head row (t, s, a) or one thread
-// per output element; every sum runs in a fixed order, so results are reproducible.
+// Plain fp32 path of the CP head: correct for every shape and storage type.  It serves fp32
+// storage and shapes the bf16 matrix-core path does not take, and its per-position bookkeeping
+// kernels (gate, mixture, expert draw) are shared with that path.  Every contraction runs on the
+// fp32 matrix instruction (gemm_f32.hpp) with the row's bookkeeping in the epilogue; every sum
+// runs in a fixed order, so results are reproducible.
 //
 // Head rows are ordered m = (t*n + s)*r + a, so X[m / r] is the row's target and
 // m / (n*r) its position.
 #include "cp_internal.hpp"
+#include "gemm_f32.hpp"
 
 #include <math.h>
 
@@ -48,11 +49,12 @@ __global__ void __launch_bounds__(kWave) k_gate(int d, int r, const TIn *__restr
 }
 
 // ------------------------------------------------------------------------------------------
-// y = W_sa h for one head row m = (t, s, a); optional rounding of y to bf16
+// y = W_sa h rounded to bf16, one block per head row m = (t, s, a): the draft-type calls with bf16 storage.
+// The rounding is discontinuous, so these calls keep this kernel's summation order: an element of y within fp32
+// accumulation error of a rounding midpoint would otherwise fall on its other side and move a row's logits by 1e-2.
 // ------------------------------------------------------------------------------------------
-template <typename TIn>
-__global__ void __launch_bounds__(kBlock) k_y_generic(int d, int nr, const TIn *__restrict__ H,
-                                                      const TIn *__restrict__ W, float *__restrict__ Y, int round_y)
+__global__ void __launch_bounds__(kBlock) k_y_rounded(int d, int nr, const bf16_t *__restrict__ H, const bf16_t *__restrict__ W,
+                                                      float *__restrict__ Y)
 {
     extern __shared__ float hs[];
     const size_t m = blockIdx.x;
@@ -60,58 +62,323 @@ __global__ void __launch_bounds__(kBlock) k_y_generic(int d, int nr, const TIn *
     const int sa = (int)(m % nr);
     for (int k = threadIdx.x; k < d; k += kBlock) hs[k] = ld_f32(H, t * d + k);
     __syncthreads();
-    const TIn *Wsa = W + (size_t)sa * d * d;
+    const bf16_t *Wsa = W + (size_t)sa * d * d;
     const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
     for (int k = wave; k < d; k += kWavesPerBlock) {
         float p = 0.f;
         for (int j = lane; j < d; j += kWave) p += ld_f32(Wsa, (size_t)k * d + j) * hs[j];
         p = wave_sum(p);
-        if (lane == 0) Y[m * d + k] = round_y ? bf16_to_f32(f32_to_bf16(p)) : p;
+        if (lane == 0) Y[m * d + k] = bf16_to_f32(f32_to_bf16(p));
     }
 }
 
 // ------------------------------------------------------------------------------------------
-// z = U y for one head row; running (max, sum exp) over the vocabulary gives the
-// log-normaliser (eq. 5); C = z[x] - lse (eq. 8).  Block b serves row m0 + b; lse and C are indexed by the row,
-// z_out (written only if not NULL) by the block.
+// epilogues of the fp32 products.  A sub-tile's element v of block (i, j) is row f32_row, column f32_col from its origin.
 // ------------------------------------------------------------------------------------------
+
+// C[row, col] = acc (+ what is there); a split sum's parts go to partial[split, M, N].
+struct EpiF32Store {
+    float *C;
+    long ldc;
+    int accumulate;
+    float *partial;
+    template <class Tile>
+    __device__ __forceinline__ void run(f32v4_t (&acc)[Tile::TM][Tile::TN], long row0, long col0, const F32Problem &p, int split,
+                                        int, int lane) const
+    {
+        const bool part = p.splits > 1, add = accumulate && !part;
+        float *out = part ? partial + (size_t)split * p.M * p.N : C;
+        const long ld = part ? p.N : ldc;
+#pragma unroll
+        for (int i = 0; i < Tile::TM; ++i)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const long row = row0 + f32_row(i, v, lane);
+                if (row >= p.M) continue;
+#pragma unroll
+                for (int j = 0; j < Tile::TN; ++j) {
+                    const long col = col0 + f32_col(j, lane);
+                    if (col >= p.N) continue;
+                    float *o = out + row * ld + col;
+                    *o = add ? *o + acc[i][j][v] : acc[i][j][v];
+                }
+            }
+    }
+};
+
+// Logits of the head rows m = row * row_mul + row_add: (maximum, sum of exp(z - maximum)) over the sub-tile's columns
+// to part[m, slots], the target logit to zt[m] (if X is given), and the logits themselves to z[row, ldz] (if z is
+// given; columns from V up to ldz become zero).
+struct EpiF32Logits {
+    float2 *part;
+    int slots;
+    long row_mul, row_add;
+    const int32_t *X;       // null: no target logits
+    int r;
+    float *zt;
+    float *z;               // null: logits are not kept
+    long ldz;
+    template <class Tile>
+    __device__ __forceinline__ void run(f32v4_t (&acc)[Tile::TM][Tile::TN], long row0, long col0, const F32Problem &p, int, int slot,
+                                        int lane) const
+    {
+#pragma unroll
+        for (int i = 0; i < Tile::TM; ++i)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const long row = row0 + f32_row(i, v, lane);
+                const long m = row * row_mul + row_add;
+                const bool in = row < p.M;
+                if (z && in) {
+#pragma unroll
+                    for (int j = 0; j < Tile::TN; ++j) {
+                        const long col = col0 + f32_col(j, lane);
+                        if (col < ldz) z[row * ldz + col] = col < p.N ? acc[i][j][v] : 0.f;
+                    }
+                }
+                if (part) {
+                    float mx = -INFINITY;
+#pragma unroll
+                    for (int j = 0; j < Tile::TN; ++j)
+                        if (col0 + f32_col(j, lane) < p.N) mx = fmaxf(mx, acc[i][j][v]);
+                    mx = row16_max(mx);
+                    float sum = 0.f;
+#pragma unroll
+                    for (int j = 0; j < Tile::TN; ++j)
+                        if (col0 + f32_col(j, lane) < p.N) sum += expf(acc[i][j][v] - mx);
+                    sum = row16_sum(sum);
+                    if (in && (lane & 15) == 0) part[m * slots + slot] = make_float2(mx, sum);
+                }
+                if (X && in) {
+                    const long x = X[(unsigned)m / (unsigned)r];       // fewer than 2^31 head rows
+#pragma unroll
+                    for (int j = 0; j < Tile::TN; ++j)
+                        if (x == col0 + f32_col(j, lane)) zt[m] = acc[i][j][v];
+                }
+            }
+    }
+};
+
+// Logit gradients of the head rows m = m0 + row * row_mul + row_add from their recomputed logits:
+//   dz[v] = up_t gamma[t, a] (exp(z - lse[m]) - 1[v = x]),  zero for a dropped factor and from V up to ldz,
+// written to dZ[row, ldz] (row-strided by ldz; a head's rows start at dZ).  The first column slot also writes
+// dg[t, a] = up_t (w - gamma), the derivative of eq. 9 with respect to the gate pre-activations, if dg is given.
+struct EpiF32Dz {
+    float *dZ;
+    long ldz, columns;      // columns to write (V, or V rounded up to the padding)
+    size_t m0;
+    long row_mul, row_add;
+    int n, r;
+    const int32_t *X;
+    const float *lse, *w, *gamma, *dloss;
+    float scale;
+    float *dg;
+    template <class Tile>
+    __device__ __forceinline__ void run(f32v4_t (&acc)[Tile::TM][Tile::TN], long row0, long col0, const F32Problem &p, int, int slot,
+                                        int lane) const
+    {
+#pragma unroll
+        for (int i = 0; i < Tile::TM; ++i)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const long row = row0 + f32_row(i, v, lane);
+                if (row >= p.M) continue;
+                const unsigned m = (unsigned)(m0 + row * row_mul + row_add), g = m / (unsigned)r;     // fewer than 2^31 head rows
+                const unsigned a = m - g * r;
+                const size_t t = g / (unsigned)n;
+                const long x = X[g];
+                const float up = dloss ? dloss[t] * scale : scale;
+                const float gm = gamma[t * r + a];
+                const float coef = x < 0 ? 0.f : up * gm, l = lse[m];
+                if (dg && slot == 0 && (lane & 15) == 0 && g == t * n) dg[t * r + a] = up * (w[t * r + a] - gm);
+#pragma unroll
+                for (int j = 0; j < Tile::TN; ++j) {
+                    const long col = col0 + f32_col(j, lane);
+                    if (col >= columns) continue;
+                    dZ[row * ldz + col] = x < 0 || col >= p.N ? 0.f : coef * (expf(acc[i][j][v] - l) - (col == x ? 1.f : 0.f));
+                }
+            }
+    }
+};
+
+// dH[t, j] = acc + sum_a dg[t, a] G[a, j]; a split sum's parts go to partial[split, M, N] without the gate's term
 template <typename TIn>
-__global__ void __launch_bounds__(kBlock) k_zstats_generic(int d, int V, int r, size_t m0, const TIn *__restrict__ U,
-                                                           const float *__restrict__ Y, const int32_t *__restrict__ X,
-                                                           float *__restrict__ lse_out, float *__restrict__ C_out,
-                                                           float *__restrict__ z_out)
+struct EpiF32Dh {
+    float *dH;
+    const float *dg;
+    const TIn *G;
+    int r;
+    float *partial;
+    template <class Tile>
+    __device__ __forceinline__ void run(f32v4_t (&acc)[Tile::TM][Tile::TN], long row0, long col0, const F32Problem &p, int split,
+                                        int, int lane) const
+    {
+        const bool part = p.splits > 1;
+        float *out = part ? partial + (size_t)split * p.M * p.N : dH;
+        const int terms = part ? 0 : r;
+#pragma unroll
+        for (int i = 0; i < Tile::TM; ++i)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const long row = row0 + f32_row(i, v, lane);
+                if (row >= p.M) continue;
+#pragma unroll
+                for (int j = 0; j < Tile::TN; ++j) {
+                    const long col = col0 + f32_col(j, lane);
+                    if (col >= p.N) continue;
+                    float x = acc[i][j][v];
+                    for (int a = 0; a < terms; ++a) x += dg[row * r + a] * ld_f32(G, (size_t)a * p.N + col);
+                    out[row * p.N + col] = x;
+                }
+            }
+    }
+};
+
+// The split sums of a launch, added in split order: out[i] (+)= sum_s partial[s, i]; with dg, + sum_a dg[t, a] G[a, j] for
+// i = t * N + j.  Job b covers the blocks from first[b] on.
+struct AddSplits {
+    int count;
+    unsigned first[4];
+    size_t size[3];
+    int splits[3], accumulate[3];
+    const float *partial[3];
+    float *out[3];
+    long N;
+    int r, gate_job;
+    const float *dg;
+    const void *G;
+    void add(const F32Plan &plan, long M, long Nn, const float *from, float *to, bool acc)
+    {
+        if (plan.splits == 1) return;
+        size[count] = (size_t)M * Nn;
+        splits[count] = plan.splits;
+        accumulate[count] = acc ? 1 : 0;
+        partial[count] = from;
+        out[count] = to;
+        first[count + 1] = first[count] + blocks_for(size[count], kBlock);
+        ++count;
+    }
+};
+template <typename TIn>
+__global__ void __launch_bounds__(kBlock) k_add_splits(AddSplits job)
 {
-    extern __shared__ float ys[];
-    __shared__ float red_m[kWavesPerBlock], red_l[kWavesPerBlock], red_zt;
-    const size_t m = m0 + blockIdx.x;
-    for (int k = threadIdx.x; k < d; k += kBlock) ys[k] = Y[m * d + k];
-    if (threadIdx.x == 0) red_zt = 0.f;
-    __syncthreads();
-    const int x = X ? X[m / r] : -1;
-    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-    float mx = -INFINITY, l = 0.f;
-    for (int v = wave; v < V; v += kWavesPerBlock) {
-        float p = 0.f;
-        for (int k = lane; k < d; k += kWave) p += ld_f32(U, (size_t)v * d + k) * ys[k];
-        const float z = wave_sum(p);
-        if (z_out && lane == 0) z_out[(size_t)blockIdx.x * V + v] = z;
-        if (z > mx) { l = l * expf(mx - z) + 1.f; mx = z; }
-        else l += expf(z - mx);
-        if (v == x && lane == 0) red_zt = z;
+    int b = 0;
+    while (b + 1 < job.count && blockIdx.x >= job.first[b + 1]) ++b;
+    const size_t i = (size_t)(blockIdx.x - job.first[b]) * kBlock + threadIdx.x;
+    if (i >= job.size[b]) return;
+    float x = 0.f;
+    for (int s = 0; s < job.splits[b]; ++s) x += job.partial[b][(size_t)s * job.size[b] + i];
+    if (b == job.gate_job) {
+        const size_t t = i / job.N, j = i % job.N;
+        for (int a = 0; a < job.r; ++a) x += job.dg[t * job.r + a] * ld_f32((const TIn *)job.G, (size_t)a * job.N + j);
     }
-    if (lane == 0) { red_m[wave] = mx; red_l[wave] = l; }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        float Mx = red_m[0];
-        for (int i = 1; i < kWavesPerBlock; ++i) Mx = fmaxf(Mx, red_m[i]);
-        float L = 0.f;
-        for (int i = 0; i < kWavesPerBlock; ++i) L += red_l[i] * expf(red_m[i] - Mx);
-        const float lse = Mx + logf(L);
-        if (lse_out) lse_out[m] = lse;
-        if (C_out) C_out[m] = (x >= 0) ? red_zt - lse : 0.f;
-    }
+    job.out[b][i] = job.accumulate[b] ? job.out[b][i] + x : x;
 }
 
+// One block per position: the log-normalisers (eq. 5) of its n r head rows from their per-slot statistics, a
+// wavefront per row; C = z[x] - lse (eq. 8) in place of the target logits; the gate's log-softmax (eq. 7) in place of
+// its pre-activations; and the mixture over the experts (eq. 9).  X, C null: log-normalisers only.  gate null:
+// logw is already a log-softmax.  loss null: no mixture.
+__global__ void __launch_bounds__(kBlock) k_position_finish(int n, int r, int slots, const float2 *__restrict__ part,
+                                                            const int32_t *__restrict__ X, float *__restrict__ C,
+                                                            float *__restrict__ lse_out, float *__restrict__ gate,
+                                                            float *__restrict__ w_out, float *__restrict__ gamma,
+                                                            float *__restrict__ loss)
+{
+    extern __shared__ float C_s[];                      // n r values
+    const size_t t = blockIdx.x;
+    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave, nr = n * r;
+    for (int j = wave; j < nr; j += kWavesPerBlock) {
+        const size_t m = t * nr + j;
+        float mx = -INFINITY, l = 0.f;
+        for (int q = lane; q < slots; q += kWave) {
+            const float2 v = part[m * slots + q];
+            if (v.x > mx) { l = l * expf(mx - v.x) + v.y; mx = v.x; }
+            else if (v.x != -INFINITY) l += v.y * expf(v.x - mx);
+        }
+        const float Mx = wave_max(mx);
+        const float L = wave_sum(mx == -INFINITY ? 0.f : l * expf(mx - Mx));
+        const float lse = Mx + logf(L);
+        if (lane == 0) {
+            lse_out[m] = lse;
+            if (C) {
+                const float c = X[m / r] >= 0 ? C[m] - lse : 0.f;
+                C[m] = c;
+                C_s[j] = c;
+            }
+        }
+    }
+    __syncthreads();
+    if (wave != 0) return;
+    float lw = -INFINITY;
+    if (gate) {
+        const float g = lane < r ? gate[t * r + lane] : -INFINITY;
+        const float mx = wave_max(g);
+        const float lse = mx + logf(wave_sum(lane < r ? expf(g - mx) : 0.f));
+        lw = g - lse;
+        if (lane < r) {
+            gate[t * r + lane] = lw;
+            w_out[t * r + lane] = expf(lw);
+        }
+    }
+    if (!loss) return;
+    float a = -INFINITY;
+    if (lane < r) {
+        a = lw;
+        for (int s = 0; s < n; ++s) a += C_s[s * r + lane];
+    }
+    const float mx = wave_max(a);
+    const float L = mx + logf(wave_sum(lane < r ? expf(a - mx) : 0.f));
+    if (lane == 0) loss[t] = -L;
+    if (lane < r) gamma[t * r + lane] = expf(a - L);
+}
+
+// ---- launches: the plan picks the tile
+template <typename F>
+void with_f32_tile(int kind, const F &f)
+{
+    if (kind == kF32LargeTile) f(F32Large{});
+    else if (kind == kF32MidTile) f(F32Mid{});
+    else f(F32Small{});
+}
+template <typename TA, typename TB, bool AKM, bool BKM, class Epi>
+void launch_f32(const F32Problem &p, int kind, const Epi &e, hipStream_t st)
+{
+    with_f32_tile(kind, [&](auto tile) {
+        k_gemm_f32<F32Gemm<decltype(tile), TA, TB, AKM, BKM>, Epi, NoF32Problem, NoEpi, NoF32Problem, NoEpi>
+            <<<(unsigned)p.tiles(), kF32Threads, 0, st>>>(p, e, F32Problem{}, NoEpi{}, F32Problem{}, NoEpi{});
+    });
+}
+template <typename TIn>
+void launch_add_splits(const AddSplits &job, hipStream_t st)
+{
+    if (job.count) k_add_splits<TIn><<<job.first[job.count], kBlock, 0, st>>>(job);
+}
+// y = W_sa h for `heads` head matrices, and with `gate` its pre-activations G h
+template <typename TIn>
+void launch_f32_y(const cp_head_desc &ds, int heads, const TIn *H, const TIn *W, const TIn *G, float *Y, float *gate, hipStream_t st)
+{
+    const long d = ds.d, T = (long)ds.T, cols = (long)heads * d;
+    const F32Plan plan = f32_plan(T, cols, d, false);
+    const F32Problem py = f32_problem<false, false>(H, d, W, d, T, cols, d, d, plan);
+    F32Problem pg{};
+    if (gate) pg = f32_problem<false, false>(H, d, G, d, T, ds.r, d, d, plan);
+    with_f32_tile(plan.kind, [&](auto tile) {
+        typedef F32Gemm<decltype(tile), TIn, TIn, false, false> Gm;
+        // the few gate tiles first: they share the launch's first round
+        k_gemm_f32<Gm, EpiF32Store, Gm, EpiF32Store, NoF32Problem, NoEpi><<<(unsigned)(py.tiles() + pg.tiles()), kF32Threads, 0, st>>>(
+            pg, EpiF32Store{gate, ds.r, 0, nullptr}, py, EpiF32Store{Y, cols, 0, nullptr}, F32Problem{}, NoEpi{});
+    });
+}
+// y of the draft-type calls: with bf16 storage its rounding is part of the distribution's definition
+void launch_draft_y(const cp_head_desc &ds, int heads, const float *H, const float *W, const float *G, float *Y, hipStream_t st)
+{
+    launch_f32_y<float>(ds, heads, H, W, G, Y, nullptr, st);
+}
+void launch_draft_y(const cp_head_desc &ds, int heads, const bf16_t *H, const bf16_t *W, const bf16_t *, float *Y, hipStream_t st)
+{
+    k_y_rounded<<<(unsigned)(ds.T * heads), kBlock, (size_t)ds.d * sizeof(float), st>>>(ds.d, heads, H, W, Y);
+}
 // ------------------------------------------------------------------------------------------
 // mixture over experts (eq. 9) and the posterior gamma_a = exp(a_a - L); one wavefront per position
 // ------------------------------------------------------------------------------------------
@@ -141,120 +408,6 @@ __global__ void k_fill_zero(size_t count, float *__restrict__ p)
 {
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < count) p[i] = 0.f;
-}
-
-// dg[t,a] = up_t (w_a - gamma_a): derivative of eq. 9 with respect to the gate pre-activations
-__global__ void k_dgate(size_t Tr, int r, const float *__restrict__ w, const float *__restrict__ gamma,
-                        const float *__restrict__ dloss, float scale, float *__restrict__ dg)
-{
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= Tr) return;
-    const float up = dloss ? dloss[i / r] * scale : scale;
-    dg[i] = up * (w[i] - gamma[i]);
-}
-
-// dz[v] = up_t gamma_a (softmax(z)[v] - 1[v = x]) for the rows m0 .. m0+gridDim.x-1
-template <typename TIn>
-__global__ void __launch_bounds__(kBlock) k_dz_generic(int d, int V, int n, int r, size_t m0,
-                                                       const TIn *__restrict__ U, const float *__restrict__ Y,
-                                                       const int32_t *__restrict__ X, const float *__restrict__ lse,
-                                                       const float *__restrict__ gamma,
-                                                       const float *__restrict__ dloss, float scale,
-                                                       float *__restrict__ dZ)
-{
-    extern __shared__ float ys[];
-    const size_t mc = blockIdx.x, m = m0 + mc;
-    for (int k = threadIdx.x; k < d; k += kBlock) ys[k] = Y[m * d + k];
-    __syncthreads();
-    const size_t t = m / ((size_t)n * r);
-    const int a = (int)(m % r);
-    const int x = X[m / r];
-    const float up = dloss ? dloss[t] * scale : scale;
-    const float coef = up * gamma[t * r + a];
-    const float l = lse[m];
-    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-    for (int v = wave; v < V; v += kWavesPerBlock) {
-        float p = 0.f;
-        for (int k = lane; k < d; k += kWave) p += ld_f32(U, (size_t)v * d + k) * ys[k];
-        const float z = wave_sum(p);
-        if (lane == 0) dZ[mc * V + v] = (x < 0) ? 0.f : coef * (expf(z - l) - (v == x ? 1.f : 0.f));
-    }
-}
-
-// dY[m,k] = sum_v dZ[mc,v] U[v,k]
-template <typename TIn>
-__global__ void __launch_bounds__(kBlock) k_dy_generic(int d, int V, size_t m0, size_t Mc,
-                                                       const TIn *__restrict__ U, const float *__restrict__ dZ,
-                                                       float *__restrict__ dY)
-{
-    const size_t idx = (size_t)blockIdx.x * kBlock + threadIdx.x;
-    if (idx >= Mc * d) return;
-    const size_t mc = idx / d;
-    const int k = (int)(idx % d);
-    float acc = 0.f;
-    for (int v = 0; v < V; ++v) acc += dZ[mc * V + v] * ld_f32(U, (size_t)v * d + k);
-    dY[(m0 + mc) * d + k] = acc;
-}
-
-// dU[v,k] (+)= sum_mc dZ[mc,v] Y[m0+mc,k]
-__global__ void __launch_bounds__(kBlock) k_du_generic(int d, int V, size_t m0, size_t Mc,
-                                                       const float *__restrict__ dZ, const float *__restrict__ Y,
-                                                       float *__restrict__ dU, int accumulate)
-{
-    const size_t idx = (size_t)blockIdx.x * kBlock + threadIdx.x;
-    if (idx >= (size_t)V * d) return;
-    const size_t v = idx / d;
-    const int k = (int)(idx % d);
-    float acc = accumulate ? dU[idx] : 0.f;
-    for (size_t mc = 0; mc < Mc; ++mc) acc += dZ[mc * V + v] * Y[(m0 + mc) * d + k];
-    dU[idx] = acc;
-}
-
-// dW[sa,k,j] = sum_t dY[(t,sa),k] H[t,j]
-template <typename TIn>
-__global__ void __launch_bounds__(kBlock) k_dw_generic(size_t T, int d, int nr, const TIn *__restrict__ H,
-                                                       const float *__restrict__ dY, float *__restrict__ dW)
-{
-    const size_t idx = (size_t)blockIdx.x * kBlock + threadIdx.x;
-    if (idx >= (size_t)nr * d * d) return;
-    const int j = (int)(idx % d);
-    const size_t sak = idx / d;
-    const size_t sa = sak / d;
-    const int k = (int)(sak % d);
-    float acc = 0.f;
-    for (size_t t = 0; t < T; ++t) acc += dY[(t * nr + sa) * d + k] * ld_f32(H, t * d + j);
-    dW[idx] = acc;
-}
-
-// dH[t,j] = sum_{sa,k} dY[(t,sa),k] W[sa,k,j] + sum_a dg[t,a] G[a,j]
-template <typename TIn>
-__global__ void __launch_bounds__(kBlock) k_dh_generic(size_t T, int d, int nr, int r, const TIn *__restrict__ W,
-                                                       const TIn *__restrict__ G, const float *__restrict__ dY,
-                                                       const float *__restrict__ dg, float *__restrict__ dH)
-{
-    const size_t idx = (size_t)blockIdx.x * kBlock + threadIdx.x;
-    if (idx >= T * d) return;
-    const size_t t = idx / d;
-    const int j = (int)(idx % d);
-    float acc = 0.f;
-    for (int sa = 0; sa < nr; ++sa)
-        for (int k = 0; k < d; ++k) acc += dY[(t * nr + sa) * d + k] * ld_f32(W, ((size_t)sa * d + k) * d + j);
-    for (int a = 0; a < r; ++a) acc += dg[t * r + a] * ld_f32(G, (size_t)a * d + j);
-    dH[idx] = acc;
-}
-
-// dG[a,j] = sum_t dg[t,a] H[t,j]
-template <typename TIn>
-__global__ void __launch_bounds__(kBlock) k_dg_generic(size_t T, int d, int r, const TIn *__restrict__ H,
-                                                       const float *__restrict__ dg, float *__restrict__ dG)
-{
-    const size_t idx = (size_t)blockIdx.x * kBlock + threadIdx.x;
-    if (idx >= (size_t)r * d) return;
-    const int a = (int)(idx / d);
-    const int j = (int)(idx % d);
-    float acc = 0.f;
-    for (size_t t = 0; t < T; ++t) acc += dg[t * r + a] * ld_f32(H, t * d + j);
-    dG[idx] = acc;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -425,102 +578,6 @@ __global__ void __launch_bounds__(kBlock) k_sample_sequential_generic(int V, int
 }
 
 // ------------------------------------------------------------------------------------------
-// full heads (eq. 6 as printed): z_sa = F_sa h with one V x d matrix per (s, a); rows m = (t n + s) r + a
-// ------------------------------------------------------------------------------------------
-
-// running statistics of z = F_sa h for one head row, C = z[x] - lse; with dZ != NULL (backward) the
-// second sweep writes dz[v] = coef (softmax(z)[v] - 1[v = x]) for chunk row m - m0 instead
-template <typename TIn>
-__global__ void __launch_bounds__(kBlock) k_full_row_generic(int d, int V, int n, int r, size_t m0,
-                                                             const TIn *__restrict__ H, const TIn *__restrict__ F,
-                                                             const int32_t *__restrict__ X, float *__restrict__ lse_io,
-                                                             float *__restrict__ C_out,
-                                                             const float *__restrict__ gamma,
-                                                             const float *__restrict__ dloss, float scale,
-                                                             float *__restrict__ dZ)
-{
-    extern __shared__ float hs[];
-    __shared__ float red_m[kWavesPerBlock], red_l[kWavesPerBlock], red_zt;
-    const size_t mc = blockIdx.x, m = m0 + mc;
-    const int nr = n * r;
-    const size_t t = m / nr;
-    const int sa = (int)(m % nr), a = sa % r;
-    for (int k = threadIdx.x; k < d; k += kBlock) hs[k] = ld_f32(H, t * d + k);
-    if (threadIdx.x == 0) red_zt = 0.f;
-    __syncthreads();
-    const TIn *Fsa = F + (size_t)sa * V * d;
-    const int x = X[m / r];
-    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-    if (!dZ) {
-        float mx = -INFINITY, l = 0.f;
-        for (int v = wave; v < V; v += kWavesPerBlock) {
-            float p = 0.f;
-            for (int k = lane; k < d; k += kWave) p += ld_f32(Fsa, (size_t)v * d + k) * hs[k];
-            const float z = wave_sum(p);
-            if (z > mx) { l = l * expf(mx - z) + 1.f; mx = z; }
-            else l += expf(z - mx);
-            if (v == x && lane == 0) red_zt = z;
-        }
-        if (lane == 0) { red_m[wave] = mx; red_l[wave] = l; }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            float Mx = red_m[0];
-            for (int i = 1; i < kWavesPerBlock; ++i) Mx = fmaxf(Mx, red_m[i]);
-            float L = 0.f;
-            for (int i = 0; i < kWavesPerBlock; ++i) L += red_l[i] * expf(red_m[i] - Mx);
-            const float lse = Mx + logf(L);
-            lse_io[m] = lse;
-            C_out[m] = (x >= 0) ? red_zt - lse : 0.f;
-        }
-    } else {
-        const float up = dloss ? dloss[t] * scale : scale;
-        const float coef = up * gamma[t * r + a];
-        const float l = lse_io[m];
-        for (int v = wave; v < V; v += kWavesPerBlock) {
-            float p = 0.f;
-            for (int k = lane; k < d; k += kWave) p += ld_f32(Fsa, (size_t)v * d + k) * hs[k];
-            const float z = wave_sum(p);
-            if (lane == 0) dZ[mc * V + v] = (x < 0) ? 0.f : coef * (expf(z - l) - (v == x ? 1.f : 0.f));
-        }
-    }
-}
-
-// dF[sa,v,j] (+)= sum over the positions t0 .. t0+Tc-1 of dZ[(t - t0) nr + sa, v] H[t, j]
-template <typename TIn>
-__global__ void __launch_bounds__(kBlock) k_df_generic(int d, int V, int nr, size_t t0, size_t Tc,
-                                                       const TIn *__restrict__ H, const float *__restrict__ dZ,
-                                                       float *__restrict__ dF, int accumulate)
-{
-    const size_t idx = (size_t)blockIdx.x * kBlock + threadIdx.x;
-    if (idx >= (size_t)nr * V * d) return;
-    const int j = (int)(idx % d);
-    const size_t sav = idx / d;
-    const int v = (int)(sav % V);
-    const size_t sa = sav / V;
-    float acc = accumulate ? dF[idx] : 0.f;
-    for (size_t tc = 0; tc < Tc; ++tc) acc += dZ[(tc * nr + sa) * V + v] * ld_f32(H, (t0 + tc) * d + j);
-    dF[idx] = acc;
-}
-
-// dH[t,j] = sum_{sa,v} dZ[(t - t0) nr + sa, v] F[sa,v,j] + sum_a dg[t,a] G[a,j] for the positions of the chunk
-template <typename TIn>
-__global__ void __launch_bounds__(kBlock) k_dh_full_generic(int d, int V, int nr, int r, size_t t0, size_t Tc,
-                                                            const TIn *__restrict__ F, const TIn *__restrict__ G,
-                                                            const float *__restrict__ dZ, const float *__restrict__ dg,
-                                                            float *__restrict__ dH)
-{
-    const size_t idx = (size_t)blockIdx.x * kBlock + threadIdx.x;
-    if (idx >= Tc * d) return;
-    const size_t tc = idx / d, t = t0 + tc;
-    const int j = (int)(idx % d);
-    float acc = 0.f;
-    for (int sa = 0; sa < nr; ++sa)
-        for (int v = 0; v < V; ++v) acc += dZ[(tc * nr + sa) * V + v] * ld_f32(F, ((size_t)sa * V + v) * d + j);
-    for (int a = 0; a < r; ++a) acc += dg[t * r + a] * ld_f32(G, (size_t)a * d + j);
-    dH[t * d + j] = acc;
-}
-
-// ------------------------------------------------------------------------------------------
 // next-token distribution (eq. 11) and the balancing statistic (eq. 10)
 // ------------------------------------------------------------------------------------------
 
@@ -597,8 +654,41 @@ inline size_t generic_chunk_rows(const cp_head_desc &ds)
     return rows < M ? rows : (M ? M : (size_t)ds.r);
 }
 
+// A chunk's logit gradients have rows of V rounded up to 4 floats (the rest zero): the products below read them with
+// 16-byte loads whatever V is.
+inline long dz_row(const cp_head_desc &ds) { return (long)round_up((size_t)ds.V, 4); }
+
+// Tiles and splits of the backward products; those of a chunk are planned for a whole chunk.
+struct BwdPlans {
+    F32Plan z, chunk[2], weights[3];            // {dY, dU}, {dH, dW, dG}: each set shares a launch
+    size_t part_chunk[2], part_weights[3];      // where their partial sums start in the scratch
+    size_t scratch;
+};
+inline BwdPlans bwd_plans(const cp_head_desc &ds)
+{
+    BwdPlans b;
+    const long rows = (long)generic_chunk_rows(ds), d = ds.d, V = ds.V, T = (long)ds.T, nrd = (long)ds.n * ds.r * d;
+    const F32Shape chunk[2] = {{rows, d, V}, {V, d, rows}}, weights[3] = {{T, d, nrd}, {nrd, d, T}, {ds.r, d, T}};
+    b.z = f32_plan(rows, V, d, false);
+    f32_plan(chunk, 2, true, b.chunk);
+    f32_plan(weights, 3, true, b.weights);
+    size_t off = 0;
+    for (int i = 0; i < 2; ++i) {
+        b.part_chunk[i] = off;
+        off += b.chunk[i].scratch(chunk[i].M, chunk[i].N);
+    }
+    b.scratch = off;
+    off = 0;
+    for (int i = 0; i < 3; ++i) {
+        b.part_weights[i] = off;
+        off += b.weights[i].scratch(weights[i].M, weights[i].N);
+    }
+    b.scratch = std::max(b.scratch, off);
+    return b;
+}
+
 struct GenericWs {
-    size_t logw, C, dY, dZ, dg, w, Y, z, lse, total;
+    size_t logw, C, part, dY, dZ, dg, partial, w, Y, z, lse, total;
 };
 
 inline GenericWs generic_ws(const cp_head_desc &ds, int op)
@@ -607,40 +697,63 @@ inline GenericWs generic_ws(const cp_head_desc &ds, int op)
     const size_t M = (size_t)ds.T * ds.n * ds.r, Tr = (size_t)ds.T * ds.r;
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes); return o; };
+    auto take_part = [&] { return take(M * f32_slots(f32_plan((long)M, ds.V, ds.d, false).kind, ds.V) * sizeof(float2)); };
     if (op == CP_HEAD_OP_LOSS_FWD) {
         g.logw = take(Tr * 4);
         g.C = take(M * 4);
+        g.part = take_part();
     } else if (op == CP_HEAD_OP_LOSS_BWD) {
         g.dY = take(M * ds.d * 4);
-        g.dZ = take(generic_chunk_rows(ds) * ds.V * 4);
+        g.dZ = take(generic_chunk_rows(ds) * dz_row(ds) * 4);
         g.dg = take(Tr * 4);
+        g.partial = take(bwd_plans(ds).scratch);
     } else {
         g.logw = take(Tr * 4);
         g.w = take(Tr * 4);
         g.Y = take(M * ds.d * 4);
         g.z = take(M * ds.V * 4);
         g.lse = take(M * 4);
+        g.part = take_part();
     }
     g.total = off;
     return g;
 }
 
+// gate, y, statistics of z and what follows per position; loss null: no mixture
+template <typename TIn>
+void fwd_rows_t(const cp_head_desc &ds, const TIn *H, const TIn *W, const TIn *U, const TIn *G, const int32_t *X,
+                const GenericFwdBuffers &b, float2 *part, float *loss, hipStream_t st)
+{
+    const long M = (long)ds.T * ds.n * ds.r, d = ds.d, V = ds.V;
+    launch_f32_y<TIn>(ds, ds.n * ds.r, H, W, G, b.Y, b.logw, st);
+    const F32Plan plan = f32_plan(M, V, d, false);
+    const int slots = f32_slots(plan.kind, V);
+    launch_f32<float, TIn, false, false>(f32_problem<false, false>((const float *)b.Y, d, U, d, M, V, d, d, plan), plan.kind,
+                                         EpiF32Logits{part, slots, 1, 0, X, ds.r, b.C, nullptr, 0}, st);
+    k_position_finish<<<(unsigned)ds.T, kBlock, (size_t)ds.n * ds.r * sizeof(float), st>>>(ds.n, ds.r, slots, part, X, b.C, b.lse,
+                                                                                          b.logw, b.w, b.gamma, loss);
+}
+
+inline GenericFwdBuffers fwd_buffers(const cp_head_desc &ds, void *ctx, void *ws)
+{
+    const CtxLayout cl = ctx_layout(ds, false);
+    const GenericWs g = generic_ws(ds, CP_HEAD_OP_LOSS_FWD);
+    GenericFwdBuffers b;
+    b.lse = at<float>(ctx, cl.lse);
+    b.w = at<float>(ctx, cl.w);
+    b.gamma = at<float>(ctx, cl.gamma);
+    b.Y = at<float>(ctx, cl.Y);
+    b.logw = at<float>(ws, g.logw);
+    b.C = at<float>(ws, g.C);
+    return b;
+}
 
 template <typename TIn>
 int loss_fwd_t(const cp_head_desc &ds, const TIn *H, const TIn *W, const TIn *U, const TIn *G, const int32_t *X,
                float *loss, void *ctx, void *ws, hipStream_t st)
 {
-    const CtxLayout cl = ctx_layout(ds, false);
     const GenericWs g = generic_ws(ds, CP_HEAD_OP_LOSS_FWD);
-    const size_t M = (size_t)ds.T * ds.n * ds.r;
-    float *lse = at<float>(ctx, cl.lse), *w = at<float>(ctx, cl.w), *gamma = at<float>(ctx, cl.gamma);
-    float *Y = at<float>(ctx, cl.Y);
-    float *logw = at<float>(ws, g.logw), *C = at<float>(ws, g.C);
-    const size_t lds = (size_t)ds.d * sizeof(float);
-    k_gate<TIn><<<(unsigned)ds.T, kWave, 0, st>>>(ds.d, ds.r, H, G, logw, w);
-    k_y_generic<TIn><<<(unsigned)M, kBlock, lds, st>>>(ds.d, ds.n * ds.r, H, W, Y, 0);
-    k_zstats_generic<TIn><<<(unsigned)M, kBlock, lds, st>>>(ds.d, ds.V, ds.r, 0, U, Y, X, lse, C, nullptr);
-    k_mixture<<<(unsigned)ds.T, kWave, 0, st>>>(ds.n, ds.r, logw, C, loss, gamma, -1.f);
+    fwd_rows_t<TIn>(ds, H, W, U, G, X, fwd_buffers(ds, ctx, ws), at<float2>(ws, g.part), loss, st);
     return hipGetLastError() == hipSuccess ? CP_HEAD_OK : CP_HEAD_ERR_LAUNCH;
 }
 
@@ -652,24 +765,51 @@ int bwd_from_dz_t(const cp_head_desc &ds, const TIn *H, const TIn *W, const TIn 
                   hipStream_t st)
 {
     const GenericWs g = generic_ws(ds, CP_HEAD_OP_LOSS_BWD);
-    const size_t T = (size_t)ds.T, M = T * ds.n * ds.r;
+    const BwdPlans pl = bwd_plans(ds);
+    const long T = (long)ds.T, nr = (long)ds.n * ds.r, M = T * nr, d = ds.d, V = ds.V, nrd = nr * d, Vp = dz_row(ds);
     float *dY = at<float>(ws, g.dY), *dZ = at<float>(ws, g.dZ);
-    const size_t chunk = generic_chunk_rows(ds);
-    int first = 1;
-    for (size_t m0 = 0; m0 < M; m0 += chunk) {
-        const size_t Mc = (M - m0 < chunk) ? M - m0 : chunk;
-        fn(user, m0, Mc, dZ, st);
-        k_dy_generic<TIn><<<blocks_for(Mc * ds.d, kBlock), kBlock, 0, st>>>(ds.d, ds.V, m0, Mc, U, dZ, dY);
-        if (dU)
-            k_du_generic<<<blocks_for((size_t)ds.V * ds.d, kBlock), kBlock, 0, st>>>(ds.d, ds.V, m0, Mc, dZ, Y, dU,
-                                                                                    first ? 0 : 1);
-        first = 0;
+    auto part = [&](size_t off) { return at<float>(ws, g.partial + off); };
+    const long chunk = (long)generic_chunk_rows(ds);
+    for (long m0 = 0; m0 < M; m0 += chunk) {
+        const long Mc = std::min(chunk, M - m0);
+        fn(user, (size_t)m0, (size_t)Mc, dZ, Vp, st);
+        // dY = dZ U and dU (+)= dZ^T Y
+        float *py_part = part(pl.part_chunk[0]), *pu_part = part(pl.part_chunk[1]);
+        const F32Problem py = f32_problem<false, true>((const float *)dZ, Vp, U, d, Mc, d, Vp, V, pl.chunk[0]);
+        F32Problem pu{};
+        if (dU) pu = f32_problem<true, true>((const float *)dZ, Vp, Y + m0 * d, d, V, d, Mc, Mc, pl.chunk[1]);
+        with_f32_tile(pl.chunk[0].kind, [&](auto tile) {
+            typedef decltype(tile) Tile;
+            k_gemm_f32<F32Gemm<Tile, float, TIn, false, true>, EpiF32Store, F32Gemm<Tile, float, float, true, true>, EpiF32Store,
+                       NoF32Problem, NoEpi><<<(unsigned)(py.tiles() + pu.tiles()), kF32Threads, 0, st>>>(
+                py, EpiF32Store{dY + m0 * d, d, 0, py_part}, pu, EpiF32Store{dU, d, m0 ? 1 : 0, pu_part}, F32Problem{}, NoEpi{});
+        });
+        AddSplits add{};
+        add.gate_job = -1;
+        add.add(pl.chunk[0], Mc, d, py_part, dY + m0 * d, false);
+        if (dU) add.add(pl.chunk[1], V, d, pu_part, dU, m0 != 0);
+        launch_add_splits<TIn>(add, st);
     }
-    if (dW)
-        k_dw_generic<TIn><<<blocks_for((size_t)ds.n * ds.r * ds.d * ds.d, kBlock), kBlock, 0, st>>>(T, ds.d,
-                                                                                                  ds.n * ds.r, H, dY, dW);
-    k_dh_generic<TIn><<<blocks_for(T * ds.d, kBlock), kBlock, 0, st>>>(T, ds.d, ds.n * ds.r, ds.r, W, G, dY, dg, dH);
-    if (dG) k_dg_generic<TIn><<<blocks_for((size_t)ds.r * ds.d, kBlock), kBlock, 0, st>>>(T, ds.d, ds.r, H, dg, dG);
+    // dH = dY W + dg G, dW_sa = dY_sa^T H and dG = dg^T H (contractions over the positions)
+    float *ph_part = part(pl.part_weights[0]), *pw_part = part(pl.part_weights[1]), *pg_part = part(pl.part_weights[2]);
+    const F32Problem ph = f32_problem<false, true>((const float *)dY, nrd, W, d, T, d, nrd, nrd, pl.weights[0]);
+    F32Problem pw{}, pg{};
+    if (dW) pw = f32_problem<true, true>((const float *)dY, nrd, H, d, nrd, d, T, T, pl.weights[1]);
+    if (dG) pg = f32_problem<true, true>(dg, ds.r, H, d, ds.r, d, T, T, pl.weights[2]);
+    with_f32_tile(pl.weights[0].kind, [&](auto tile) {
+        typedef decltype(tile) Tile;
+        typedef F32Gemm<Tile, float, TIn, true, true> Gw;
+        k_gemm_f32<F32Gemm<Tile, float, TIn, false, true>, EpiF32Dh<TIn>, Gw, EpiF32Store, Gw, EpiF32Store>
+            <<<(unsigned)(ph.tiles() + pw.tiles() + pg.tiles()), kF32Threads, 0, st>>>(
+                ph, EpiF32Dh<TIn>{dH, dg, G, ds.r, ph_part}, pw, EpiF32Store{dW, d, 0, pw_part}, pg, EpiF32Store{dG, d, 0, pg_part});
+    });
+    AddSplits add{};
+    add.N = d; add.r = ds.r; add.dg = dg; add.G = G;
+    add.gate_job = pl.weights[0].splits > 1 ? 0 : -1;
+    add.add(pl.weights[0], T, d, ph_part, dH, false);
+    if (dW) add.add(pl.weights[1], nrd, d, pw_part, dW, false);
+    if (dG) add.add(pl.weights[2], ds.r, d, pg_part, dG, false);
+    launch_add_splits<TIn>(add, st);
     return hipGetLastError() == hipSuccess ? CP_HEAD_OK : CP_HEAD_ERR_LAUNCH;
 }
 
@@ -677,17 +817,21 @@ template <typename TIn>
 struct LossDzArgs {
     const cp_head_desc *ds;
     const TIn *U;
-    const float *Y, *lse, *gamma, *dloss;
+    const float *Y, *lse, *w, *gamma, *dloss;
     const int32_t *X;
     float scale;
+    float *dg;
 };
 template <typename TIn>
-void loss_dz_launch(void *user, size_t m0, size_t Mc, float *dZ, hipStream_t st)
+void loss_dz_launch(void *user, size_t m0, size_t Mc, float *dZ, long ldz, hipStream_t st)
 {
     const LossDzArgs<TIn> *a = static_cast<const LossDzArgs<TIn> *>(user);
     const cp_head_desc &ds = *a->ds;
-    k_dz_generic<TIn><<<(unsigned)Mc, kBlock, (size_t)ds.d * sizeof(float), st>>>(ds.d, ds.V, ds.n, ds.r, m0, a->U, a->Y, a->X,
-                                                                                  a->lse, a->gamma, a->dloss, a->scale, dZ);
+    const long d = ds.d;
+    const F32Plan plan = f32_plan((long)generic_chunk_rows(ds), ds.V, d, false);
+    launch_f32<float, TIn, false, false>(f32_problem<false, false>(a->Y + m0 * d, d, a->U, d, (long)Mc, ds.V, d, d, plan), plan.kind,
+                                         EpiF32Dz{dZ, ldz, ldz, m0, 1, 0, ds.n, ds.r, a->X, a->lse, a->w, a->gamma, a->dloss, a->scale,
+                                                  a->dg}, st);
 }
 
 template <typename TIn>
@@ -697,13 +841,25 @@ int loss_bwd_t(const cp_head_desc &ds, const TIn *H, const TIn *W, const TIn *U,
 {
     const CtxLayout cl = ctx_layout(ds, false);
     const GenericWs g = generic_ws(ds, CP_HEAD_OP_LOSS_BWD);
-    const size_t Tr = (size_t)ds.T * ds.r;
     const float *lse = at<float>(ctx, cl.lse), *w = at<float>(ctx, cl.w), *gamma = at<float>(ctx, cl.gamma);
     const float *Y = at<float>(ctx, cl.Y);
     float *dg = at<float>(ws, g.dg);
-    k_dgate<<<blocks_for(Tr, kBlock), kBlock, 0, st>>>(Tr, ds.r, w, gamma, dloss, scale, dg);
-    LossDzArgs<TIn> args{&ds, U, Y, lse, gamma, dloss, X, scale};
+    LossDzArgs<TIn> args{&ds, U, Y, lse, w, gamma, dloss, X, scale, dg};
     return bwd_from_dz_t<TIn>(ds, H, W, U, G, Y, dg, dH, dW, dU, dG, ws, loss_dz_launch<TIn>, &args, st);
+}
+
+// The logits of all `rows` head rows (row-major, V apart) and their log-normalisers, for the draft-type calls
+template <typename TIn>
+void launch_f32_kept_logits(const cp_head_desc &ds, long rows, int heads, const TIn *U, const float *Y, float *z, float2 *part,
+                            float *lse, hipStream_t st)
+{
+    const long d = ds.d, V = ds.V;
+    const F32Plan plan = f32_plan(rows, V, d, false);
+    const int slots = f32_slots(plan.kind, V);
+    launch_f32<float, TIn, false, false>(f32_problem<false, false>(Y, d, U, d, rows, V, d, d, plan), plan.kind,
+                                         EpiF32Logits{part, slots, 1, 0, nullptr, 1, nullptr, z, V}, st);
+    k_position_finish<<<(unsigned)(rows / heads), kBlock, (size_t)heads * sizeof(float), st>>>(1, heads, slots, part, nullptr, nullptr,
+                                                                                              lse, nullptr, nullptr, nullptr, nullptr);
 }
 
 template <typename TIn>
@@ -714,12 +870,10 @@ int draft_t(const cp_head_desc &ds, const TIn *H, const TIn *W, const TIn *U, co
     const size_t B = (size_t)ds.T, M = B * ds.n * ds.r;
     float *logw = at<float>(ws, g.logw), *w = at<float>(ws, g.w), *Y = at<float>(ws, g.Y);
     float *z = at<float>(ws, g.z), *lse = at<float>(ws, g.lse);
-    const size_t lds = (size_t)ds.d * sizeof(float);
-    const int round_y = ds.dtype == CP_HEAD_BF16 ? 1 : 0;
     k_gate<TIn><<<(unsigned)B, kWave, 0, st>>>(ds.d, ds.r, H, G, logw, w);
     k_pick_alpha<<<blocks_for(B, kWave), kWave, 0, st>>>(B, ds.n, ds.r, w, uniforms, alpha);
-    k_y_generic<TIn><<<(unsigned)M, kBlock, lds, st>>>(ds.d, ds.n * ds.r, H, W, Y, round_y);
-    k_zstats_generic<TIn><<<(unsigned)M, kBlock, lds, st>>>(ds.d, ds.V, ds.r, 0, U, Y, nullptr, lse, nullptr, z);
+    launch_draft_y(ds, ds.n * ds.r, H, W, G, Y, st);
+    launch_f32_kept_logits<TIn>(ds, (long)M, ds.n * ds.r, U, Y, z, at<float2>(ws, g.part), lse, st);
     k_sample_generic<<<(unsigned)(B * ds.n), kBlock, 0, st>>>(ds.V, ds.n, ds.r, z, lse, alpha, uniforms, tokens);
     if (logq) k_logq_generic<<<(unsigned)B, kWave, 0, st>>>(ds.V, ds.n, ds.r, logw, z, lse, tokens, logq);
     return hipGetLastError() == hipSuccess ? CP_HEAD_OK : CP_HEAD_ERR_LAUNCH;
@@ -733,11 +887,9 @@ int draft_sequential_t(const cp_head_desc &ds, const TIn *H, const TIn *W, const
     const size_t B = (size_t)ds.T, M = B * ds.n * ds.r;
     float *logw = at<float>(ws, g.logw), *w = at<float>(ws, g.w), *Y = at<float>(ws, g.Y);
     float *z = at<float>(ws, g.z), *lse = at<float>(ws, g.lse);
-    const size_t lds = (size_t)ds.d * sizeof(float);
-    const int round_y = ds.dtype == CP_HEAD_BF16 ? 1 : 0;
     k_gate<TIn><<<(unsigned)B, kWave, 0, st>>>(ds.d, ds.r, H, G, logw, w);
-    k_y_generic<TIn><<<(unsigned)M, kBlock, lds, st>>>(ds.d, ds.n * ds.r, H, W, Y, round_y);
-    k_zstats_generic<TIn><<<(unsigned)M, kBlock, lds, st>>>(ds.d, ds.V, ds.r, 0, U, Y, nullptr, lse, nullptr, z);
+    launch_draft_y(ds, ds.n * ds.r, H, W, G, Y, st);
+    launch_f32_kept_logits<TIn>(ds, (long)M, ds.n * ds.r, U, Y, z, at<float2>(ws, g.part), lse, st);
     k_sample_sequential_generic<<<(unsigned)B, kBlock, 0, st>>>(ds.V, ds.n, ds.r, z, lse, logw, uniforms, tokens, logq);
     return hipGetLastError() == hipSuccess ? CP_HEAD_OK : CP_HEAD_ERR_LAUNCH;
 }
@@ -758,49 +910,33 @@ int generic_draft_sequential(const cp_head_desc &ds, const void *H, const void *
 size_t generic_workspace_bytes(const cp_head_desc &ds, int op) { return generic_ws(ds, op).total; }
 
 size_t generic_bwd_chunk_rows(const cp_head_desc &ds) { return generic_chunk_rows(ds); }
-
-namespace {
-template <typename TIn>
-void fwd_rows_t(const cp_head_desc &ds, const TIn *H, const TIn *W, const TIn *U, const TIn *G, const int32_t *X,
-                const GenericFwdBuffers &b, hipStream_t st)
-{
-    const size_t M = (size_t)ds.T * ds.n * ds.r, lds = (size_t)ds.d * sizeof(float);
-    k_gate<TIn><<<(unsigned)ds.T, kWave, 0, st>>>(ds.d, ds.r, H, G, b.logw, b.w);
-    k_y_generic<TIn><<<(unsigned)M, kBlock, lds, st>>>(ds.d, ds.n * ds.r, H, W, b.Y, 0);
-    k_zstats_generic<TIn><<<(unsigned)M, kBlock, lds, st>>>(ds.d, ds.V, ds.r, 0, U, b.Y, X, b.lse, b.C, nullptr);
-}
-}  // namespace
+long generic_dz_row(const cp_head_desc &ds) { return dz_row(ds); }
 
 int generic_fwd_rows(const cp_head_desc &ds, const void *H, const void *W, const void *U, const void *G,
                      const int32_t *X, void *ctx, void *ws, GenericFwdBuffers *out, hipStream_t st)
 {
-    const CtxLayout cl = ctx_layout(ds, false);
-    const GenericWs g = generic_ws(ds, CP_HEAD_OP_LOSS_FWD);
-    GenericFwdBuffers b;
-    b.lse = at<float>(ctx, cl.lse);
-    b.w = at<float>(ctx, cl.w);
-    b.gamma = at<float>(ctx, cl.gamma);
-    b.Y = at<float>(ctx, cl.Y);
-    b.logw = at<float>(ws, g.logw);
-    b.C = at<float>(ws, g.C);
+    const GenericFwdBuffers b = fwd_buffers(ds, ctx, ws);
+    float2 *part = at<float2>(ws, generic_ws(ds, CP_HEAD_OP_LOSS_FWD).part);
     if (ds.dtype == CP_HEAD_FP32)
-        fwd_rows_t<float>(ds, (const float *)H, (const float *)W, (const float *)U, (const float *)G, X, b, st);
+        fwd_rows_t<float>(ds, (const float *)H, (const float *)W, (const float *)U, (const float *)G, X, b, part, nullptr, st);
     else
-        fwd_rows_t<bf16_t>(ds, (const bf16_t *)H, (const bf16_t *)W, (const bf16_t *)U, (const bf16_t *)G, X, b, st);
+        fwd_rows_t<bf16_t>(ds, (const bf16_t *)H, (const bf16_t *)W, (const bf16_t *)U, (const bf16_t *)G, X, b, part, nullptr, st);
     *out = b;
     return hipGetLastError() == hipSuccess ? CP_HEAD_OK : CP_HEAD_ERR_LAUNCH;
 }
 
-void generic_logits_rows(const cp_head_desc &ds, const void *U, const float *Y, size_t m0, size_t Mc, float *z,
+void generic_logits_rows(const cp_head_desc &ds, const void *U, const float *Y, size_t m0, size_t Mc, float *z, long ldz,
                          hipStream_t st)
 {
-    const size_t lds = (size_t)ds.d * sizeof(float);
+    const long d = ds.d, V = ds.V;
+    const F32Plan plan = f32_plan((long)generic_chunk_rows(ds), V, d, false);
+    const EpiF32Logits epi{nullptr, 0, 1, 0, nullptr, 1, nullptr, z, ldz};
     if (ds.dtype == CP_HEAD_FP32)
-        k_zstats_generic<float><<<(unsigned)Mc, kBlock, lds, st>>>(ds.d, ds.V, ds.r, m0, (const float *)U, Y, nullptr,
-                                                                   nullptr, nullptr, z);
+        launch_f32<float, float, false, false>(f32_problem<false, false>(Y + m0 * d, d, (const float *)U, d, (long)Mc, V, d, d, plan),
+                                               plan.kind, epi, st);
     else
-        k_zstats_generic<bf16_t><<<(unsigned)Mc, kBlock, lds, st>>>(ds.d, ds.V, ds.r, m0, (const bf16_t *)U, Y, nullptr,
-                                                                    nullptr, nullptr, z);
+        launch_f32<float, bf16_t, false, false>(f32_problem<false, false>(Y + m0 * d, d, (const bf16_t *)U, d, (long)Mc, V, d, d, plan),
+                                                plan.kind, epi, st);
 }
 
 int generic_bwd_from_dz(const cp_head_desc &ds, const void *H, const void *W, const void *U, const void *G,
@@ -860,7 +996,7 @@ int generic_draft(const cp_head_desc &ds, const void *H, const void *W, const vo
 
 // ---- first-token marginal on the plain path: z of the r first-head rows is stored, then mixed
 struct GenericFirstWs {
-    size_t logw, w, Y, z, lse, total;
+    size_t logw, w, Y, z, lse, part, total;
 };
 static GenericFirstWs generic_first_ws(const cp_head_desc &ds)
 {
@@ -873,6 +1009,7 @@ static GenericFirstWs generic_first_ws(const cp_head_desc &ds)
     g.Y = take(rows * ds.d * 4);
     g.z = take(rows * ds.V * 4);
     g.lse = take(rows * 4);
+    g.part = take(rows * f32_slots(f32_plan((long)rows, ds.V, ds.d, false).kind, ds.V) * sizeof(float2));
     g.total = off;
     return g;
 }
@@ -894,12 +1031,10 @@ static int first_token_t(const cp_head_desc &ds, const TIn *H, const TIn *W, con
     const size_t rows = (size_t)ds.T * ds.r;
     float *logw = at<float>(ws, g.logw), *w = at<float>(ws, g.w), *Y = at<float>(ws, g.Y);
     float *z = at<float>(ws, g.z), *lse = at<float>(ws, g.lse);
-    const size_t lds = (size_t)ds.d * sizeof(float);
-    const int round_y = ds.dtype == CP_HEAD_BF16 ? 1 : 0;
     k_gate<TIn><<<(unsigned)ds.T, kWave, 0, st>>>(ds.d, ds.r, H, G, logw, w);
     // the first head's matrices are the first r blocks of W, so its rows are (b, a) with nr = r
-    k_y_generic<TIn><<<(unsigned)rows, kBlock, lds, st>>>(ds.d, ds.r, H, W, Y, round_y);
-    k_zstats_generic<TIn><<<(unsigned)rows, kBlock, lds, st>>>(ds.d, ds.V, ds.r, 0, U, Y, nullptr, lse, nullptr, z);
+    launch_draft_y(ds, ds.r, H, W, G, Y, st);
+    launch_f32_kept_logits<TIn>(ds, (long)rows, ds.r, U, Y, z, at<float2>(ws, g.part), lse, st);
     launch_first_token_mix(ds, z, (size_t)ds.V, lse, logw, logp, st);
     return hipGetLastError() == hipSuccess ? CP_HEAD_OK : CP_HEAD_ERR_LAUNCH;
 }
@@ -930,25 +1065,36 @@ int aux_balance(const cp_head_desc &ds, const void *H, const void *G, int64_t *c
     return hipGetLastError() == hipSuccess ? CP_HEAD_OK : CP_HEAD_ERR_LAUNCH;
 }
 
-// ---- full heads on the plain path
+// ---- full heads on the plain path: one product per (s, a) over the positions, whose head rows are
+// m = t n r + sa.  A chunk's gradients are stored [positions, n r, V], so that dH and dF are one product each.
 struct GenericFullWs {
-    size_t logw, C, dg, dZ, total;
+    size_t logw, C, part, dg, dZ, partial, total;
     size_t chunk_pos;
+    F32Plan z, zc, dh, df, dG;
 };
 static GenericFullWs generic_full_ws(const cp_head_desc &ds)
 {
     GenericFullWs g;
     const size_t T = (size_t)ds.T, nr = (size_t)ds.n * ds.r;
+    const long d = ds.d, V = ds.V, nrV = (long)nr * V;
     // whole positions per chunk: at most 512 MiB of fp32 logit gradients at a time, at least one position
     size_t pos = ((size_t)1 << 27) / ((size_t)ds.V * nr);
     if (pos < 1) pos = 1;
     g.chunk_pos = pos < T ? pos : (T ? T : 1);
+    const long P = (long)g.chunk_pos;
+    g.z = f32_plan((long)T, V, d, false);
+    g.zc = f32_plan(P, V, d, false);
+    g.dh = f32_plan(P, d, nrV, true);
+    g.df = f32_plan(nrV, d, P, false);
+    g.dG = f32_plan(ds.r, d, (long)T, true);
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes); return o; };
     g.logw = take(T * ds.r * 4);
     g.C = take(T * nr * 4);
+    g.part = take(T * nr * f32_slots(g.z.kind, V) * sizeof(float2));
     g.dg = take(T * ds.r * 4);
     g.dZ = take(g.chunk_pos * nr * ds.V * 4);
+    g.partial = take(std::max(g.dh.scratch(P, d), g.dG.scratch(ds.r, d)));
     g.total = off;
     return g;
 }
@@ -960,14 +1106,17 @@ static int full_fwd_t(const cp_head_desc &ds, const TIn *H, const TIn *F, const 
 {
     const CtxLayout cl = ctx_layout(ds, false);      // lse, w, gamma at the same offsets; no y is kept
     const GenericFullWs g = generic_full_ws(ds);
-    const size_t M = (size_t)ds.T * ds.n * ds.r;
+    const long T = (long)ds.T, d = ds.d, V = ds.V, nr = (long)ds.n * ds.r;
     float *lse = at<float>(ctx, cl.lse), *w = at<float>(ctx, cl.w), *gamma = at<float>(ctx, cl.gamma);
     float *logw = at<float>(ws, g.logw), *C = at<float>(ws, g.C);
-    const size_t lds = (size_t)ds.d * sizeof(float);
-    k_gate<TIn><<<(unsigned)ds.T, kWave, 0, st>>>(ds.d, ds.r, H, G, logw, w);
-    k_full_row_generic<TIn><<<(unsigned)M, kBlock, lds, st>>>(ds.d, ds.V, ds.n, ds.r, 0, H, F, X, lse, C, nullptr, nullptr,
-                                                              0.f, nullptr);
-    k_mixture<<<(unsigned)ds.T, kWave, 0, st>>>(ds.n, ds.r, logw, C, loss, gamma, -1.f);
+    float2 *part = at<float2>(ws, g.part);
+    const int slots = f32_slots(g.z.kind, V);
+    const F32Plan pg = f32_plan(T, ds.r, d, false);
+    launch_f32<TIn, TIn, false, false>(f32_problem<false, false>(H, d, G, d, T, ds.r, d, d, pg), pg.kind, EpiF32Store{logw, ds.r, 0, nullptr}, st);
+    for (long sa = 0; sa < nr; ++sa)
+        launch_f32<TIn, TIn, false, false>(f32_problem<false, false>(H, d, F + sa * V * d, d, T, V, d, d, g.z), g.z.kind,
+                                           EpiF32Logits{part, slots, nr, sa, X, ds.r, C, nullptr, 0}, st);
+    k_position_finish<<<(unsigned)T, kBlock, (size_t)nr * sizeof(float), st>>>(ds.n, ds.r, slots, part, X, C, lse, logw, w, gamma, loss);
     return hipGetLastError() == hipSuccess ? CP_HEAD_OK : CP_HEAD_ERR_LAUNCH;
 }
 
@@ -978,26 +1127,34 @@ static int full_bwd_t(const cp_head_desc &ds, const TIn *H, const TIn *F, const 
 {
     const CtxLayout cl = ctx_layout(ds, false);
     const GenericFullWs g = generic_full_ws(ds);
-    const size_t T = (size_t)ds.T, Tr = T * ds.r;
-    const int nr = ds.n * ds.r;
-    float *lse = const_cast<float *>(at<float>(ctx, cl.lse));
-    const float *w = at<float>(ctx, cl.w), *gamma = at<float>(ctx, cl.gamma);
-    float *dg = at<float>(ws, g.dg), *dZ = at<float>(ws, g.dZ);
-    const size_t lds = (size_t)ds.d * sizeof(float);
-    k_dgate<<<blocks_for(Tr, kBlock), kBlock, 0, st>>>(Tr, ds.r, w, gamma, dloss, scale, dg);
-    int first = 1;
-    for (size_t t0 = 0; t0 < T; t0 += g.chunk_pos) {
-        const size_t Tc = (T - t0 < g.chunk_pos) ? T - t0 : g.chunk_pos;
-        k_full_row_generic<TIn><<<(unsigned)(Tc * nr), kBlock, lds, st>>>(ds.d, ds.V, ds.n, ds.r, t0 * nr, H, F, X, lse,
-                                                                          nullptr, gamma, dloss, scale, dZ);
-        k_dh_full_generic<TIn><<<blocks_for(Tc * ds.d, kBlock), kBlock, 0, st>>>(ds.d, ds.V, nr, ds.r, t0, Tc, F, G, dZ,
-                                                                                 dg, dH);
+    const long T = (long)ds.T, d = ds.d, V = ds.V, nr = (long)ds.n * ds.r, nrV = nr * V;
+    const float *lse = at<float>(ctx, cl.lse), *w = at<float>(ctx, cl.w), *gamma = at<float>(ctx, cl.gamma);
+    float *dg = at<float>(ws, g.dg), *dZ = at<float>(ws, g.dZ), *partial = at<float>(ws, g.partial);
+    for (long t0 = 0; t0 < T; t0 += (long)g.chunk_pos) {
+        const long Tc = std::min((long)g.chunk_pos, T - t0);
+        for (long sa = 0; sa < nr; ++sa)
+            launch_f32<TIn, TIn, false, false>(f32_problem<false, false>(H + t0 * d, d, F + sa * V * d, d, Tc, V, d, d, g.zc), g.zc.kind,
+                                               EpiF32Dz{dZ + sa * V, nrV, V, (size_t)(t0 * nr), nr, sa, ds.n, ds.r, X, lse, w, gamma,
+                                                        dloss, scale, dg}, st);
+        // dH = dZ F + dg G (contraction over heads and vocabulary), dF (+)= dZ^T H (over the chunk's positions)
+        const F32Problem ph = f32_problem<false, true>((const float *)dZ, nrV, F, d, Tc, d, nrV, nrV, g.dh);
+        launch_f32<float, TIn, false, true>(ph, g.dh.kind, EpiF32Dh<TIn>{dH + t0 * d, dg + t0 * ds.r, G, ds.r, partial}, st);
+        AddSplits add{};
+        add.N = d; add.r = ds.r; add.dg = dg + t0 * ds.r; add.G = G;
+        add.add(g.dh, Tc, d, partial, dH + t0 * d, false);
+        launch_add_splits<TIn>(add, st);
         if (dF)
-            k_df_generic<TIn><<<blocks_for((size_t)nr * ds.V * ds.d, kBlock), kBlock, 0, st>>>(ds.d, ds.V, nr, t0, Tc, H,
-                                                                                               dZ, dF, first ? 0 : 1);
-        first = 0;
+            launch_f32<float, TIn, true, true>(f32_problem<true, true>((const float *)dZ, nrV, H + t0 * d, d, nrV, d, Tc, Tc, g.df),
+                                               g.df.kind, EpiF32Store{dF, d, t0 ? 1 : 0, nullptr}, st);
     }
-    if (dG) k_dg_generic<TIn><<<blocks_for((size_t)ds.r * ds.d, kBlock), kBlock, 0, st>>>(T, ds.d, ds.r, H, dg, dG);
+    if (dG) {
+        launch_f32<float, TIn, true, true>(f32_problem<true, true>((const float *)dg, ds.r, H, d, ds.r, d, T, T, g.dG), g.dG.kind,
+                                           EpiF32Store{dG, d, 0, partial}, st);
+        AddSplits add{};
+        add.gate_job = -1;
+        add.add(g.dG, ds.r, d, partial, dG, false);
+        launch_add_splits<TIn>(add, st);
+    }
     return hipGetLastError() == hipSuccess ? CP_HEAD_OK : CP_HEAD_ERR_LAUNCH;
 }
 
