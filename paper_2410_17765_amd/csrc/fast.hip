@@ -948,38 +948,6 @@ __global__ void k_add_gate_to_dh(size_t T, int d, int r, const bf16_t *__restric
     dH[idx] = acc;
 }
 
-// dG[a, j] = sum_t dg[t, a] H[t, j] in two deterministic stages: partial sums over chunks of 512
-// positions (one thread per column j, eight experts at a time), then the chunks in increasing order.
-constexpr int kGateChunk = 512;
-__global__ void __launch_bounds__(kBlock) k_dgate_partial(size_t T, int d, int r, const bf16_t *__restrict__ H,
-                                                          const float *__restrict__ dg, float *__restrict__ partial)
-{
-    const int j = blockIdx.x * kBlock + threadIdx.x;
-    const size_t tc = blockIdx.y;
-    if (j >= d) return;
-    const size_t t0 = tc * kGateChunk, t1 = min(T, t0 + kGateChunk);
-    for (int a0 = 0; a0 < r; a0 += 8) {
-        float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        for (size_t t = t0; t < t1; ++t) {
-            const float h = bf16_to_f32(H[t * d + j]);
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                if (a0 + e < r) acc[e] += dg[t * r + a0 + e] * h;
-        }
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-            if (a0 + e < r) partial[(tc * r + a0 + e) * d + j] = acc[e];
-    }
-}
-__global__ void k_dgate_reduce(int chunks, int d, int r, const float *__restrict__ partial, float *__restrict__ dG)
-{
-    const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= (size_t)r * d) return;
-    float acc = 0.f;
-    for (int c = 0; c < chunks; ++c) acc += partial[(size_t)c * r * d + idx];
-    dG[idx] = acc;
-}
-
 // ------------------------------------------------------------------------------------------
 // full heads (eq. 6 as printed: one V x d matrix F_sa per (s, a), no shared unembedding)
 // Per-row quantities of this variant are kept head-major, index sa * T + t: every (s, a) runs its own
@@ -1089,7 +1057,7 @@ inline BwdWs bwd_ws(const cp_head_desc &ds)
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes); return o; };
     b.coef = take(M * 16);
     b.dg = take(T * ds.r * 4);
-    b.dGpart = take(((T + kGateChunk - 1) / kGateChunk) * ds.r * ds.d * 4);
+    b.dGpart = take(gate_chunks(T) * ds.r * ds.d * 4);
     b.Ut = take((size_t)ds.d * b.ldV * 2);
     b.Wt = take((size_t)ds.d * b.ldN * 2);
     b.dY = take(M * ds.d * 2);
@@ -1175,7 +1143,7 @@ inline FullBwdWs full_bwd_ws(const cp_head_desc &ds)
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes); return o; };
     b.coef = take(M * 16);
     b.dg = take(T * ds.r * 4);
-    b.dGpart = take(((T + kGateChunk - 1) / kGateChunk) * ds.r * ds.d * 4);
+    b.dGpart = take(gate_chunks(T) * ds.r * ds.d * 4);
     b.Ht = take((size_t)ds.d * b.ldT * 2);
     b.dZ = take(b.chunk * b.Vp * 2);
     b.dZt = take((size_t)ds.V * b.ldM * 2);
@@ -1356,11 +1324,7 @@ static int bwd_below_dy(const cp_head_desc &ds, const bf16_t *H, const bf16_t *W
         // dW_sa = dY_sa^T H   (contraction over positions: both operands K-major, any number of positions)
         launch_gemm_nt<CfgTN>("gemm_dw", dY, (long)nrd, (int)nrd, H, d, d, (int)T, EpiStoreF32{dW, (long)d, (int)nrd, d, 0}, st,
                               kGroupRowsNarrow);
-    if (dG) {
-        const unsigned chunks = (unsigned)((T + kGateChunk - 1) / kGateChunk);
-        k_dgate_partial<<<dim3(blocks_for((size_t)d, kBlock), chunks), kBlock, 0, st>>>(T, d, r, H, dg, dGpart);
-        k_dgate_reduce<<<blocks_for((size_t)r * d, kBlock), kBlock, 0, st>>>((int)chunks, d, r, dGpart, dG);
-    }
+    if (dG) launch_gate_gradient_bf16(ds, H, dg, dGpart, dG, st);
     return hipGetLastError() == hipSuccess ? CP_HEAD_OK : CP_HEAD_ERR_LAUNCH;
 }
 
@@ -1502,7 +1466,7 @@ inline StepWs step_ws(const cp_head_desc &ds)
     f.w = take(T * ds.r * 4);
     f.gamma = take(T * ds.r * 4);
     f.dg = take(T * ds.r * 4);
-    f.dGpart = take(((T + kGateChunk - 1) / kGateChunk) * ds.r * ds.d * 4);
+    f.dGpart = take(gate_chunks(T) * ds.r * ds.d * 4);
     f.Ut = take((size_t)ds.d * (f.Vp + 64) * 2);
     f.Wt = take((size_t)ds.d * (nrd + 64) * 2);
     f.dY = take(M * ds.d * 2);
@@ -1751,12 +1715,7 @@ int fast_full_loss_bwd(const cp_head_desc &ds, const void *Hv, const void *Fv, c
         first_chunk = 0;
     }
     k_add_gate_to_dh<<<blocks_for(T * d, kBlock), kBlock, 0, st>>>(T, d, r, G, dg, dH);       // + G^T dg
-    if (dG) {
-        float *part = at<float>(ws, b.dGpart);
-        const unsigned chunks = (unsigned)((T + kGateChunk - 1) / kGateChunk);
-        k_dgate_partial<<<dim3(blocks_for((size_t)d, kBlock), chunks), kBlock, 0, st>>>(T, d, r, H, dg, part);
-        k_dgate_reduce<<<blocks_for((size_t)r * d, kBlock), kBlock, 0, st>>>((int)chunks, d, r, part, dG);
-    }
+    if (dG) launch_gate_gradient_bf16(ds, H, dg, at<float>(ws, b.dGpart), dG, st);
     return hipGetLastError() == hipSuccess ? CP_HEAD_OK : CP_HEAD_ERR_LAUNCH;
 }
 

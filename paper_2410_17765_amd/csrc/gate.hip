@@ -1,0 +1,215 @@
+// The gate of the matrix-core path (bf16 storage, d a multiple of 64): G h for all positions, as log-softmax
+// (eq. 7), as arg-max counts (eq. 10), and the gate gradient dG = dg^T H.
+//
+// All three read H once and do almost nothing else: they are bound by that stream (T d 2 bytes).
+#include "cp_internal.hpp"
+
+namespace cph {
+
+namespace {
+
+constexpr int kBlock = 256, kWaves = kBlock / kWave;
+
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+// H and G are only promised to be bf16 arrays: 16 bytes at any even address (one load instruction all the same)
+typedef uint32_t u32x4_any_t __attribute__((ext_vector_type(4), aligned(2)));
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ u32x4_t load16(const bf16_t *p) { return *reinterpret_cast<const u32x4_any_t *>(p); }
+
+// ------------------------------------------------------------------------------------------
+// G h of 16 positions per step of a workgroup on the 16x16x32 matrix instruction.
+// The kernel it replaces walked H with 2-byte loads, once per expert, one position per wavefront: 353 us for the
+// arg-max at T = 16384, d = 4096, r = 8 (0.4 TB/s); this one takes 35 us (3.9 TB/s), and 6.6 instead of 22 us for the
+// log-softmax at T = 1500, d = 768, r = 5.  Here the four wavefronts share the contraction (blocks of 64
+// columns in turn), a lane loads 32 consecutive bytes of its row per block, so that four lanes cover a cache line of
+// H, and the partial products meet in LDS.  Experts beyond r repeat the last row of G and are dropped.
+// The order of the columns inside a block of 64 is the same permutation for both operands.
+// ------------------------------------------------------------------------------------------
+constexpr int kRows = 16;
+
+// out[row][expert] for the rows t0 .. t0+15 (rows past T repeat the last one); 16 NG >= r
+template <int NG>
+__device__ __forceinline__ void gate_rows(size_t t0, size_t T, int d, int r, const bf16_t *__restrict__ H,
+                                          const bf16_t *__restrict__ G, float (&red)[kWaves][kRows][NG * 16 + 1])
+{
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int row = lane & 15, q = lane >> 4;
+    const size_t t = t0 + row < T ? t0 + row : T - 1;
+    const bf16_t *h = H + t * d + q * 16;
+    const bf16_t *g[NG];
+#pragma unroll
+    for (int e = 0; e < NG; ++e) g[e] = G + (size_t)min(e * 16 + row, r - 1) * d + q * 16;
+    f32x4_t acc[NG];
+#pragma unroll
+    for (int e = 0; e < NG; ++e) acc[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    // four blocks in flight per wavefront; a block past the end re-reads the last one and is left out
+    constexpr int UN = 4;
+    const int blocks = d / 64;
+    for (int kb = wave; kb < blocks; kb += kWaves * UN) {
+        u32x4_t a[UN][2], b[UN][NG][2];
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            const int k = min(kb + kWaves * u, blocks - 1) * 64;
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                a[u][c] = load16(h + k + 8 * c);
+#pragma unroll
+                for (int e = 0; e < NG; ++e) b[u][e][c] = load16(g[e] + k + 8 * c);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            if (kb + kWaves * u >= blocks) break;
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+#pragma unroll
+                for (int e = 0; e < NG; ++e)
+                    acc[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a[u][c]),
+                                                                     __builtin_bit_cast(bf16x8_t, b[u][e][c]), acc[e], 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < NG; ++e)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) red[wave][4 * q + v][e * 16 + row] = acc[e][v];
+}
+
+// logw = log_softmax(G h), w = exp(logw)   (eq. 7)
+template <int NG>
+__global__ void __launch_bounds__(kBlock) k_gate_bf16(size_t T, int d, int r, const bf16_t *__restrict__ H, const bf16_t *__restrict__ G,
+                                                      float *__restrict__ logw, float *__restrict__ w)
+{
+    __shared__ float red[kWaves][kRows][NG * 16 + 1];
+    const size_t t0 = (size_t)blockIdx.x * kRows;
+    gate_rows<NG>(t0, T, d, r, H, G, red);
+    __syncthreads();
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int row = wave; row < kRows && t0 + row < T; row += kWaves) {
+        float mine = -INFINITY;
+        if (lane < r) mine = (red[0][row][lane] + red[1][row][lane]) + (red[2][row][lane] + red[3][row][lane]);
+        const float mx = wave_max(mine);
+        const float lse = mx + logf(wave_sum(lane < r ? expf(mine - mx) : 0.f));
+        if (lane < r) {
+            logw[(t0 + row) * r + lane] = mine - lse;
+            w[(t0 + row) * r + lane] = expf(mine - lse);
+        }
+    }
+}
+
+// counts[a] += positions whose largest gate is expert a, the first index on ties (eq. 10)
+template <int NG>
+__global__ void __launch_bounds__(kBlock) k_aux_argmax_bf16(size_t T, int d, int r, const bf16_t *__restrict__ H,
+                                                            const bf16_t *__restrict__ G, unsigned long long *__restrict__ counts)
+{
+    __shared__ float red[kWaves][kRows][NG * 16 + 1];
+    __shared__ unsigned int hist[64];
+    if (threadIdx.x < 64) hist[threadIdx.x] = 0;
+    for (size_t t0 = (size_t)blockIdx.x * kRows; t0 < T; t0 += (size_t)gridDim.x * kRows) {
+        gate_rows<NG>(t0, T, d, r, H, G, red);
+        __syncthreads();
+        const int row = threadIdx.x;
+        if (row < kRows && t0 + row < T) {
+            float best = -INFINITY;
+            int arg = 0;
+            for (int a = 0; a < r; ++a) {
+                const float p = (red[0][row][a] + red[1][row][a]) + (red[2][row][a] + red[3][row][a]);
+                if (p > best) { best = p; arg = a; }
+            }
+            atomicAdd(&hist[arg], 1u);
+        }
+        __syncthreads();
+    }
+    if ((int)threadIdx.x < r && hist[threadIdx.x]) atomicAdd(&counts[threadIdx.x], (unsigned long long)hist[threadIdx.x]);
+}
+
+// dG[a, j] = sum_t dg[t, a] H[t, j] in two deterministic stages.  First stage: a workgroup takes kGateChunk positions and
+// 512 columns, a lane eight of them (16-byte loads) for eight experts at a time; the four wavefronts take the positions
+// in turn and add up in LDS, wavefront 0 first.  Second stage: the chunks in increasing order.
+// (One thread per column over 512 positions, 2-byte loads: 234-266 us at T = 1500, d = 768 as at T = 4096, d = 4096,
+// a chain of 512 load latencies; this pair takes 23 us at the former.)
+__global__ void __launch_bounds__(kBlock) k_dgate_partial(size_t T, int d, int r, const bf16_t *__restrict__ H,
+                                                          const float *__restrict__ dg, float *__restrict__ partial)
+{
+    __shared__ float red[kWaves][8][64 + 1];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int j = blockIdx.y * 512 + lane * 8;
+    const size_t t0 = (size_t)blockIdx.x * kGateChunk, t1 = t0 + kGateChunk < T ? t0 + kGateChunk : T;
+    for (int a0 = 0; a0 < r; a0 += 8) {
+        float acc[8][8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+#pragma unroll
+            for (int c = 0; c < 8; ++c) acc[e][c] = 0.f;
+        if (j < d) {
+#pragma unroll 4
+            for (size_t t = t0 + wave; t < t1; t += kWaves) {
+                const u32x4_t x = load16(H + t * d + j);
+                float g[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) g[e] = dg[t * r + min(a0 + e, r - 1)];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const float lo = __uint_as_float(x[c] << 16), hi = __uint_as_float(x[c] & 0xFFFF0000u);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        acc[e][2 * c] += g[e] * lo;
+                        acc[e][2 * c + 1] += g[e] * hi;
+                    }
+                }
+            }
+        }
+        // column c of every lane's eight in turn: [wave][expert][lane], then thread (expert pair, lane) adds the waves
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) red[wave][e][lane] = acc[e][c];
+            __syncthreads();
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int e = wave + 4 * h;
+                const float s = ((red[0][e][lane] + red[1][e][lane]) + red[2][e][lane]) + red[3][e][lane];
+                if (a0 + e < r && j < d) partial[((size_t)blockIdx.x * r + a0 + e) * d + j + c] = s;
+            }
+            __syncthreads();
+        }
+    }
+}
+__global__ void __launch_bounds__(kBlock) k_dgate_reduce(int chunks, size_t rd, const float *__restrict__ partial, float *__restrict__ dG)
+{
+    const size_t idx = (size_t)blockIdx.x * kBlock + threadIdx.x;
+    if (idx >= rd) return;
+    float acc = 0.f;
+#pragma unroll 8
+    for (int c = 0; c < chunks; ++c) acc += partial[(size_t)c * rd + idx];
+    dG[idx] = acc;
+}
+
+}  // namespace
+
+void launch_gate_bf16(const cp_head_desc &ds, const bf16_t *H, const bf16_t *G, float *logw, float *w, hipStream_t st)
+{
+    const size_t T = (size_t)ds.T;
+    if (ds.r <= 16) k_gate_bf16<1><<<blocks_for(T, kRows), kBlock, 0, st>>>(T, ds.d, ds.r, H, G, logw, w);
+    else k_gate_bf16<4><<<blocks_for(T, kRows), kBlock, 0, st>>>(T, ds.d, ds.r, H, G, logw, w);
+}
+
+void launch_aux_argmax_bf16(const cp_head_desc &ds, const bf16_t *H, const bf16_t *G, unsigned long long *counts, hipStream_t st)
+{
+    const size_t T = (size_t)ds.T;
+    // at most two workgroups per compute unit: each ends with up to r atomic additions to the same few counters
+    const unsigned tiles = blocks_for(T, kRows), blocks = tiles < 512 ? tiles : 512;
+    if (ds.r <= 16) k_aux_argmax_bf16<1><<<blocks, kBlock, 0, st>>>(T, ds.d, ds.r, H, G, counts);
+    else k_aux_argmax_bf16<4><<<blocks, kBlock, 0, st>>>(T, ds.d, ds.r, H, G, counts);
+}
+
+void launch_gate_gradient_bf16(const cp_head_desc &ds, const bf16_t *H, const float *dg, float *partial, float *dG, hipStream_t st)
+{
+    const unsigned chunks = (unsigned)gate_chunks((size_t)ds.T);
+    const size_t rd = (size_t)ds.r * ds.d;
+    k_dgate_partial<<<dim3(chunks, blocks_for((size_t)ds.d, 512)), kBlock, 0, st>>>((size_t)ds.T, ds.d, ds.r, H, dg, partial);
+    k_dgate_reduce<<<blocks_for(rd, kBlock), kBlock, 0, st>>>((int)chunks, rd, partial, dG);
+}
+
+}  // namespace cph

@@ -1055,7 +1055,9 @@ int aux_balance(const cp_head_desc &ds, const void *H, const void *G, int64_t *c
     k_fill_zero_u64<<<1, 64, 0, st>>>(ds.r, c);
     if (ds.T > 0) {
         const unsigned blocks = (unsigned)std::min<size_t>(((size_t)ds.T + kWavesPerBlock - 1) / kWavesPerBlock, 4096);
-        if (ds.dtype == CP_HEAD_FP32)
+        if (use_fast_path(ds))
+            launch_aux_argmax_bf16(ds, (const bf16_t *)H, (const bf16_t *)G, c, st);
+        else if (ds.dtype == CP_HEAD_FP32)
             k_aux_argmax<float><<<blocks, kBlock, 0, st>>>((size_t)ds.T, ds.d, ds.r, (const float *)H, (const float *)G, c);
         else
             k_aux_argmax<bf16_t><<<blocks, kBlock, 0, st>>>((size_t)ds.T, ds.d, ds.r, (const bf16_t *)H,
@@ -1186,6 +1188,7 @@ int generic_full_loss_bwd(const cp_head_desc &ds, const void *H, const void *F, 
 void launch_gate(const cp_head_desc &ds, const void *H, const void *G, float *logw, float *w, hipStream_t st)
 {
     if (ds.T == 0) return;
+    if (use_fast_path(ds)) return launch_gate_bf16(ds, (const bf16_t *)H, (const bf16_t *)G, logw, w, st);
     if (ds.dtype == CP_HEAD_FP32)
         k_gate<float><<<(unsigned)ds.T, kWave, 0, st>>>(ds.d, ds.r, (const float *)H, (const float *)G, logw, w);
     else
