@@ -37,6 +37,14 @@ struct EpiStoreBf16 {
     bf16_t *lo;     // may be null
     long ldc;
     int M, N;
+    static constexpr bool kSplittable = true;
+    __device__ __forceinline__ void put(int row, int col, float a) const
+    {
+        const size_t at = (size_t)row * ldc + col;
+        const bf16_t h = f32_to_bf16(a);
+        hi[at] = h;
+        if (lo) lo[at] = f32_to_bf16(a - bf16_to_f32(h));
+    }
     template <class C>
     __device__ void run(f32x4_t (&acc)[C::TM16][C::TN16], int row0, int col0, int lane, int wave, int, char *smem) const
     {
@@ -58,6 +66,12 @@ struct EpiStoreF32 {
     long ldc;
     int M, N;
     int accumulate;
+    static constexpr bool kSplittable = true;
+    __device__ __forceinline__ void put(int row, int col, float a) const
+    {
+        float *o = C + (size_t)row * ldc + col;
+        *o = accumulate ? a + *o : a;
+    }
     template <class Cf>
     __device__ void run(f32x4_t (&acc)[Cf::TM16][Cf::TN16], int row0, int col0, int lane, int wave, int, char *smem) const
     {
@@ -998,8 +1012,34 @@ __global__ void k_full_bwd_coefficients(size_t T, int n, int r, const float *__r
 // workspace layouts
 // ------------------------------------------------------------------------------------------
 
+// Scratch for splitting the last round of a call's products (the largest of them), none with CP_HEAD_MIN_WORKSPACE
+struct SplitNeed {
+    size_t bytes = 0;
+    bool off;
+    explicit SplitNeed(const cp_head_desc &ds) : off((ds.flags & CP_HEAD_MIN_WORKSPACE) != 0) {}
+    template <class C>
+    void product(size_t M, size_t N, size_t K)
+    {
+        const size_t b = off ? 0 : split_scratch_bytes<C>(M, N, K, kGroupRowsNarrow);
+        if (b > bytes) bytes = b;
+    }
+    // the chunks of `total` rows: whole ones and the rest
+    template <class F>
+    static void chunks(size_t total, size_t chunk, F f)
+    {
+        if (total >= chunk) f(chunk);
+        if (total % chunk) f(total % chunk);
+    }
+};
+inline SplitScratch split_scratch(void *ws, size_t off, size_t bytes)
+{
+    SplitScratch s;
+    if (bytes) { s.p = at<void>(ws, off); s.bytes = bytes; }
+    return s;
+}
+
 struct FwdWs {
-    size_t logw, C, Ylo, part, total;
+    size_t logw, C, Ylo, part, split, split_bytes, total;
     int parts;
 };
 inline FwdWs fwd_ws(const cp_head_desc &ds)
@@ -1014,6 +1054,10 @@ inline FwdWs fwd_ws(const cp_head_desc &ds)
     f.Ylo = take(M * ds.d * 2);
     // with kept logits the statistics live in ctx: the backward pass needs the maxima again
     f.part = (ds.flags & CP_HEAD_KEEP_LOGITS) ? off : take(M * f.parts * sizeof(float2));
+    SplitNeed need(ds);
+    need.product<Cfg>((size_t)ds.T, (size_t)ds.n * ds.r * ds.d, (size_t)ds.d);       // y
+    f.split_bytes = need.bytes;
+    f.split = take(need.bytes);
     f.total = off;
     return f;
 }
@@ -1040,8 +1084,20 @@ inline size_t bwd_chunk_rows(const cp_head_desc &ds)
     return rows < M ? rows : (M ? M : 1);
 }
 
+// the products of the backward pass below dz
+inline void need_below_dz(const cp_head_desc &ds, size_t chunk, SplitNeed &need)
+{
+    const size_t T = (size_t)ds.T, d = (size_t)ds.d, V = (size_t)ds.V, nrd = (size_t)ds.n * ds.r * d;
+    SplitNeed::chunks(T * ds.n * ds.r, chunk, [&](size_t Mc) {
+        need.product<CfgBlockedA>(Mc, d, round_up(V, 64));                           // dY
+        need.product<Cfg>(V, d, round_up(Mc, 64));                                   // dU
+    });
+    need.product<Cfg>(T, d, nrd);                                                    // dH
+    need.product<CfgTN>(nrd, d, T);                                                  // dW
+}
+
 struct BwdWs {
-    size_t coef, dg, dGpart, Ut, Wt, dY, dZ, dZt, Yt, total;
+    size_t coef, dg, dGpart, Ut, Wt, dY, dZ, dZt, Yt, split, split_bytes, total;
     size_t Vp, chunk, chunk_p;
     size_t ldV, ldM, ldN;   // leading dimensions of the transposed operands (K padded to 64, plus 64)
 };
@@ -1064,6 +1120,10 @@ inline BwdWs bwd_ws(const cp_head_desc &ds)
     b.dZ = take(round_up(b.chunk, 256) * b.Vp * 2);   // stored in blocks of 256 rows x 64 columns
     b.dZt = take((size_t)ds.V * b.ldM * 2);
     b.Yt = take((size_t)ds.d * b.ldM * 2);
+    SplitNeed need(ds);
+    need_below_dz(ds, b.chunk, need);
+    b.split_bytes = need.bytes;
+    b.split = take(need.bytes);
     b.total = off;
     return b;
 }
@@ -1126,7 +1186,7 @@ inline size_t full_chunk_rows(const cp_head_desc &ds)
 }
 
 struct FullBwdWs {
-    size_t coef, dg, dGpart, Ht, dZ, dZt, total;
+    size_t coef, dg, dGpart, Ht, dZ, dZt, split, split_bytes, total;
     size_t Vp, Tp, chunk, chunk_p;
     size_t ldT, ldM;
 };
@@ -1147,6 +1207,13 @@ inline FullBwdWs full_bwd_ws(const cp_head_desc &ds)
     b.Ht = take((size_t)ds.d * b.ldT * 2);
     b.dZ = take(b.chunk * b.Vp * 2);
     b.dZt = take((size_t)ds.V * b.ldM * 2);
+    SplitNeed need(ds);
+    SplitNeed::chunks(T, b.chunk, [&](size_t Tc) {
+        need.product<CfgNN>(Tc, (size_t)ds.d, b.Vp);                                 // dH
+        need.product<Cfg>((size_t)ds.V, (size_t)ds.d, round_up(Tc, 64));             // dF
+    });
+    b.split_bytes = need.bytes;
+    b.split = take(need.bytes);
     b.total = off;
     return b;
 }
@@ -1275,7 +1342,8 @@ int fast_fwd_rows(const cp_head_desc &ds, const void *Hv, const void *Wv, const 
     if (cl.keep && (cl.parts != f.parts || kKeptTile != Cfg::WTN)) return CP_HEAD_ERR_UNSUPPORTED;
 
     launch_gate(ds, Hv, Gv, logw, w, st);                                                      // eq. 7
-    launch_gemm_nt<Cfg>("gemm_y", H, d, T, W, d, nrd, d, EpiStoreBf16{Y, Ylo, (long)nrd, T, nrd}, st, kGroupRowsNarrow);   // y = W_sa h
+    launch_gemm_nt<Cfg>("gemm_y", H, d, T, W, d, nrd, d, EpiStoreBf16{Y, Ylo, (long)nrd, T, nrd}, st, kGroupRowsNarrow,
+                        NoSideJob{0}, -1, -1, split_scratch(ws, f.split, f.split_bytes));                       // y = W_sa h
     if (cl.keep)                                                                               // z = U y, statistics, z kept
         launch_gemm_nt<Cfg>("gemm_z_stats_keep", Y, d, (int)M, U, d, V, d,
                             EpiRowStatsKeep{part, f.parts, (int)M, V, at<uint16_t>(ctx, cl.zs), (long)cl.Vp, (int)cl.Vp}, st);
@@ -1310,7 +1378,8 @@ int fast_loss_fwd(const cp_head_desc &ds, const void *Hv, const void *Wv, const 
 // The backward pass below dY: dH = dY W + G^T dg, dW = dY^T H, dG = dg^T H.  Wt: scratch for W^T [d, n r d + 64];
 // dGpart: the partial sums of the two-stage gate gradient.
 static int bwd_below_dy(const cp_head_desc &ds, const bf16_t *H, const bf16_t *W, const bf16_t *G, const bf16_t *dY,
-                        const float *dg, float *dH, float *dW, float *dG, bf16_t *Wt, float *dGpart, hipStream_t st)
+                        const float *dg, float *dH, float *dW, float *dG, bf16_t *Wt, float *dGpart,
+                        const SplitScratch &split, hipStream_t st)
 {
     const int d = ds.d, r = ds.r;
     const size_t T = (size_t)ds.T, nrd = (size_t)ds.n * r * d;
@@ -1318,12 +1387,12 @@ static int bwd_below_dy(const cp_head_desc &ds, const bf16_t *H, const bf16_t *W
     // dH = dY W + G^T dg   (contraction over (s, a, k))
     transpose_bf16(W, d, (int)nrd, d, Wt, ldN, (int)nrd, st);         // Wt[d, nrd]
     launch_gemm_nt<Cfg>("gemm_dh", dY, (long)nrd, (int)T, Wt, ldN, d, (int)nrd, EpiStoreF32{dH, (long)d, (int)T, d, 0}, st,
-                        kGroupRowsNarrow);
+                        kGroupRowsNarrow, NoSideJob{0}, -1, -1, split);
     k_add_gate_to_dh<<<blocks_for(T * d, kBlock), kBlock, 0, st>>>(T, d, r, G, dg, dH);
     if (dW)
         // dW_sa = dY_sa^T H   (contraction over positions: both operands K-major, any number of positions)
         launch_gemm_nt<CfgTN>("gemm_dw", dY, (long)nrd, (int)nrd, H, d, d, (int)T, EpiStoreF32{dW, (long)d, (int)nrd, d, 0}, st,
-                              kGroupRowsNarrow);
+                              kGroupRowsNarrow, NoSideJob{0}, -1, -1, split);
     if (dG) launch_gate_gradient_bf16(ds, H, dg, dGpart, dG, st);
     return hipGetLastError() == hipSuccess ? CP_HEAD_OK : CP_HEAD_ERR_LAUNCH;
 }
@@ -1333,19 +1402,20 @@ static int bwd_below_dy(const cp_head_desc &ds, const bf16_t *H, const bf16_t *W
 // touches 256 separate cache lines of it, and the product, which streams the chunk's 4 GiB of it from HBM, runs 4 %
 // slower.  Ut: U^T [d, Vp + 64]; Yt: scratch for the chunk's Y^T [d, Mcp + 64].
 static void bwd_chunk_products(const cp_head_desc &ds, const bf16_t *dZ, const bf16_t *dZt, long ldM, const bf16_t *Yc,
-                               int Mc, const bf16_t *Ut, bf16_t *Yt, bf16_t *dYc, float *dU, bool accumulate, hipStream_t st)
+                               int Mc, const bf16_t *Ut, bf16_t *Yt, bf16_t *dYc, float *dU, bool accumulate,
+                               const SplitScratch &split, hipStream_t st)
 {
     const int d = ds.d, V = ds.V;
     const int Vp = (int)round_up((size_t)V, 64), Mcp = (int)round_up((size_t)Mc, 64);
     const long ldV = (long)Vp + 64;
     // dY = dz U   (contraction over the vocabulary)
     launch_gemm_nt<CfgBlockedA>("gemm_dy", dZ, Vp, Mc, Ut, ldV, d, Vp, EpiStoreBf16{dYc, nullptr, (long)d, Mc, d}, st,
-                                kGroupRowsNarrow);
+                                kGroupRowsNarrow, NoSideJob{0}, -1, -1, split);
     if (dU) {
         // dU += dz^T Y   (contraction over the rows of the chunk)
         transpose_bf16(Yc, d, Mc, d, Yt, ldM, Mcp, st);               // Yt[d, Mcp]
         launch_gemm_nt<Cfg>("gemm_du", dZt, ldM, V, Yt, ldM, d, Mcp, EpiStoreF32{dU, (long)d, V, d, accumulate ? 1 : 0}, st,
-                            kGroupRowsNarrow);
+                            kGroupRowsNarrow, NoSideJob{0}, -1, -1, split);
     }
 }
 
@@ -1364,6 +1434,7 @@ int fast_bwd_from_dz(const cp_head_desc &ds, const void *Hv, const void *Wv, con
     bf16_t *Ut = at<bf16_t>(ws, b.Ut), *Wt = at<bf16_t>(ws, b.Wt), *dY = at<bf16_t>(ws, b.dY);
     bf16_t *dZ = at<bf16_t>(ws, b.dZ), *dZt = at<bf16_t>(ws, b.dZt), *Yt = at<bf16_t>(ws, b.Yt);
     const int Vp = (int)b.Vp;
+    const SplitScratch split = split_scratch(ws, b.split, b.split_bytes);
 
     transpose_bf16(U, d, V, d, Ut, (long)b.ldV, Vp, st);              // Ut[d, Vp]
     int first = 1;
@@ -1374,10 +1445,10 @@ int fast_bwd_from_dz(const cp_head_desc &ds, const void *Hv, const void *Wv, con
         // recompute z for the chunk; the epilogue turns it into dz (bf16); the tiles over V also
         // cover the padding columns V..Vp-1, which the epilogue zero-fills
         dz_launch(user, Yc, Mc, Mcp, m0, dZ, (long)Vp, true, dU ? dZt : nullptr, (long)b.ldM, st);
-        bwd_chunk_products(ds, dZ, dZt, (long)b.ldM, Yc, Mc, Ut, Yt, dY + m0 * d, dU, !first, st);
+        bwd_chunk_products(ds, dZ, dZt, (long)b.ldM, Yc, Mc, Ut, Yt, dY + m0 * d, dU, !first, split, st);
         first = 0;
     }
-    return bwd_below_dy(ds, H, W, G, dY, dg, dH, dW, dG, Wt, at<float>(ws, b.dGpart), st);
+    return bwd_below_dy(ds, H, W, G, dY, dg, dH, dW, dG, Wt, at<float>(ws, b.dGpart), split, st);
 }
 
 bool fast_dims_fit(const cp_head_desc &ds) { return dims_fit(ds); }
@@ -1445,7 +1516,7 @@ int fast_loss_bwd(const cp_head_desc &ds, const void *Hv, const void *Wv, const 
 
 // Positions per chunk: whole positions whose head rows fit the backward pass's bound on logit-sized buffers.
 struct StepWs {
-    size_t logw, w, gamma, dg, dGpart, Ut, Wt, dY, C, lse, coef, Yc, Ylo, part, zs, dZ, dZt, Yt, total;
+    size_t logw, w, gamma, dg, dGpart, Ut, Wt, dY, C, lse, coef, Yc, Ylo, part, zs, dZ, dZt, Yt, split, split_bytes, total;
     size_t Vp, pos, rows, ldM;
     int parts;
 };
@@ -1480,6 +1551,11 @@ inline StepWs step_ws(const cp_head_desc &ds)
     f.dZ = take(round_up(f.rows, 256) * f.Vp * 2);   // stored in blocks of 256 rows x 64 columns
     f.dZt = take((size_t)ds.V * f.ldM * 2);
     f.Yt = take((size_t)ds.d * f.ldM * 2);
+    SplitNeed need(ds);
+    SplitNeed::chunks(T, f.pos, [&](size_t P) { need.product<Cfg>(P, nrd, (size_t)ds.d); });      // y
+    need_below_dz(ds, f.rows, need);
+    f.split_bytes = need.bytes;
+    f.split = take(need.bytes);
     f.total = off;
     return f;
 }
@@ -1510,6 +1586,7 @@ int fast_loss_step(const cp_head_desc &ds, const void *Hv, const void *Wv, const
     float2 *part = at<float2>(ws, f.part);
     uint16_t *zs = at<uint16_t>(ws, f.zs);
     const int Vp = (int)f.Vp;
+    const SplitScratch split = split_scratch(ws, f.split, f.split_bytes);
 
     bf16_t *Ut = at<bf16_t>(ws, f.Ut), *dZt = at<bf16_t>(ws, f.dZt), *Yt = at<bf16_t>(ws, f.Yt);
     launch_gate(ds, Hv, Gv, logw, w, st);                                                             // eq. 7, all positions
@@ -1524,7 +1601,7 @@ int fast_loss_step(const cp_head_desc &ds, const void *Hv, const void *Wv, const
         const int32_t *Xc = X + t0 * n;
         // forward of the chunk: y, statistics of z with the logits kept, log-normalisers and C (eq. 5, 8), mixture (eq. 9)
         launch_gemm_nt<Cfg>("gemm_y", H + t0 * d, d, (int)P, W, d, (int)nrd, d, EpiStoreBf16{Yc, Ylo, (long)nrd, (int)P, (int)nrd}, st,
-                            kGroupRowsNarrow);
+                            kGroupRowsNarrow, NoSideJob{0}, -1, -1, split);
         launch_gemm_nt<Cfg>("gemm_z_stats_keep", Yc, d, Mc, U, d, V, d, EpiRowStatsKeep{part, f.parts, Mc, V, zs, (long)Vp, Vp}, st);
         k_row_finish<<<blocks_for((size_t)Mc, kBlock / kWave), kBlock, 0, st>>>((size_t)Mc, d, r, f.parts, part, Yc, Ylo, U, Xc, lse, C);
         launch_mixture(sub, logw + t0 * r, C, loss + t0, gamma + t0 * r, -1.f, st);
@@ -1534,10 +1611,10 @@ int fast_loss_step(const cp_head_desc &ds, const void *Hv, const void *Wv, const
                                                                             dg + t0 * r);
         launch_dz_from_kept(KeptLogits{zs, part, (long)Vp, f.parts}, 0, rowinfo, LossDzRule{}, Mc, Mcp, V, dZ, (long)Vp, true,
                             dU ? dZt : nullptr, (long)f.ldM, st);
-        bwd_chunk_products(ds, dZ, dZt, (long)f.ldM, Yc, Mc, Ut, Yt, dY + m0 * d, dU, !first, st);
+        bwd_chunk_products(ds, dZ, dZt, (long)f.ldM, Yc, Mc, Ut, Yt, dY + m0 * d, dU, !first, split, st);
         first = 0;
     }
-    return bwd_below_dy(ds, H, W, G, dY, dg, dH, dW, dG, at<bf16_t>(ws, f.Wt), at<float>(ws, f.dGpart), st);
+    return bwd_below_dy(ds, H, W, G, dY, dg, dH, dW, dG, at<bf16_t>(ws, f.Wt), at<float>(ws, f.dGpart), split, st);
 }
 
 int fast_draft(const cp_head_desc &ds, const void *Hv, const void *Wv, const void *Uv, const void *Gv,
@@ -1684,6 +1761,7 @@ int fast_full_loss_bwd(const cp_head_desc &ds, const void *Hv, const void *Fv, c
     bf16_t *dZ = at<bf16_t>(ws, b.dZ), *dZt = at<bf16_t>(ws, b.dZt);
     const int Vp = (int)b.Vp, Tp = (int)b.Tp;
     const long ldT = (long)b.ldT, ldM = (long)b.ldM;
+    const SplitScratch split = split_scratch(ws, b.split, b.split_bytes);
 
     k_full_bwd_coefficients<<<blocks_for(M, kBlock), kBlock, 0, st>>>(T, n, r, w, gamma, lse, dloss, scale, X, rowinfo, dg);
     if (dF) transpose_bf16(H, d, (int)T, d, Ht, ldT, Tp, st);         // Ht[d, Tp]
@@ -1705,12 +1783,12 @@ int fast_full_loss_bwd(const cp_head_desc &ds, const void *Hv, const void *Fv, c
             // dH += dz F_sa   (contraction over the vocabulary; F_sa as it is stored is K-major for this product, and
             // a transposed copy of every head matrix per chunk would cost more than the K-major loop does)
             launch_gemm_nt<CfgNN>("full_gemm_dh", dZ, Vp, Tc, Fsa, d, d, Vp,
-                                  EpiStoreF32{dH + t0 * d, (long)d, Tc, d, sa ? 1 : 0}, st, kGroupRowsNarrow, NoSideJob{0}, -1, V);
+                                  EpiStoreF32{dH + t0 * d, (long)d, Tc, d, sa ? 1 : 0}, st, kGroupRowsNarrow, NoSideJob{0}, -1, V, split);
             // dF_sa += dz^T H   (contraction over the positions of the chunk)
             if (dF)
                 launch_gemm_nt<Cfg>("full_gemm_df", dZt, ldM, V, Ht + t0, ldT, d, Tcp,
                                     EpiStoreF32{dF + (size_t)sa * V * d, (long)d, V, d, first_chunk ? 0 : 1}, st,
-                                    kGroupRowsNarrow);
+                                    kGroupRowsNarrow, NoSideJob{0}, -1, -1, split);
         }
         first_chunk = 0;
     }

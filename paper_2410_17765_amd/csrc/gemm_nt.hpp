@@ -413,8 +413,24 @@ struct NoSideJob {
     int blocks;
     __device__ void run(int, char *) const {}
 };
+// row / column of accumulator element v of block (i, j) for lane l, relative to the sub-tile origin
+__device__ __forceinline__ int acc_row(int i, int v, int lane) { return i * 16 + 4 * (lane >> 4) + v; }
+__device__ __forceinline__ int acc_col(int j, int lane) { return j * 16 + (lane & 15); }
+
+// Epilogues whose result is a plain function of the sum over K (kSplittable) may have the launch's last round split along
+// K (split_plan): put(row, col, value) stores one element.
+template <class Epi, class = void> struct IsSplittable { static constexpr bool value = false; };
+template <class Epi> struct IsSplittable<Epi, decltype((void)Epi::kSplittable)> { static constexpr bool value = true; };
+
+// The accumulators of a tile as they lie in the registers: element (i, j) of thread `tid` is one 16-byte piece.
+template <class Cfg>
+__device__ __forceinline__ size_t partial_index(int item, int i, int j, int tid)
+{
+    return (((size_t)item * Cfg::TM16 + i) * Cfg::TN16 + j) * Cfg::THREADS + tid;
+}
+
 template <class Cfg, class Epi, class Side>
-__global__ void __launch_bounds__(Cfg::THREADS) k_gemm_nt(GemmOperands g, Epi epi, Side side)
+__global__ void __launch_bounds__(Cfg::THREADS) k_gemm_nt(GemmOperands g, Epi epi, Side side, SplitPlan split, f32x4_t *partial)
 {
     __shared__ __attribute__((aligned(16))) char smem[Cfg::LDS_BYTES];
     int bid = blockIdx.x;
@@ -425,6 +441,18 @@ __global__ void __launch_bounds__(Cfg::THREADS) k_gemm_nt(GemmOperands g, Epi ep
         }
         bid -= side.blocks;
     }
+    int item = -1;
+    if (IsSplittable<Epi>::value && split.parts > 1 && bid >= split.first) {
+        int part, k0, k1;
+        item = bid - split.first;
+        split_item(split, item, (g.K + Cfg::BK - 1) / Cfg::BK, bid, part, k0, k1);
+        // the operands from K-step k0 on
+        g.A += Cfg::AKM ? (size_t)k0 * Cfg::BK * g.lda : (size_t)k0 * (Cfg::ABL ? Cfg::BM * Cfg::BK : Cfg::BK);
+        g.B += Cfg::BKM ? (size_t)k0 * Cfg::BK * g.ldb : (size_t)k0 * (Cfg::BBL ? Cfg::BN * Cfg::BK : Cfg::BK);
+        g.ka_rows = max(g.ka_rows - k0 * Cfg::BK, 0);
+        g.kb_rows = max(g.kb_rows - k0 * Cfg::BK, 0);
+        g.K = min(g.K, k1 * Cfg::BK) - k0 * Cfg::BK;
+    }
     int tm, tn;
     if (!tile_of_block(bid, g.tiles_m, g.tiles_n, g.gm, tm, tn)) return;
     f32x4_t acc[Cfg::TM16][Cfg::TN16];
@@ -432,13 +460,70 @@ __global__ void __launch_bounds__(Cfg::THREADS) k_gemm_nt(GemmOperands g, Epi ep
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int row0 = tm * Cfg::BM + (wave / Cfg::WN) * Cfg::WTM;
     const int col0 = tn * Cfg::BN + (wave % Cfg::WN) * Cfg::WTN;
+    if (IsSplittable<Epi>::value && item >= 0) {
+#pragma unroll
+        for (int i = 0; i < Cfg::TM16; ++i)
+            if (row0 + i * 16 < g.M) {                  // blocks past the last row are not read back either
+#pragma unroll
+                for (int j = 0; j < Cfg::TN16; ++j) partial[partial_index<Cfg>(item, i, j, threadIdx.x)] = acc[i][j];
+            }
+        return;
+    }
     epi.template run<Cfg>(acc, row0, col0, lane, wave, tn, smem);
+}
+
+// Second stage of a split round: one workgroup per tile and 16-row block of its wavefronts; the parts in increasing order.
+template <class Cfg, class Epi>
+__global__ void __launch_bounds__(Cfg::THREADS) k_gemm_add_parts(GemmOperands g, Epi epi, SplitPlan split, const f32x4_t *__restrict__ partial)
+{
+    const int slot = blockIdx.x / Cfg::TM16, i = blockIdx.x % Cfg::TM16;
+    int tm, tn;
+    if (!tile_of_block(split.first + slot, g.tiles_m, g.tiles_n, g.gm, tm, tn)) return;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int row = tm * Cfg::BM + (wave / Cfg::WN) * Cfg::WTM + acc_row(i, 0, lane);
+    const int col = tn * Cfg::BN + (wave % Cfg::WN) * Cfg::WTN + acc_col(0, lane);
+    if (row - 4 * (lane >> 4) >= g.M) return;
+    f32x4_t sum[Cfg::TN16];
+#pragma unroll
+    for (int j = 0; j < Cfg::TN16; ++j) sum[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 2
+    for (int p = 0; p < split.parts; ++p)
+#pragma unroll
+        for (int j = 0; j < Cfg::TN16; ++j) sum[j] += partial[partial_index<Cfg>(p * split.tail + slot, i, j, threadIdx.x)];
+#pragma unroll
+    for (int j = 0; j < Cfg::TN16; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            if (row + v < g.M && col + j * 16 < g.N) epi.put(row + v, col + j * 16, sum[j][v]);
+}
+
+// Scratch for the partial tiles of a split round; none: launches are never split.
+struct SplitScratch {
+    void *p = nullptr;
+    size_t bytes = 0;
+};
+template <class Cfg>
+inline SplitPlan plan_split(int M, int N, int K, int gm, size_t scratch_bytes)
+{
+    constexpr size_t kItemBytes = (size_t)Cfg::BM * Cfg::BN * 4;
+    static_assert(Cfg::BM == 256 && Cfg::BN == 256, "one workgroup per compute unit; the plan's times are this tile's");
+    const int grid = gemm_grid((M + Cfg::BM - 1) / Cfg::BM, (N + Cfg::BN - 1) / Cfg::BN, gm);
+    const size_t items = scratch_bytes / kItemBytes;
+    return split_plan(grid, 256, (K + Cfg::BK - 1) / Cfg::BK, items < kMaxSplitItems ? (int)items : kMaxSplitItems);
+}
+// bytes of scratch with which the launch's last round is split as it is best; at most 128 MiB
+template <class Cfg>
+inline size_t split_scratch_bytes(size_t M, size_t N, size_t K, int gm)
+{
+    if (!M || !N || !K) return 0;
+    const SplitPlan p = plan_split<Cfg>((int)M, (int)N, (int)K, gm, ~(size_t)0);
+    return p.parts > 1 ? (size_t)p.parts * p.tail * Cfg::BM * Cfg::BN * 4 : 0;
 }
 
 template <class Cfg, class Epi, class Side = NoSideJob>
 inline void launch_gemm_nt(const char *name, const bf16_t *A, long lda, int M, const bf16_t *B, long ldb, int N, int K,
                            const Epi &epi, hipStream_t st, int gm = kGroupRowsWide, const Side &side = Side{0},
-                           int ka_rows = -1, int kb_rows = -1)
+                           int ka_rows = -1, int kb_rows = -1, const SplitScratch &scratch = SplitScratch())
 {
     ProfileScope prof(name, 2.0 * (double)M * (double)N * (double)K, st);
     GemmOperands g;
@@ -447,8 +532,18 @@ inline void launch_gemm_nt(const char *name, const bf16_t *A, long lda, int M, c
     g.tiles_m = (M + Cfg::BM - 1) / Cfg::BM;
     g.tiles_n = (N + Cfg::BN - 1) / Cfg::BN;
     g.gm = gm;
+    int grid = gemm_grid(g.tiles_m, g.tiles_n, g.gm);
+    SplitPlan split{grid, 0, 1};
+    f32x4_t *partial = static_cast<f32x4_t *>(scratch.p);
+    if constexpr (IsSplittable<Epi>::value && Cfg::BM == 256 && Cfg::BN == 256) {
+        if (partial) split = plan_split<Cfg>(M, N, K, gm, scratch.bytes);
+        if (split.parts > 1) grid = split.first + split.tail * split.parts;
+    }
     const int extra = Side::kActive ? side.blocks : 0;
-    k_gemm_nt<Cfg, Epi, Side><<<gemm_grid(g.tiles_m, g.tiles_n, g.gm) + extra, Cfg::THREADS, 0, st>>>(g, epi, side);
+    k_gemm_nt<Cfg, Epi, Side><<<grid + extra, Cfg::THREADS, 0, st>>>(g, epi, side, split, partial);
+    if constexpr (IsSplittable<Epi>::value && Cfg::BM == 256 && Cfg::BN == 256)
+        if (split.parts > 1)
+            k_gemm_add_parts<Cfg, Epi><<<split.tail * Cfg::TM16, Cfg::THREADS, 0, st>>>(g, epi, split, partial);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -461,9 +556,6 @@ inline void launch_gemm_nt(const char *name, const bf16_t *A, long lda, int M, c
 // only ever indexed with constants and stay in registers.
 // ---------------------------------------------------------------------------------------------
 
-// row / column of accumulator element v of block (i, j) for lane l, relative to the sub-tile origin
-__device__ __forceinline__ int acc_row(int i, int v, int lane) { return i * 16 + 4 * (lane >> 4) + v; }
-__device__ __forceinline__ int acc_col(int j, int lane) { return j * 16 + (lane & 15); }
 
 // P0, P1 restrict the call to the 32-row passes P0 .. P1-1 (default: all of them).  blocked: dst is stored block by
 // block (blocked64_index) instead of row-major.

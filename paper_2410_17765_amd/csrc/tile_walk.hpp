@@ -55,6 +55,39 @@ inline int gemm_grid(int tiles_m, int tiles_n, int GM)
     return 8 * (w.band_tiles + w.rest_per_xcd);
 }
 
+// The last, partial round of a launch, split along K.  A launch of G workgroups runs in rounds of `slots` (the
+// workgroups the chip holds at a time); the G % slots of the last round leave the rest of the chip idle for a whole
+// tile's time (264 tiles: 8 busy of 256).  Their K-steps are dealt to `parts` workgroups each, which leave fp32 partial
+// tiles in scratch, and a small launch adds those up in order and stores them.  Measured at T = 1500, d = 768, V = 50257,
+// n = 3, r = 5: dY (264 tiles, 786 K-steps) 2416 -> 1336 us, dU (591 tiles) 1610 -> 1385, dH (18 tiles, 180 K-steps) 238 -> 60.
+struct SplitPlan {
+    int first;      // workgroups before this one compute whole tiles
+    int tail;       // workgroups of the last round (a multiple of 8, as `first` is: a part stays on its tile's XCD)
+    int parts;      // workgroups per tile of the last round; 1: nothing is split
+};
+constexpr int kMaxSplitItems = 512;
+// Estimated times in us, measured on 256 x 256 tiles: a K-step 1.6, the extra launch 6, an item's partial tile written and
+// read back 0.13 (256 KB each way at about 4 TB/s).  A part is at least four K-steps long.
+inline SplitPlan split_plan(int grid, int slots, int k_steps, int max_items)
+{
+    SplitPlan best{grid / slots * slots, grid % slots, 1};
+    double least = 1.6 * k_steps;
+    for (int parts = 2; parts * best.tail <= max_items && parts * 4 <= k_steps && best.tail; ++parts) {
+        const int items = parts * best.tail, rounds = (items + slots - 1) / slots;
+        const double t = rounds * 1.6 * ((k_steps + parts - 1) / parts) + 6.0 + 0.13 * items;
+        if (t < least) { least = t; best.parts = parts; }
+    }
+    return best;
+}
+// Item i of the split round -> the workgroup id whose tile it works on, and its K-steps [k0, k1).
+CPH_HD void split_item(const SplitPlan &p, int i, int k_steps, int &bid, int &part, int &k0, int &k1)
+{
+    part = i / p.tail;
+    bid = p.first + i % p.tail;
+    k0 = (int)((long)part * k_steps / p.parts);
+    k1 = (int)((long)(part + 1) * k_steps / p.parts);
+}
+
 // Element (row, col) of a bf16 matrix stored block by block, [rows / 256][ld / 64][256][64] (ld a multiple of 64, the
 // rows allocated up to a multiple of 256): the layout in which the main loop reads an operand flagged ABL / BBL, one
 // K-step of a tile being 32 KB of consecutive memory.

@@ -45,6 +45,32 @@ int main()
                     }
                 ++shapes;
             }
+    // the split last round: whole rounds stay whole, every K-step of every tile of the last round belongs to one part, no
+    // part is empty, and a part keeps the XCD (workgroup id mod 8) of its tile
+    for (int tm = 1; tm <= 70; ++tm)
+        for (int tn : tns)
+            for (int k_steps : {1, 3, 4, 8, 12, 33, 180, 786})
+                for (int max_items : {0, 64, 512}) {
+                    const int grid = gemm_grid(tm, tn, 4);
+                    const SplitPlan p = split_plan(grid, 256, k_steps, max_items);
+                    if (p.parts < 1 || p.first % 256 || p.first + p.tail != grid || (p.parts > 1 && p.parts * p.tail > max_items)) {
+                        std::printf("plan: grid %d steps %d items %d -> %d %d %d\n", grid, k_steps, max_items, p.first, p.tail, p.parts);
+                        return 1;
+                    }
+                    if (p.parts == 1) continue;
+                    std::vector<int> done((size_t)p.tail * k_steps, 0);
+                    for (int i = 0; i < p.parts * p.tail; ++i) {
+                        int bid, part, k0, k1;
+                        split_item(p, i, k_steps, bid, part, k0, k1);
+                        if (bid < p.first || bid >= grid || bid % 8 != (p.first + i) % 8 || part * p.tail + bid - p.first != i || k1 <= k0) {
+                            std::printf("item: grid %d steps %d item %d -> %d %d %d %d\n", grid, k_steps, i, bid, part, k0, k1);
+                            return 1;
+                        }
+                        for (int k = k0; k < k1; ++k) ++done[(size_t)(bid - p.first) * k_steps + k];
+                    }
+                    for (int c : done)
+                        if (c != 1) { std::printf("steps: grid %d steps %d\n", grid, k_steps); return 1; }
+                }
     // the block-by-block layout: a bijection onto [0, rows * ld) for rows a multiple of 256 and ld of 64, 8-column
     // pieces contiguous, and the 256 x 64 block of a tile's K-step contiguous
     for (long ld : {64L, 192L, 1024L})
