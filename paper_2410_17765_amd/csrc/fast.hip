@@ -457,6 +457,7 @@ __device__ __forceinline__ float wave_dot_bf16(const bf16_t *__restrict__ a, con
 // (fp64) exceeds u, clamped to r-1.  One block per row of the batch, a wavefront per expert at a time.
 // g_s: at least r floats of LDS.  uniforms = null: log w only.
 constexpr int kWideBlock = 1024;
+constexpr int kMaxSegCols = 128;                // columns of a statistics segment: 64 or 128
 __device__ __forceinline__ void draft_gate_pick_row(size_t b, int nwaves, float *g_s, int d, int n, int r,
                                                     const bf16_t *__restrict__ H, const bf16_t *__restrict__ G,
                                                     const float *__restrict__ uniforms, float *__restrict__ logw,
@@ -500,175 +501,6 @@ struct GatePickSide {
     }
 };
 
-// Per (b, s): the log-normalisers of its r head rows from the per-segment statistics (eq. 5), then for
-// the drawn expert's row the segment of the vocabulary in which the running sum of probabilities
-// passes u: segment masses exp(max_j - lse) * sum_j accumulated in vocabulary order in fp64
-// (lane-local runs, then a wavefront scan).  seg = -1 if the sum never passes u.
-__global__ void __launch_bounds__(kWideBlock) k_draft_lse_segment(int n, int r, int parts, const float2 *__restrict__ part,
-                                                              const int32_t *__restrict__ alpha,
-                                                              const float *__restrict__ uniforms,
-                                                              float *__restrict__ lse_out, int32_t *__restrict__ seg_out,
-                                                              double *__restrict__ base_out)
-{
-    __shared__ float lse_s[64];
-    const size_t bs = blockIdx.x;                 // b*n + s
-    const size_t b = bs / n;
-    const int s = (int)(bs % n);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int a = wave; a < r; a += kWideBlock / kWave) {
-        const float2 *pm = part + (bs * r + a) * parts;
-        float mx = -INFINITY, l = 0.f;
-        for (int p = lane; p < parts; p += kWave) {
-            const float2 q = pm[p];
-            if (q.x > mx) { l = l * __expf(mx - q.x) + q.y; mx = q.x; }
-            else if (q.x != -INFINITY) l += q.y * __expf(q.x - mx);
-        }
-        const float Mx = wave_max(mx);
-        const float L = wave_sum(mx == -INFINITY ? 0.f : l * __expf(mx - Mx));
-        const float lse = Mx + logf(L);
-        if (lane == 0) { lse_out[bs * r + a] = lse; lse_s[a] = lse; }
-    }
-    __syncthreads();
-    if (wave != 0) return;
-    const int astar = alpha[b];
-    const float l = lse_s[astar];
-    const double u = (double)uniforms[b * (1 + n) + 1 + s];
-    const float2 *pm = part + (bs * r + astar) * parts;
-    const int per = (parts + kWave - 1) / kWave;  // consecutive segments per lane: lane order = vocabulary order
-    const int lo = min(parts, lane * per), hi = min(parts, lo + per);
-    double sum = 0.0;
-    for (int j = lo; j < hi; ++j) {
-        const float2 q = pm[j];
-        sum += (q.x == -INFINITY) ? 0.0 : (double)(q.y * expf(q.x - l));
-    }
-    const double incl = wave_scan_inclusive(sum, lane);
-    const unsigned long long crossed = __ballot(incl > u);
-    if (crossed == 0ull) {
-        if (lane == 0) { seg_out[bs] = -1; base_out[bs] = 0.0; }
-        return;
-    }
-    const int first = __ffsll((long long)crossed) - 1;
-    if (lane == first) {
-        double c = incl - sum;
-        int seg = hi - 1;
-        for (int j = lo; j < hi; ++j) {
-            const float2 q = pm[j];
-            const double mj = (q.x == -INFINITY) ? 0.0 : (double)(q.y * expf(q.x - l));
-            if (c + mj > u) { seg = j; break; }
-            c += mj;
-        }
-        seg_out[bs] = seg;
-        base_out[bs] = c;
-    }
-}
-
-// Per (b, s): recompute the logits of the chosen segment (one wavefront per column, fp32 dot products
-// of U rows with the bf16 y) and continue the scan token by token: first index whose running sum
-// exceeds u; the last token of the segment if rounding between the two passes leaves none; V-1 if
-// the running sum over the whole vocabulary never passed u.
-constexpr int kPickBlock = 1024;
-__global__ void __launch_bounds__(kPickBlock) k_draft_logits_pick(int d, int V, int n, int r, int seg_cols,
-                                                                  const float *__restrict__ lse,
-                                                                  const bf16_t *__restrict__ Y,
-                                                                  const bf16_t *__restrict__ U,
-                                                                  const int32_t *__restrict__ alpha,
-                                                                  const int32_t *__restrict__ seg_in,
-                                                                  const double *__restrict__ base_in,
-                                                                  const float *__restrict__ uniforms,
-                                                                  int32_t *__restrict__ tokens)
-{
-    __shared__ float p_s[256];
-    const size_t bs = blockIdx.x;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int seg = seg_in[bs];
-    if (seg < 0) {
-        if (threadIdx.x == 0) tokens[bs] = V - 1;
-        return;
-    }
-    const size_t m = bs * r + alpha[bs / n];
-    const float l = lse[m];
-    const int v0 = seg * seg_cols, cols = min(seg_cols, V - v0);
-    // a wavefront owns up to four columns at a time and walks k for all of them together
-    constexpr int NW = kPickBlock / kWave, CW = 4;
-    const u32x4_t *yrow = reinterpret_cast<const u32x4_t *>(Y + m * d);
-    for (int c0 = wave * CW; c0 < seg_cols; c0 += NW * CW) {
-        float acc[CW] = {0.f, 0.f, 0.f, 0.f};
-        const u32x4_t *urow[CW];
-#pragma unroll
-        for (int e = 0; e < CW; ++e)
-            urow[e] = reinterpret_cast<const u32x4_t *>(U + (size_t)(v0 + min(c0 + e, cols - 1)) * d);
-        for (int k = lane; k < d / 8; k += kWave) {
-            const u32x4_t yv = yrow[k];
-            u32x4_t uv[CW];
-#pragma unroll
-            for (int e = 0; e < CW; ++e) uv[e] = urow[e][k];
-#pragma unroll
-            for (int e = 0; e < CW; ++e)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    acc[e] += __uint_as_float(uv[e][q] << 16) * __uint_as_float(yv[q] << 16);
-                    acc[e] += __uint_as_float(uv[e][q] & 0xFFFF0000u) * __uint_as_float(yv[q] & 0xFFFF0000u);
-                }
-        }
-#pragma unroll
-        for (int e = 0; e < CW; ++e) {
-            const float z = wave_sum(acc[e]);
-            if (lane == 0 && c0 + e < seg_cols) p_s[c0 + e] = (c0 + e < cols) ? expf(z - l) : 0.f;
-        }
-    }
-    __syncthreads();
-    if (wave != 0) return;
-    const double u = (double)uniforms[(bs / n) * (1 + n) + 1 + (bs % n)];
-    const int per = (seg_cols + kWave - 1) / kWave;
-    const int lo = lane * per;
-    double sum = 0.0;
-    for (int i = lo; i < lo + per && i < cols; ++i) sum += (double)p_s[i];
-    const double incl = base_in[bs] + wave_scan_inclusive(sum, lane);
-    const unsigned long long crossed = __ballot(incl > u);
-    if (crossed == 0ull) {
-        if (lane == 0) tokens[bs] = v0 + cols - 1;
-        return;
-    }
-    const int first = __ffsll((long long)crossed) - 1;
-    if (lane == first) {
-        double c = incl - sum;
-        int tok = v0 + min(cols, lo + per) - 1;
-        for (int i = lo; i < lo + per && i < cols; ++i) {
-            c += (double)p_s[i];
-            if (c > u) { tok = v0 + i; break; }
-        }
-        tokens[bs] = tok;
-    }
-}
-
-// logq[b] = logsumexp_a( log w_a + sum_s (z_sa[tok_s] - lse_sa) ): eq. 9 at the drawn tuple over all experts
-__global__ void __launch_bounds__(kWideBlock) k_draft_logq(int d, int n, int r, const float *__restrict__ logw,
-                                                       const float *__restrict__ lse, const bf16_t *__restrict__ Y,
-                                                       const bf16_t *__restrict__ U, const int32_t *__restrict__ tokens,
-                                                       float *__restrict__ logq)
-{
-    __shared__ float C_s[64 * 64];
-    const size_t b = blockIdx.x;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int nr = n * r;
-    for (int j = wave; j < nr; j += kWideBlock / kWave) {
-        const size_t m = b * nr + j;
-        const int tok = tokens[b * n + j / r];
-        const float zt = wave_dot_bf16(U + (size_t)tok * d, Y + m * d, d, lane);
-        if (lane == 0) C_s[j] = zt - lse[m];
-    }
-    __syncthreads();
-    if (wave != 0) return;
-    float a = -INFINITY;
-    if (lane < r) {
-        a = logw[b * r + lane];
-        for (int s = 0; s < n; ++s) a += C_s[s * r + lane];
-    }
-    const float mx = wave_max(a);
-    const float sum = wave_sum(lane < r ? expf(a - mx) : 0.f);
-    if (lane == 0) logq[b] = mx + logf(sum);
-}
-
 // Log-normaliser (eq. 5) of one row from its per-segment statistics, by one wavefront.
 __device__ __forceinline__ float row_lse_from_parts(const float2 *__restrict__ pm, int parts, int lane)
 {
@@ -693,6 +525,193 @@ __device__ __forceinline__ float row_lse_from_parts(const float2 *__restrict__ p
     const float Mx = wave_max(mx);
     const float L = wave_sum(mx == -INFINITY ? 0.f : l * __expf(mx - Mx));
     return Mx + logf(L);
+}
+
+// Block-wide search for the segment of the vocabulary in which a running sum of probabilities passes u: mass(j) of
+// the segments in vocabulary order, fp64, a run of consecutive segments per thread.  *seg_out is the segment, *base_out
+// the sum before it; if the sum never passes u, ~(last segment) and 0.  All kWideBlock threads.
+template <class F>
+__device__ __forceinline__ void find_segment(int parts, int last_seg, double u, F mass, int32_t *seg_out, double *base_out)
+{
+    __shared__ double wave_tot[kWideBlock / kWave];
+    __shared__ int first_wave[kWideBlock / kWave];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int per = (parts + kWideBlock - 1) / kWideBlock;
+    const int lo = min(parts, tid * per), hi = min(parts, lo + per);
+    double sum = 0.0;
+    for (int j = lo; j < hi; ++j) sum += mass(j);
+    double incl = wave_scan_inclusive(sum, lane);
+    if (lane == kWave - 1) wave_tot[wave] = incl;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) incl += wave_tot[w];
+    const unsigned long long crossed = __ballot(incl > u);
+    if (lane == 0) first_wave[wave] = crossed ? __ffsll((long long)crossed) - 1 : -1;
+    __syncthreads();
+    int at = -1;                                     // the first thread whose running sum passes u
+    for (int w = kWideBlock / kWave - 1; w >= 0; --w)
+        if (first_wave[w] >= 0) at = w * kWave + first_wave[w];
+    if (at < 0) {
+        if (tid == 0) { *seg_out = ~last_seg; *base_out = 0.0; }
+    } else if (tid == at) {
+        double c = incl - sum;
+        int seg = hi - 1;
+        for (int j = lo; j < hi; ++j) {
+            const double mj = mass(j);
+            if (c + mj > u) { seg = j; break; }
+            c += mj;
+        }
+        *seg_out = min(seg, last_seg);               // rounding may let the sum pass in the empty segments after it
+        *base_out = c;
+    }
+}
+
+// One wavefront continues that scan token by token through the `cols` tokens of the segment, prob(i) each: the first
+// index whose running sum exceeds u, the last one if rounding between the two passes leaves none.
+template <class F>
+__device__ __forceinline__ int wave_pick_token(int seg_cols, int cols, double base, double u, int lane, F prob)
+{
+    const int per = (seg_cols + kWave - 1) / kWave;
+    const int lo = lane * per;
+    double sum = 0.0;
+    for (int i = lo; i < lo + per && i < cols; ++i) sum += prob(i);
+    const double incl = base + wave_scan_inclusive(sum, lane);
+    const unsigned long long crossed = __ballot(incl > u);
+    if (crossed == 0ull) return cols - 1;
+    const int first = __ffsll((long long)crossed) - 1;
+    int tok = min(cols, lo + per) - 1;
+    if (lane == first) {
+        double c = incl - sum;
+        for (int i = lo; i < lo + per && i < cols; ++i) {
+            c += prob(i);
+            if (c > u) { tok = i; break; }
+        }
+    }
+    return __shfl(tok, first, kWave);
+}
+
+// Per (b, s): the log-normalisers of its r head rows from the per-segment statistics (eq. 5), then the segment in which
+// the running sum of the drawn expert's probabilities passes u.
+__global__ void __launch_bounds__(kWideBlock) k_draft_lse_segment(int n, int r, int parts, int last_seg,
+                                                                  const float2 *__restrict__ part,
+                                                                  const int32_t *__restrict__ alpha,
+                                                                  const float *__restrict__ uniforms,
+                                                                  float *__restrict__ lse_out, int32_t *__restrict__ seg_out,
+                                                                  double *__restrict__ base_out)
+{
+    __shared__ float lse_s[64];
+    const size_t bs = blockIdx.x;                 // b*n + s
+    const size_t b = bs / n;
+    const int s = (int)(bs % n);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int a = wave; a < r; a += kWideBlock / kWave) {
+        const float lse = row_lse_from_parts(part + (bs * r + a) * parts, parts, lane);
+        if (lane == 0) { lse_out[bs * r + a] = lse; lse_s[a] = lse; }
+    }
+    __syncthreads();
+    const int astar = alpha[b];
+    const float l = lse_s[astar];
+    const float2 *pm = part + (bs * r + astar) * parts;
+    find_segment(parts, last_seg, (double)uniforms[b * (1 + n) + 1 + s],
+                 [&](int j) {
+                     const float2 q = pm[j];
+                     return q.x == -INFINITY ? 0.0 : (double)(q.y * expf(q.x - l));
+                 },
+                 seg_out + bs, base_out + bs);
+}
+
+// The logits of a segment for the r head rows of a (row, draw), z[(row0 + a) * seg_cols + i] = U[v0 + i] . y[row0 + a]:
+// a workgroup per (b, draw), 16 tokens and 16 experts, on the 16x16x32 matrix instruction; its eight wavefronts share
+// the contraction in blocks of 64 columns (a lane loads 32 consecutive bytes of its row per block, four lanes a cache
+// line) and their partial products meet in LDS.  Bound by the latency of the cold rows of U: the rows of a segment are
+// spread over 4 or 8 workgroups with 16 lines per lane in flight each, where one workgroup per draw had the whole segment
+// (0.5 or 1 MB) to fetch: the draft call 397 -> 371 us at B = 1, d = 4096, V = 128256, n = 4, r = 8.  draw0, draws: (b, s) of workgroup x is b = x / draws, s = draw0 + x % draws; seg is indexed
+// by x.
+constexpr int kSegWaves = 8;
+__global__ void __launch_bounds__(kSegWaves * kWave) k_segment_logits(int d, int V, int n, int r, int seg_cols, int draw0,
+                                                                      int draws, const bf16_t *__restrict__ Y,
+                                                                      const bf16_t *__restrict__ U,
+                                                                      const int32_t *__restrict__ seg_in,
+                                                                      float *__restrict__ z)
+{
+    __shared__ float red[kSegWaves][16][17];
+    const int x = (int)blockIdx.x, code = seg_in[x];
+    const int v0 = (code < 0 ? ~code : code) * seg_cols + (int)blockIdx.y * 16;
+    if (v0 >= V) return;
+    const size_t row0 = ((size_t)(x / draws) * n + draw0 + x % draws) * r;
+    const int a0 = (int)blockIdx.z * 16;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int row = lane & 15, q = lane >> 4;
+    // tokens past V and experts past r repeat the last one: the former are never used, the latter not stored
+    const u32x4_t *pu = reinterpret_cast<const u32x4_t *>(U + (size_t)min(v0 + row, V - 1) * d + q * 16);
+    const u32x4_t *py = reinterpret_cast<const u32x4_t *>(Y + (row0 + min(a0 + row, r - 1)) * d + q * 16);
+    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+    constexpr int UN = 4;
+    const int blocks = d / 64;
+    for (int kb = wave; kb < blocks; kb += kSegWaves * UN) {
+        u32x4_t a[UN][2], b[UN][2];
+#pragma unroll
+        for (int i = 0; i < UN; ++i) {
+            const int k = min(kb + kSegWaves * i, blocks - 1) * 8;     // a block is eight 16-byte pieces
+#pragma unroll
+            for (int c = 0; c < 2; ++c) { a[i][c] = pu[k + c]; b[i][c] = py[k + c]; }
+        }
+#pragma unroll
+        for (int i = 0; i < UN; ++i) {
+            if (kb + kSegWaves * i >= blocks) break;
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a[i][c]),
+                                                              __builtin_bit_cast(bf16x8_t, b[i][c]), acc, 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) red[wave][4 * q + v][row] = acc[v];
+    __syncthreads();
+    const int tok = threadIdx.x & 15, e = threadIdx.x >> 4;
+    if (e < 16 && a0 + e < r) {
+        float sum = 0.f;
+#pragma unroll
+        for (int w = 0; w < kSegWaves; ++w) sum += red[w][tok][e];
+        z[(row0 + a0 + e) * seg_cols + blockIdx.y * 16 + tok] = sum;
+    }
+}
+
+// Per b: the tokens of its n draws from the logits of their segments (a wavefront per draw), then
+// logq[b] = logsumexp_a( log w_a + sum_s (z_sa[tok_s] - lse_sa) ): eq. 9 at the drawn tuple over all experts
+__global__ void __launch_bounds__(kWideBlock) k_draft_pick(int V, int n, int r, int seg_cols, const float *__restrict__ logw,
+                                                           const float *__restrict__ lse, const float *__restrict__ z,
+                                                           const int32_t *__restrict__ alpha,
+                                                           const int32_t *__restrict__ seg, const double *__restrict__ base,
+                                                           const float *__restrict__ uniforms, int32_t *__restrict__ tokens,
+                                                           float *__restrict__ logq)
+{
+    __shared__ int at_s[64];                          // the drawn token's place in its segment
+    const size_t b = blockIdx.x;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int s = wave; s < n; s += kWideBlock / kWave) {
+        const size_t bs = b * n + s, m = bs * r + alpha[b];
+        const int code = seg[bs], v0 = (code < 0 ? ~code : code) * seg_cols, cols = min(seg_cols, V - v0);
+        const float l = lse[m];
+        const float *zr = z + m * seg_cols;
+        // the running sum over the whole vocabulary never passes u: the last token
+        const int at = code < 0 ? cols - 1
+                                : wave_pick_token(seg_cols, cols, base[bs], (double)uniforms[b * (1 + n) + 1 + s], lane,
+                                                  [&](int i) { return (double)expf(zr[i] - l); });
+        if (lane == 0) { tokens[bs] = v0 + at; at_s[s] = at; }
+    }
+    __syncthreads();
+    if (!logq || wave != 0) return;
+    float a = -INFINITY;
+    if (lane < r) {
+        a = logw[b * r + lane];
+        for (int s = 0; s < n; ++s) {
+            const size_t m = (b * n + s) * r + lane;
+            a += z[m * seg_cols + at_s[s]] - lse[m];
+        }
+    }
+    const float mx = wave_max(a);
+    const float sum = wave_sum(lane < r ? expf(a - mx) : 0.f);
+    if (lane == 0) logq[b] = mx + logf(sum);
 }
 
 __global__ void __launch_bounds__(kBlock) k_lse_from_parts(size_t rows, int parts, const float2 *__restrict__ part,
@@ -753,184 +772,83 @@ __global__ void __launch_bounds__(kBlock) k_row_stats_f32(int V, size_t ld, int 
     }
 }
 
-// The paper's sequential scheme (eq. 11-13) for one row b of the batch, all n draws in one block.
+// The paper's sequential scheme (eq. 11-13), one workgroup per row b of the batch.
 // For step s the conditional is the mixture sum_a qhat_a P^(s)(. | a) with qhat = softmax(q),
 // q_a = log w_a + sum_{k<s} log P^(k)(x_k | a).  It is sampled exactly like the single-expert draw of
-// cp_head_draft_sample, with every mass replaced by its qhat-weighted sum over the r experts:
-// segment masses from the GEMM's per-segment statistics (fp64, vocabulary order), then the logits of
-// the crossing segment are recomputed for all r experts and the scan continues token by token.
-// y of the step's r rows is staged in LDS when it fits (r*d <= 32768 elements), else read from memory.
-constexpr int kSeqBlock = 1024;
-constexpr int kSeqYElems = 32768;
-__global__ void __launch_bounds__(kSeqBlock) k_draft_sequential(int d, int V, int n, int r, int parts, int seg_cols,
-                                                                const float2 *__restrict__ part,
-                                                                const bf16_t *__restrict__ Y,
-                                                                const bf16_t *__restrict__ U,
-                                                                const float *__restrict__ logw,
-                                                                const float *__restrict__ uniforms,
-                                                                int32_t *__restrict__ tokens, float *__restrict__ logq)
+// cp_head_draft_sample, with every mass replaced by its qhat-weighted sum over the r experts.
+// Launch s picks the token of draw s - 1 from the logits of its segment (k_segment_logits, between the launches), adds
+// its log-probabilities to q, and finds the segment of draw s; launch n only picks and writes logq.
+__global__ void __launch_bounds__(kWideBlock) k_sequential_step(int step, int V, int n, int r, int parts, int seg_cols,
+                                                                const float2 *__restrict__ part, const float *__restrict__ z,
+                                                                const float *__restrict__ lse, float *__restrict__ q,
+                                                                const float *__restrict__ uniforms, int32_t *__restrict__ seg,
+                                                                double *__restrict__ base, int32_t *__restrict__ tokens,
+                                                                float *__restrict__ logq)
 {
-    __shared__ __attribute__((aligned(16))) bf16_t y_s[kSeqYElems];
-    __shared__ float lse_s[64 * 64];
-    __shared__ float z_s[64 * 128];
-    __shared__ float q_s[64], qh_s[64];
-    __shared__ double wave_tot[kSeqBlock / kWave];
-    __shared__ double base_sh;
-    __shared__ int cross_sh, seg_sh;
+    __shared__ float lse_s[64], q_s[64], qh_s[64];
+    __shared__ double p_s[kMaxSegCols];
     const size_t b = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    constexpr int NW = kSeqBlock / kWave;
-    const int nr = n * r;
-    const bool stage_y = r * d <= kSeqYElems;
-
-    // log-normalisers of all n*r rows of this b (eq. 5)
-    for (int j = wave; j < nr; j += NW) {
-        const float v = row_lse_from_parts(part + (b * nr + j) * parts, parts, lane);
-        if (lane == 0) lse_s[j] = v;
-    }
-    if (tid < r) q_s[tid] = logw[b * r + tid];
-    __syncthreads();
-
-    for (int s = 0; s < n; ++s) {
-        const double u = (double)uniforms[b * n + s];
-        const size_t row0 = (b * n + s) * r;             // first of the r head rows of this step
+    // weights of the mixture and log-normalisers of draw s
+    auto load_draw = [&](int s) {
         if (wave == 0) {
             const float qa = lane < r ? q_s[lane] : -INFINITY;
             const float mx = wave_max(qa);
             const float qn = mx + logf(wave_sum(lane < r ? expf(qa - mx) : 0.f));
             if (lane < r) qh_s[lane] = expf(qa - qn);
-        }
-        if (tid == 0) cross_sh = 0x7FFFFFFF;
-        if (stage_y) {
-            const u32x4_t *src = reinterpret_cast<const u32x4_t *>(Y + row0 * d);
-            u32x4_t *dst = reinterpret_cast<u32x4_t *>(y_s);
-            for (int i = tid; i < r * d / 8; i += kSeqBlock) dst[i] = src[i];
+        } else if (wave == 1 && lane < r) {
+            lse_s[lane] = lse[(b * n + s) * r + lane];
         }
         __syncthreads();
-
-        // mixture mass of every segment, running sum over the vocabulary in fp64
-        const int per = (parts + kSeqBlock - 1) / kSeqBlock;
-        const int lo = min(parts, tid * per), hi = min(parts, lo + per);
-        double sum = 0.0;
-        for (int j = lo; j < hi; ++j)
-            for (int a = 0; a < r; ++a) {
-                const float2 qv = part[(row0 + a) * parts + j];
-                if (qv.x != -INFINITY) sum += (double)(qh_s[a] * qv.y * expf(qv.x - lse_s[s * r + a]));
-            }
-        double incl = wave_scan_inclusive(sum, lane);
-        if (lane == kWave - 1) wave_tot[wave] = incl;
-        __syncthreads();
-        for (int w2 = 0; w2 < wave; ++w2) incl += wave_tot[w2];
-        if (incl > u) atomicMin(&cross_sh, tid);
-        __syncthreads();
-        const bool forced = cross_sh == 0x7FFFFFFF;      // the running sum never passes u: last token
-        if (forced) {
-            if (tid == 0) { seg_sh = (V - 1) / seg_cols; base_sh = 0.0; }
-        } else if (tid == cross_sh) {
-            double c = incl - sum;
-            int seg = hi - 1;
-            for (int j = lo; j < hi; ++j) {
-                double mj = 0.0;
-                for (int a = 0; a < r; ++a) {
-                    const float2 qv = part[(row0 + a) * parts + j];
-                    if (qv.x != -INFINITY) mj += (double)(qh_s[a] * qv.y * expf(qv.x - lse_s[s * r + a]));
-                }
-                if (c + mj > u) { seg = j; break; }
-                c += mj;
-            }
-            seg_sh = seg;
-            base_sh = c;
+    };
+    if (tid < r) q_s[tid] = q[b * r + tid];
+    __syncthreads();
+    if (step > 0) {
+        const int s = step - 1;
+        load_draw(s);
+        const int code = seg[b], v0 = (code < 0 ? ~code : code) * seg_cols, cols = min(seg_cols, V - v0);
+        const float *zr = z + (b * n + s) * r * seg_cols;
+        if (tid < cols) {
+            double p = 0.0;
+            for (int a = 0; a < r; ++a) p += (double)(qh_s[a] * expf(zr[a * seg_cols + tid] - lse_s[a]));
+            p_s[tid] = p;
         }
         __syncthreads();
-        const int seg = seg_sh;
-        const int v0 = seg * seg_cols, cols = min(seg_cols, V - v0);
-
-        // logits of the segment for all r experts: a wavefront walks k for four columns and up to
-        // eight experts together (the four loads of U per step are independent and stay in flight)
-        const bf16_t *ybase = stage_y ? y_s : Y + row0 * d;
-        constexpr int CW = 4, EW = 8;
-        for (int c0 = wave * CW; c0 < cols; c0 += NW * CW) {
-            const u32x4_t *urow[CW];
-#pragma unroll
-            for (int e = 0; e < CW; ++e)
-                urow[e] = reinterpret_cast<const u32x4_t *>(U + (size_t)(v0 + min(c0 + e, cols - 1)) * d);
-            for (int a0 = 0; a0 < r; a0 += EW) {
-                float acc[EW][CW];
-#pragma unroll
-                for (int e = 0; e < EW; ++e)
-#pragma unroll
-                    for (int c = 0; c < CW; ++c) acc[e][c] = 0.f;
-#pragma unroll 1
-                for (int k = lane; k < d / 8; k += kWave) {
-                    u32x4_t uv[CW];
-#pragma unroll
-                    for (int c = 0; c < CW; ++c) uv[c] = urow[c][k];
-#pragma unroll
-                    for (int e = 0; e < EW; ++e) {
-                        // experts past r repeat the last one (their sums are dropped below)
-                        const u32x4_t yv = reinterpret_cast<const u32x4_t *>(ybase + (size_t)min(a0 + e, r - 1) * d)[k];
-#pragma unroll
-                        for (int c = 0; c < CW; ++c)
-#pragma unroll
-                            for (int qd = 0; qd < 4; ++qd) {
-                                acc[e][c] += __uint_as_float(uv[c][qd] << 16) * __uint_as_float(yv[qd] << 16);
-                                acc[e][c] += __uint_as_float(uv[c][qd] & 0xFFFF0000u) * __uint_as_float(yv[qd] & 0xFFFF0000u);
-                            }
-                    }
-                }
-#pragma unroll
-                for (int e = 0; e < EW; ++e)
-#pragma unroll
-                    for (int c = 0; c < CW; ++c) {
-                        const float zz = wave_sum(acc[e][c]);
-                        if (lane == 0 && a0 + e < r && c0 + c < cols) z_s[(a0 + e) * seg_cols + c0 + c] = zz;
-                    }
-            }
-        }
-        __syncthreads();
-
         if (wave == 0) {
-            int tok;
-            if (forced) {
-                tok = V - 1;
-            } else {
-                const int per2 = (seg_cols + kWave - 1) / kWave;
-                const int lo2 = lane * per2;
-                double ps = 0.0;
-                for (int i = lo2; i < lo2 + per2 && i < cols; ++i)
-                    for (int a = 0; a < r; ++a) ps += (double)(qh_s[a] * expf(z_s[a * seg_cols + i] - lse_s[s * r + a]));
-                const double in2 = base_sh + wave_scan_inclusive(ps, lane);
-                const unsigned long long crossed = __ballot(in2 > u);
-                if (crossed == 0ull) {
-                    tok = v0 + cols - 1;
-                } else {
-                    const int first = __ffsll((long long)crossed) - 1;
-                    int mine = v0 + min(cols, lo2 + per2) - 1;
-                    if (lane == first) {
-                        double c = in2 - ps;
-                        for (int i = lo2; i < lo2 + per2 && i < cols; ++i) {
-                            double pi = 0.0;
-                            for (int a = 0; a < r; ++a)
-                                pi += (double)(qh_s[a] * expf(z_s[a * seg_cols + i] - lse_s[s * r + a]));
-                            c += pi;
-                            if (c > u) { mine = v0 + i; break; }
-                        }
-                    }
-                    tok = __shfl(mine, first, kWave);
-                }
-            }
-            if (lane == 0) tokens[b * n + s] = tok;
+            // the running sum over the whole vocabulary never passes u: the last token
+            const int at = code < 0 ? cols - 1
+                                    : wave_pick_token(seg_cols, cols, base[b], (double)uniforms[b * n + s], lane,
+                                                      [&](int i) { return p_s[i]; });
+            if (lane == 0) tokens[b * n + s] = v0 + at;
             // expert log-weights take the log-probability of the drawn token (text under eq. 12)
-            if (lane < r) q_s[lane] += z_s[lane * seg_cols + (tok - v0)] - lse_s[s * r + lane];
+            if (lane < r) {
+                q_s[lane] += zr[lane * seg_cols + at] - lse_s[lane];
+                q[b * r + lane] = q_s[lane];
+            }
         }
         __syncthreads();
     }
-    if (logq && wave == 0) {
-        const float qa = lane < r ? q_s[lane] : -INFINITY;
-        const float mx = wave_max(qa);
-        const float sum = wave_sum(lane < r ? expf(qa - mx) : 0.f);
-        if (lane == 0) logq[b] = mx + logf(sum);
+    if (step == n) {
+        if (logq && wave == 0) {
+            const float qa = lane < r ? q_s[lane] : -INFINITY;
+            const float mx = wave_max(qa);
+            const float sum = wave_sum(lane < r ? expf(qa - mx) : 0.f);
+            if (lane == 0) logq[b] = mx + logf(sum);
+        }
+        return;
     }
+    load_draw(step);
+    const float2 *pm = part + (b * n + step) * r * parts;
+    find_segment(parts, (V - 1) / seg_cols, (double)uniforms[b * n + step],
+                 [&](int j) {
+                     double m = 0.0;
+                     for (int a = 0; a < r; ++a) {
+                         const float2 qv = pm[(size_t)a * parts + j];
+                         if (qv.x != -INFINITY) m += (double)(qh_s[a] * qv.y * expf(qv.x - lse_s[a]));
+                     }
+                     return m;
+                 },
+                 seg + b, base + b);
 }
 
 // Per head row {lse, coef = up_t * gamma[t, a] (zero for dropped factors), target}; dg[t, a] = up_t (w - gamma)
@@ -1270,7 +1188,7 @@ inline void z_segments(int rows, int V, int &parts, int &seg_cols)
 }
 
 struct DraftWs {
-    size_t logw, Y, part, lse, seg, base, total;
+    size_t logw, Y, part, lse, seg, base, zseg, total;
     int parts_max;
 };
 inline DraftWs draft_ws(const cp_head_desc &ds)
@@ -1286,6 +1204,7 @@ inline DraftWs draft_ws(const cp_head_desc &ds)
     f.lse = take(M * 4);
     f.seg = take((size_t)ds.T * ds.n * 4);
     f.base = take((size_t)ds.T * ds.n * 8);
+    f.zseg = take(M * kMaxSegCols * 4);     // logits of the segments that the draws fall into
     f.total = off;
     return f;
 }
@@ -1632,6 +1551,7 @@ int fast_draft(const cp_head_desc &ds, const void *Hv, const void *Wv, const voi
     float2 *part = at<float2>(ws, f.part);
     int32_t *seg = at<int32_t>(ws, f.seg);
     double *base = at<double>(ws, f.base);
+    float *zseg = at<float>(ws, f.zseg);
     const unsigned rows = (unsigned)(B * n);
 
     // y = W_sa h, rounded to bf16 (part of the draft distribution's definition); streams W once.  The gate and the
@@ -1643,17 +1563,15 @@ int fast_draft(const cp_head_desc &ds, const void *Hv, const void *Wv, const voi
     launch_z_streamed("draft_gemm_z", Y, d, (int)M, U, V, EpiRowStats{part, parts, (int)M, V}, st);
     {
         ProfileScope prof("draft_lse_segment", (double)M * parts * 8, st);
-        k_draft_lse_segment<<<rows, kWideBlock, 0, st>>>(n, r, parts, part, alpha, uniforms, lse, seg, base);
+        k_draft_lse_segment<<<rows, kWideBlock, 0, st>>>(n, r, parts, (V - 1) / seg_cols, part, alpha, uniforms, lse, seg, base);
     }
     {
-        ProfileScope prof("draft_logits_pick", (double)rows * seg_cols * d * 2, st);
-        k_draft_logits_pick<<<rows, kPickBlock, 0, st>>>(d, V, n, r, seg_cols, lse, Y, U, alpha, seg, base, uniforms,
-                                                        tokens);
+        ProfileScope prof("draft_segment_logits", (double)rows * seg_cols * d * 2, st);
+        k_segment_logits<<<dim3(rows, (unsigned)seg_cols / 16, (unsigned)(r + 15) / 16), kSegWaves * kWave, 0, st>>>(
+            d, V, n, r, seg_cols, 0, n, Y, U, seg, zseg);
     }
-    if (logq) {
-        ProfileScope prof("draft_logq", (double)M * d * 4, st);
-        k_draft_logq<<<(unsigned)B, kWideBlock, 0, st>>>(d, n, r, logw, lse, Y, U, tokens, logq);
-    }
+    ProfileScope prof("draft_pick", (double)M * seg_cols * 4, st);
+    k_draft_pick<<<(unsigned)B, kWideBlock, 0, st>>>(V, n, r, seg_cols, logw, lse, zseg, alpha, seg, base, uniforms, tokens, logq);
     return hipGetLastError() == hipSuccess ? CP_HEAD_OK : CP_HEAD_ERR_LAUNCH;
 }
 
@@ -1697,9 +1615,21 @@ int fast_draft_sequential(const cp_head_desc &ds, const void *Hv, const void *Wv
     int parts, seg_cols;
     z_segments((int)M, V, parts, seg_cols);
     launch_z_streamed("seq_gemm_z", Y, d, (int)M, U, V, EpiRowStats{part, parts, (int)M, V}, st);
+    // A draw is two launches: a workgroup per row for everything but the logits of the segment, which many share.
+    // (One launch with a workgroup per row for all draws fetched them on one
+    // compute unit: the call took 691 us at B = 8, d = 4096, V = 128256, n = 4, r = 8 and takes 534 us this way.)
     ProfileScope prof("seq_draw", (double)B * n * r * seg_cols * d * 2, st);
-    k_draft_sequential<<<(unsigned)B, kSeqBlock, 0, st>>>(d, V, n, r, parts, seg_cols, part, Y, U, logw, uniforms, tokens,
-                                                          logq);                                             // eq. 11-13
+    float *lse = at<float>(ws, f.lse), *zseg = at<float>(ws, f.zseg);
+    int32_t *seg = at<int32_t>(ws, f.seg);
+    double *base = at<double>(ws, f.base);
+    k_lse_from_parts<<<blocks_for(M, kBlock / kWave), kBlock, 0, st>>>(M, parts, part, lse);
+    for (int step = 0; step <= n; ++step) {
+        k_sequential_step<<<(unsigned)B, kWideBlock, 0, st>>>(step, V, n, r, parts, seg_cols, part, zseg, lse, logw, uniforms,
+                                                              seg, base, tokens, logq);                    // eq. 11-13
+        if (step < n)
+            k_segment_logits<<<dim3((unsigned)B, (unsigned)seg_cols / 16, (unsigned)(r + 15) / 16), kSegWaves * kWave, 0, st>>>(
+                d, V, n, r, seg_cols, step, 1, Y, U, seg, zseg);
+    }
     return hipGetLastError() == hipSuccess ? CP_HEAD_OK : CP_HEAD_ERR_LAUNCH;
 }
 
