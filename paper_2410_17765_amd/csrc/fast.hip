@@ -436,6 +436,13 @@ __device__ __forceinline__ double wave_scan_inclusive(double v, int lane)
     return v;
 }
 
+// 16 bytes at any even address (one load instruction all the same)
+__device__ __forceinline__ u32x4_t load16_any(const bf16_t *p)
+{
+    typedef unsigned int u32x4_any_t __attribute__((ext_vector_type(4), aligned(2)));
+    return *reinterpret_cast<const u32x4_any_t *>(p);
+}
+
 // fp32 dot product of two bf16 vectors of length d (a multiple of 64) over one wavefront, 16-byte loads
 __device__ __forceinline__ float wave_dot_bf16(const bf16_t *__restrict__ a, const bf16_t *__restrict__ b, int d, int lane)
 {
@@ -1164,6 +1171,62 @@ inline void launch_z_streamed(const char *name, const bf16_t *Y, int d, int rows
     if (rows <= kSkinnyRows) launch_gemm_nt<CfgSkinny>(name, Y, d, rows, U, d, V, d, epi, st, kSkinnyRows / CfgSkinny::BM);
     else launch_gemm_nt<Cfg>(name, Y, d, rows, U, d, V, d, epi, st);
 }
+// y = W_sa h for at most 16 positions: W goes from memory straight into the registers that the matrix instruction
+// reads.  The tiled main loop waits for a stage of LDS at every K-step, d / 64 times a memory latency, which the other
+// workgroups of a compute unit hide only where there are two on each (512 tiles of 256 columns); here a workgroup has
+// 16 columns of y, every wavefront 8 KB of W in flight, and eight or more workgroups share a compute unit.
+// The four wavefronts share the contraction in blocks of 64 columns of W (a lane loads 32 consecutive bytes of its row
+// per block, four lanes a cache line; the order of the columns inside a block is the same for both operands) and
+// their partial products meet in LDS.
+constexpr int kStreamRows = 16, kStreamWaves = 4, kStreamBlock = kStreamWaves * kWave;
+__global__ void __launch_bounds__(kStreamBlock) k_stream_y(const bf16_t *__restrict__ H, int B, int d,
+                                                           const bf16_t *__restrict__ W, int cols, bf16_t *__restrict__ Y,
+                                                           GatePickSide side)
+{
+    __shared__ float sums[kStreamWaves][16][17];
+    if ((int)blockIdx.x < side.blocks) {
+        side.run(blockIdx.x, reinterpret_cast<char *>(sums));
+        return;
+    }
+    const int col0 = ((int)blockIdx.x - side.blocks) * 16;       // cols is a multiple of 64
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int row = lane & 15, q = lane >> 4;
+    const bf16_t *ph = H + (size_t)min(row, B - 1) * d + q * 16;     // rows past the last one repeat it, not stored
+    const bf16_t *pw = W + (size_t)(col0 + row) * d + q * 16;
+    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+    constexpr int UN = 4;
+    const int blocks = d / 64;
+    for (int kb = wave; kb < blocks; kb += kStreamWaves * UN) {
+        u32x4_t a[UN][2], b[UN][2];
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            const int k = min(kb + kStreamWaves * u, blocks - 1) * 64;       // a block past the end is left out below
+#pragma unroll
+            for (int c = 0; c < 2; ++c) { a[u][c] = load16_any(pw + k + 8 * c); b[u][c] = load16_any(ph + k + 8 * c); }
+        }
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            if (kb + kStreamWaves * u >= blocks) break;
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a[u][c]),
+                                                              __builtin_bit_cast(bf16x8_t, b[u][c]), acc, 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) sums[wave][4 * q + v][row] = acc[v];
+    __syncthreads();
+    const int t = threadIdx.x >> 4, col = threadIdx.x & 15;
+    if (t < B)
+        Y[(size_t)t * cols + col0 + col] = f32_to_bf16((sums[0][col][t] + sums[1][col][t]) + (sums[2][col][t] + sums[3][col][t]));
+}
+// Where it is the faster one (whole first-token calls at V = 16000, us, this against the tiles; T positions):
+//   cols 16384 (d 2048): T = 1 64 / 84, T = 16 82 / 99       cols 32768 (d 4096): T = 1 133 / 163, T = 16 174 / 185
+//   cols 65536 (d 4096): T = 1 182 / 211, T = 8 223 / 232, T = 16 256 / 238
+//   cols 98304 (d 4096): T = 1 228 / 246, T = 4 257 / 253, T = 16 323 / 261
+// The tiles catch up where they fill the chip and where the rows of H differ: each workgroup reads all of them from L2.
+inline bool stream_y(int B, int cols) { return B <= kStreamRows && (cols <= 32768 || (cols <= 65536 && B <= 8)); }
+
 // y = W_sa h for the first `heads` of the n r head matrices (bf16, rounded: part of the draft distribution's
 // definition), with the gate (and the expert draw, if uniforms is given) as the launch's side job
 inline void launch_y_with_gate(const char *name, const cp_head_desc &ds, const bf16_t *H, const bf16_t *W, const bf16_t *G,
@@ -1172,7 +1235,10 @@ inline void launch_y_with_gate(const char *name, const cp_head_desc &ds, const b
     const int B = (int)ds.T, d = ds.d, cols = heads * d;
     const GatePickSide side{(B + 7) / 8 * 8, B, d, ds.n, ds.r, H, G, uniforms, logw, alpha};
     const EpiStoreBf16 epi{Y, nullptr, (long)cols, B, cols};
-    if (B <= CfgSkinny::BM) launch_gemm_nt<CfgSkinny>(name, H, d, B, W, d, cols, d, epi, st, kGroupRowsWide, side);
+    if (stream_y(B, cols)) {
+        ProfileScope prof(name, 2.0 * (double)B * (double)cols * (double)d, st);
+        k_stream_y<<<side.blocks + cols / 16, kStreamBlock, 0, st>>>(H, B, d, W, cols, Y, side);
+    } else if (B <= CfgSkinny::BM) launch_gemm_nt<CfgSkinny>(name, H, d, B, W, d, cols, d, epi, st, kGroupRowsWide, side);
     else launch_gemm_nt<Cfg>(name, H, d, B, W, d, cols, d, epi, st, kGroupRowsWide, side);
 }
 // statistics segments (pairs per row, columns per segment) of that choice

@@ -1,5 +1,6 @@
 """Draws of both decoding calls at the edges of the segment kernels: 16 tokens and 16 experts per product, 8 x 4 blocks
-of 64 columns per round, 64- and 128-column segments, more segments than the 1024 threads that search them."""
+of 64 columns per round, 64- and 128-column segments, more segments than the 1024 threads that search them; and on both
+sides of the limits of the streamed y product: 16 positions, 8 of them beyond 32768 columns."""
 import numpy as np
 import pytest
 
@@ -10,7 +11,7 @@ pytestmark = pytest.mark.gpu
 
 # T, d, V, n, r
 CASES = [(1, 64, 17, 1, 1), (3, 320, 1000, 2, 16), (2, 576, 66001, 2, 17), (1, 2112, 4097, 3, 2), (5, 128, 513, 17, 5),
-         (70, 64, 257, 2, 33)]
+         (70, 64, 257, 2, 33), (16, 448, 100, 1, 4), (17, 64, 100, 1, 4), (8, 1088, 65, 1, 31), (9, 1088, 65, 1, 31)]
 
 
 @pytest.mark.parametrize("shape", CASES, ids=lambda s: "x".join(map(str, s)))
