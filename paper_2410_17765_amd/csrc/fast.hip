@@ -1163,6 +1163,7 @@ typedef TileCfg<64, 256, 1, 4> CfgSkinny;
 #define CPH_SKINNY_ROWS 64
 #endif
 constexpr int kSkinnyRows = CPH_SKINNY_ROWS;
+static_assert(kSkinnyRows == 64, "draft_ws counts on it");
 // z = U y for the few rows of a draft-type call: picks the tile by the number of rows
 template <class Epi>
 inline void launch_z_streamed(const char *name, const bf16_t *Y, int d, int rows, const bf16_t *U, int V, const Epi &epi,
@@ -1270,7 +1271,11 @@ inline DraftWs draft_ws(const cp_head_desc &ds)
     f.lse = take(M * 4);
     f.seg = take((size_t)ds.T * ds.n * 4);
     f.base = take((size_t)ds.T * ds.n * 8);
-    f.zseg = take(M * kMaxSegCols * 4);     // logits of the segments that the draws fall into
+    // logits of the segments that the draws fall into: with 128-column segments half of `part` is free, and holds them
+    // from 32 tiles of 256 columns on (2 pairs of 8 bytes per tile and row); otherwise they have room of their own
+    const size_t tiles = ((size_t)ds.V + Cfg::BN - 1) / Cfg::BN;
+    if (M > 64 && tiles * 16 >= kMaxSegCols * 4) f.zseg = f.part + M * tiles * Cfg::WN * sizeof(float2);
+    else f.zseg = take(M * kMaxSegCols * 4);
     f.total = off;
     return f;
 }
