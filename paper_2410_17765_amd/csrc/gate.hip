@@ -1,8 +1,10 @@
 // The gate of the matrix-core path (bf16 storage, d a multiple of 64): G h for all positions, as log-softmax
 // (eq. 7), as arg-max counts (eq. 10), and the gate gradient dG = dg^T H.
 //
-// All three read H once and do almost nothing else: they are bound by that stream (T d 2 bytes).
+// All three read H once and do little else: they are bound by that stream (T d 2 bytes).
 #include "cp_internal.hpp"
+
+#include <type_traits>
 
 namespace cph {
 
@@ -19,10 +21,9 @@ typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ u32x4_t load16(const bf16_t *p) { return *reinterpret_cast<const u32x4_any_t *>(p); }
 
 // ------------------------------------------------------------------------------------------
-// G h of 16 positions per step of a workgroup on the 16x16x32 matrix instruction.
+// G h of 16 positions per step of a workgroup on the 16x16x32 matrix instruction, for the arg-max counts.
 // The kernel it replaces walked H with 2-byte loads, once per expert, one position per wavefront: 353 us for the
-// arg-max at T = 16384, d = 4096, r = 8 (0.4 TB/s); this one takes 35 us (3.9 TB/s), and 6.6 instead of 22 us for the
-// log-softmax at T = 1500, d = 768, r = 5.  Here the four wavefronts share the contraction (blocks of 64
+// arg-max at T = 16384, d = 4096, r = 8 (0.4 TB/s); this one takes 35 us (3.9 TB/s).  Here the four wavefronts share the contraction (blocks of 64
 // columns in turn), a lane loads 32 consecutive bytes of its row per block, so that four lanes cover a cache line of
 // H, and the partial products meet in LDS.  Experts beyond r repeat the last row of G and are dropped.
 // The order of the columns inside a block of 64 is the same permutation for both operands.
@@ -77,23 +78,95 @@ __device__ __forceinline__ void gate_rows(size_t t0, size_t T, int d, int r, con
 }
 
 // logw = log_softmax(G h), w = exp(logw)   (eq. 7)
-template <int NG>
+//
+// Every sum has one order, which does not depend on the shape: lane l adds the columns l, l + 64, ... in turn, then lanes
+// 32, 16, ... 1 apart add up.  The log-weights enter exponentials whose results are rounded to bf16, in the fine-tuning
+// loss next to logits of magnitude ten, so that another order of the same fp32 sums moved its gradients by 1e-4 (the order
+// of the matrix instruction, which the arg-max counts above keep).
+// A wavefront takes four positions and eight experts at a time: a value of H meets eight experts and one of G four
+// positions in registers, and 48 loads are in flight, where one position and one expert at a time had each load feed one
+// multiplication, one latency after the other.  Bound by those latencies for few positions, by the stream of H and the
+// vector units next to it for many: 8.7 us at T = 1500, d = 768, r = 5 (22 one at a time, 6.3 with the matrix instruction),
+// 36 us at T = 16384, d = 4096, r = 8 (3.7 TB/s; 29 with the matrix instruction), in calls of 7 and 440 ms.
+constexpr int kGatePos = 4, kGateExperts = 8;
+
+// v[i], summed over the wavefront for each of the COUNT of them, arrives in v[0] of the lanes whose upper bits are i: at
+// each step a lane hands half of its values to the lane OFF away and adds what it gets for the other half.
+template <int COUNT, int OFF, int N>
+__device__ __forceinline__ void wave_sum_each(float (&v)[N], int lane)
+{
+    if constexpr (COUNT > 1) {
+        const bool up = lane & OFF;
+#pragma unroll
+        for (int i = 0; i < COUNT / 2; ++i) {
+            const float keep = up ? v[i + COUNT / 2] : v[i], give = up ? v[i] : v[i + COUNT / 2];
+            v[i] = keep + __shfl_xor(give, OFF, kWave);
+        }
+    } else {
+        v[0] += __shfl_xor(v[0], OFF, kWave);
+    }
+    if constexpr (OFF > 1) wave_sum_each<(COUNT > 1 ? COUNT / 2 : 1), OFF / 2>(v, lane);
+}
+
+// element at a byte offset from a pointer that all lanes share
+__device__ __forceinline__ bf16_t ld_at(const bf16_t *p, unsigned bytes)
+{
+    return *reinterpret_cast<const bf16_t *>(reinterpret_cast<const char *>(p) + bytes);
+}
+
 __global__ void __launch_bounds__(kBlock) k_gate_bf16(size_t T, int d, int r, const bf16_t *__restrict__ H, const bf16_t *__restrict__ G,
                                                       float *__restrict__ logw, float *__restrict__ w)
 {
-    __shared__ float red[kWaves][kRows][NG * 16 + 1];
-    const size_t t0 = (size_t)blockIdx.x * kRows;
-    gate_rows<NG>(t0, T, d, r, H, G, red);
+    __shared__ float g_s[kWaves][kGatePos][64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const size_t t0 = ((size_t)blockIdx.x * kWaves + wave) * kGatePos;
+    const bf16_t *h[kGatePos];                      // positions past T and experts past r repeat the last one, not stored
+#pragma unroll
+    for (int p = 0; p < kGatePos; ++p) h[p] = H + (t0 + p < T ? t0 + p : T - 1) * d;
+    for (int a0 = 0; a0 < r; a0 += kGateExperts) {
+        const bf16_t *g[kGateExperts];
+#pragma unroll
+        for (int e = 0; e < kGateExperts; ++e) g[e] = G + (size_t)min(a0 + e, r - 1) * d;
+        float acc[kGatePos * kGateExperts];
+#pragma unroll
+        for (int i = 0; i < kGatePos * kGateExperts; ++i) acc[i] = 0.f;
+        // `blocks` blocks of 64 columns, all their loads ahead of the arithmetic
+        auto add = [&](int k0, auto blocks) {
+            constexpr int UN = decltype(blocks)::value;
+            bf16_t hv[UN][kGatePos], gv[UN][kGateExperts];
+#pragma unroll
+            for (int u = 0; u < UN; ++u) {
+                const unsigned at = (unsigned)(k0 + u * kWave + lane) * sizeof(bf16_t);
+#pragma unroll
+                for (int p = 0; p < kGatePos; ++p) hv[u][p] = ld_at(h[p], at);
+#pragma unroll
+                for (int e = 0; e < kGateExperts; ++e) gv[u][e] = ld_at(g[e], at);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < UN; ++u)
+#pragma unroll
+                for (int p = 0; p < kGatePos; ++p)
+#pragma unroll
+                    for (int e = 0; e < kGateExperts; ++e)
+                        acc[p * kGateExperts + e] += bf16_to_f32(gv[u][e]) * bf16_to_f32(hv[u][p]);
+        };
+        int k0 = 0;
+        for (; k0 + 4 * kWave <= d; k0 += 4 * kWave) add(k0, std::integral_constant<int, 4>());
+        for (; k0 < d; k0 += kWave) add(k0, std::integral_constant<int, 1>());
+        wave_sum_each<kGatePos * kGateExperts, 32>(acc, lane);
+        const int at = lane >> 1;                   // which of the 32 sums this lane holds
+        if (!(lane & 1) && a0 + at % kGateExperts < r) g_s[wave][at / kGateExperts][a0 + at % kGateExperts] = acc[0];
+    }
     __syncthreads();
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int row = wave; row < kRows && t0 + row < T; row += kWaves) {
-        float mine = -INFINITY;
-        if (lane < r) mine = (red[0][row][lane] + red[1][row][lane]) + (red[2][row][lane] + red[3][row][lane]);
+    for (int p = 0; p < kGatePos && t0 + p < T; ++p) {
+        const float mine = lane < r ? g_s[wave][p][lane] : -INFINITY;
         const float mx = wave_max(mine);
-        const float lse = mx + logf(wave_sum(lane < r ? expf(mine - mx) : 0.f));
+        const float s = wave_sum(lane < r ? expf(mine - mx) : 0.f);
+        const float lse = mx + logf(s);
         if (lane < r) {
-            logw[(t0 + row) * r + lane] = mine - lse;
-            w[(t0 + row) * r + lane] = expf(mine - lse);
+            logw[(t0 + p) * r + lane] = mine - lse;
+            w[(t0 + p) * r + lane] = expf(mine - lse);
         }
     }
 }
@@ -191,8 +264,7 @@ __global__ void __launch_bounds__(kBlock) k_dgate_reduce(int chunks, size_t rd, 
 void launch_gate_bf16(const cp_head_desc &ds, const bf16_t *H, const bf16_t *G, float *logw, float *w, hipStream_t st)
 {
     const size_t T = (size_t)ds.T;
-    if (ds.r <= 16) k_gate_bf16<1><<<blocks_for(T, kRows), kBlock, 0, st>>>(T, ds.d, ds.r, H, G, logw, w);
-    else k_gate_bf16<4><<<blocks_for(T, kRows), kBlock, 0, st>>>(T, ds.d, ds.r, H, G, logw, w);
+    k_gate_bf16<<<blocks_for(T, kWaves * kGatePos), kBlock, 0, st>>>(T, ds.d, ds.r, H, G, logw, w);
 }
 
 void launch_aux_argmax_bf16(const cp_head_desc &ds, const bf16_t *H, const bf16_t *G, unsigned long long *counts, hipStream_t st)
