@@ -170,7 +170,7 @@ void launch_gate(const cp_head_desc &ds, const void *H, const void *G, float *lo
 // gate gradient dG = dg^T H, whose partial sums take gate_chunks(T) r d floats of `partial`.
 void launch_gate_bf16(const cp_head_desc &ds, const bf16_t *H, const bf16_t *G, float *logw, float *w, hipStream_t st);
 void launch_aux_argmax_bf16(const cp_head_desc &ds, const bf16_t *H, const bf16_t *G, unsigned long long *counts, hipStream_t st);
-constexpr int kGateChunk = 128;     // positions per partial sum: 512 left d = 768 with six workgroups
+constexpr int kGateChunk = 512;     // positions per partial sum
 inline size_t gate_chunks(size_t T) { return (T + kGateChunk - 1) / kGateChunk; }
 void launch_gate_gradient_bf16(const cp_head_desc &ds, const bf16_t *H, const float *dg, float *partial, float *dG, hipStream_t st);
 // out[t] = sign * logsumexp_a(logw + sum_s C): sign = -1 gives the loss, +1 the joint log-probability

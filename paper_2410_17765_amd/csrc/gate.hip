@@ -197,57 +197,65 @@ __global__ void __launch_bounds__(kBlock) k_aux_argmax_bf16(size_t T, int d, int
     if ((int)threadIdx.x < r && hist[threadIdx.x]) atomicAdd(&counts[threadIdx.x], (unsigned long long)hist[threadIdx.x]);
 }
 
-// dG[a, j] = sum_t dg[t, a] H[t, j] in two deterministic stages.  First stage: a workgroup takes kGateChunk positions and
-// 512 columns, a lane eight of them (16-byte loads) for eight experts at a time; the four wavefronts take the positions
-// in turn and add up in LDS, wavefront 0 first.  Second stage: the chunks in increasing order.
-// (One thread per column over 512 positions, 2-byte loads: 234-266 us at T = 1500, d = 768 as at T = 4096, d = 4096,
-// a chain of 512 load latencies; this pair takes 23 us at the former.)
-__global__ void __launch_bounds__(kBlock) k_dgate_partial(size_t T, int d, int r, const bf16_t *__restrict__ H,
-                                                          const float *__restrict__ dg, float *__restrict__ partial)
+// dG[a, j] = sum_t dg[t, a] H[t, j] in two deterministic stages: partial sums over chunks of kGateChunk positions in turn,
+// then the chunks in increasing order.  First stage: a wavefront takes a chunk, 64 columns and eight experts; it is bound by
+// the chain of the chunk's positions, so the values of H are fetched a batch ahead of their use and dg lies in LDS.
+// 26 us at T = 1500, d = 768, r = 5 (one thread per column without any prefetch: 230), 28 at T = 4096, d = 4096, r = 8,
+// 50 at T = 16384; 28 at T = 2048, d = 1024, r = 64.  Chunks of 128 positions with 16-byte loads took 16 / 24 / 44 / 100 us
+// and, whatever the batch, four times the workspace (134 MB at T = 16384, d = 4096, r = 64), and added up in another order.
+constexpr int kGateBatch = 32, kGateStep = 16;
+__global__ void __launch_bounds__(kWave) k_dgate_partial(size_t T, int d, int r, const bf16_t *__restrict__ H,
+                                                         const float *__restrict__ dg, float *__restrict__ partial)
 {
-    __shared__ float red[kWaves][8][64 + 1];
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int j = blockIdx.y * 512 + lane * 8;
-    const size_t t0 = (size_t)blockIdx.x * kGateChunk, t1 = t0 + kGateChunk < T ? t0 + kGateChunk : T;
-    for (int a0 = 0; a0 < r; a0 += 8) {
-        float acc[8][8];
+    __shared__ __attribute__((aligned(16))) float dg_s[kGateChunk][8];
+    static_assert(kGateChunk % kGateBatch == 0 && kGateChunk * 8 % (16 * kWave) == 0, "whole batches in LDS");
+    const int lane = threadIdx.x, a0 = (int)blockIdx.z * 8;
+    const size_t t0 = (size_t)blockIdx.x * kGateChunk;
+    const int count = (int)min((size_t)kGateChunk, T - t0);
+    const int padded = (count + kGateBatch - 1) / kGateBatch * kGateBatch;      // positions past the last one add zeros
+    constexpr int kFill = 16;                                                   // loads in flight
+    for (int i0 = 0; i0 < padded * 8; i0 += kFill * kWave) {
+        float v[kFill];
 #pragma unroll
-        for (int e = 0; e < 8; ++e)
-#pragma unroll
-            for (int c = 0; c < 8; ++c) acc[e][c] = 0.f;
-        if (j < d) {
-#pragma unroll 4
-            for (size_t t = t0 + wave; t < t1; t += kWaves) {
-                const u32x4_t x = load16(H + t * d + j);
-                float g[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) g[e] = dg[t * r + min(a0 + e, r - 1)];
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const float lo = __uint_as_float(x[c] << 16), hi = __uint_as_float(x[c] & 0xFFFF0000u);
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        acc[e][2 * c] += g[e] * lo;
-                        acc[e][2 * c + 1] += g[e] * hi;
-                    }
-                }
-            }
+        for (int u = 0; u < kFill; ++u) {
+            const int t = (i0 + u * kWave + lane) / 8, e = min(a0 + lane % 8, r - 1);
+            v[u] = dg[(t0 + min(t, count - 1)) * r + e];
+            if (t >= count) v[u] = 0.f;
         }
-        // column c of every lane's eight in turn: [wave][expert][lane], then thread (expert pair, lane) adds the waves
 #pragma unroll
-        for (int c = 0; c < 8; ++c) {
+        for (int u = 0; u < kFill; ++u) dg_s[(i0 + u * kWave + lane) / 8][lane % 8] = v[u];
+    }
+    __syncthreads();
+    const bf16_t *h = H + t0 * d + (size_t)blockIdx.y * kWave;
+    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    bf16_t next[kGateBatch];
+    auto fetch = [&](int t) {
 #pragma unroll
-            for (int e = 0; e < 8; ++e) red[wave][e][lane] = acc[e][c];
-            __syncthreads();
+        for (int u = 0; u < kGateBatch; ++u) next[u] = ld_at(h + (size_t)min(t + u, count - 1) * d, lane * sizeof(bf16_t));
+    };
+    fetch(0);
+    for (int t = 0; t < padded; t += kGateBatch) {
+        float hv[kGateBatch];
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int e = wave + 4 * h;
-                const float s = ((red[0][e][lane] + red[1][e][lane]) + red[2][e][lane]) + red[3][e][lane];
-                if (a0 + e < r && j < d) partial[((size_t)blockIdx.x * r + a0 + e) * d + j + c] = s;
-            }
-            __syncthreads();
+        for (int u = 0; u < kGateBatch; ++u) hv[u] = t + u < count ? bf16_to_f32(next[u]) : 0.f;
+        fetch(t + kGateBatch);
+#pragma unroll
+        for (int u0 = 0; u0 < kGateBatch; u0 += kGateStep) {
+            f32x4_t g[kGateStep][2];
+#pragma unroll
+            for (int u = 0; u < kGateStep; ++u)
+#pragma unroll
+                for (int c = 0; c < 2; ++c) g[u][c] = *reinterpret_cast<const f32x4_t *>(&dg_s[t + u0 + u][4 * c]);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < kGateStep; ++u)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) acc[e] += g[u][e / 4][e % 4] * hv[u0 + u];
         }
     }
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+        if (a0 + e < r) partial[((size_t)blockIdx.x * r + a0 + e) * d + blockIdx.y * kWave + lane] = acc[e];
 }
 __global__ void __launch_bounds__(kBlock) k_dgate_reduce(int chunks, size_t rd, const float *__restrict__ partial, float *__restrict__ dG)
 {
@@ -280,7 +288,8 @@ void launch_gate_gradient_bf16(const cp_head_desc &ds, const bf16_t *H, const fl
 {
     const unsigned chunks = (unsigned)gate_chunks((size_t)ds.T);
     const size_t rd = (size_t)ds.r * ds.d;
-    k_dgate_partial<<<dim3(chunks, blocks_for((size_t)ds.d, 512)), kBlock, 0, st>>>((size_t)ds.T, ds.d, ds.r, H, dg, partial);
+    k_dgate_partial<<<dim3(chunks, (unsigned)ds.d / kWave, blocks_for((size_t)ds.r, 8)), kWave, 0, st>>>((size_t)ds.T, ds.d, ds.r, H, dg,
+                                                                                                        partial);
     k_dgate_reduce<<<blocks_for(rd, kBlock), kBlock, 0, st>>>((int)chunks, rd, partial, dG);
 }
 

@@ -51,3 +51,47 @@ def test_log_weights(shape):
     assert clear.sum() >= 0.8 * T or r == 2
     expect = g.max(axis=1) - g[:, 0]
     np.testing.assert_array_equal(loss[clear], expect[clear])
+
+
+def weighted_sum_in_order(dg, H):
+    """sum_t dg[t] H[t, :] over chunks of 512 positions, one fused multiply-add after the other, the chunks in turn."""
+    total = np.zeros(H.shape[1], np.float32)
+    for lo in range(0, len(dg), 512):
+        acc = np.zeros(H.shape[1], np.float32)
+        for g, h in zip(dg[lo:lo + 512], H[lo:lo + 512]):
+            # a product has 32 bits: exact with 64 of them, like nearly every sum
+            acc = (acc.astype(np.longdouble) + np.longdouble(g) * h.astype(np.longdouble)).astype(np.float32)
+        total = total + acc
+    return total
+
+
+# one position, a batch of 16 positions and one more, a whole chunk of 512 and one more, three chunks; one and two groups
+# of eight experts
+@pytest.mark.parametrize("shape", [(1, 64, 2), (17, 192, 8), (512, 64, 3), (513, 128, 9), (1500, 64, 10)], ids=lambda s: "x".join(map(str, s)))
+def test_gate_gradient(shape):
+    import torch
+    from paper_2410_17765_amd import head
+    T, d, r = shape
+    print(f"case {shape}", flush=True)
+    rng = np.random.default_rng(6)
+    H = synth.bf16_round(rng.standard_normal((T, d)).astype(np.float32))
+    H[:, 0] = 1                                       # as above: expert 0 explains every target
+    W = np.zeros((1, r, d, d), np.float32)
+    W[0, :, 0, 0] = -1024
+    W[0, 0, 0, 0] = 1024
+    U = np.zeros((2, d), np.float32)
+    U[:, 0] = 1024, -1024
+    h = head.CpHead(W, U, np.zeros((r, d), np.float32), dtype="bf16")
+    Hd, X = head.to_device(H, "bf16"), torch.zeros((T, 1), dtype=torch.int32, device="cuda")
+    up = rng.standard_normal(T).astype(np.float32)
+    h.loss_fwd(Hd, X)
+    dG = h.loss_bwd(Hd, X, torch.from_numpy(up).cuda())["dG"].cpu().numpy()
+    # G = 0: all weights are one number next to 1/r, which only the device's exponential knows to the last bits
+    one = np.float32(1) / np.float32(r)
+    matches = []
+    for ulps in range(-4, 5):
+        w = (one.view(np.int32) + np.int32(ulps)).view(np.float32)
+        if (weighted_sum_in_order(up * w, H) == dG[1:]).all():
+            matches.append(w)
+    assert len(matches) == 1
+    np.testing.assert_array_equal(weighted_sum_in_order(up * (matches[0] - np.float32(1)), H), dG[0])

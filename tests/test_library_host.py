@@ -61,6 +61,17 @@ def test_headline_shape_sizes(lib):
     assert binding.cp_head_workspace_bytes(ds, binding.OP_LOSS_FWD) < logits_bytes // 4
 
 
+def test_gate_gradient_workspace(lib):
+    """The partial sums of the gate gradient: one per 512 positions, not more."""
+    sizes = [binding.cp_head_workspace_bytes(binding.make_desc(16384, 4096, 512, 1, r, binding.BF16), binding.OP_LOSS_BWD) for r in (63, 64)]
+    per_expert = sizes[1] - sizes[0]
+    # the other buffers that grow with r, at their size per expert: {lse, coefficient, target}, dg, dY, W^T (and the dz rows of
+    # one chunk, which holds them all here: dz, its transpose, y^T)
+    T, d, V = 16384, 4096, 512
+    others = T * 16 + T * 4 + T * d * 2 + d * d * 2 + 2 * T * V * 2 + d * T * 2
+    assert per_expert - others <= T // 512 * d * 4 + 65536
+
+
 @pytest.mark.parametrize("kw", [dict(T=-1), dict(d=0), dict(V=0), dict(n=0), dict(r=0)])
 def test_bad_dimensions(lib, kw):
     base = dict(T=4, d=8, V=16, n=2, r=2)
