@@ -106,6 +106,10 @@ struct EpiF32Store {
     }
 };
 
+// exp(x - mx) where mx is the largest of the x.  An infinite mx weighs its own kind 1 and the rest 0, as a running
+// maximum does, and a NaN stays one, also where it is alone and mx is still -infinity.
+__device__ __forceinline__ float exp_below(float x, float mx) { return x == mx ? 1.f : expf(x - mx); }
+
 // Logits of the head rows m = row * row_mul + row_add: (maximum, sum of exp(z - maximum)) over the sub-tile's columns
 // to part[m, slots], the target logit to zt[m] (if X is given), and the logits themselves to z[row, ldz] (if z is
 // given; columns from V up to ldz become zero).
@@ -145,7 +149,7 @@ struct EpiF32Logits {
                     float sum = 0.f;
 #pragma unroll
                     for (int j = 0; j < Tile::TN; ++j)
-                        if (col0 + f32_col(j, lane) < p.N) sum += expf(acc[i][j][v] - mx);
+                        if (col0 + f32_col(j, lane) < p.N) sum += exp_below(acc[i][j][v], mx);
                     sum = row16_sum(sum);
                     if (in && (lane & 15) == 0) part[m * slots + slot] = make_float2(mx, sum);
                 }
@@ -293,11 +297,12 @@ __global__ void __launch_bounds__(kBlock) k_position_finish(int n, int r, int sl
         float mx = -INFINITY, l = 0.f;
         for (int q = lane; q < slots; q += kWave) {
             const float2 v = part[m * slots + q];
+            // a slot without columns is (-infinity, 0); one whose columns are all NaN is (-infinity, NaN)
             if (v.x > mx) { l = l * expf(mx - v.x) + v.y; mx = v.x; }
-            else if (v.x != -INFINITY) l += v.y * expf(v.x - mx);
+            else l += v.y * exp_below(v.x, mx);
         }
         const float Mx = wave_max(mx);
-        const float L = wave_sum(mx == -INFINITY ? 0.f : l * expf(mx - Mx));
+        const float L = wave_sum(l * exp_below(mx, Mx));
         const float lse = Mx + logf(L);
         if (lane == 0) {
             lse_out[m] = lse;
