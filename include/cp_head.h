@@ -56,7 +56,9 @@ enum {
     CP_HEAD_MIN_WORKSPACE = 2,  /* flags bit 1: the backward pass holds logit gradients for one
                                    tile of 256 head rows at a time (least workspace, slower)
                                    instead of its default of 32768 rows or 4 GiB worth of them,
-                                   whichever is more, up to 8 GiB (0.5 GiB on the plain path) */
+                                   whichever is more, up to 8 GiB (0.5 GiB on the plain path), and
+                                   the plain path's forward pass the row statistics of about 256
+                                   rows instead of 64 MiB of them */
     CP_HEAD_KEEP_LOGITS = 4     /* flags bit 2, off by default (by default no logit is ever stored).
                                    Matrix-core path of the three loss call pairs only (cp_head_loss_,
                                    cp_head_full_loss_, cp_head_distill_loss_ fwd / bwd; ignored on the

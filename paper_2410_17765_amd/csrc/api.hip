@@ -65,7 +65,7 @@ int check_desc(const cp_head_desc *ds)
     if (ds->r > kMaxRank || ds->n > kMaxHeads) return CP_HEAD_ERR_UNSUPPORTED;
     const double rows = (double)ds->T * ds->n * ds->r;
     if (rows * (double)(ds->d > ds->V ? ds->d : ds->V) >= 4.6e18) return CP_HEAD_ERR_UNSUPPORTED;
-    if (rows >= 2147483647.0) return CP_HEAD_ERR_UNSUPPORTED;   // one thread block per head row
+    if (rows >= 2147483647.0) return CP_HEAD_ERR_UNSUPPORTED;   // head rows are counted in 32 bits
     if (!use_fast_path(*ds) && ds->d > kMaxGenericD) return CP_HEAD_ERR_UNSUPPORTED;
     return CP_HEAD_OK;
 }

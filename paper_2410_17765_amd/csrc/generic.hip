@@ -692,6 +692,33 @@ inline BwdPlans bwd_plans(const cp_head_desc &ds)
     return b;
 }
 
+// The forward pass takes its logits a chunk of whole positions at a time, so that the statistics of their rows, a pair per
+// row and column slot (up to a quarter of V floats per row), take at most 64 MiB however many positions there are, or
+// 256 rows' worth with the least-workspace flag, or one position's.  64 MiB are 64 rounds of tiles over the compute units
+// at any V, so the chunks' last rounds cost less than 2 %.
+struct FwdChunk {
+    size_t pos;         // positions
+    F32Plan plan;
+    int slots;
+    size_t part_bytes;
+};
+inline FwdChunk fwd_chunk(const cp_head_desc &ds)
+{
+    FwdChunk c;
+    const size_t nr = (size_t)ds.n * ds.r, T = (size_t)ds.T;
+    const size_t most_slots = 2 * (((size_t)ds.V + 63) / 64);
+    const size_t rows = (ds.flags & CP_HEAD_MIN_WORKSPACE) ? 256 : ((size_t)64 << 20) / (most_slots * sizeof(float2));
+    c.pos = std::max<size_t>(rows / nr, 1);
+    size_t step = 128;                                  // positions whose rows are whole tiles of rows
+    for (size_t k = nr; k % 2 == 0 && step > 1; k /= 2) step /= 2;
+    if (c.pos > step) c.pos -= c.pos % step;
+    c.pos = std::min(c.pos, std::max<size_t>(T, 1));
+    c.plan = f32_plan((long)(c.pos * nr), ds.V, ds.d, false);
+    c.slots = f32_slots(c.plan.kind, ds.V);
+    c.part_bytes = c.pos * nr * c.slots * sizeof(float2);
+    return c;
+}
+
 struct GenericWs {
     size_t logw, C, part, dY, dZ, dg, partial, w, Y, z, lse, total;
 };
@@ -706,7 +733,7 @@ inline GenericWs generic_ws(const cp_head_desc &ds, int op)
     if (op == CP_HEAD_OP_LOSS_FWD) {
         g.logw = take(Tr * 4);
         g.C = take(M * 4);
-        g.part = take_part();
+        g.part = take(fwd_chunk(ds).part_bytes);
     } else if (op == CP_HEAD_OP_LOSS_BWD) {
         g.dY = take(M * ds.d * 4);
         g.dZ = take(generic_chunk_rows(ds) * dz_row(ds) * 4);
@@ -724,19 +751,23 @@ inline GenericWs generic_ws(const cp_head_desc &ds, int op)
     return g;
 }
 
-// gate, y, statistics of z and what follows per position; loss null: no mixture
+// gate, y, then by chunks of positions the statistics of z and what follows per position; loss null: no mixture
 template <typename TIn>
 void fwd_rows_t(const cp_head_desc &ds, const TIn *H, const TIn *W, const TIn *U, const TIn *G, const int32_t *X,
                 const GenericFwdBuffers &b, float2 *part, float *loss, hipStream_t st)
 {
-    const long M = (long)ds.T * ds.n * ds.r, d = ds.d, V = ds.V;
-    launch_f32_y<TIn>(ds, ds.n * ds.r, H, W, G, b.Y, b.logw, st);
-    const F32Plan plan = f32_plan(M, V, d, false);
-    const int slots = f32_slots(plan.kind, V);
-    launch_f32<float, TIn, false, false>(f32_problem<false, false>((const float *)b.Y, d, U, d, M, V, d, d, plan), plan.kind,
-                                         EpiF32Logits{part, slots, 1, 0, X, ds.r, b.C, nullptr, 0}, st);
-    k_position_finish<<<(unsigned)ds.T, kBlock, (size_t)ds.n * ds.r * sizeof(float), st>>>(ds.n, ds.r, slots, part, X, b.C, b.lse,
-                                                                                          b.logw, b.w, b.gamma, loss);
+    const size_t T = (size_t)ds.T, n = (size_t)ds.n, r = (size_t)ds.r, nr = n * r;
+    const long d = ds.d, V = ds.V;
+    launch_f32_y<TIn>(ds, (int)nr, H, W, G, b.Y, b.logw, st);
+    const FwdChunk c = fwd_chunk(ds);
+    for (size_t t0 = 0; t0 < T; t0 += c.pos) {
+        const size_t Tc = std::min(c.pos, T - t0), m0 = t0 * nr;
+        launch_f32<float, TIn, false, false>(f32_problem<false, false>((const float *)b.Y + m0 * d, d, U, d, (long)(Tc * nr), V, d, d, c.plan),
+                                             c.plan.kind, EpiF32Logits{part, c.slots, 1, 0, X + t0 * n, ds.r, b.C + m0, nullptr, 0}, st);
+        k_position_finish<<<(unsigned)Tc, kBlock, nr * sizeof(float), st>>>(ds.n, ds.r, c.slots, part, X + t0 * n, b.C + m0, b.lse + m0,
+                                                                           b.logw + t0 * r, b.w + t0 * r, b.gamma + t0 * r,
+                                                                           loss ? loss + t0 : nullptr);
+    }
 }
 
 inline GenericFwdBuffers fwd_buffers(const cp_head_desc &ds, void *ctx, void *ws)

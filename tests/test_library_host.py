@@ -72,6 +72,20 @@ def test_gate_gradient_workspace(lib):
     assert per_expert - others <= T // 512 * d * 4 + 65536
 
 
+def test_plain_forward_workspace_is_bounded(lib):
+    """The plain path's forward pass holds per row two floats and for a bounded chunk of rows their statistics."""
+    for T, d, V, n, r in ((16384, 512, 32000, 4, 8), (4096, 512, 128256, 4, 8), (1 << 20, 64, 512, 2, 2), (3, 16, 128256, 64, 64)):
+        for flags in (0, binding.MIN_WORKSPACE):
+            for op in (binding.OP_LOSS_FWD, binding.OP_DISTILL_FWD):
+                need = binding.cp_head_workspace_bytes(binding.make_desc(T, d, V, n, r, binding.FP32, flags), op)
+                rows = T * r * (n + 1) * 4
+                statistics = max(n * r, 256) * (V // 32 + 1) * 8 if flags else max(64 << 20, n * r * (V // 32 + 1) * 8)
+                if op == binding.OP_DISTILL_FWD:                # two more floats and a pair per row, a chunk of fp32 logits
+                    rows += T * n * r * 16
+                    statistics += max(n * r, 256) * (V + 3) * 4 if flags else max((1 << 29) + 1, n * r * (V + 3) * 4)
+                assert need <= rows + statistics + 4096, (T, V, flags, op)
+
+
 @pytest.mark.parametrize("kw", [dict(T=-1), dict(d=0), dict(V=0), dict(n=0), dict(r=0)])
 def test_bad_dimensions(lib, kw):
     base = dict(T=4, d=8, V=16, n=2, r=2)
