@@ -1106,8 +1106,8 @@ int aux_balance(const cp_head_desc &ds, const void *H, const void *G, int64_t *c
 // ---- full heads on the plain path: one product per (s, a) over the positions, whose head rows are
 // m = t n r + sa.  A chunk's gradients are stored [positions, n r, V], so that dH and dF are one product each.
 struct GenericFullWs {
-    size_t logw, C, part, dg, dZ, partial, total;
-    size_t chunk_pos;
+    size_t logw, C, dg, dZ, partial, total;     // dZ: in the forward pass, the row statistics of a chunk
+    size_t chunk_pos, fwd_pos;                  // positions per chunk of the backward and of the forward pass
     F32Plan z, zc, dh, df, dG;
 };
 static GenericFullWs generic_full_ws(const cp_head_desc &ds)
@@ -1120,7 +1120,12 @@ static GenericFullWs generic_full_ws(const cp_head_desc &ds)
     if (pos < 1) pos = 1;
     g.chunk_pos = pos < T ? pos : (T ? T : 1);
     const long P = (long)g.chunk_pos;
-    g.z = f32_plan((long)T, V, d, false);
+    // the forward pass: as many positions as have room for their rows' statistics where the backward pass has its gradients
+    const size_t dz_bytes = g.chunk_pos * nr * ds.V * 4, most_slots = 2 * (((size_t)ds.V + 63) / 64);
+    size_t fwd = std::max<size_t>(dz_bytes / (nr * most_slots * sizeof(float2)), 1);
+    if (fwd > 128) fwd -= fwd % 128;
+    g.fwd_pos = std::min(fwd, std::max<size_t>(T, 1));
+    g.z = f32_plan((long)g.fwd_pos, V, d, false);
     g.zc = f32_plan(P, V, d, false);
     g.dh = f32_plan(P, d, nrV, true);
     g.df = f32_plan(nrV, d, P, false);
@@ -1129,9 +1134,8 @@ static GenericFullWs generic_full_ws(const cp_head_desc &ds)
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes); return o; };
     g.logw = take(T * ds.r * 4);
     g.C = take(T * nr * 4);
-    g.part = take(T * nr * f32_slots(g.z.kind, V) * sizeof(float2));
     g.dg = take(T * ds.r * 4);
-    g.dZ = take(g.chunk_pos * nr * ds.V * 4);
+    g.dZ = take(std::max(dz_bytes, g.fwd_pos * nr * f32_slots(g.z.kind, V) * sizeof(float2)));
     g.partial = take(std::max(g.dh.scratch(P, d), g.dG.scratch(ds.r, d)));
     g.total = off;
     return g;
@@ -1147,14 +1151,20 @@ static int full_fwd_t(const cp_head_desc &ds, const TIn *H, const TIn *F, const 
     const long T = (long)ds.T, d = ds.d, V = ds.V, nr = (long)ds.n * ds.r;
     float *lse = at<float>(ctx, cl.lse), *w = at<float>(ctx, cl.w), *gamma = at<float>(ctx, cl.gamma);
     float *logw = at<float>(ws, g.logw), *C = at<float>(ws, g.C);
-    float2 *part = at<float2>(ws, g.part);
+    float2 *part = at<float2>(ws, g.dZ);
     const int slots = f32_slots(g.z.kind, V);
     const F32Plan pg = f32_plan(T, ds.r, d, false);
     launch_f32<TIn, TIn, false, false>(f32_problem<false, false>(H, d, G, d, T, ds.r, d, d, pg), pg.kind, EpiF32Store{logw, ds.r, 0, nullptr}, st);
-    for (long sa = 0; sa < nr; ++sa)
-        launch_f32<TIn, TIn, false, false>(f32_problem<false, false>(H, d, F + sa * V * d, d, T, V, d, d, g.z), g.z.kind,
-                                           EpiF32Logits{part, slots, nr, sa, X, ds.r, C, nullptr, 0}, st);
-    k_position_finish<<<(unsigned)T, kBlock, (size_t)nr * sizeof(float), st>>>(ds.n, ds.r, slots, part, X, C, lse, logw, w, gamma, loss);
+    for (long t0 = 0; t0 < T; t0 += (long)g.fwd_pos) {
+        const long Tc = std::min((long)g.fwd_pos, T - t0), m0 = t0 * nr;
+        const int32_t *Xc = X + t0 * ds.n;
+        for (long sa = 0; sa < nr; ++sa)
+            launch_f32<TIn, TIn, false, false>(f32_problem<false, false>(H + t0 * d, d, F + sa * V * d, d, Tc, V, d, d, g.z), g.z.kind,
+                                               EpiF32Logits{part, slots, nr, sa, Xc, ds.r, C + m0, nullptr, 0}, st);
+        k_position_finish<<<(unsigned)Tc, kBlock, (size_t)nr * sizeof(float), st>>>(ds.n, ds.r, slots, part, Xc, C + m0, lse + m0,
+                                                                                   logw + t0 * ds.r, w + t0 * ds.r, gamma + t0 * ds.r,
+                                                                                   loss + t0);
+    }
     return hipGetLastError() == hipSuccess ? CP_HEAD_OK : CP_HEAD_ERR_LAUNCH;
 }
 

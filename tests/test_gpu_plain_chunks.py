@@ -56,3 +56,19 @@ def test_fine_tuning_loss(gpu, oracle):
                                       torch.from_numpy(tz).cuda(), 0.9, 0.8).cpu().numpy())
     # the same sums over tiles of another width: a few units in the last place
     assert np.abs(got[0] - got[1]).max() <= 4e-6 * np.abs(got[0]).max()
+
+
+# T, d, V, n, r: the forward pass of the full heads in chunks of 75 positions, and of 1024 and a rest
+@pytest.mark.parametrize("shape", [(300, 24, 1, 1, 2), (1500, 8, 3, 1, 3)], ids=lambda s: "x".join(map(str, s)))
+def test_full_heads(gpu, oracle, shape):
+    import torch
+    T, d, V, n, r = shape
+    print(f"case {shape}", flush=True)
+    rng = np.random.default_rng(8)
+    H, F, G = (rng.standard_normal(s).astype(np.float32) for s in ((T, d), (n, r, V, d), (r, d)))
+    X = rng.integers(0, V, (T, n), dtype=np.int32)
+    h = gpu.CpFullHead(F, G, dtype="fp32")
+    Hd, Xd = gpu.to_device(H, "fp32"), torch.from_numpy(X).cuda()
+    loss = h.loss_fwd(Hd, Xd).cpu().numpy()
+    ref = oracle.full_loss_fwd(H, F, G, X)
+    assert np.abs(loss - ref).max() <= 4e-6 * max(1.0, np.abs(ref).max())

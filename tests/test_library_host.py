@@ -86,6 +86,18 @@ def test_plain_forward_workspace_is_bounded(lib):
                 assert need <= rows + statistics + 4096, (T, V, flags, op)
 
 
+def test_plain_full_heads_workspace_is_bounded(lib):
+    """Per row two floats, and for a bounded chunk of positions their logit gradients; the forward pass's statistics have no
+    room of their own."""
+    for T, d, V, n, r in ((8192, 512, 32000, 2, 4), (1 << 20, 64, 512, 2, 2), (1 << 18, 8, 2, 1, 1)):
+        ds = binding.make_desc(T, d, V, n, r, binding.FP32)
+        for op in (binding.OP_FULL_LOSS_FWD, binding.OP_FULL_LOSS_BWD):
+            rows = T * r * (n + 2) * 4
+            gradients = max(1 << 29, n * r * V * 4)
+            parts = 16 * max(r * d, 1 << 20) * 4                # the gate gradient and dH of few positions, split sums
+            assert binding.cp_head_workspace_bytes(ds, op) <= rows + gradients + parts + 4096, (T, V, op)
+
+
 @pytest.mark.parametrize("kw", [dict(T=-1), dict(d=0), dict(V=0), dict(n=0), dict(r=0)])
 def test_bad_dimensions(lib, kw):
     base = dict(T=4, d=8, V=16, n=2, r=2)
