@@ -281,8 +281,7 @@ __global__ void __launch_bounds__(kBlock) k_add_splits(AddSplits job)
 
 // One block per position: the log-normalisers (eq. 5) of its n r head rows from their per-slot statistics, a
 // wavefront per row; C = z[x] - lse (eq. 8) in place of the target logits; the gate's log-softmax (eq. 7) in place of
-// its pre-activations; and the mixture over the experts (eq. 9).  X, C null: log-normalisers only.  gate null:
-// logw is already a log-softmax.  loss null: no mixture.
+// its pre-activations; and the mixture over the experts (eq. 9).  loss null: no mixture.
 __global__ void __launch_bounds__(kBlock) k_position_finish(int n, int r, int slots, const float2 *__restrict__ part,
                                                             const int32_t *__restrict__ X, float *__restrict__ C,
                                                             float *__restrict__ lse_out, float *__restrict__ gate,
@@ -306,25 +305,19 @@ __global__ void __launch_bounds__(kBlock) k_position_finish(int n, int r, int sl
         const float lse = Mx + logf(L);
         if (lane == 0) {
             lse_out[m] = lse;
-            if (C) {
-                const float c = X[m / r] >= 0 ? C[m] - lse : 0.f;
-                C[m] = c;
-                C_s[j] = c;
-            }
+            const float c = X[m / r] >= 0 ? C[m] - lse : 0.f;
+            C[m] = c;
+            C_s[j] = c;
         }
     }
     __syncthreads();
     if (wave != 0) return;
-    float lw = -INFINITY;
-    if (gate) {
-        const float g = lane < r ? gate[t * r + lane] : -INFINITY;
-        const float mx = wave_max(g);
-        const float lse = mx + logf(wave_sum(lane < r ? expf(g - mx) : 0.f));
-        lw = g - lse;
-        if (lane < r) {
-            gate[t * r + lane] = lw;
-            w_out[t * r + lane] = expf(lw);
-        }
+    const float g = lane < r ? gate[t * r + lane] : -INFINITY;
+    const float gm = wave_max(g);
+    const float lw = g - (gm + logf(wave_sum(lane < r ? expf(g - gm) : 0.f)));
+    if (lane < r) {
+        gate[t * r + lane] = lw;
+        w_out[t * r + lane] = expf(lw);
     }
     if (!loss) return;
     float a = -INFINITY;
@@ -336,6 +329,42 @@ __global__ void __launch_bounds__(kBlock) k_position_finish(int n, int r, int sl
     const float L = mx + logf(wave_sum(lane < r ? expf(a - mx) : 0.f));
     if (lane == 0) loss[t] = -L;
     if (lane < r) gamma[t * r + lane] = expf(a - L);
+}
+
+// Log-normalisers (eq. 5) of stored rows of logits: a workgroup per row at a time, eight loads of a thread in flight.  The
+// draft-type calls store their logits anyway, and reading them back costs V floats per row next to the 2 d V operations
+// that made them; statistics in the product's epilogue would take room beside the logits.
+__global__ void __launch_bounds__(1024) k_lse_of_rows(size_t rows, int V, const float *__restrict__ z, float *__restrict__ lse_out)
+{
+    __shared__ float2 red[1024 / kWave];
+    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave, waves = blockDim.x / kWave;
+    for (size_t m = blockIdx.x; m < rows; m += gridDim.x) {
+        const float *zr = z + m * V;
+        float mx = -INFINITY, l = 0.f;
+        for (int v0 = threadIdx.x; v0 < V; v0 += 8 * (int)blockDim.x) {
+            float x[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) x[i] = zr[min(v0 + i * (int)blockDim.x, V - 1)];
+            float mn = mx;
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                if (v0 + i * (int)blockDim.x < V) mn = fmaxf(mn, x[i]);
+            l *= exp_below(mx, mn);
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                if (v0 + i * (int)blockDim.x < V) l += exp_below(x[i], mn);
+            mx = mn;
+        }
+        const float wm = wave_max(mx), wl = wave_sum(l * exp_below(mx, wm));
+        if (lane == 0) red[wave] = make_float2(wm, wl);
+        __syncthreads();
+        if (wave == 0) {
+            const float2 q = lane < waves ? red[lane] : make_float2(-INFINITY, 0.f);
+            const float Mx = wave_max(q.x), L = wave_sum(q.y * exp_below(q.x, Mx));
+            if (lane == 0) lse_out[m] = Mx + logf(L);
+        }
+        __syncthreads();
+    }
 }
 
 // ---- launches: the plan picks the tile
@@ -729,7 +758,6 @@ inline GenericWs generic_ws(const cp_head_desc &ds, int op)
     const size_t M = (size_t)ds.T * ds.n * ds.r, Tr = (size_t)ds.T * ds.r;
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes); return o; };
-    auto take_part = [&] { return take(M * f32_slots(f32_plan((long)M, ds.V, ds.d, false).kind, ds.V) * sizeof(float2)); };
     if (op == CP_HEAD_OP_LOSS_FWD) {
         g.logw = take(Tr * 4);
         g.C = take(M * 4);
@@ -745,7 +773,6 @@ inline GenericWs generic_ws(const cp_head_desc &ds, int op)
         g.Y = take(M * ds.d * 4);
         g.z = take(M * ds.V * 4);
         g.lse = take(M * 4);
-        g.part = take_part();
     }
     g.total = off;
     return g;
@@ -886,16 +913,13 @@ int loss_bwd_t(const cp_head_desc &ds, const TIn *H, const TIn *W, const TIn *U,
 
 // The logits of all `rows` head rows (row-major, V apart) and their log-normalisers, for the draft-type calls
 template <typename TIn>
-void launch_f32_kept_logits(const cp_head_desc &ds, long rows, int heads, const TIn *U, const float *Y, float *z, float2 *part,
-                            float *lse, hipStream_t st)
+void launch_f32_kept_logits(const cp_head_desc &ds, long rows, const TIn *U, const float *Y, float *z, float *lse, hipStream_t st)
 {
     const long d = ds.d, V = ds.V;
     const F32Plan plan = f32_plan(rows, V, d, false);
-    const int slots = f32_slots(plan.kind, V);
     launch_f32<float, TIn, false, false>(f32_problem<false, false>(Y, d, U, d, rows, V, d, d, plan), plan.kind,
-                                         EpiF32Logits{part, slots, 1, 0, nullptr, 1, nullptr, z, V}, st);
-    k_position_finish<<<(unsigned)(rows / heads), kBlock, (size_t)heads * sizeof(float), st>>>(1, heads, slots, part, nullptr, nullptr,
-                                                                                              lse, nullptr, nullptr, nullptr, nullptr);
+                                         EpiF32Logits{nullptr, 0, 1, 0, nullptr, 1, nullptr, z, V}, st);
+    k_lse_of_rows<<<(unsigned)std::min<long>(rows, 1 << 20), V > 2048 ? 1024 : 256, 0, st>>>((size_t)rows, ds.V, z, lse);
 }
 
 template <typename TIn>
@@ -909,7 +933,7 @@ int draft_t(const cp_head_desc &ds, const TIn *H, const TIn *W, const TIn *U, co
     k_gate<TIn><<<(unsigned)B, kWave, 0, st>>>(ds.d, ds.r, H, G, logw, w);
     k_pick_alpha<<<blocks_for(B, kWave), kWave, 0, st>>>(B, ds.n, ds.r, w, uniforms, alpha);
     launch_draft_y(ds, ds.n * ds.r, H, W, G, Y, st);
-    launch_f32_kept_logits<TIn>(ds, (long)M, ds.n * ds.r, U, Y, z, at<float2>(ws, g.part), lse, st);
+    launch_f32_kept_logits<TIn>(ds, (long)M, U, Y, z, lse, st);
     k_sample_generic<<<(unsigned)(B * ds.n), kBlock, 0, st>>>(ds.V, ds.n, ds.r, z, lse, alpha, uniforms, tokens);
     if (logq) k_logq_generic<<<(unsigned)B, kWave, 0, st>>>(ds.V, ds.n, ds.r, logw, z, lse, tokens, logq);
     return hipGetLastError() == hipSuccess ? CP_HEAD_OK : CP_HEAD_ERR_LAUNCH;
@@ -925,7 +949,7 @@ int draft_sequential_t(const cp_head_desc &ds, const TIn *H, const TIn *W, const
     float *z = at<float>(ws, g.z), *lse = at<float>(ws, g.lse);
     k_gate<TIn><<<(unsigned)B, kWave, 0, st>>>(ds.d, ds.r, H, G, logw, w);
     launch_draft_y(ds, ds.n * ds.r, H, W, G, Y, st);
-    launch_f32_kept_logits<TIn>(ds, (long)M, ds.n * ds.r, U, Y, z, at<float2>(ws, g.part), lse, st);
+    launch_f32_kept_logits<TIn>(ds, (long)M, U, Y, z, lse, st);
     k_sample_sequential_generic<<<(unsigned)B, kBlock, 0, st>>>(ds.V, ds.n, ds.r, z, lse, logw, uniforms, tokens, logq);
     return hipGetLastError() == hipSuccess ? CP_HEAD_OK : CP_HEAD_ERR_LAUNCH;
 }
@@ -1032,7 +1056,7 @@ int generic_draft(const cp_head_desc &ds, const void *H, const void *W, const vo
 
 // ---- first-token marginal on the plain path: z of the r first-head rows is stored, then mixed
 struct GenericFirstWs {
-    size_t logw, w, Y, z, lse, part, total;
+    size_t logw, w, Y, z, lse, total;
 };
 static GenericFirstWs generic_first_ws(const cp_head_desc &ds)
 {
@@ -1045,7 +1069,6 @@ static GenericFirstWs generic_first_ws(const cp_head_desc &ds)
     g.Y = take(rows * ds.d * 4);
     g.z = take(rows * ds.V * 4);
     g.lse = take(rows * 4);
-    g.part = take(rows * f32_slots(f32_plan((long)rows, ds.V, ds.d, false).kind, ds.V) * sizeof(float2));
     g.total = off;
     return g;
 }
@@ -1070,7 +1093,7 @@ static int first_token_t(const cp_head_desc &ds, const TIn *H, const TIn *W, con
     k_gate<TIn><<<(unsigned)ds.T, kWave, 0, st>>>(ds.d, ds.r, H, G, logw, w);
     // the first head's matrices are the first r blocks of W, so its rows are (b, a) with nr = r
     launch_draft_y(ds, ds.r, H, W, G, Y, st);
-    launch_f32_kept_logits<TIn>(ds, (long)rows, ds.r, U, Y, z, at<float2>(ws, g.part), lse, st);
+    launch_f32_kept_logits<TIn>(ds, (long)rows, U, Y, z, lse, st);
     launch_first_token_mix(ds, z, (size_t)ds.V, lse, logw, logp, st);
     return hipGetLastError() == hipSuccess ? CP_HEAD_OK : CP_HEAD_ERR_LAUNCH;
 }

@@ -98,6 +98,21 @@ def test_plain_full_heads_workspace_is_bounded(lib):
             assert binding.cp_head_workspace_bytes(ds, op) <= rows + gradients + parts + 4096, (T, V, op)
 
 
+def test_plain_draft_workspace(lib):
+    """The plain path's draft-type calls hold the gate, y, the logits and a log-normaliser per row, nothing else that grows
+    with the vocabulary: the static scratch array takes what its size says."""
+    def aligned(x):
+        return (x + 255) // 256 * 256
+    for T, d, V, n, r in ((8, 512, 48500, 4, 8), (1, 63, 1000, 1, 1), (40, 50, 333, 3, 4)):
+        ds = binding.make_desc(T, d, V, n, r, binding.FP32)
+        for op, rows in ((binding.OP_DRAFT, T * n * r), (binding.OP_DRAFT_SEQUENTIAL, T * n * r), (binding.OP_FIRST_TOKEN, T * r)):
+            need = sum(map(aligned, (T * r * 4, T * r * 4, rows * d * 4, rows * V * 4, rows * 4)))
+            assert binding.cp_head_workspace_bytes(ds, op) == need
+    # the largest batch of this model that the array held before any statistics were kept beside the logits
+    ds = binding.make_desc(8, 512, 48500, 4, 8, binding.FP32)
+    assert binding.cp_head_workspace_bytes(ds, binding.OP_DRAFT) <= binding.STATIC_SCRATCH_BYTES
+
+
 @pytest.mark.parametrize("kw", [dict(T=-1), dict(d=0), dict(V=0), dict(n=0), dict(r=0)])
 def test_bad_dimensions(lib, kw):
     base = dict(T=4, d=8, V=16, n=2, r=2)
