@@ -35,13 +35,14 @@ typedef F32Tile<32, 32, 1, 1, 4, 64> F32Small;
 constexpr int kF32Threads = 256;
 
 // One contraction.  The tile index runs over tiles_m * tiles_n * splits; split s takes the k-values
-// [s * k_split, (s + 1) * k_split).
+// [s * k_split, (s + 1) * k_split).  With batch_b, the splits are contractions of their own instead: the s-th takes all of K
+// and B from s * batch_b elements on.
 struct F32Problem {
     const void *A, *B;
     long lda, ldb;          // elements
     long M, N;
     long ka, kb;            // k-values that may be read of A and of B; the sum runs over the smaller number
-    long k_split;
+    long k_split, batch_b;
     int tiles_m, tiles_n, splits;
     int vec;                // four consecutive elements of either operand may be loaded at once
     __host__ __device__ long tiles() const { return (long)tiles_m * tiles_n * splits; }
@@ -168,13 +169,13 @@ struct F32Gemm {
         const int rows_in_band = min(8, p.tiles_m - band * 8);
         const int tm = band * 8 + in_band % rows_in_band, tn = in_band / rows_in_band;
         const long m0 = (long)tm * Tile::BM, n0 = (long)tn * Tile::BN;
-        const long k_lo = split * p.k_split, k_all = p.ka < p.kb ? p.ka : p.kb;
+        const long k_lo = p.batch_b ? 0 : split * p.k_split, k_all = p.ka < p.kb ? p.ka : p.kb;
         const long k_hi = k_lo + p.k_split < k_all ? k_lo + p.k_split : k_all;
 
         LoadA la;
         LoadB lb;
         la.init(static_cast<const TA *>(p.A), p.lda, m0, p.M, k_hi);
-        lb.init(static_cast<const TB *>(p.B), p.ldb, n0, p.N, k_hi);
+        lb.init(static_cast<const TB *>(p.B) + split * p.batch_b, p.ldb, n0, p.N, k_hi);
         f32v4_t acc[TM][TN];
 #pragma unroll
         for (int i = 0; i < TM; ++i)
@@ -284,6 +285,7 @@ struct F32Plan {
 };
 struct F32Shape {
     long M, N, K;
+    long batch = 1;
 };
 // The choice is the one with the least time in a model with measured constants: rounds of tiles over the compute units
 // at the average cost of a tile, not less than the longest tile alone on its compute unit, plus, if a sum is split, the
@@ -304,7 +306,7 @@ inline void f32_plan(const F32Shape *shape, int count, bool may_split, F32Plan *
             for (int i = 0; i < count; ++i) {
                 const F32Shape &q = shape[i];
                 const int s = 1 << choice[i];
-                const double n = (double)((q.M + e - 1) / e) * (double)((q.N + e - 1) / e) * s, k = (double)q.K / s;
+                const double n = (double)((q.M + e - 1) / e) * (double)((q.N + e - 1) / e) * s * q.batch, k = (double)q.K / s;
                 units += n;
                 work += n * (k * kShared[kind] + kFixed[kind]);
                 longest = longest > k ? longest : k;
@@ -325,9 +327,9 @@ inline void f32_plan(const F32Shape *shape, int count, bool may_split, F32Plan *
         }
     }
 }
-inline F32Plan f32_plan(long M, long N, long K, bool may_split)
+inline F32Plan f32_plan(long M, long N, long K, bool may_split, long batch = 1)
 {
-    const F32Shape q{M, N, K};
+    const F32Shape q{M, N, K, batch};
     F32Plan p;
     f32_plan(&q, 1, may_split, &p);
     return p;
@@ -344,6 +346,7 @@ inline F32Problem f32_problem(const TA *A, long lda, const TB *B, long ldb, long
     p.tiles_m = (int)((M + e - 1) / e);
     p.tiles_n = (int)((N + e - 1) / e);
     p.splits = plan.splits;
+    p.batch_b = 0;
     const long K = ka < kb ? ka : kb;
     p.k_split = (K + plan.splits - 1) / plan.splits;
     p.k_split = (p.k_split + 63) / 64 * 64;              // whole K-steps, and every split's start stays aligned
@@ -351,6 +354,16 @@ inline F32Problem f32_problem(const TA *A, long lda, const TB *B, long ldb, long
         return ld % 4 == 0 && extent % 4 == 0 && reinterpret_cast<uintptr_t>(X) % (4 * elem) == 0 ? 1 : 0;
     };
     p.vec = four(A, sizeof(TA), lda, AKM ? 0 : ka) && four(B, sizeof(TB), ldb, BKM ? 0 : kb);
+    return p;
+}
+
+// `batch` contractions of one A with the matrices B, B + stride, ... in one launch; the epilogue's split is the matrix.
+inline F32Problem f32_batch(F32Problem p, int batch, long stride)
+{
+    p.splits = batch;
+    p.batch_b = stride;
+    p.k_split = p.ka < p.kb ? p.ka : p.kb;
+    if (stride % 4) p.vec = 0;
     return p;
 }
 

@@ -110,28 +110,28 @@ struct EpiF32Store {
 // maximum does, and a NaN stays one, also where it is alone and mx is still -infinity.
 __device__ __forceinline__ float exp_below(float x, float mx) { return x == mx ? 1.f : expf(x - mx); }
 
-// Logits of the head rows m = row * row_mul + row_add: (maximum, sum of exp(z - maximum)) over the sub-tile's columns
+// Logits of the head rows m = row * row_mul + batch: (maximum, sum of exp(z - maximum)) over the sub-tile's columns
 // to part[m, slots], the target logit to zt[m] (if X is given), and the logits themselves to z[row, ldz] (if z is
 // given; columns from V up to ldz become zero).
 struct EpiF32Logits {
     float2 *part;
     int slots;
-    long row_mul, row_add;
+    long row_mul;
     const int32_t *X;       // null: no target logits
     int r;
     float *zt;
     float *z;               // null: logits are not kept
     long ldz;
     template <class Tile>
-    __device__ __forceinline__ void run(f32v4_t (&acc)[Tile::TM][Tile::TN], long row0, long col0, const F32Problem &p, int, int slot,
-                                        int lane) const
+    __device__ __forceinline__ void run(f32v4_t (&acc)[Tile::TM][Tile::TN], long row0, long col0, const F32Problem &p, int batch,
+                                        int slot, int lane) const
     {
 #pragma unroll
         for (int i = 0; i < Tile::TM; ++i)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const long row = row0 + f32_row(i, v, lane);
-                const long m = row * row_mul + row_add;
+                const long m = row * row_mul + batch;
                 const bool in = row < p.M;
                 if (z && in) {
 #pragma unroll
@@ -163,31 +163,32 @@ struct EpiF32Logits {
     }
 };
 
-// Logit gradients of the head rows m = m0 + row * row_mul + row_add from their recomputed logits:
+// Logit gradients of the head rows m = m0 + row * row_mul + batch from their recomputed logits:
 //   dz[v] = up_t gamma[t, a] (exp(z - lse[m]) - 1[v = x]),  zero for a dropped factor and from V up to ldz,
-// written to dZ[row, ldz] (row-strided by ldz; a head's rows start at dZ).  The first column slot also writes
+// written to dZ[row, ldz] (row-strided by ldz; the heads of a batch lie side by side in the row).  The first column slot also writes
 // dg[t, a] = up_t (w - gamma), the derivative of eq. 9 with respect to the gate pre-activations, if dg is given.
 struct EpiF32Dz {
     float *dZ;
     long ldz, columns;      // columns to write (V, or V rounded up to the padding)
     size_t m0;
-    long row_mul, row_add;
+    long row_mul;
     int n, r;
     const int32_t *X;
     const float *lse, *w, *gamma, *dloss;
     float scale;
     float *dg;
     template <class Tile>
-    __device__ __forceinline__ void run(f32v4_t (&acc)[Tile::TM][Tile::TN], long row0, long col0, const F32Problem &p, int, int slot,
-                                        int lane) const
+    __device__ __forceinline__ void run(f32v4_t (&acc)[Tile::TM][Tile::TN], long row0, long col0, const F32Problem &p, int batch,
+                                        int slot, int lane) const
     {
+        float *out = dZ + batch * p.N;
 #pragma unroll
         for (int i = 0; i < Tile::TM; ++i)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const long row = row0 + f32_row(i, v, lane);
                 if (row >= p.M) continue;
-                const unsigned m = (unsigned)(m0 + row * row_mul + row_add), g = m / (unsigned)r;     // fewer than 2^31 head rows
+                const unsigned m = (unsigned)(m0 + row * row_mul + batch), g = m / (unsigned)r;     // fewer than 2^31 head rows
                 const unsigned a = m - g * r;
                 const size_t t = g / (unsigned)n;
                 const long x = X[g];
@@ -199,7 +200,7 @@ struct EpiF32Dz {
                 for (int j = 0; j < Tile::TN; ++j) {
                     const long col = col0 + f32_col(j, lane);
                     if (col >= columns) continue;
-                    dZ[row * ldz + col] = x < 0 || col >= p.N ? 0.f : coef * (expf(acc[i][j][v] - l) - (col == x ? 1.f : 0.f));
+                    out[row * ldz + col] = x < 0 || col >= p.N ? 0.f : coef * (expf(acc[i][j][v] - l) - (col == x ? 1.f : 0.f));
                 }
             }
     }
@@ -790,7 +791,7 @@ void fwd_rows_t(const cp_head_desc &ds, const TIn *H, const TIn *W, const TIn *U
     for (size_t t0 = 0; t0 < T; t0 += c.pos) {
         const size_t Tc = std::min(c.pos, T - t0), m0 = t0 * nr;
         launch_f32<float, TIn, false, false>(f32_problem<false, false>((const float *)b.Y + m0 * d, d, U, d, (long)(Tc * nr), V, d, d, c.plan),
-                                             c.plan.kind, EpiF32Logits{part, c.slots, 1, 0, X + t0 * n, ds.r, b.C + m0, nullptr, 0}, st);
+                                             c.plan.kind, EpiF32Logits{part, c.slots, 1, X + t0 * n, ds.r, b.C + m0, nullptr, 0}, st);
         k_position_finish<<<(unsigned)Tc, kBlock, nr * sizeof(float), st>>>(ds.n, ds.r, c.slots, part, X + t0 * n, b.C + m0, b.lse + m0,
                                                                            b.logw + t0 * r, b.w + t0 * r, b.gamma + t0 * r,
                                                                            loss ? loss + t0 : nullptr);
@@ -893,7 +894,7 @@ void loss_dz_launch(void *user, size_t m0, size_t Mc, float *dZ, long ldz, hipSt
     const long d = ds.d;
     const F32Plan plan = f32_plan((long)generic_chunk_rows(ds), ds.V, d, false);
     launch_f32<float, TIn, false, false>(f32_problem<false, false>(a->Y + m0 * d, d, a->U, d, (long)Mc, ds.V, d, d, plan), plan.kind,
-                                         EpiF32Dz{dZ, ldz, ldz, m0, 1, 0, ds.n, ds.r, a->X, a->lse, a->w, a->gamma, a->dloss, a->scale,
+                                         EpiF32Dz{dZ, ldz, ldz, m0, 1, ds.n, ds.r, a->X, a->lse, a->w, a->gamma, a->dloss, a->scale,
                                                   a->dg}, st);
 }
 
@@ -918,7 +919,7 @@ void launch_f32_kept_logits(const cp_head_desc &ds, long rows, const TIn *U, con
     const long d = ds.d, V = ds.V;
     const F32Plan plan = f32_plan(rows, V, d, false);
     launch_f32<float, TIn, false, false>(f32_problem<false, false>(Y, d, U, d, rows, V, d, d, plan), plan.kind,
-                                         EpiF32Logits{nullptr, 0, 1, 0, nullptr, 1, nullptr, z, V}, st);
+                                         EpiF32Logits{nullptr, 0, 1, nullptr, 1, nullptr, z, V}, st);
     k_lse_of_rows<<<(unsigned)std::min<long>(rows, 1 << 20), V > 2048 ? 1024 : 256, 0, st>>>((size_t)rows, ds.V, z, lse);
 }
 
@@ -990,7 +991,7 @@ void generic_logits_rows(const cp_head_desc &ds, const void *U, const float *Y, 
 {
     const long d = ds.d, V = ds.V;
     const F32Plan plan = f32_plan((long)generic_chunk_rows(ds), V, d, false);
-    const EpiF32Logits epi{nullptr, 0, 1, 0, nullptr, 1, nullptr, z, ldz};
+    const EpiF32Logits epi{nullptr, 0, 1, nullptr, 1, nullptr, z, ldz};
     if (ds.dtype == CP_HEAD_FP32)
         launch_f32<float, float, false, false>(f32_problem<false, false>(Y + m0 * d, d, (const float *)U, d, (long)Mc, V, d, d, plan),
                                                plan.kind, epi, st);
@@ -1126,7 +1127,7 @@ int aux_balance(const cp_head_desc &ds, const void *H, const void *G, int64_t *c
     return hipGetLastError() == hipSuccess ? CP_HEAD_OK : CP_HEAD_ERR_LAUNCH;
 }
 
-// ---- full heads on the plain path: one product per (s, a) over the positions, whose head rows are
+// ---- full heads on the plain path: the products of all (s, a) with the positions in one launch, whose head rows are
 // m = t n r + sa.  A chunk's gradients are stored [positions, n r, V], so that dH and dF are one product each.
 struct GenericFullWs {
     size_t logw, C, dg, dZ, partial, total;     // dZ: in the forward pass, the row statistics of a chunk
@@ -1148,8 +1149,8 @@ static GenericFullWs generic_full_ws(const cp_head_desc &ds)
     size_t fwd = std::max<size_t>(dz_bytes / (nr * most_slots * sizeof(float2)), 1);
     if (fwd > 128) fwd -= fwd % 128;
     g.fwd_pos = std::min(fwd, std::max<size_t>(T, 1));
-    g.z = f32_plan((long)g.fwd_pos, V, d, false);
-    g.zc = f32_plan(P, V, d, false);
+    g.z = f32_plan((long)g.fwd_pos, V, d, false, (long)nr);
+    g.zc = f32_plan(P, V, d, false, (long)nr);
     g.dh = f32_plan(P, d, nrV, true);
     g.df = f32_plan(nrV, d, P, false);
     g.dG = f32_plan(ds.r, d, (long)T, true);
@@ -1181,9 +1182,8 @@ static int full_fwd_t(const cp_head_desc &ds, const TIn *H, const TIn *F, const 
     for (long t0 = 0; t0 < T; t0 += (long)g.fwd_pos) {
         const long Tc = std::min((long)g.fwd_pos, T - t0), m0 = t0 * nr;
         const int32_t *Xc = X + t0 * ds.n;
-        for (long sa = 0; sa < nr; ++sa)
-            launch_f32<TIn, TIn, false, false>(f32_problem<false, false>(H + t0 * d, d, F + sa * V * d, d, Tc, V, d, d, g.z), g.z.kind,
-                                               EpiF32Logits{part, slots, nr, sa, Xc, ds.r, C + m0, nullptr, 0}, st);
+        launch_f32<TIn, TIn, false, false>(f32_batch(f32_problem<false, false>(H + t0 * d, d, F, d, Tc, V, d, d, g.z), (int)nr, V * d),
+                                           g.z.kind, EpiF32Logits{part, slots, nr, Xc, ds.r, C + m0, nullptr, 0}, st);
         k_position_finish<<<(unsigned)Tc, kBlock, (size_t)nr * sizeof(float), st>>>(ds.n, ds.r, slots, part, Xc, C + m0, lse + m0,
                                                                                    logw + t0 * ds.r, w + t0 * ds.r, gamma + t0 * ds.r,
                                                                                    loss + t0);
@@ -1203,10 +1203,9 @@ static int full_bwd_t(const cp_head_desc &ds, const TIn *H, const TIn *F, const 
     float *dg = at<float>(ws, g.dg), *dZ = at<float>(ws, g.dZ), *partial = at<float>(ws, g.partial);
     for (long t0 = 0; t0 < T; t0 += (long)g.chunk_pos) {
         const long Tc = std::min((long)g.chunk_pos, T - t0);
-        for (long sa = 0; sa < nr; ++sa)
-            launch_f32<TIn, TIn, false, false>(f32_problem<false, false>(H + t0 * d, d, F + sa * V * d, d, Tc, V, d, d, g.zc), g.zc.kind,
-                                               EpiF32Dz{dZ + sa * V, nrV, V, (size_t)(t0 * nr), nr, sa, ds.n, ds.r, X, lse, w, gamma,
-                                                        dloss, scale, dg}, st);
+        launch_f32<TIn, TIn, false, false>(f32_batch(f32_problem<false, false>(H + t0 * d, d, F, d, Tc, V, d, d, g.zc), (int)nr, V * d),
+                                           g.zc.kind, EpiF32Dz{dZ, nrV, V, (size_t)(t0 * nr), nr, ds.n, ds.r, X, lse, w, gamma, dloss,
+                                                               scale, dg}, st);
         // dH = dZ F + dg G (contraction over heads and vocabulary), dF (+)= dZ^T H (over the chunk's positions)
         const F32Problem ph = f32_problem<false, true>((const float *)dZ, nrV, F, d, Tc, d, nrV, nrV, g.dh);
         launch_f32<float, TIn, false, true>(ph, g.dh.kind, EpiF32Dh<TIn>{dH + t0 * d, dg + t0 * ds.r, G, ds.r, partial}, st);
