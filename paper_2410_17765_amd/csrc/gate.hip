@@ -83,12 +83,13 @@ __device__ __forceinline__ void gate_rows(size_t t0, size_t T, int d, int r, con
 // 32, 16, ... 1 apart add up.  The log-weights enter exponentials whose results are rounded to bf16, in the fine-tuning
 // loss next to logits of magnitude ten, so that another order of the same fp32 sums moved its gradients by 1e-4 (the order
 // of the matrix instruction, which the arg-max counts above keep).
-// A wavefront takes four positions and eight experts at a time: a value of H meets eight experts and one of G four
+// A wavefront takes four positions and up to eight experts at a time: a value of H meets eight experts and one of G four
 // positions in registers, and 48 loads are in flight, where one position and one expert at a time had each load feed one
 // multiplication, one latency after the other.  Bound by those latencies for few positions, by the stream of H and the
 // vector units next to it for many: 8.7 us at T = 1500, d = 768, r = 5 (22 one at a time, 6.3 with the matrix instruction),
 // 36 us at T = 16384, d = 4096, r = 8 (3.7 TB/s; 29 with the matrix instruction), in calls of 7 and 440 ms.
-constexpr int kGatePos = 4, kGateExperts = 8;
+// UN blocks of 64 columns are in flight, so that the loads per wavefront stay near 48 with fewer experts.
+constexpr int kGatePos = 4;
 
 // v[i], summed over the wavefront for each of the COUNT of them, arrives in v[0] of the lanes whose upper bits are i: at
 // each step a lane hands half of its values to the lane OFF away and adds what it gets for the other half.
@@ -114,6 +115,7 @@ __device__ __forceinline__ bf16_t ld_at(const bf16_t *p, unsigned bytes)
     return *reinterpret_cast<const bf16_t *>(reinterpret_cast<const char *>(p) + bytes);
 }
 
+template <int EXPERTS, int UN>
 __global__ void __launch_bounds__(kBlock) k_gate_bf16(size_t T, int d, int r, const bf16_t *__restrict__ H, const bf16_t *__restrict__ G,
                                                       float *__restrict__ logw, float *__restrict__ w)
 {
@@ -123,40 +125,41 @@ __global__ void __launch_bounds__(kBlock) k_gate_bf16(size_t T, int d, int r, co
     const bf16_t *h[kGatePos];                      // positions past T and experts past r repeat the last one, not stored
 #pragma unroll
     for (int p = 0; p < kGatePos; ++p) h[p] = H + (t0 + p < T ? t0 + p : T - 1) * d;
-    for (int a0 = 0; a0 < r; a0 += kGateExperts) {
-        const bf16_t *g[kGateExperts];
+    for (int a0 = 0; a0 < r; a0 += EXPERTS) {
+        const bf16_t *g[EXPERTS];
 #pragma unroll
-        for (int e = 0; e < kGateExperts; ++e) g[e] = G + (size_t)min(a0 + e, r - 1) * d;
-        float acc[kGatePos * kGateExperts];
+        for (int e = 0; e < EXPERTS; ++e) g[e] = G + (size_t)min(a0 + e, r - 1) * d;
+        float acc[kGatePos * EXPERTS];
 #pragma unroll
-        for (int i = 0; i < kGatePos * kGateExperts; ++i) acc[i] = 0.f;
+        for (int i = 0; i < kGatePos * EXPERTS; ++i) acc[i] = 0.f;
         // `blocks` blocks of 64 columns, all their loads ahead of the arithmetic
         auto add = [&](int k0, auto blocks) {
-            constexpr int UN = decltype(blocks)::value;
-            bf16_t hv[UN][kGatePos], gv[UN][kGateExperts];
+            constexpr int N = decltype(blocks)::value;
+            bf16_t hv[N][kGatePos], gv[N][EXPERTS];
 #pragma unroll
-            for (int u = 0; u < UN; ++u) {
+            for (int u = 0; u < N; ++u) {
                 const unsigned at = (unsigned)(k0 + u * kWave + lane) * sizeof(bf16_t);
 #pragma unroll
                 for (int p = 0; p < kGatePos; ++p) hv[u][p] = ld_at(h[p], at);
 #pragma unroll
-                for (int e = 0; e < kGateExperts; ++e) gv[u][e] = ld_at(g[e], at);
+                for (int e = 0; e < EXPERTS; ++e) gv[u][e] = ld_at(g[e], at);
             }
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int u = 0; u < UN; ++u)
+            for (int u = 0; u < N; ++u)
 #pragma unroll
                 for (int p = 0; p < kGatePos; ++p)
 #pragma unroll
-                    for (int e = 0; e < kGateExperts; ++e)
-                        acc[p * kGateExperts + e] += bf16_to_f32(gv[u][e]) * bf16_to_f32(hv[u][p]);
+                    for (int e = 0; e < EXPERTS; ++e)
+                        acc[p * EXPERTS + e] += bf16_to_f32(gv[u][e]) * bf16_to_f32(hv[u][p]);
         };
         int k0 = 0;
-        for (; k0 + 4 * kWave <= d; k0 += 4 * kWave) add(k0, std::integral_constant<int, 4>());
+        for (; k0 + UN * kWave <= d; k0 += UN * kWave) add(k0, std::integral_constant<int, UN>());
         for (; k0 < d; k0 += kWave) add(k0, std::integral_constant<int, 1>());
-        wave_sum_each<kGatePos * kGateExperts, 32>(acc, lane);
-        const int at = lane >> 1;                   // which of the 32 sums this lane holds
-        if (!(lane & 1) && a0 + at % kGateExperts < r) g_s[wave][at / kGateExperts][a0 + at % kGateExperts] = acc[0];
+        wave_sum_each<kGatePos * EXPERTS, 32>(acc, lane);
+        constexpr int kLanes = kWave / (kGatePos * EXPERTS);      // that hold the same sum
+        const int at = lane / kLanes;
+        if (lane % kLanes == 0 && a0 + at % EXPERTS < r) g_s[wave][at / EXPERTS][a0 + at % EXPERTS] = acc[0];
     }
     __syncthreads();
     for (int p = 0; p < kGatePos && t0 + p < T; ++p) {
@@ -272,7 +275,11 @@ __global__ void __launch_bounds__(kBlock) k_dgate_reduce(int chunks, size_t rd, 
 void launch_gate_bf16(const cp_head_desc &ds, const bf16_t *H, const bf16_t *G, float *logw, float *w, hipStream_t st)
 {
     const size_t T = (size_t)ds.T;
-    k_gate_bf16<<<blocks_for(T, kWaves * kGatePos), kBlock, 0, st>>>(T, ds.d, ds.r, H, G, logw, w);
+    const unsigned blocks = blocks_for(T, kWaves * kGatePos);
+    if (ds.r == 1) k_gate_bf16<1, 8><<<blocks, kBlock, 0, st>>>(T, ds.d, ds.r, H, G, logw, w);
+    else if (ds.r == 2) k_gate_bf16<2, 8><<<blocks, kBlock, 0, st>>>(T, ds.d, ds.r, H, G, logw, w);
+    else if (ds.r <= 4) k_gate_bf16<4, 6><<<blocks, kBlock, 0, st>>>(T, ds.d, ds.r, H, G, logw, w);
+    else k_gate_bf16<8, 4><<<blocks, kBlock, 0, st>>>(T, ds.d, ds.r, H, G, logw, w);
 }
 
 void launch_aux_argmax_bf16(const cp_head_desc &ds, const bf16_t *H, const bf16_t *G, unsigned long long *counts, hipStream_t st)

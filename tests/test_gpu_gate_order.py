@@ -24,8 +24,9 @@ def gates_in_order(H, G):
     return out
 
 
-# T, d, r: less than one tile of 4 positions and 8 experts, one more than a tile of either, several groups of experts
-@pytest.mark.parametrize("shape", [(1, 64, 2), (16, 128, 8), (37, 320, 9), (130, 1088, 64)], ids=lambda s: "x".join(map(str, s)))
+# T, d, r: less than one tile of 4 positions and 8 experts, one more than a tile of either, several groups of experts; fewer
+# experts and more columns in flight, whole rounds of columns and a rest
+@pytest.mark.parametrize("shape", [(1, 64, 2), (16, 128, 8), (37, 320, 9), (130, 1088, 64), (33, 1088, 2), (20, 704, 4), (9, 448, 3)], ids=lambda s: "x".join(map(str, s)))
 def test_log_weights(shape):
     import torch
     from paper_2410_17765_amd import head
@@ -48,7 +49,7 @@ def test_log_weights(shape):
     top = np.sort(g, axis=1)
     # where the largest gate leads by 20, the sum of exponentials is 1 and the log-weight g_0 - max g, exactly
     clear = top[:, -1] - top[:, -2] > 20
-    assert clear.sum() >= 0.8 * T or r == 2
+    assert clear.sum() >= 0.7 * T or T == 1
     expect = g.max(axis=1) - g[:, 0]
     np.testing.assert_array_equal(loss[clear], expect[clear])
 
