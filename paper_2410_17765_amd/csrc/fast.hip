@@ -693,6 +693,63 @@ __global__ void __launch_bounds__(kSegWaves * kWave) k_segment_logits(int d, int
     }
 }
 
+// The same two steps for calls that want no log-probability: a workgroup per (b, s) forms the logits of the drawn expert's
+// segment alone (a wavefront walks the contraction for four tokens together) and picks the token from them.  One launch
+// instead of two for the numbers of draws that just fill the chip, whole calls, us, this against the two: 256 draws (d = 512,
+// V = 1000) 39.5 / 44.5, 512 (d = 1024, V = 32000) 174 / 179, 600 (d = 512, V = 7000) 77.1 / 79.8; but 2000 (d = 128, V = 3000)
+// 85.3 / 74.8 and 4096 (d = 256, V = 100) 134 / 124, where the matrix instruction counts, and the same from 36 draws down.
+constexpr unsigned kAloneDraws = 64, kAloneDrawsMost = 1024;
+__global__ void __launch_bounds__(kWideBlock) k_draft_pick_alone(int d, int V, int n, int r, int seg_cols, const float *__restrict__ lse,
+                                                                 const bf16_t *__restrict__ Y, const bf16_t *__restrict__ U,
+                                                                 const int32_t *__restrict__ alpha, const int32_t *__restrict__ seg,
+                                                                 const double *__restrict__ base,
+                                                                 const float *__restrict__ uniforms, int32_t *__restrict__ tokens)
+{
+    __shared__ float p_s[kMaxSegCols];
+    const size_t bs = blockIdx.x;                 // b*n + s
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int code = seg[bs];
+    if (code < 0) {                               // the running sum over the whole vocabulary never passes u
+        if (threadIdx.x == 0) tokens[bs] = V - 1;
+        return;
+    }
+    const size_t b = bs / n, m = bs * r + alpha[b];
+    const float l = lse[m];
+    const int v0 = code * seg_cols, cols = min(seg_cols, V - v0);
+    constexpr int CW = 4;
+    const u32x4_t *yrow = reinterpret_cast<const u32x4_t *>(Y + m * d);
+    for (int c0 = wave * CW; c0 < cols; c0 += kWideBlock / kWave * CW) {
+        float acc[CW] = {0.f, 0.f, 0.f, 0.f};
+        const u32x4_t *urow[CW];
+#pragma unroll
+        for (int e = 0; e < CW; ++e)
+            urow[e] = reinterpret_cast<const u32x4_t *>(U + (size_t)(v0 + min(c0 + e, cols - 1)) * d);
+        for (int k = lane; k < d / 8; k += kWave) {
+            const u32x4_t yv = yrow[k];
+            u32x4_t uv[CW];
+#pragma unroll
+            for (int e = 0; e < CW; ++e) uv[e] = urow[e][k];
+#pragma unroll
+            for (int e = 0; e < CW; ++e)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    acc[e] += __uint_as_float(uv[e][q] << 16) * __uint_as_float(yv[q] << 16);
+                    acc[e] += __uint_as_float(uv[e][q] & 0xFFFF0000u) * __uint_as_float(yv[q] & 0xFFFF0000u);
+                }
+        }
+#pragma unroll
+        for (int e = 0; e < CW; ++e) {
+            const float z = wave_sum(acc[e]);
+            if (lane == 0 && c0 + e < cols) p_s[c0 + e] = expf(z - l);
+        }
+    }
+    __syncthreads();
+    if (wave != 0) return;
+    const int at = wave_pick_token(seg_cols, cols, base[bs], (double)uniforms[b * (1 + n) + 1 + bs % n], lane,
+                                   [&](int i) { return (double)p_s[i]; });
+    if (lane == 0) tokens[bs] = v0 + at;
+}
+
 // Per b: the tokens of its n draws from the logits of their segments (a wavefront per draw), then
 // logq[b] = logsumexp_a( log w_a + sum_s (z_sa[tok_s] - lse_sa) ): eq. 9 at the drawn tuple over all experts
 __global__ void __launch_bounds__(kWideBlock) k_draft_pick(int V, int n, int r, int seg_cols, const float *__restrict__ logw,
@@ -1645,6 +1702,11 @@ int fast_draft(const cp_head_desc &ds, const void *Hv, const void *Wv, const voi
     {
         ProfileScope prof("draft_lse_segment", (double)M * parts * 8, st);
         k_draft_lse_segment<<<rows, kWideBlock, 0, st>>>(n, r, parts, (V - 1) / seg_cols, part, alpha, uniforms, lse, seg, base);
+    }
+    if (!logq && rows >= kAloneDraws && rows <= kAloneDrawsMost) {
+        ProfileScope prof("draft_pick", (double)rows * seg_cols * d * 2, st);
+        k_draft_pick_alone<<<rows, kWideBlock, 0, st>>>(d, V, n, r, seg_cols, lse, Y, U, alpha, seg, base, uniforms, tokens);
+        return hipGetLastError() == hipSuccess ? CP_HEAD_OK : CP_HEAD_ERR_LAUNCH;
     }
     {
         ProfileScope prof("draft_segment_logits", (double)rows * seg_cols * d * 2, st);
