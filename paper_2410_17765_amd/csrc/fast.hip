@@ -636,22 +636,22 @@ __global__ void __launch_bounds__(kWideBlock) k_draft_lse_segment(int n, int r, 
                  seg_out + bs, base_out + bs);
 }
 
-// The logits of a segment for the r head rows of a (row, draw), z[(row0 + a) * seg_cols + i] = U[v0 + i] . y[row0 + a]:
+// The logits of a segment for the r head rows of a (row, draw), z[(x * r + a) * seg_cols + i] = U[v0 + i] . y[row0 + a]:
 // a workgroup per (b, draw), 16 tokens and 16 experts, on the 16x16x32 matrix instruction; its eight wavefronts share
 // the contraction in blocks of 64 columns (a lane loads 32 consecutive bytes of its row per block, four lanes a cache
 // line) and their partial products meet in LDS.  Bound by the latency of the cold rows of U: the rows of a segment are
 // spread over 4 or 8 workgroups with 16 lines per lane in flight each, where one workgroup per draw had the whole segment
-// (0.5 or 1 MB) to fetch: the draft call 397 -> 371 us at B = 1, d = 4096, V = 128256, n = 4, r = 8.  draw0, draws: (b, s) of workgroup x is b = x / draws, s = draw0 + x % draws; seg is indexed
-// by x.
+// (0.5 or 1 MB) to fetch: the draft call 397 -> 371 us at B = 1, d = 4096, V = 128256, n = 4, r = 8.
+// (b, s) of workgroup x is b = x / draws, s = draw0 + x % draws; its segment is seg_in[b * seg_ld + x % draws].
 constexpr int kSegWaves = 8;
 __global__ void __launch_bounds__(kSegWaves * kWave) k_segment_logits(int d, int V, int n, int r, int seg_cols, int draw0,
                                                                       int draws, const bf16_t *__restrict__ Y,
                                                                       const bf16_t *__restrict__ U,
-                                                                      const int32_t *__restrict__ seg_in,
+                                                                      const int32_t *__restrict__ seg_in, int seg_ld,
                                                                       float *__restrict__ z)
 {
     __shared__ float red[kSegWaves][16][17];
-    const int x = (int)blockIdx.x, code = seg_in[x];
+    const int x = (int)blockIdx.x, code = seg_in[(size_t)(x / draws) * seg_ld + x % draws];
     const int v0 = (code < 0 ? ~code : code) * seg_cols + (int)blockIdx.y * 16;
     if (v0 >= V) return;
     const size_t row0 = ((size_t)(x / draws) * n + draw0 + x % draws) * r;
@@ -689,7 +689,7 @@ __global__ void __launch_bounds__(kSegWaves * kWave) k_segment_logits(int d, int
         float sum = 0.f;
 #pragma unroll
         for (int w = 0; w < kSegWaves; ++w) sum += red[w][tok][e];
-        z[(row0 + a0 + e) * seg_cols + blockIdx.y * 16 + tok] = sum;
+        z[((size_t)x * r + a0 + e) * seg_cols + blockIdx.y * 16 + tok] = sum;
     }
 }
 
@@ -750,9 +750,10 @@ __global__ void __launch_bounds__(kWideBlock) k_draft_pick_alone(int d, int V, i
     if (lane == 0) tokens[bs] = v0 + at;
 }
 
-// Per b: the tokens of its n draws from the logits of their segments (a wavefront per draw), then
-// logq[b] = logsumexp_a( log w_a + sum_s (z_sa[tok_s] - lse_sa) ): eq. 9 at the drawn tuple over all experts
-__global__ void __launch_bounds__(kWideBlock) k_draft_pick(int V, int n, int r, int seg_cols, const float *__restrict__ logw,
+// Per b: the tokens of its draws s0 .. s0 + draws - 1 from the logits of their segments (a wavefront per draw; z as
+// k_segment_logits leaves it), then logq[b] = logsumexp_a( log w_a + sum_s (z_sa[tok_s] - lse_sa) ): eq. 9 at the drawn
+// tuple over all experts, the sum so far in logw between launches.
+__global__ void __launch_bounds__(kWideBlock) k_draft_pick(int V, int n, int r, int seg_cols, int s0, int draws, float *__restrict__ logw,
                                                            const float *__restrict__ lse, const float *__restrict__ z,
                                                            const int32_t *__restrict__ alpha,
                                                            const int32_t *__restrict__ seg, const double *__restrict__ base,
@@ -762,27 +763,27 @@ __global__ void __launch_bounds__(kWideBlock) k_draft_pick(int V, int n, int r, 
     __shared__ int at_s[64];                          // the drawn token's place in its segment
     const size_t b = blockIdx.x;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int s = wave; s < n; s += kWideBlock / kWave) {
-        const size_t bs = b * n + s, m = bs * r + alpha[b];
+    for (int i = wave; i < draws; i += kWideBlock / kWave) {
+        const int s = s0 + i;
+        const size_t bs = b * n + s;
         const int code = seg[bs], v0 = (code < 0 ? ~code : code) * seg_cols, cols = min(seg_cols, V - v0);
-        const float l = lse[m];
-        const float *zr = z + m * seg_cols;
+        const float l = lse[bs * r + alpha[b]];
+        const float *zr = z + ((b * draws + i) * r + alpha[b]) * seg_cols;
         // the running sum over the whole vocabulary never passes u: the last token
         const int at = code < 0 ? cols - 1
                                 : wave_pick_token(seg_cols, cols, base[bs], (double)uniforms[b * (1 + n) + 1 + s], lane,
-                                                  [&](int i) { return (double)expf(zr[i] - l); });
-        if (lane == 0) { tokens[bs] = v0 + at; at_s[s] = at; }
+                                                  [&](int k) { return (double)expf(zr[k] - l); });
+        if (lane == 0) { tokens[bs] = v0 + at; at_s[i] = at; }
     }
     __syncthreads();
     if (!logq || wave != 0) return;
     float a = -INFINITY;
     if (lane < r) {
         a = logw[b * r + lane];
-        for (int s = 0; s < n; ++s) {
-            const size_t m = (b * n + s) * r + lane;
-            a += z[m * seg_cols + at_s[s]] - lse[m];
-        }
+        for (int i = 0; i < draws; ++i) a += z[((b * draws + i) * r + lane) * seg_cols + at_s[i]] - lse[(b * n + s0 + i) * r + lane];
+        if (s0 + draws < n) logw[b * r + lane] = a;
     }
+    if (s0 + draws < n) return;
     const float mx = wave_max(a);
     const float sum = wave_sum(lane < r ? expf(a - mx) : 0.f);
     if (lane == 0) logq[b] = mx + logf(sum);
@@ -881,7 +882,7 @@ __global__ void __launch_bounds__(kWideBlock) k_sequential_step(int step, int V,
         const int s = step - 1;
         load_draw(s);
         const int code = seg[b], v0 = (code < 0 ? ~code : code) * seg_cols, cols = min(seg_cols, V - v0);
-        const float *zr = z + (b * n + s) * r * seg_cols;
+        const float *zr = z + b * r * seg_cols;
         if (tid < cols) {
             double p = 0.0;
             for (int a = 0; a < r; ++a) p += (double)(qh_s[a] * expf(zr[a * seg_cols + tid] - lse_s[a]));
@@ -1230,7 +1231,6 @@ typedef TileCfg<64, 256, 1, 4> CfgSkinny;
 #define CPH_SKINNY_ROWS 64
 #endif
 constexpr int kSkinnyRows = CPH_SKINNY_ROWS;
-static_assert(kSkinnyRows == 64, "draft_ws counts on it");
 // z = U y for the few rows of a draft-type call: picks the tile by the number of rows
 template <class Epi>
 inline void launch_z_streamed(const char *name, const bf16_t *Y, int d, int rows, const bf16_t *U, int V, const Epi &epi,
@@ -1322,27 +1322,43 @@ inline void z_segments(int rows, int V, int &parts, int &seg_cols)
 }
 
 struct DraftWs {
-    size_t logw, Y, part, lse, seg, base, zseg, total;
+    size_t logw, Y, part, lse, seg, base, zseg, zseg_bytes, total;
     int parts_max;
 };
-inline DraftWs draft_ws(const cp_head_desc &ds)
+// The logits of the segments that the draws fall into lie where the statistics are.  The expert-first draws are all
+// found before any of those logits are formed, so the statistics have done their work then; `part` grows to what all draws
+// need (256 or 512 bytes per head row, more than the statistics of vocabularies below 2048 or 4096) unless the call fits
+// CP_HEAD_STATIC_SCRATCH_BYTES only without: then it takes what is left there, and the logits come a group of draws at a
+// time.  The sequential draws need the statistics to the end but only one draw's logits at a time, for which the half
+// of `part` that 128-column segments leave free is enough from 32 tiles of 256 columns and draws on.
+inline DraftWs draft_ws(const cp_head_desc &ds, bool sequential)
 {
     DraftWs f;
-    const size_t M = (size_t)ds.T * ds.n * ds.r;
-    f.parts_max = ((ds.V + Cfg::BN - 1) / Cfg::BN) * CfgSkinny::WN;   // the finer of the two segmentations
+    const size_t rows = (size_t)ds.T * ds.r, M = rows * ds.n;
+    const size_t tiles = ((size_t)ds.V + Cfg::BN - 1) / Cfg::BN;
+    const size_t draw_bytes = (size_t)ds.r * (M > (size_t)kSkinnyRows ? Cfg::WTN : CfgSkinny::WTN) * 4;      // of one draw
+    f.parts_max = (int)tiles * CfgSkinny::WN;   // the finer of the two segmentations
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes); return o; };
-    f.logw = take((size_t)ds.T * ds.r * 4);
+    f.logw = take(rows * 4);
     f.Y = take(M * ds.d * 2);
-    f.part = take(M * f.parts_max * sizeof(float2));
     f.lse = take(M * 4);
     f.seg = take((size_t)ds.T * ds.n * 4);
     f.base = take((size_t)ds.T * ds.n * 8);
-    // logits of the segments that the draws fall into: with 128-column segments half of `part` is free, and holds them
-    // from 32 tiles of 256 columns on (2 pairs of 8 bytes per tile and row); otherwise they have room of their own
-    const size_t tiles = ((size_t)ds.V + Cfg::BN - 1) / Cfg::BN;
-    if (M > 64 && tiles * 16 >= kMaxSegCols * 4) f.zseg = f.part + M * tiles * Cfg::WN * sizeof(float2);
-    else f.zseg = take(M * kMaxSegCols * 4);
+    const size_t part_bytes = align_up(M * f.parts_max * sizeof(float2));
+    f.part = off;
+    if (!sequential) {
+        f.zseg = f.part;
+        const size_t all = std::max(part_bytes, align_up((size_t)ds.T * ds.n * draw_bytes)), limit = CP_HEAD_STATIC_SCRATCH_BYTES;
+        f.zseg_bytes = off + part_bytes <= limit && off + all > limit ? std::max(limit - off, align_up(draw_bytes)) : all;
+        off += f.zseg_bytes;
+    } else {
+        off += part_bytes;
+        f.zseg_bytes = (size_t)ds.T * draw_bytes;
+        const size_t used = M * tiles * Cfg::WN * sizeof(float2);
+        if (M > (size_t)kSkinnyRows && used + f.zseg_bytes <= part_bytes) f.zseg = f.part + used;
+        else f.zseg = take(f.zseg_bytes);
+    }
     f.total = off;
     return f;
 }
@@ -1376,7 +1392,7 @@ size_t fast_workspace_bytes(const cp_head_desc &ds, int op)
     if (op == CP_HEAD_OP_FIRST_TOKEN) return first_token_ws(ds).total;
     if (op == CP_HEAD_OP_FULL_LOSS_FWD) return full_fwd_ws(ds).total;
     if (op == CP_HEAD_OP_FULL_LOSS_BWD) return full_bwd_ws(ds).total;
-    return draft_ws(ds).total;   // both draft calls
+    return draft_ws(ds, op == CP_HEAD_OP_DRAFT_SEQUENTIAL).total;
 }
 
 // Everything of the forward pass that is per head row: gate (eq. 7), y, the statistics of z, the
@@ -1681,7 +1697,7 @@ int fast_draft(const cp_head_desc &ds, const void *Hv, const void *Wv, const voi
     if (ds.T == 0) return CP_HEAD_OK;
     if (!dims_fit(ds)) return CP_HEAD_ERR_UNSUPPORTED;
     const bf16_t *H = (const bf16_t *)Hv, *W = (const bf16_t *)Wv, *U = (const bf16_t *)Uv, *G = (const bf16_t *)Gv;
-    const DraftWs f = draft_ws(ds);
+    const DraftWs f = draft_ws(ds, false);
     const int B = (int)ds.T, d = ds.d, V = ds.V, n = ds.n, r = ds.r;
     const size_t M = (size_t)B * n * r;
     float *logw = at<float>(ws, f.logw), *lse = at<float>(ws, f.lse);
@@ -1708,13 +1724,23 @@ int fast_draft(const cp_head_desc &ds, const void *Hv, const void *Wv, const voi
         k_draft_pick_alone<<<rows, kWideBlock, 0, st>>>(d, V, n, r, seg_cols, lse, Y, U, alpha, seg, base, uniforms, tokens);
         return hipGetLastError() == hipSuccess ? CP_HEAD_OK : CP_HEAD_ERR_LAUNCH;
     }
-    {
-        ProfileScope prof("draft_segment_logits", (double)rows * seg_cols * d * 2, st);
-        k_segment_logits<<<dim3(rows, (unsigned)seg_cols / 16, (unsigned)(r + 15) / 16), kSegWaves * kWave, 0, st>>>(
-            d, V, n, r, seg_cols, 0, n, Y, U, seg, zseg);
-    }
-    ProfileScope prof("draft_pick", (double)M * seg_cols * 4, st);
-    k_draft_pick<<<(unsigned)B, kWideBlock, 0, st>>>(V, n, r, seg_cols, logw, lse, zseg, alpha, seg, base, uniforms, tokens, logq);
+    // as many draws at a time as there is room for their logits: whole rows of the batch, or a part of one row's draws
+    const int room = (int)std::min<size_t>(f.zseg_bytes / ((size_t)r * seg_cols * 4), rows);
+    const int draws = std::min(n, room), group = std::max(room / n, 1);
+    for (int b0 = 0; b0 < B; b0 += group)
+        for (int s0 = 0; s0 < n; s0 += draws) {
+            const int Bg = std::min(group, B - b0), Sg = std::min(draws, n - s0);
+            const size_t bs0 = (size_t)b0 * n;
+            {
+                ProfileScope prof("draft_segment_logits", (double)Bg * Sg * seg_cols * d * 2, st);
+                k_segment_logits<<<dim3((unsigned)(Bg * Sg), (unsigned)seg_cols / 16, (unsigned)(r + 15) / 16), kSegWaves * kWave, 0, st>>>(
+                    d, V, n, r, seg_cols, s0, Sg, Y + bs0 * r * d, U, seg + bs0 + s0, n, zseg);
+            }
+            ProfileScope prof("draft_pick", (double)Bg * Sg * r * seg_cols * 4, st);
+            k_draft_pick<<<(unsigned)Bg, kWideBlock, 0, st>>>(V, n, r, seg_cols, s0, Sg, logw + (size_t)b0 * r, lse + bs0 * r, zseg, alpha + b0,
+                                                              seg + bs0, base + bs0, uniforms + (size_t)b0 * (1 + n), tokens + bs0,
+                                                              logq ? logq + b0 : nullptr);
+        }
     return hipGetLastError() == hipSuccess ? CP_HEAD_OK : CP_HEAD_ERR_LAUNCH;
 }
 
@@ -1748,7 +1774,7 @@ int fast_draft_sequential(const cp_head_desc &ds, const void *Hv, const void *Wv
     if (ds.T == 0) return CP_HEAD_OK;
     if (!dims_fit(ds)) return CP_HEAD_ERR_UNSUPPORTED;
     const bf16_t *H = (const bf16_t *)Hv, *W = (const bf16_t *)Wv, *U = (const bf16_t *)Uv, *G = (const bf16_t *)Gv;
-    const DraftWs f = draft_ws(ds);
+    const DraftWs f = draft_ws(ds, true);
     const int B = (int)ds.T, d = ds.d, V = ds.V, n = ds.n, r = ds.r;
     const size_t M = (size_t)B * n * r;
     float *logw = at<float>(ws, f.logw);
@@ -1771,7 +1797,7 @@ int fast_draft_sequential(const cp_head_desc &ds, const void *Hv, const void *Wv
                                                               seg, base, tokens, logq);                    // eq. 11-13
         if (step < n)
             k_segment_logits<<<dim3((unsigned)B, (unsigned)seg_cols / 16, (unsigned)(r + 15) / 16), kSegWaves * kWave, 0, st>>>(
-                d, V, n, r, seg_cols, step, 1, Y, U, seg, zseg);
+                d, V, n, r, seg_cols, step, 1, Y, U, seg, 1, zseg);
     }
     return hipGetLastError() == hipSuccess ? CP_HEAD_OK : CP_HEAD_ERR_LAUNCH;
 }

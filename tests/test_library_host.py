@@ -113,6 +113,26 @@ def test_plain_draft_workspace(lib):
     assert binding.cp_head_workspace_bytes(ds, binding.OP_DRAFT) <= binding.STATIC_SCRATCH_BYTES
 
 
+def test_draft_calls_that_fit_the_static_array(lib):
+    """Matrix-core path: gate, y, a log-normaliser, a segment with the sum before it per draw, and the statistics are what a
+    draft call has to have at once; every shape whose sum fits the static array is taken."""
+    def aligned(x):
+        return (x + 255) // 256 * 256
+    limit, fits = binding.STATIC_SCRATCH_BYTES, 0
+    for V in (17, 300, 1000, 3000, 5000, 7000, 7936, 12000, 128256):
+        for d in (64, 512, 2048, 4096):
+            for n, r in ((1, 1), (2, 3), (4, 8), (4, 64), (64, 62)):
+                per_row = n * r * (2 * d + (V + 255) // 256 * 32 + 4) + 4 * r + 12 * n
+                for T in {max(1, limit // per_row - k) for k in (-1, 0, 1, 2, 5)} | {1, 9, 36, 64}:
+                    M = T * n * r
+                    parts = map(aligned, (4 * T * r, 2 * M * d, M * ((V + 255) // 256) * 32, 4 * M, 4 * T * n, 8 * T * n))
+                    least = sum(parts)
+                    need = binding.cp_head_workspace_bytes(binding.make_desc(T, d, V, n, r, binding.BF16), binding.OP_DRAFT)
+                    assert need >= least and (need <= limit) == (least <= limit), (T, d, V, n, r, need, least)
+                    fits += least <= limit < least + 512 * M
+    assert fits > 50
+
+
 @pytest.mark.parametrize("kw", [dict(T=-1), dict(d=0), dict(V=0), dict(n=0), dict(r=0)])
 def test_bad_dimensions(lib, kw):
     base = dict(T=4, d=8, V=16, n=2, r=2)
