@@ -536,31 +536,30 @@ __device__ __forceinline__ float row_lse_from_parts(const float2 *__restrict__ p
 
 // Search by a workgroup for the segment of the vocabulary in which a running sum of probabilities passes u: mass(j) of
 // the segments in vocabulary order, fp64, a run of consecutive segments per thread.  *seg_out is the segment, *base_out
-// the sum before it; if the sum never passes u, ~(last segment) and 0.  All kWideBlock threads call it; up to
-// 64 RUN segments the first wavefront does it alone, RUN of them per lane, where meeting 15 idle wavefronts twice costs
-// more than the longer runs (k_draft_lse_segment of 600 draws over 56 segments: 8.4 -> 5.6 us).
-template <int RUN, class F>
+// the sum before it; if the sum never passes u, ~(last segment) and 0.  All kWideBlock threads call it; ALONE: the first
+// wavefront does it alone, where meeting 15 idle ones twice costs more than longer runs (k_draft_lse_segment of 600 draws
+// over 56 segments: 8.4 -> 5.6 us).
+template <bool ALONE, class F>
 __device__ __forceinline__ void find_segment(int parts, int last_seg, double u, F mass, int32_t *seg_out, double *base_out)
 {
     __shared__ double wave_tot[kWideBlock / kWave];
     __shared__ int first_wave[kWideBlock / kWave];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const bool alone = parts <= RUN * kWave;
-    if (alone && wave > 0) return;
-    const int threads = alone ? kWave : kWideBlock;
+    if (ALONE && wave > 0) return;
+    constexpr int threads = ALONE ? kWave : kWideBlock;
     const int per = (parts + threads - 1) / threads;
     const int lo = min(parts, tid * per), hi = min(parts, lo + per);
     double sum = 0.0;
     for (int j = lo; j < hi; ++j) sum += mass(j);
     double incl = wave_scan_inclusive(sum, lane);
-    if (!alone) {
+    if (!ALONE) {
         if (lane == kWave - 1) wave_tot[wave] = incl;
         __syncthreads();
         for (int w = 0; w < wave; ++w) incl += wave_tot[w];
     }
     const unsigned long long crossed = __ballot(incl > u);
     int at = crossed ? __ffsll((long long)crossed) - 1 : -1;      // the first thread whose running sum passes u
-    if (!alone) {
+    if (!ALONE) {
         if (lane == 0) first_wave[wave] = at;
         __syncthreads();
         at = -1;
@@ -608,6 +607,7 @@ __device__ __forceinline__ int wave_pick_token(int seg_cols, int cols, double ba
 
 // Per (b, s): the log-normalisers of its r head rows from the per-segment statistics (eq. 5), then the segment in which
 // the running sum of the drawn expert's probabilities passes u.
+template <bool ALONE>
 __global__ void __launch_bounds__(kWideBlock) k_draft_lse_segment(int n, int r, int parts, int last_seg,
                                                                   const float2 *__restrict__ part,
                                                                   const int32_t *__restrict__ alpha,
@@ -628,7 +628,7 @@ __global__ void __launch_bounds__(kWideBlock) k_draft_lse_segment(int n, int r, 
     const int astar = alpha[b];
     const float l = lse_s[astar];
     const float2 *pm = part + (bs * r + astar) * parts;
-    find_segment<4>(parts, last_seg, (double)uniforms[b * (1 + n) + 1 + s],
+    find_segment<ALONE>(parts, last_seg, (double)uniforms[b * (1 + n) + 1 + s],
                  [&](int j) {
                      const float2 q = pm[j];
                      return q.x == -INFINITY ? 0.0 : (double)(q.y * expf(q.x - l));
@@ -853,6 +853,7 @@ __global__ void __launch_bounds__(kBlock) k_row_stats_f32(int V, size_t ld, int 
 // cp_head_draft_sample, with every mass replaced by its qhat-weighted sum over the r experts.
 // Launch s picks the token of draw s - 1 from the logits of its segment (k_segment_logits, between the launches), adds
 // its log-probabilities to q, and finds the segment of draw s; launch n only picks and writes logq.
+template <bool ALONE>
 __global__ void __launch_bounds__(kWideBlock) k_sequential_step(int step, int V, int n, int r, int parts, int seg_cols,
                                                                 const float2 *__restrict__ part, const float *__restrict__ z,
                                                                 const float *__restrict__ lse, float *__restrict__ q,
@@ -914,7 +915,7 @@ __global__ void __launch_bounds__(kWideBlock) k_sequential_step(int step, int V,
     }
     load_draw(step);
     const float2 *pm = part + (b * n + step) * r * parts;
-    find_segment<1>(parts, (V - 1) / seg_cols, (double)uniforms[b * n + step],
+    find_segment<ALONE>(parts, (V - 1) / seg_cols, (double)uniforms[b * n + step],
                  [&](int j) {
                      double m = 0.0;
                      for (int a = 0; a < r; ++a) {
@@ -1717,7 +1718,9 @@ int fast_draft(const cp_head_desc &ds, const void *Hv, const void *Wv, const voi
     launch_z_streamed("draft_gemm_z", Y, d, (int)M, U, V, EpiRowStats{part, parts, (int)M, V}, st);
     {
         ProfileScope prof("draft_lse_segment", (double)M * parts * 8, st);
-        k_draft_lse_segment<<<rows, kWideBlock, 0, st>>>(n, r, parts, (V - 1) / seg_cols, part, alpha, uniforms, lse, seg, base);
+        // one wavefront up to four segments a lane
+        auto kernel = parts <= 4 * kWave ? k_draft_lse_segment<true> : k_draft_lse_segment<false>;
+        kernel<<<rows, kWideBlock, 0, st>>>(n, r, parts, (V - 1) / seg_cols, part, alpha, uniforms, lse, seg, base);
     }
     if (!logq && rows >= kAloneDraws && rows <= kAloneDrawsMost) {
         ProfileScope prof("draft_pick", (double)rows * seg_cols * d * 2, st);
@@ -1793,8 +1796,10 @@ int fast_draft_sequential(const cp_head_desc &ds, const void *Hv, const void *Wv
     double *base = at<double>(ws, f.base);
     k_lse_from_parts<<<blocks_for(M, kBlock / kWave), kBlock, 0, st>>>(M, parts, part, lse);
     for (int step = 0; step <= n; ++step) {
-        k_sequential_step<<<(unsigned)B, kWideBlock, 0, st>>>(step, V, n, r, parts, seg_cols, part, zseg, lse, logw, uniforms,
-                                                              seg, base, tokens, logq);                    // eq. 11-13
+        // one wavefront up to a segment a lane, whose mass is a sum over r experts
+        auto kernel = parts <= kWave ? k_sequential_step<true> : k_sequential_step<false>;
+        kernel<<<(unsigned)B, kWideBlock, 0, st>>>(step, V, n, r, parts, seg_cols, part, zseg, lse, logw, uniforms, seg, base, tokens,
+                                                   logq);                                                      // eq. 11-13
         if (step < n)
             k_segment_logits<<<dim3((unsigned)B, (unsigned)seg_cols / 16, (unsigned)(r + 15) / 16), kSegWaves * kWave, 0, st>>>(
                 d, V, n, r, seg_cols, step, 1, Y, U, seg, 1, zseg);
