@@ -297,12 +297,13 @@ inline void f32_plan(const F32Shape *shape, int count, bool may_split, F32Plan *
     constexpr double kCus = 256, kFixed[3] = {6000, 5000, 3000}, kReduceFixed = 10000, kBytesPerCycle = 2000;
     constexpr double kAlone[3] = {171, 51, 16}, kShared[3] = {156, 44, 13.3};
     constexpr int kSplits = 5;                              // 1, 2, 4, 8, 16
+    constexpr double kMaxScratch = 128 << 20;               // bytes of partial sums per launch
     double best = -1;
     for (int kind = 0; kind < 3; ++kind) {
         const long e = f32_tile_edge(kind);
         int choice[3] = {0, 0, 0};
         for (;;) {
-            double units = 0, work = 0, longest = 0, reduce = 0;
+            double units = 0, work = 0, longest = 0, reduce = 0, scratch = 0;
             for (int i = 0; i < count; ++i) {
                 const F32Shape &q = shape[i];
                 const int s = 1 << choice[i];
@@ -310,14 +311,17 @@ inline void f32_plan(const F32Shape *shape, int count, bool may_split, F32Plan *
                 units += n;
                 work += n * (k * kShared[kind] + kFixed[kind]);
                 longest = longest > k ? longest : k;
-                if (s > 1) reduce += (s + 1.0) * q.M * q.N * 4 / kBytesPerCycle;
+                if (s > 1) {
+                    reduce += (s + 1.0) * q.M * q.N * 4 / kBytesPerCycle;
+                    scratch += (double)s * q.M * q.N * 4;
+                }
             }
             const double rounds = (double)(long)((units + kCus - 1) / kCus);
             double t = rounds * work / units;
             const double alone = longest * kAlone[kind] + kFixed[kind];
             if (t < alone) t = alone;
             if (reduce > 0) t += kReduceFixed + reduce;
-            if (best < 0 || t < best) {
+            if (scratch <= kMaxScratch && (best < 0 || t < best)) {
                 best = t;
                 for (int i = 0; i < count; ++i) out[i] = F32Plan{kind, 1 << choice[i]};
             }

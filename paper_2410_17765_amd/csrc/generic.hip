@@ -693,7 +693,8 @@ inline size_t generic_chunk_rows(const cp_head_desc &ds)
 // 16-byte loads whatever V is.
 inline long dz_row(const cp_head_desc &ds) { return (long)round_up((size_t)ds.V, 4); }
 
-// Tiles and splits of the backward products; those of a chunk are planned for a whole chunk.
+// Tiles and splits of the backward products; those of a chunk are planned for a whole chunk.  The partial sums of a launch
+// take at most 128 MiB; with the least-workspace flag nothing is split.
 struct BwdPlans {
     F32Plan z, chunk[2], weights[3];            // {dY, dU}, {dH, dW, dG}: each set shares a launch
     size_t part_chunk[2], part_weights[3];      // where their partial sums start in the scratch
@@ -705,8 +706,9 @@ inline BwdPlans bwd_plans(const cp_head_desc &ds)
     const long rows = (long)generic_chunk_rows(ds), d = ds.d, V = ds.V, T = (long)ds.T, nrd = (long)ds.n * ds.r * d;
     const F32Shape chunk[2] = {{rows, d, V}, {V, d, rows}}, weights[3] = {{T, d, nrd}, {nrd, d, T}, {ds.r, d, T}};
     b.z = f32_plan(rows, V, d, false);
-    f32_plan(chunk, 2, true, b.chunk);
-    f32_plan(weights, 3, true, b.weights);
+    const bool may_split = !(ds.flags & CP_HEAD_MIN_WORKSPACE);
+    f32_plan(chunk, 2, may_split, b.chunk);
+    f32_plan(weights, 3, may_split, b.weights);
     size_t off = 0;
     for (int i = 0; i < 2; ++i) {
         b.part_chunk[i] = off;
@@ -1151,9 +1153,10 @@ static GenericFullWs generic_full_ws(const cp_head_desc &ds)
     g.fwd_pos = std::min(fwd, std::max<size_t>(T, 1));
     g.z = f32_plan((long)g.fwd_pos, V, d, false, (long)nr);
     g.zc = f32_plan(P, V, d, false, (long)nr);
-    g.dh = f32_plan(P, d, nrV, true);
+    const bool may_split = !(ds.flags & CP_HEAD_MIN_WORKSPACE);
+    g.dh = f32_plan(P, d, nrV, may_split);
     g.df = f32_plan(nrV, d, P, false);
-    g.dG = f32_plan(ds.r, d, (long)T, true);
+    g.dG = f32_plan(ds.r, d, (long)T, may_split);
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes); return o; };
     g.logw = take(T * ds.r * 4);
