@@ -677,21 +677,21 @@ __global__ void __launch_bounds__(kWave) k_aux_finish(size_t T, int r, const uns
     if (lane == 0) *laux = s;
 }
 
+// A chunk's logit gradients have rows of V rounded up to 4 floats (the rest zero): the products below read them with
+// 16-byte loads whatever V is.
+inline long dz_row(const cp_head_desc &ds) { return (long)round_up((size_t)ds.V, 4); }
+
 // rows of the dZ chunk on this path: about 512 MiB of fp32 logit gradients at a time (256 rows with the
 // least-workspace flag), and the r rows of one token never split over two chunks
 inline size_t generic_chunk_rows(const cp_head_desc &ds)
 {
     const size_t M = (size_t)ds.T * ds.n * ds.r;
-    size_t rows = ((size_t)1 << 27) / (size_t)ds.V;
+    size_t rows = ((size_t)1 << 27) / (size_t)dz_row(ds);
     if (ds.flags & CP_HEAD_MIN_WORKSPACE) rows = 256;
     rows = rows / ds.r * ds.r;
     if (rows < (size_t)ds.r) rows = (size_t)ds.r;
     return rows < M ? rows : (M ? M : (size_t)ds.r);
 }
-
-// A chunk's logit gradients have rows of V rounded up to 4 floats (the rest zero): the products below read them with
-// 16-byte loads whatever V is.
-inline long dz_row(const cp_head_desc &ds) { return (long)round_up((size_t)ds.V, 4); }
 
 // Tiles and splits of the backward products; those of a chunk are planned for a whole chunk.  The partial sums of a launch
 // take at most 128 MiB; with the least-workspace flag nothing is split.

@@ -136,11 +136,12 @@ def test_draft_calls_that_fit_the_static_array(lib):
 def test_plain_backward_workspace_is_bounded(lib):
     """dY, a chunk of logit gradients, dg, and at most 128 MiB of split sums; none with the least-workspace flag."""
     shapes = [(T, d, V, n, r) for T in (1, 64, 500, 16384, 1 << 17) for d in (16, 512, 2048) for V in (500, 32000) for n, r in ((1, 1), (4, 8), (16, 16))]
+    shapes += [(1 << 26, 1, V, 1, r) for V in (1, 2, 3, 5) for r in (1, 2)]         # rows of the gradients are padded to 16 bytes
     for T, d, V, n, r in shapes:
         M, row = T * n * r, (V + 3) // 4 * 16
         for flags in (0, binding.MIN_WORKSPACE):
             need = binding.cp_head_workspace_bytes(binding.make_desc(T, d, V, n, r, binding.FP32, flags), binding.OP_LOSS_BWD)
-            gradients = max(256, n * r) * row if flags else min(M * row, max(r * row, (1 << 29) + (1 << 20)))
+            gradients = max(256, n * r) * row if flags else min(M * row, max(r * row, 1 << 29))
             assert need <= M * d * 4 + gradients + T * r * 4 + (0 if flags else 128 << 20) + 4096, (T, d, V, n, r, flags)
 
 
