@@ -1032,30 +1032,6 @@ inline SplitScratch split_scratch(void *ws, size_t off, size_t bytes)
     return s;
 }
 
-struct FwdWs {
-    size_t logw, C, Ylo, part, split, split_bytes, total;
-    int parts;
-};
-inline FwdWs fwd_ws(const cp_head_desc &ds)
-{
-    FwdWs f;
-    const size_t M = (size_t)ds.T * ds.n * ds.r;
-    f.parts = ((ds.V + Cfg::BN - 1) / Cfg::BN) * Cfg::WN;
-    size_t off = 0;
-    auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes); return o; };
-    f.logw = take((size_t)ds.T * ds.r * 4);
-    f.C = take(M * 4);
-    f.Ylo = take(M * ds.d * 2);
-    // with kept logits the statistics live in ctx: the backward pass needs the maxima again
-    f.part = (ds.flags & CP_HEAD_KEEP_LOGITS) ? off : take(M * f.parts * sizeof(float2));
-    SplitNeed need(ds);
-    need.product<Cfg>((size_t)ds.T, (size_t)ds.n * ds.r * ds.d, (size_t)ds.d);       // y
-    f.split_bytes = need.bytes;
-    f.split = take(need.bytes);
-    f.total = off;
-    return f;
-}
-
 // Rows of logit gradients held at a time: about 4 GiB of bf16 at V = 32000, i.e. 65536 rows.  Measured on the
 // headline step: 2 GiB 450.4 ms, 4 GiB 447.9, 8 GiB 448.3 (the dU product gains from fewer accumulation passes
 // over its fp32 output, the dz product loses about half of that).  A larger vocabulary keeps at least 32768
@@ -1078,12 +1054,42 @@ inline size_t bwd_chunk_rows(const cp_head_desc &ds)
     return rows < M ? rows : (M ? M : 1);
 }
 
+// The pair of loss calls and the single call add up every row's y and dY in the same order, so these two are split along K
+// only where both calls make the same launches: y, which the pair forms for the whole batch, if that is one chunk;
+// dY if the chunks are whole positions, as the single call's always are.
+inline bool split_y(const cp_head_desc &ds) { return bwd_chunk_rows(ds) >= (size_t)ds.T * ds.n * ds.r; }
+inline bool split_dy(const cp_head_desc &ds) { return bwd_chunk_rows(ds) % ((size_t)ds.n * ds.r) == 0; }
+
+struct FwdWs {
+    size_t logw, C, Ylo, part, split, split_bytes, total;
+    int parts;
+};
+inline FwdWs fwd_ws(const cp_head_desc &ds)
+{
+    FwdWs f;
+    const size_t M = (size_t)ds.T * ds.n * ds.r;
+    f.parts = ((ds.V + Cfg::BN - 1) / Cfg::BN) * Cfg::WN;
+    size_t off = 0;
+    auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes); return o; };
+    f.logw = take((size_t)ds.T * ds.r * 4);
+    f.C = take(M * 4);
+    f.Ylo = take(M * ds.d * 2);
+    // with kept logits the statistics live in ctx: the backward pass needs the maxima again
+    f.part = (ds.flags & CP_HEAD_KEEP_LOGITS) ? off : take(M * f.parts * sizeof(float2));
+    SplitNeed need(ds);
+    if (split_y(ds)) need.product<Cfg>((size_t)ds.T, (size_t)ds.n * ds.r * ds.d, (size_t)ds.d);    // y
+    f.split_bytes = need.bytes;
+    f.split = take(need.bytes);
+    f.total = off;
+    return f;
+}
+
 // the products of the backward pass below dz
 inline void need_below_dz(const cp_head_desc &ds, size_t chunk, SplitNeed &need)
 {
     const size_t T = (size_t)ds.T, d = (size_t)ds.d, V = (size_t)ds.V, nrd = (size_t)ds.n * ds.r * d;
     SplitNeed::chunks(T * ds.n * ds.r, chunk, [&](size_t Mc) {
-        need.product<CfgBlockedA>(Mc, d, round_up(V, 64));                           // dY
+        if (split_dy(ds)) need.product<CfgBlockedA>(Mc, d, round_up(V, 64));         // dY
         need.product<Cfg>(V, d, round_up(Mc, 64));                                   // dU
     });
     need.product<Cfg>(T, d, nrd);                                                    // dH
@@ -1484,7 +1490,7 @@ static void bwd_chunk_products(const cp_head_desc &ds, const bf16_t *dZ, const b
     const long ldV = (long)Vp + 64;
     // dY = dz U   (contraction over the vocabulary)
     launch_gemm_nt<CfgBlockedA>("gemm_dy", dZ, Vp, Mc, Ut, ldV, d, Vp, EpiStoreBf16{dYc, nullptr, (long)d, Mc, d}, st,
-                                kGroupRowsNarrow, NoSideJob{0}, -1, -1, split);
+                                kGroupRowsNarrow, NoSideJob{0}, -1, -1, split_dy(ds) ? split : SplitScratch());
     if (dU) {
         // dU += dz^T Y   (contraction over the rows of the chunk)
         transpose_bf16(Yc, d, Mc, d, Yt, ldM, Mcp, st);               // Yt[d, Mcp]
@@ -1626,7 +1632,7 @@ inline StepWs step_ws(const cp_head_desc &ds)
     f.dZt = take((size_t)ds.V * f.ldM * 2);
     f.Yt = take((size_t)ds.d * f.ldM * 2);
     SplitNeed need(ds);
-    SplitNeed::chunks(T, f.pos, [&](size_t P) { need.product<Cfg>(P, nrd, (size_t)ds.d); });      // y
+    if (split_y(ds)) need.product<Cfg>(T, nrd, (size_t)ds.d);                        // y
     need_below_dz(ds, f.rows, need);
     f.split_bytes = need.bytes;
     f.split = take(need.bytes);
@@ -1675,7 +1681,7 @@ int fast_loss_step(const cp_head_desc &ds, const void *Hv, const void *Wv, const
         const int32_t *Xc = X + t0 * n;
         // forward of the chunk: y, statistics of z with the logits kept, log-normalisers and C (eq. 5, 8), mixture (eq. 9)
         launch_gemm_nt<Cfg>("gemm_y", H + t0 * d, d, (int)P, W, d, (int)nrd, d, EpiStoreBf16{Yc, Ylo, (long)nrd, (int)P, (int)nrd}, st,
-                            kGroupRowsNarrow, NoSideJob{0}, -1, -1, split);
+                            kGroupRowsNarrow, NoSideJob{0}, -1, -1, split_y(ds) ? split : SplitScratch());
         launch_gemm_nt<Cfg>("gemm_z_stats_keep", Yc, d, Mc, U, d, V, d, EpiRowStatsKeep{part, f.parts, Mc, V, zs, (long)Vp, Vp}, st);
         k_row_finish<<<blocks_for((size_t)Mc, kBlock / kWave), kBlock, 0, st>>>((size_t)Mc, d, r, f.parts, part, Yc, Ylo, U, Xc, lse, C);
         launch_mixture(sub, logw + t0 * r, C, loss + t0, gamma + t0 * r, -1.f, st);
