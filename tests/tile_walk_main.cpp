@@ -2,11 +2,19 @@
 // produced by exactly one workgroup of the grid, the grid is a multiple of 8 with at most 7 idle workgroups, and
 // while whole bands last the eight XCDs (workgroup id mod 8) are at the same tile column at the same step.
 #include <cstdio>
+#include <cstdlib>
 #include <vector>
 #include "tile_walk.hpp"
 
-int main()
+// with arguments M N K: the plan of such a product on 256 x 256 tiles in bands of 4 rows, as "whole tiles, split tiles, parts"
+int main(int argc, char **argv)
 {
+    if (argc == 4) {
+        const int M = std::atoi(argv[1]), N = std::atoi(argv[2]), K = std::atoi(argv[3]);
+        const SplitPlan p = split_plan(gemm_grid((M + 255) / 256, (N + 255) / 256, 4), 256, (K + 63) / 64, kMaxSplitItems);
+        std::printf("%d %d %d\n", p.first, p.tail, p.parts);
+        return 0;
+    }
     long shapes = 0;
     const int gms[] = {1, 2, 4, 8, 16}, tns[] = {1, 2, 3, 16, 17, 125, 501};
     for (int gm : gms)
