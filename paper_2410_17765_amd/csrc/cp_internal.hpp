@@ -165,8 +165,7 @@ void launch_first_token_mix(const cp_head_desc &ds, const float *z, size_t ld, c
                             float *logp, hipStream_t st);
 
 // Kernels of the generic path that the matrix-core path reuses (fp32 bookkeeping per position).
-void launch_gate(const cp_head_desc &ds, const void *H, const void *G, float *logw, float *w, hipStream_t st);
-// The same for bf16 storage with d a multiple of 64 (gate.hip), the arg-max counts of eq. 10 (added to `counts`), and the
+// The gate of the matrix-core path (gate.hip): log-softmax, the arg-max counts of eq. 10 (added to `counts`), and the
 // gate gradient dG = dg^T H, whose partial sums take gate_chunks(T) r d floats of `partial`.
 void launch_gate_bf16(const cp_head_desc &ds, const bf16_t *H, const bf16_t *G, float *logw, float *w, hipStream_t st);
 void launch_aux_argmax_bf16(const cp_head_desc &ds, const bf16_t *H, const bf16_t *G, unsigned long long *counts, hipStream_t st);

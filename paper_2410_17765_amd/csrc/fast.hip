@@ -9,6 +9,7 @@
 // All products run through the one NT main loop of gemm_nt.hpp; operands that are not
 // K-contiguous are transposed first (HBM-bound passes that cost a few percent of the GEMM time).
 #include "gemm_nt.hpp"
+#include "tile16.hpp"
 #include "kept_logits.hpp"
 
 #include <math.h>
@@ -436,13 +437,6 @@ __device__ __forceinline__ double wave_scan_inclusive(double v, int lane)
     return v;
 }
 
-// 16 bytes at any even address (one load instruction all the same)
-__device__ __forceinline__ u32x4_t load16_any(const bf16_t *p)
-{
-    typedef unsigned int u32x4_any_t __attribute__((ext_vector_type(4), aligned(2)));
-    return *reinterpret_cast<const u32x4_any_t *>(p);
-}
-
 // fp32 dot product of two bf16 vectors of length d (a multiple of 64) over one wavefront, 16-byte loads
 __device__ __forceinline__ float wave_dot_bf16(const bf16_t *__restrict__ a, const bf16_t *__restrict__ b, int d, int lane)
 {
@@ -638,10 +632,9 @@ __global__ void __launch_bounds__(kWideBlock) k_draft_lse_segment(int n, int r, 
 
 // The logits of a segment for the r head rows of a (row, draw), z[(x * r + a) * seg_cols + i] = U[v0 + i] . y[row0 + a]:
 // a workgroup per (b, draw), 16 tokens and 16 experts, on the 16x16x32 matrix instruction; its eight wavefronts share
-// the contraction in blocks of 64 columns (a lane loads 32 consecutive bytes of its row per block, four lanes a cache
-// line) and their partial products meet in LDS.  Bound by the latency of the cold rows of U: the rows of a segment are
-// spread over 4 or 8 workgroups with 16 lines per lane in flight each, where one workgroup per draw had the whole segment
-// (0.5 or 1 MB) to fetch: the draft call 397 -> 371 us at B = 1, d = 4096, V = 128256, n = 4, r = 8.
+// the contraction and their partial products meet in LDS.  Bound by the latency of the cold rows of U: the rows of a segment are
+// spread over 4 or 8 workgroups of eight wavefronts, where one workgroup per draw had the whole segment (0.5 or 1 MB) to
+// fetch: the draft call 397 -> 371 us at B = 1, d = 4096, V = 128256, n = 4, r = 8.
 // (b, s) of workgroup x is b = x / draws, s = draw0 + x % draws; its segment is seg_in[b * seg_ld + x % draws].
 constexpr int kSegWaves = 8;
 __global__ void __launch_bounds__(kSegWaves * kWave) k_segment_logits(int d, int V, int n, int r, int seg_cols, int draw0,
@@ -659,30 +652,12 @@ __global__ void __launch_bounds__(kSegWaves * kWave) k_segment_logits(int d, int
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int row = lane & 15, q = lane >> 4;
     // tokens past V and experts past r repeat the last one: the former are never used, the latter not stored
-    const u32x4_t *pu = reinterpret_cast<const u32x4_t *>(U + (size_t)min(v0 + row, V - 1) * d + q * 16);
-    const u32x4_t *py = reinterpret_cast<const u32x4_t *>(Y + (row0 + min(a0 + row, r - 1)) * d + q * 16);
-    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
-    constexpr int UN = 4;
-    const int blocks = d / 64;
-    for (int kb = wave; kb < blocks; kb += kSegWaves * UN) {
-        u32x4_t a[UN][2], b[UN][2];
+    const bf16_t *pu = U + (size_t)min(v0 + row, V - 1) * d + q * 16;
+    const bf16_t *const py[1] = {Y + (row0 + min(a0 + row, r - 1)) * d + q * 16};
+    f32x4_t acc[1] = {{0.f, 0.f, 0.f, 0.f}};
+    tile16_products<kSegWaves, 1>(pu, py, d, wave, acc);
 #pragma unroll
-        for (int i = 0; i < UN; ++i) {
-            const int k = min(kb + kSegWaves * i, blocks - 1) * 8;     // a block is eight 16-byte pieces
-#pragma unroll
-            for (int c = 0; c < 2; ++c) { a[i][c] = pu[k + c]; b[i][c] = py[k + c]; }
-        }
-#pragma unroll
-        for (int i = 0; i < UN; ++i) {
-            if (kb + kSegWaves * i >= blocks) break;
-#pragma unroll
-            for (int c = 0; c < 2; ++c)
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a[i][c]),
-                                                              __builtin_bit_cast(bf16x8_t, b[i][c]), acc, 0, 0, 0);
-        }
-    }
-#pragma unroll
-    for (int v = 0; v < 4; ++v) red[wave][4 * q + v][row] = acc[v];
+    for (int v = 0; v < 4; ++v) red[wave][tile16_row(v, lane)][row] = acc[0][v];
     __syncthreads();
     const int tok = threadIdx.x & 15, e = threadIdx.x >> 4;
     if (e < 16 && a0 + e < r) {
@@ -1249,10 +1224,8 @@ inline void launch_z_streamed(const char *name, const bf16_t *Y, int d, int rows
 // y = W_sa h for at most 16 positions: W goes from memory straight into the registers that the matrix instruction
 // reads.  The tiled main loop waits for a stage of LDS at every K-step, d / 64 times a memory latency, which the other
 // workgroups of a compute unit hide only where there are two on each (512 tiles of 256 columns); here a workgroup has
-// 16 columns of y, every wavefront 8 KB of W in flight, and eight or more workgroups share a compute unit.
-// The four wavefronts share the contraction in blocks of 64 columns of W (a lane loads 32 consecutive bytes of its row
-// per block, four lanes a cache line; the order of the columns inside a block is the same for both operands) and
-// their partial products meet in LDS.
+// 16 columns of y, and eight or more workgroups, whose loads overlap, share a compute unit.
+// The four wavefronts share the contraction and their partial products meet in LDS.
 constexpr int kStreamRows = 16, kStreamWaves = 4, kStreamBlock = kStreamWaves * kWave;
 __global__ void __launch_bounds__(kStreamBlock) k_stream_y(const bf16_t *__restrict__ H, int B, int d,
                                                            const bf16_t *__restrict__ W, int cols, bf16_t *__restrict__ Y,
@@ -1266,30 +1239,12 @@ __global__ void __launch_bounds__(kStreamBlock) k_stream_y(const bf16_t *__restr
     const int col0 = ((int)blockIdx.x - side.blocks) * 16;       // cols is a multiple of 64
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int row = lane & 15, q = lane >> 4;
-    const bf16_t *ph = H + (size_t)min(row, B - 1) * d + q * 16;     // rows past the last one repeat it, not stored
+    const bf16_t *const ph[1] = {H + (size_t)min(row, B - 1) * d + q * 16};     // rows past the last one repeat it, not stored
     const bf16_t *pw = W + (size_t)(col0 + row) * d + q * 16;
-    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
-    constexpr int UN = 4;
-    const int blocks = d / 64;
-    for (int kb = wave; kb < blocks; kb += kStreamWaves * UN) {
-        u32x4_t a[UN][2], b[UN][2];
+    f32x4_t acc[1] = {{0.f, 0.f, 0.f, 0.f}};
+    tile16_products<kStreamWaves, 1>(pw, ph, d, wave, acc);
 #pragma unroll
-        for (int u = 0; u < UN; ++u) {
-            const int k = min(kb + kStreamWaves * u, blocks - 1) * 64;       // a block past the end is left out below
-#pragma unroll
-            for (int c = 0; c < 2; ++c) { a[u][c] = load16_any(pw + k + 8 * c); b[u][c] = load16_any(ph + k + 8 * c); }
-        }
-#pragma unroll
-        for (int u = 0; u < UN; ++u) {
-            if (kb + kStreamWaves * u >= blocks) break;
-#pragma unroll
-            for (int c = 0; c < 2; ++c)
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a[u][c]),
-                                                              __builtin_bit_cast(bf16x8_t, b[u][c]), acc, 0, 0, 0);
-        }
-    }
-#pragma unroll
-    for (int v = 0; v < 4; ++v) sums[wave][4 * q + v][row] = acc[v];
+    for (int v = 0; v < 4; ++v) sums[wave][tile16_row(v, lane)][row] = acc[0][v];
     __syncthreads();
     const int t = threadIdx.x >> 4, col = threadIdx.x & 15;
     if (t < B)
@@ -1421,7 +1376,7 @@ int fast_fwd_rows(const cp_head_desc &ds, const void *Hv, const void *Wv, const 
     float2 *part = cl.keep ? at<float2>(ctx, cl.zpart) : at<float2>(ws, f.part);
     if (cl.keep && (cl.parts != f.parts || kKeptTile != Cfg::WTN)) return CP_HEAD_ERR_UNSUPPORTED;
 
-    launch_gate(ds, Hv, Gv, logw, w, st);                                                      // eq. 7
+    launch_gate_bf16(ds, (const bf16_t *)Hv, (const bf16_t *)Gv, logw, w, st);                                                      // eq. 7
     launch_gemm_nt<Cfg>("gemm_y", H, d, T, W, d, nrd, d, EpiStoreBf16{Y, Ylo, (long)nrd, T, nrd}, st, kGroupRowsNarrow,
                         NoSideJob{0}, -1, -1, split_scratch(ws, f.split, f.split_bytes));                       // y = W_sa h
     if (cl.keep)                                                                               // z = U y, statistics, z kept
@@ -1669,7 +1624,7 @@ int fast_loss_step(const cp_head_desc &ds, const void *Hv, const void *Wv, const
     const SplitScratch split = split_scratch(ws, f.split, f.split_bytes);
 
     bf16_t *Ut = at<bf16_t>(ws, f.Ut), *dZt = at<bf16_t>(ws, f.dZt), *Yt = at<bf16_t>(ws, f.Yt);
-    launch_gate(ds, Hv, Gv, logw, w, st);                                                             // eq. 7, all positions
+    launch_gate_bf16(ds, (const bf16_t *)Hv, (const bf16_t *)Gv, logw, w, st);                                                             // eq. 7, all positions
     transpose_bf16(U, d, V, d, Ut, (long)f.Vp + 64, Vp, st);                                          // Ut[d, Vp]
     int first = 1;
     for (size_t t0 = 0; t0 < T; t0 += f.pos) {
@@ -1833,7 +1788,7 @@ int fast_full_loss_fwd(const cp_head_desc &ds, const void *Hv, const void *Fv, c
     float *logw = at<float>(ws, f.logw), *C = at<float>(ws, f.C);
     float2 *part = cl.keep ? at<float2>(ctx, cl.zpart) : at<float2>(ws, f.part);
     uint16_t *zs = at<uint16_t>(ctx, cl.zs);
-    launch_gate(ds, Hv, Gv, logw, w, st);                                                       // eq. 7
+    launch_gate_bf16(ds, (const bf16_t *)Hv, (const bf16_t *)Gv, logw, w, st);                                                       // eq. 7
     for (int sa = 0; sa < nr; ++sa) {                                                           // z_sa = F_sa h (eq. 6), statistics
         if (cl.keep)
             launch_gemm_nt<Cfg>("full_gemm_z_stats_keep", H, d, T, F + (size_t)sa * V * d, d, V, d,

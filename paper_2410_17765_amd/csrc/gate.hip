@@ -3,6 +3,7 @@
 //
 // All three read H once and do little else: they are bound by that stream (T d 2 bytes).
 #include "cp_internal.hpp"
+#include "tile16.hpp"
 
 #include <type_traits>
 
@@ -12,21 +13,13 @@ namespace {
 
 constexpr int kBlock = 256, kWaves = kBlock / kWave;
 
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
-// H and G are only promised to be bf16 arrays: 16 bytes at any even address (one load instruction all the same)
-typedef uint32_t u32x4_any_t __attribute__((ext_vector_type(4), aligned(2)));
-typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ u32x4_t load16(const bf16_t *p) { return *reinterpret_cast<const u32x4_any_t *>(p); }
 
 // ------------------------------------------------------------------------------------------
 // G h of 16 positions per step of a workgroup on the 16x16x32 matrix instruction, for the arg-max counts.
 // The kernel it replaces walked H with 2-byte loads, once per expert, one position per wavefront: 353 us for the
-// arg-max at T = 16384, d = 4096, r = 8 (0.4 TB/s); this one takes 35 us (3.9 TB/s).  Here the four wavefronts share the contraction (blocks of 64
-// columns in turn), a lane loads 32 consecutive bytes of its row per block, so that four lanes cover a cache line of
-// H, and the partial products meet in LDS.  Experts beyond r repeat the last row of G and are dropped.
-// The order of the columns inside a block of 64 is the same permutation for both operands.
+// arg-max at T = 16384, d = 4096, r = 8 (0.4 TB/s); this one takes 35 us (3.9 TB/s).  Here the four wavefronts share the
+// contraction, and the partial products meet in LDS.  Experts beyond r repeat the last row of G and are dropped.
 // ------------------------------------------------------------------------------------------
 constexpr int kRows = 16;
 
@@ -45,36 +38,11 @@ __device__ __forceinline__ void gate_rows(size_t t0, size_t T, int d, int r, con
     f32x4_t acc[NG];
 #pragma unroll
     for (int e = 0; e < NG; ++e) acc[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    // four blocks in flight per wavefront; a block past the end re-reads the last one and is left out
-    constexpr int UN = 4;
-    const int blocks = d / 64;
-    for (int kb = wave; kb < blocks; kb += kWaves * UN) {
-        u32x4_t a[UN][2], b[UN][NG][2];
-#pragma unroll
-        for (int u = 0; u < UN; ++u) {
-            const int k = min(kb + kWaves * u, blocks - 1) * 64;
-#pragma unroll
-            for (int c = 0; c < 2; ++c) {
-                a[u][c] = load16(h + k + 8 * c);
-#pragma unroll
-                for (int e = 0; e < NG; ++e) b[u][e][c] = load16(g[e] + k + 8 * c);
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < UN; ++u) {
-            if (kb + kWaves * u >= blocks) break;
-#pragma unroll
-            for (int c = 0; c < 2; ++c)
-#pragma unroll
-                for (int e = 0; e < NG; ++e)
-                    acc[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a[u][c]),
-                                                                     __builtin_bit_cast(bf16x8_t, b[u][e][c]), acc[e], 0, 0, 0);
-        }
-    }
+    tile16_products<kWaves, NG == 1 ? 4 : 2>(h, g, d, wave, acc);
 #pragma unroll
     for (int e = 0; e < NG; ++e)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) red[wave][4 * q + v][e * 16 + row] = acc[e][v];
+        for (int v = 0; v < 4; ++v) red[wave][tile16_row(v, lane)][e * 16 + row] = acc[e][v];
 }
 
 // logw = log_softmax(G h), w = exp(logw)   (eq. 7)

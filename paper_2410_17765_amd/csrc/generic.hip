@@ -389,7 +389,7 @@ void launch_add_splits(const AddSplits &job, hipStream_t st)
 {
     if (job.count) k_add_splits<TIn><<<job.first[job.count], kBlock, 0, st>>>(job);
 }
-// y = W_sa h for `heads` head matrices, and with `gate` its pre-activations G h
+// y = W_sa h for `heads` head matrices, and unless `gate` is null its pre-activations G h
 template <typename TIn>
 void launch_f32_y(const cp_head_desc &ds, int heads, const TIn *H, const TIn *W, const TIn *G, float *Y, float *gate, hipStream_t st)
 {
@@ -406,14 +406,15 @@ void launch_f32_y(const cp_head_desc &ds, int heads, const TIn *H, const TIn *W,
     });
 }
 // y of the draft-type calls: with bf16 storage its rounding is part of the distribution's definition
-void launch_draft_y(const cp_head_desc &ds, int heads, const float *H, const float *W, const float *G, float *Y, hipStream_t st)
+void launch_draft_y(const cp_head_desc &ds, int heads, const float *H, const float *W, float *Y, hipStream_t st)
 {
-    launch_f32_y<float>(ds, heads, H, W, G, Y, nullptr, st);
+    launch_f32_y<float>(ds, heads, H, W, nullptr, Y, nullptr, st);
 }
-void launch_draft_y(const cp_head_desc &ds, int heads, const bf16_t *H, const bf16_t *W, const bf16_t *, float *Y, hipStream_t st)
+void launch_draft_y(const cp_head_desc &ds, int heads, const bf16_t *H, const bf16_t *W, float *Y, hipStream_t st)
 {
     k_y_rounded<<<(unsigned)(ds.T * heads), kBlock, (size_t)ds.d * sizeof(float), st>>>(ds.d, heads, H, W, Y);
 }
+
 // ------------------------------------------------------------------------------------------
 // mixture over experts (eq. 9) and the posterior gamma_a = exp(a_a - L); one wavefront per position
 // ------------------------------------------------------------------------------------------
@@ -935,7 +936,7 @@ int draft_t(const cp_head_desc &ds, const TIn *H, const TIn *W, const TIn *U, co
     float *z = at<float>(ws, g.z), *lse = at<float>(ws, g.lse);
     k_gate<TIn><<<(unsigned)B, kWave, 0, st>>>(ds.d, ds.r, H, G, logw, w);
     k_pick_alpha<<<blocks_for(B, kWave), kWave, 0, st>>>(B, ds.n, ds.r, w, uniforms, alpha);
-    launch_draft_y(ds, ds.n * ds.r, H, W, G, Y, st);
+    launch_draft_y(ds, ds.n * ds.r, H, W, Y, st);
     launch_f32_kept_logits<TIn>(ds, (long)M, U, Y, z, lse, st);
     k_sample_generic<<<(unsigned)(B * ds.n), kBlock, 0, st>>>(ds.V, ds.n, ds.r, z, lse, alpha, uniforms, tokens);
     if (logq) k_logq_generic<<<(unsigned)B, kWave, 0, st>>>(ds.V, ds.n, ds.r, logw, z, lse, tokens, logq);
@@ -951,7 +952,7 @@ int draft_sequential_t(const cp_head_desc &ds, const TIn *H, const TIn *W, const
     float *logw = at<float>(ws, g.logw), *w = at<float>(ws, g.w), *Y = at<float>(ws, g.Y);
     float *z = at<float>(ws, g.z), *lse = at<float>(ws, g.lse);
     k_gate<TIn><<<(unsigned)B, kWave, 0, st>>>(ds.d, ds.r, H, G, logw, w);
-    launch_draft_y(ds, ds.n * ds.r, H, W, G, Y, st);
+    launch_draft_y(ds, ds.n * ds.r, H, W, Y, st);
     launch_f32_kept_logits<TIn>(ds, (long)M, U, Y, z, lse, st);
     k_sample_sequential_generic<<<(unsigned)B, kBlock, 0, st>>>(ds.V, ds.n, ds.r, z, lse, logw, uniforms, tokens, logq);
     return hipGetLastError() == hipSuccess ? CP_HEAD_OK : CP_HEAD_ERR_LAUNCH;
@@ -1095,7 +1096,7 @@ static int first_token_t(const cp_head_desc &ds, const TIn *H, const TIn *W, con
     float *z = at<float>(ws, g.z), *lse = at<float>(ws, g.lse);
     k_gate<TIn><<<(unsigned)ds.T, kWave, 0, st>>>(ds.d, ds.r, H, G, logw, w);
     // the first head's matrices are the first r blocks of W, so its rows are (b, a) with nr = r
-    launch_draft_y(ds, ds.r, H, W, G, Y, st);
+    launch_draft_y(ds, ds.r, H, W, Y, st);
     launch_f32_kept_logits<TIn>(ds, (long)rows, U, Y, z, lse, st);
     launch_first_token_mix(ds, z, (size_t)ds.V, lse, logw, logp, st);
     return hipGetLastError() == hipSuccess ? CP_HEAD_OK : CP_HEAD_ERR_LAUNCH;
@@ -1254,16 +1255,6 @@ int generic_full_loss_bwd(const cp_head_desc &ds, const void *H, const void *F, 
                                  ws, st);
     return full_bwd_t<bf16_t>(ds, (const bf16_t *)H, (const bf16_t *)F, (const bf16_t *)G, X, dloss, scale, ctx, dH, dF,
                               dG, ws, st);
-}
-
-void launch_gate(const cp_head_desc &ds, const void *H, const void *G, float *logw, float *w, hipStream_t st)
-{
-    if (ds.T == 0) return;
-    if (use_fast_path(ds)) return launch_gate_bf16(ds, (const bf16_t *)H, (const bf16_t *)G, logw, w, st);
-    if (ds.dtype == CP_HEAD_FP32)
-        k_gate<float><<<(unsigned)ds.T, kWave, 0, st>>>(ds.d, ds.r, (const float *)H, (const float *)G, logw, w);
-    else
-        k_gate<bf16_t><<<(unsigned)ds.T, kWave, 0, st>>>(ds.d, ds.r, (const bf16_t *)H, (const bf16_t *)G, logw, w);
 }
 
 void launch_mixture(const cp_head_desc &ds, const float *logw, const float *C, float *out, float *gamma,
