@@ -20,7 +20,7 @@ if ROOT not in sys.path:
 
 PEAK_BF16_TFLOPS = 2500.0     # MI355X dense bf16 matrix peak
 PEAK_HBM_GBS = 8000.0
-PEAK_FP32_VECTOR_TFLOPS = 157.3   # 256 compute units x 128 fp32 FMA lanes x 2 x 2.4 GHz
+PEAK_FP32_TFLOPS = 157.3   # 256 compute units x 128 fp32 multiply-adds a cycle x 2 x 2.4 GHz, vector or matrix instruction
 
 # HBM-side bytes per launch (FETCH_SIZE + WRITE_SIZE, scaled by a plain copy) from the rocprofv3 --pmc
 # runs summarised in profiles/loss_head_7b_kernel_stats.md (and ..._kept_logits_...); kernels whose counters were not separated
@@ -33,9 +33,9 @@ TRAFFIC_BYTES = {
     ("head_7b", "gemm_z_stats", 1): (210.580 + 1.294) * GIB,             # loss_head_7b_kernel_stats.md
     ("head_7b", "gemm_z_dz", 8): (25.455 + 7.813) * GIB,                 # loss_head_7b_kernel_stats.md
     # draft step: L2 fills of its kernels per step at B = 1, 8, 64 (profiles/draft_b8_kernel_stats.md)
-    ("draft", 1): 1.985 * GIB,
-    ("draft", 8): (1.0018 + 1.0106 + 0.0020 + 0.0316 + 0.0022) * GIB,
-    ("draft", 64): 5.014 * GIB,
+    ("draft", 1): 1.986 * GIB,
+    ("draft", 8): (1.0018 + 1.0105 + 0.0020 + 0.0332 + 0.0001) * GIB,
+    ("draft", 64): 5.103 * GIB,
 }
 
 
@@ -346,11 +346,11 @@ def bench_loss(args):
                 "traffic": TRAFFIC_BYTES.get((cfg.name, dom[0], dom[1] // max(args.steps, 1))),
                 "traffic_unit": "bytes per launch", "launches": dom[1], "avg_ms": dom[2] / dom[1]}
     else:
-        # the plain fp32 path (fp32 storage or shapes off the matrix-core path: the small parity workloads): plain
-        # vector arithmetic, the whole step against the fp32 vector peak
+        # the plain fp32 path (fp32 storage or shapes off the bf16 matrix-core path: the small parity workloads): products on
+        # the fp32 matrix instruction, whose peak is the vector units'; the whole step against it
         achieved = model_flops / (ms_per_step * 1e-3) / 1e12
-        roof = {"bound": "alu", "kernel": "plain fp32 path, whole step", "achieved": achieved, "peak": PEAK_FP32_VECTOR_TFLOPS,
-                "unit": "TFLOP/s", "frac": achieved / PEAK_FP32_VECTOR_TFLOPS, "traffic": None,
+        roof = {"bound": "mfma", "kernel": "plain fp32 path, whole step", "achieved": achieved, "peak": PEAK_FP32_TFLOPS,
+                "unit": "TFLOP/s", "frac": achieved / PEAK_FP32_TFLOPS, "traffic": None,
                 "traffic_unit": "bytes per launch", "launches": args.steps, "avg_ms": ms_per_step}
     out = {
         "metric": "CP-head fwd+bwd tokens/s", "value": value, "unit": "tokens/s", "n_gpus": 1,

@@ -33,7 +33,7 @@
  *
  * Limits: 1 <= r <= 64, 1 <= n <= 64, d >= 1, V >= 1, T >= 0, T*n*r*max(d,V) < 2^62.
  * The matrix-core path is taken for dtype = bf16 with d a multiple of 64; other
- * shapes and fp32 storage run on a plain fp32 path (correct for any shape, slow).
+ * shapes and fp32 storage run on a plain fp32 path (correct for any shape, slower).
  */
 #ifndef CP_HEAD_H
 #define CP_HEAD_H

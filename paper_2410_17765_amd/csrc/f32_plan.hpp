@@ -26,8 +26,8 @@ struct F32Shape {
 // The choice is the one with the least time in a model with measured constants: rounds of tiles over the compute units
 // at the average cost of a tile, not less than the longest tile alone on its compute unit, plus, if a sum is split, the
 // pass that adds the parts.  Cycles per k-value of one tile, alone and with a second tile on the compute unit,
-// at 2.4 GHz: 128-wide 171 / 156 (124 TFLOP/s on 512 and more tiles, 56 on 128), 64-wide 51 / 44 (111, 45), 32-wide 16 /
-// 13.3 (86, 31); a launch costs about 4 us whatever it does.
+// at 2.4 GHz: 128-wide 171 / 156, 64-wide 51 / 44, 32-wide 16 / 13.3 (at K = 4096, TFLOP/s on 128 and on 512 tiles: 59 / 125,
+// 46 / 107, 29 / 80; on 2048 tiles the 64-wide reach 112 and the 32-wide 92); a launch costs about 4 us whatever it does.
 inline void f32_plan(const F32Shape *shape, int count, bool may_split, F32Plan *out)
 {
     constexpr double kCus = 256, kFixed[3] = {6000, 5000, 3000}, kReduceFixed = 10000, kBytesPerCycle = 2000;

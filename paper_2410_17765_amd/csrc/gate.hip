@@ -18,7 +18,7 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 // ------------------------------------------------------------------------------------------
 // G h of 16 positions per step of a workgroup on the 16x16x32 matrix instruction, for the arg-max counts.
 // The kernel it replaces walked H with 2-byte loads, once per expert, one position per wavefront: 353 us for the
-// arg-max at T = 16384, d = 4096, r = 8 (0.4 TB/s); this one takes 35 us (3.9 TB/s).  Here the four wavefronts share the
+// arg-max at T = 16384, d = 4096, r = 8 (0.4 TB/s); this one takes 31 us (4.4 TB/s).  Here the four wavefronts share the
 // contraction, and the partial products meet in LDS.  Experts beyond r repeat the last row of G and are dropped.
 // ------------------------------------------------------------------------------------------
 constexpr int kRows = 16;
