@@ -106,9 +106,11 @@ struct EpiF32Store {
     }
 };
 
-// exp(x - mx) where mx is the largest of the x.  An infinite mx weighs its own kind 1 and the rest 0, as a running
-// maximum does, and a NaN stays one, also where it is alone and mx is still -infinity.
-__device__ __forceinline__ float exp_below(float x, float mx) { return x == mx ? 1.f : expf(x - mx); }
+// Sums of exponentials relative to their maximum mx, for logits that may be infinite or NaN as well: a term is
+// exp(x - below(mx)), so that an infinite maximum leaves +infinity of its own kind and nothing of the rest, and a NaN stays
+// one, also where it is alone and mx still -infinity; a sum moves from one maximum to a larger one with the factor shift().
+__device__ __forceinline__ float below(float mx) { return fabsf(mx) == INFINITY ? 0.f : mx; }
+__device__ __forceinline__ float shift(float from, float to) { return from == to ? 1.f : expf(from - to); }
 
 // Logits of the head rows m = row * row_mul + batch: (maximum, sum of exp(z - maximum)) over the sub-tile's columns
 // to part[m, slots], the target logit to zt[m] (if X is given), and the logits themselves to z[row, ldz] (if z is
@@ -146,10 +148,11 @@ struct EpiF32Logits {
                     for (int j = 0; j < Tile::TN; ++j)
                         if (col0 + f32_col(j, lane) < p.N) mx = fmaxf(mx, acc[i][j][v]);
                     mx = row16_max(mx);
+                    const float base = below(mx);
                     float sum = 0.f;
 #pragma unroll
                     for (int j = 0; j < Tile::TN; ++j)
-                        if (col0 + f32_col(j, lane) < p.N) sum += exp_below(acc[i][j][v], mx);
+                        if (col0 + f32_col(j, lane) < p.N) sum += expf(acc[i][j][v] - base);
                     sum = row16_sum(sum);
                     if (in && (lane & 15) == 0) part[m * slots + slot] = make_float2(mx, sum);
                 }
@@ -299,10 +302,10 @@ __global__ void __launch_bounds__(kBlock) k_position_finish(int n, int r, int sl
             const float2 v = part[m * slots + q];
             // a slot without columns is (-infinity, 0); one whose columns are all NaN is (-infinity, NaN)
             if (v.x > mx) { l = l * expf(mx - v.x) + v.y; mx = v.x; }
-            else l += v.y * exp_below(v.x, mx);
+            else l += v.y * shift(v.x, mx);
         }
         const float Mx = wave_max(mx);
-        const float L = wave_sum(l * exp_below(mx, Mx));
+        const float L = wave_sum(l * shift(mx, Mx));
         const float lse = Mx + logf(L);
         if (lane == 0) {
             lse_out[m] = lse;
@@ -350,18 +353,19 @@ __global__ void __launch_bounds__(1024) k_lse_of_rows(size_t rows, int V, const 
 #pragma unroll
             for (int i = 0; i < 8; ++i)
                 if (v0 + i * (int)blockDim.x < V) mn = fmaxf(mn, x[i]);
-            l *= exp_below(mx, mn);
+            l *= shift(mx, mn);
+            const float base = below(mn);
 #pragma unroll
             for (int i = 0; i < 8; ++i)
-                if (v0 + i * (int)blockDim.x < V) l += exp_below(x[i], mn);
+                if (v0 + i * (int)blockDim.x < V) l += expf(x[i] - base);
             mx = mn;
         }
-        const float wm = wave_max(mx), wl = wave_sum(l * exp_below(mx, wm));
+        const float wm = wave_max(mx), wl = wave_sum(l * shift(mx, wm));
         if (lane == 0) red[wave] = make_float2(wm, wl);
         __syncthreads();
         if (wave == 0) {
             const float2 q = lane < waves ? red[lane] : make_float2(-INFINITY, 0.f);
-            const float Mx = wave_max(q.x), L = wave_sum(q.y * exp_below(q.x, Mx));
+            const float Mx = wave_max(q.x), L = wave_sum(q.y * shift(q.x, Mx));
             if (lane == 0) lse_out[m] = Mx + logf(L);
         }
         __syncthreads();
