@@ -159,8 +159,9 @@ int cp_head_loss_bwd(const cp_head_desc *desc,
 /*
  * Training loss and its gradients in one call (section "Training procedure", eq. 9 and its derivative), for
  * training loops in which the loss is the last node of the graph, so that the upstream gradient is known
- * before the forward pass: dloss[T] / scale as in cp_head_loss_bwd.  loss[T] and the gradients are exactly
- * what cp_head_loss_fwd followed by cp_head_loss_bwd return (same kernels, same arithmetic); no ctx is needed,
+ * before the forward pass: dloss[T] / scale as in cp_head_loss_bwd.  loss[T] is exactly what cp_head_loss_fwd returns, and
+ * the gradients are exactly what the pair of calls returns with CP_HEAD_KEEP_LOGITS on the matrix-core path (same kernels,
+ * same arithmetic; where n r does not divide the rows of a chunk, dU in another order of its fp32 sums).  No ctx is needed,
  * the workspace is sized by cp_head_workspace_bytes with CP_HEAD_OP_LOSS_FWD_BWD.
  * What the single call buys on the matrix-core path: forward and backward are interleaved per chunk of
  * positions, and the logits of a chunk are kept as 16-bit floats from the product that forms their statistics to
