@@ -29,7 +29,7 @@ namespace cph {
 
 namespace {
 
-typedef TileCfg<256, 256, 2, 2> Cfg;
+typedef TileCfg<256, 256, 2, 2, false, false, false, true> Cfg;     // four rows of a column per lane
 constexpr int kBlock = 256;
 
 // ------------------------------------------------------------------------------------------
@@ -249,7 +249,7 @@ struct EpiDistillStats {
             float S[4] = {0.f, 0.f, 0.f, 0.f}, KL[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int j = 0; j < C::TN16; ++j) {
-                const int col = col0 + acc_col(j, lane);
+                const int col = col0 + acc_col_of_lane(j, lane);
                 const bool cv = col < V;
                 const int cc = cv ? col : V - 1;
                 float l[4], lm[4];
@@ -363,7 +363,7 @@ struct EpiDzDistill {
             }
 #pragma unroll
             for (int j = 0; j < C::TN16; ++j) {
-                const int col = col0 + acc_col(j, lane);
+                const int col = col0 + acc_col_of_lane(j, lane);
                 const bool cv = col < V;
                 const int cc = cv ? col : V - 1;
                 float l[4], lm[4];

@@ -23,7 +23,9 @@ typedef TileCfg<256, 256, 2, 2> Cfg;
 typedef TileCfg<256, 256, 2, 2, false, true> CfgNN;
 typedef TileCfg<256, 256, 2, 2, true, true> CfgTN;
 // A stored in blocks of 256 rows x 64 columns (the chunk's logit gradients as the dY product reads them)
-typedef TileCfg<256, 256, 2, 2, false, false, true, false> CfgBlockedA;
+typedef TileCfg<256, 256, 2, 2, false, false, true> CfgBlockedA;
+// four rows of a column per lane
+typedef TileCfg<256, 256, 2, 2, false, false, false, true> CfgRows;
 constexpr int kBlock = 256;
 
 
@@ -39,25 +41,36 @@ struct EpiStoreBf16 {
     long ldc;
     int M, N;
     static constexpr bool kSplittable = true;
-    __device__ __forceinline__ void put(int row, int col, float a) const
+    static __device__ __forceinline__ uint2 round4(f32x4_t a) { return make_uint2(f32x2_to_bf16x2(a[0], a[1]), f32x2_to_bf16x2(a[2], a[3])); }
+    static __device__ __forceinline__ uint2 residual4(f32x4_t a, uint2 h)
+    {
+        return make_uint2(f32x2_to_bf16x2(a[0] - __uint_as_float(h.x << 16), a[1] - __uint_as_float(h.x & 0xFFFF0000u)),
+                          f32x2_to_bf16x2(a[2] - __uint_as_float(h.y << 16), a[3] - __uint_as_float(h.y & 0xFFFF0000u)));
+    }
+    __device__ __forceinline__ void put(int row, int col, f32x4_t a) const
     {
         const size_t at = (size_t)row * ldc + col;
-        const bf16_t h = f32_to_bf16(a);
-        hi[at] = h;
-        if (lo) lo[at] = f32_to_bf16(a - bf16_to_f32(h));
+        const uint2 h = round4(a);
+        *reinterpret_cast<uint2 *>(hi + at) = h;
+        if (lo) *reinterpret_cast<uint2 *>(lo + at) = residual4(a, h);
     }
     template <class C>
-    __device__ void run(f32x4_t (&acc)[C::TM16][C::TN16], int row0, int col0, int lane, int wave, int, char *smem) const
+    __device__ void run(f32x4_t (&acc)[C::TM16][C::TN16], int row0, int col0, int lane, int, int, char *) const
     {
-        if (lo)
-            store_tile_bf16_pair<C>(smem, wave, lane, row0, col0, M, N, hi, lo, ldc, [&](int i, int j, int v) {
-                const float a = acc[i][j][v];
-                const bf16_t h = f32_to_bf16(a);
-                return (uint32_t)h | ((uint32_t)f32_to_bf16(a - bf16_to_f32(h)) << 16);
-            });
-        else
-            store_tile_bf16<C>(smem, wave, lane, row0, col0, M, N, hi, ldc,
-                               [&](int i, int j, int v, int, int) { return f32_to_bf16(acc[i][j][v]); });
+        const RowsOut16<C, false> out(lane, row0, col0, M, N, hi, ldc), out_lo(lane, row0, col0, M, N, lo, ldc);
+#pragma unroll
+        for (int i = 0; i < C::TM16; ++i) {
+            uint2 h[C::TN16];
+#pragma unroll
+            for (int j = 0; j < C::TN16; ++j) h[j] = round4(acc[i][j]);
+            if (lo) {
+                uint2 l[C::TN16];
+#pragma unroll
+                for (int j = 0; j < C::TN16; ++j) l[j] = residual4(acc[i][j], h[j]);
+                out_lo.put(i, l);
+            }
+            out.put(i, h);
+        }
     }
 };
 
@@ -68,16 +81,15 @@ struct EpiStoreF32 {
     int M, N;
     int accumulate;
     static constexpr bool kSplittable = true;
-    __device__ __forceinline__ void put(int row, int col, float a) const
+    __device__ __forceinline__ void put(int row, int col, f32x4_t a) const
     {
-        float *o = C + (size_t)row * ldc + col;
+        f32x4_t *o = reinterpret_cast<f32x4_t *>(C + (size_t)row * ldc + col);
         *o = accumulate ? a + *o : a;
     }
     template <class Cf>
-    __device__ void run(f32x4_t (&acc)[Cf::TM16][Cf::TN16], int row0, int col0, int lane, int wave, int, char *smem) const
+    __device__ void run(f32x4_t (&acc)[Cf::TM16][Cf::TN16], int row0, int col0, int lane, int, int, char *) const
     {
-        store_tile_f32<Cf>(smem, wave, lane, row0, col0, M, N, C, ldc, accumulate != 0,
-                           [&](int i, int j, int v, int, int) { return acc[i][j][v]; });
+        store_rows_f32<Cf>(acc, lane, row0, col0, M, N, C, ldc, accumulate != 0);
     }
 };
 
@@ -90,19 +102,30 @@ __device__ __forceinline__ void mask_columns_past_vocabulary(f32x4_t (&acc)[C::T
     if (col0 + C::WTN <= V) return;
 #pragma unroll
     for (int j = 0; j < C::TN16; ++j)
-        if (col0 + acc_col(j, lane) >= V) {
 #pragma unroll
-            for (int i = 0; i < C::TM16; ++i)
+        for (int v = 0; v < 4; ++v) {
+            const bool past = col0 + acc_col(j, v, lane) >= V;
 #pragma unroll
-                for (int v = 0; v < 4; ++v) acc[i][j][v] = -INFINITY;
+            for (int i = 0; i < C::TM16; ++i) acc[i][j][v] = past ? -INFINITY : acc[i][j][v];
         }
+}
+
+// Of block row i of a sub-tile (a lane has 4 TN16 columns of one row): the row's largest logit over the sub-tile, and the
+// reference that its exponentials are taken against (the same, or 0 for a row with no valid column).
+template <class C>
+__device__ __forceinline__ void row_max(const f32x4_t (&acc)[C::TN16], float &mx, float &ref)
+{
+    mx = -INFINITY;
+#pragma unroll
+    for (int j = 0; j < C::TN16; ++j) mx = fmaxf(mx, fmaxf(fmaxf(acc[j][0], acc[j][1]), fmaxf(acc[j][2], acc[j][3])));
+    mx = groups_max(mx);
+    ref = (mx == -INFINITY) ? 0.f : mx;
 }
 
 // Running statistics of the logits (eq. 5 in log space): for every row of the wavefront's
 // sub-tile the maximum and the sum of exp(z - max) over its columns.  One (max, sum) pair per
 // row and per (tile column, wavefront column) goes to `part`; the logits themselves are dropped.
-// A row of the sub-tile lives in one 16-lane group (its column blocks in the lane's registers), so a
-// wavefront reduces four rows at a time with moves inside 16 lanes; the group's first lane writes the pair.
+// A row of the sub-tile lives in the four lanes l % 16 + 16 k; the first of them writes the pair.
 struct EpiRowStats {
     float2 *part;   // [M, parts]
     int parts;      // tiles_n * WN
@@ -113,22 +136,18 @@ struct EpiRowStats {
         const int slot = tn * C::WN + (wave % C::WN);
         mask_columns_past_vocabulary<C>(acc, col0, lane, V);
 #pragma unroll
-        for (int i = 0; i < C::TM16; ++i)
+        for (int i = 0; i < C::TM16; ++i) {
+            float mx, ref, s[4] = {0.f, 0.f, 0.f, 0.f};
+            row_max<C>(acc[i], mx, ref);
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                float mx = -INFINITY;
+            for (int j = 0; j < C::TN16; ++j)
 #pragma unroll
-                for (int j = 0; j < C::TN16; ++j) mx = fmaxf(mx, acc[i][j][v]);
-                mx = row16_max(mx);
-                const float ref = (mx == -INFINITY) ? 0.f : mx;
-                float s = 0.f;
-#pragma unroll
-                for (int j = 0; j < C::TN16; ++j) s += __expf(acc[i][j][v] - ref);
-                s = row16_sum(s);
-                const int r = row0 + acc_row(i, v, lane);
-                if ((lane & 15) == 0 && r < M)
-                    part[(size_t)r * parts + slot] = make_float2(mx, (mx == -INFINITY) ? 0.f : s);
-            }
+                for (int v = 0; v < 4; ++v) s[v] += __expf(acc[i][j][v] - ref);
+            const float sum = groups_sum((s[0] + s[1]) + (s[2] + s[3]));
+            const int r = row0 + acc_row(i, lane);
+            if (lane < 16 && r < M) part[(size_t)r * parts + slot] = make_float2(mx, (mx == -INFINITY) ? 0.f : sum);
+            __builtin_amdgcn_sched_barrier(0);      // one block row at a time: more of them spill registers
+        }
     }
 };
 
@@ -143,43 +162,34 @@ struct EpiRowStatsKeep {
     uint16_t *zs;   // [M, ldzs]
     long ldzs;
     int Vp;         // columns of zs that are written (V rounded up to 64; those from V on hold junk)
-    template <class C, int P>
-    __device__ __forceinline__ void pass(f32x4_t (&acc)[C::TM16][C::TN16], int row0, int col0, int lane, int wave,
-                                         int slot, char *smem) const
-    {
-#pragma unroll
-        for (int i = 2 * P; i < 2 * P + 2; ++i)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                float mx = -INFINITY;
-#pragma unroll
-                for (int j = 0; j < C::TN16; ++j) mx = fmaxf(mx, acc[i][j][v]);
-                mx = row16_max(mx);
-                const float ref = (mx == -INFINITY) ? 0.f : mx;
-                float s = 0.f;
-#pragma unroll
-                for (int j = 0; j < C::TN16; ++j) {
-                    acc[i][j][v] -= ref;
-                    s += __expf(acc[i][j][v]);
-                }
-                s = row16_sum(s);
-                const int r = row0 + acc_row(i, v, lane);
-                if ((lane & 15) == 0 && r < M)
-                    part[(size_t)r * parts + slot] = make_float2(mx, (mx == -INFINITY) ? 0.f : s);
-            }
-        auto half = [&](int i, int j, int v, int, int) { return f32_to_f16_bits(acc[i][j][v]); };
-        store_tile_bf16<C, decltype(half), P, P + 1>(smem, wave, lane, row0, col0, M, Vp, zs, ldzs, half);
-    }
     template <class C>
-    __device__ void run(f32x4_t (&acc)[C::TM16][C::TN16], int row0, int col0, int lane, int wave, int tn, char *smem) const
+    __device__ void run(f32x4_t (&acc)[C::TM16][C::TN16], int row0, int col0, int lane, int wave, int tn, char *) const
     {
-        static_assert(C::WTM == 128 && C::WTN == 128, "blocks of 128 columns, four passes of 32 rows");
+        static_assert(C::WTN == 128, "blocks of 128 columns");
         const int slot = tn * C::WN + (wave % C::WN);
         mask_columns_past_vocabulary<C>(acc, col0, lane, V);
-        pass<C, 0>(acc, row0, col0, lane, wave, slot, smem);
-        pass<C, 1>(acc, row0, col0, lane, wave, slot, smem);
-        pass<C, 2>(acc, row0, col0, lane, wave, slot, smem);
-        pass<C, 3>(acc, row0, col0, lane, wave, slot, smem);
+        const RowsOut16<C, false> out(lane, row0, col0, M, Vp, zs, ldzs);
+#pragma unroll
+        for (int i = 0; i < C::TM16; ++i) {
+            float mx, ref, s[4] = {0.f, 0.f, 0.f, 0.f};
+            row_max<C>(acc[i], mx, ref);
+            uint2 w[C::TN16];
+#pragma unroll
+            for (int j = 0; j < C::TN16; ++j) {
+                float z[4];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    z[v] = acc[i][j][v] - ref;
+                    s[v] += __expf(z[v]);
+                }
+                w[j] = make_uint2(f32x2_to_f16x2(z[0], z[1]), f32x2_to_f16x2(z[2], z[3]));
+            }
+            out.put(i, w);
+            const float sum = groups_sum((s[0] + s[1]) + (s[2] + s[3]));
+            const int r = row0 + acc_row(i, lane);
+            if (lane < 16 && r < M) part[(size_t)r * parts + slot] = make_float2(mx, (mx == -INFINITY) ? 0.f : sum);
+            __builtin_amdgcn_sched_barrier(0);      // one block row at a time: more of them spill registers
+        }
     }
 };
 
@@ -242,7 +252,7 @@ struct EpiDz {
         for (int i = 4 * IP; i < 4 * IP + 4; ++i) {
 #pragma unroll
             for (int v = 0; v < 4; v += 2) {
-                const int lrow = acc_row(i, v, lane);                // rows lrow and lrow + 1 of the sub-tile
+                const int lrow = acc_row_of_lane(i, v, lane);                // rows lrow and lrow + 1 of the sub-tile
                 const int row = row0 + lrow;
                 const float4 ra = winfo[lrow];                       // rows past the chunk hold the last row's values
                 const float4 rb = winfo[lrow + 1];
@@ -1499,7 +1509,7 @@ void loss_dz_launch(void *user, const bf16_t *Yc, int Mc, int Mcp, size_t m0, bf
                     bf16_t *dZt, long ldzt, hipStream_t st)
 {
     const LossDzArgs *a = static_cast<const LossDzArgs *>(user);
-    launch_gemm_nt<Cfg>("gemm_z_dz", Yc, a->d, Mc, a->U, a->d, a->V, a->d,
+    launch_gemm_nt<CfgRows>("gemm_z_dz", Yc, a->d, Mc, a->U, a->d, a->V, a->d,
                         EpiDz{dZ, ldz, dZt, ldzt, a->rowinfo + m0, Mc, Mcp, a->V, (int)ldz, dz_blocked ? 1 : 0}, st);
 }
 
@@ -1842,7 +1852,7 @@ int fast_full_loss_bwd(const cp_head_desc &ds, const void *Hv, const void *Fv, c
                 KeptDzArgs kept{KeptLogits{at<uint16_t>(ctx, cl.zs), at<float2>(ctx, cl.zpart), (long)cl.Vp, cl.parts}, rowinfo, V};
                 kept_dz_launch(&kept, nullptr, Tc, Tcp, (size_t)sa * T + t0, dZ, (long)Vp, false, dF ? dZt : nullptr, ldM, st);
             } else {
-                launch_gemm_nt<Cfg>("full_gemm_z_dz", Hc, d, Tc, Fsa, d, V, d,
+                launch_gemm_nt<CfgRows>("full_gemm_z_dz", Hc, d, Tc, Fsa, d, V, d,
                                     EpiDz{dZ, (long)Vp, dF ? dZt : nullptr, ldM, rowinfo + (size_t)sa * T + t0, Tc, Tcp, V, Vp, 0}, st);
             }
             // dH += dz F_sa   (contraction over the vocabulary; F_sa as it is stored is K-major for this product, and

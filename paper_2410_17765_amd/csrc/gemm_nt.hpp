@@ -57,12 +57,13 @@ struct GemmOperands {
 constexpr int kKmPassBytes = 2 * 2048 + 128;
 constexpr int kKmTileBytes = 8 * kKmPassBytes;
 
-template <int BM_, int BN_, int WM_, int WN_, bool AKM_ = false, bool BKM_ = false, bool ABL_ = false, bool BBL_ = false>
+template <int BM_, int BN_, int WM_, int WN_, bool AKM_ = false, bool BKM_ = false, bool ABL_ = false, bool ROWS_IN_LANE_ = false>
 struct TileCfg {
     static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, BK = 64;
     static constexpr bool AKM = AKM_, BKM = BKM_;     // operand is K-major
-    static constexpr bool ABL = ABL_, BBL = BBL_;     // operand is stored tile by tile: [rows/256][K/64][256][64]
-    static_assert(!(AKM_ && ABL_) && !(BKM_ && BBL_), "an operand is K-major or blocked, not both");
+    static constexpr bool ABL = ABL_;                 // A is stored block by block: [rows/256][K/64][256][64]
+    // which four neighbouring elements a lane holds of a 16x16 block of the result: one row's columns, or one column's rows
+    static constexpr bool ROWS_IN_LANE = ROWS_IN_LANE_;
     static constexpr int THREADS = WM * WN * kWave;
     static constexpr int WTM = BM / WM, WTN = BN / WN;       // wavefront sub-tile
     static constexpr int TM16 = WTM / 16, TN16 = WTN / 16;   // 16x16 MFMA blocks per wavefront
@@ -71,6 +72,7 @@ struct TileCfg {
     static constexpr int A_BYTES = AKM_ ? kKmTileBytes : BM * BK * 2, B_BYTES = BKM_ ? kKmTileBytes : BN * BK * 2;
     static_assert(!(AKM_ || BKM_) || WM_ * WN_ == 4, "K-major operands: four wavefronts");
     static_assert((!AKM_ || BM_ == 256) && (!BKM_ || BN_ == 256), "a K-major tile has 256 columns");
+    static_assert(!(AKM_ && ABL_), "an operand is K-major or blocked, not both");
     static constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
     static constexpr int LDS_BYTES = 2 * STAGE_BYTES;
     static_assert(BM % (WM * 64) == 0 && BN % (WN * 32) == 0, "wave tile must be a multiple of 64 rows x 32 columns");
@@ -131,8 +133,12 @@ constexpr int kGroupRowsWide = 8, kGroupRowsNarrow = 4;
 //   phase 3   rows half 1, k 32..63   + reads from tile kt+1: A half 0, B (k 0..31)          + 1st half of the loads of tile kt+2
 // Memory instructions are issued one at a time between MFMAs (the order is pinned with scheduling
 // barriers): a wavefront issues in order, so a cluster of loads would hold back its MFMAs.
-// On return acc[i][j] holds the 16x16 block (i, j) of the wavefront's sub-tile: element v of lane l is
-// row 4*(l/16) + v, column l%16 of that block.
+// On return acc[i][j] holds the 16x16 block (i, j) of the wavefront's sub-tile.  The instruction gives lane l the
+// elements 4*(l/16) + v, v = 0..3, of its first operand's rows, all at its second operand's row l%16.  With B as the first
+// operand (the default) those are four columns of row l%16 of the block, so that a lane's results are consecutive in memory:
+// the epilogues store straight from the registers, and a row's maximum and sum are 32 steps inside a lane and two
+// across lanes.  With A first (ROWS_IN_LANE) they are four rows of column l%16, which is what the mixtures over the expert
+// rows of a token need.
 template <class Cfg>
 __device__ __forceinline__ void gemm_nt_mainloop_direct(const GemmOperands &g, int tm, int tn, char *smem,
                                                           f32x4_t (&acc)[Cfg::TM16][Cfg::TN16])
@@ -167,10 +173,10 @@ __device__ __forceinline__ void gemm_nt_mainloop_direct(const GemmOperands &g, i
     // read as zero, columns past M or N read whatever follows in the row and only reach accumulators that are
     // never stored.
     // bytes between two rows of the tile: the leading dimension, or 128 for a blocked operand
-    const unsigned rsa = Cfg::ABL ? 128u : (unsigned)g.lda * 2u, rsb = Cfg::BBL ? 128u : (unsigned)g.ldb * 2u;
+    const unsigned rsa = Cfg::ABL ? 128u : (unsigned)g.lda * 2u, rsb = (unsigned)g.ldb * 2u;
     // (a blocked operand's descriptor spans the whole panel of its tile row: all 256 rows of every block exist)
     const unsigned span_a = Cfg::ABL ? (unsigned)((size_t)BM * g.K * 2) : (unsigned)((size_t)rows_a * g.lda * 2);
-    const unsigned span_b = Cfg::BBL ? (unsigned)((size_t)BN * g.K * 2) : (unsigned)((size_t)rows_b * g.ldb * 2);
+    const unsigned span_b = (unsigned)((size_t)rows_b * g.ldb * 2);
     const __amdgpu_buffer_rsrc_t ra = make_rsrc(g.A + (size_t)m0 * g.lda, span_a);
     const __amdgpu_buffer_rsrc_t rb = make_rsrc(g.B + (size_t)n0 * g.ldb, span_b);
     // A K-major operand's descriptor is kept for the K-tile whose loads are being issued and moved on by one tile
@@ -241,8 +247,8 @@ __device__ __forceinline__ void gemm_nt_mainloop_direct(const GemmOperands &g, i
     // operand and part of the descriptor's base for a K-major one.  Kernels with a K-major operand issue all their
     // loads spelled out (see load_lds_16_spelled_out).
     auto load_one = [&](int kt, int stage, int q) {
-        // the K-step: 128 bytes along the row, or one block of BM (BN) rows x 128 bytes of a blocked operand
-        const int soff = q < Cfg::A_PASSES ? kt * (Cfg::ABL ? BM * 128 : BK * 2) : kt * (Cfg::BBL ? BN * 128 : BK * 2);
+        // the K-step: 128 bytes along the row, or one block of BM rows x 128 bytes of a blocked operand
+        const int soff = q < Cfg::A_PASSES ? kt * (Cfg::ABL ? BM * 128 : BK * 2) : kt * (BK * 2);
         char *base = smem + stage * Cfg::STAGE_BYTES + lds_wave;
         const unsigned lbase = lds_smem + stage * Cfg::STAGE_BYTES + lds_wave;
         if (q < Cfg::A_PASSES) {
@@ -297,10 +303,11 @@ __device__ __forceinline__ void gemm_nt_mainloop_direct(const GemmOperands &g, i
         if (Cfg::AKM || Cfg::BKM)
             asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0"
                          : "+a"(acc[half * HA + i][j])
-                         : "v"(fa[abuf][i]), "v"(fb[bbuf][j]));
+                         : "v"(Cfg::ROWS_IN_LANE ? fa[abuf][i] : fb[bbuf][j]), "v"(Cfg::ROWS_IN_LANE ? fb[bbuf][j] : fa[abuf][i]));
         else
             acc[half * HA + i][j] =
-                __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[abuf][i], fb[bbuf][j], acc[half * HA + i][j], 0, 0, 0);
+                __builtin_amdgcn_mfma_f32_16x16x32_bf16(Cfg::ROWS_IN_LANE ? fa[abuf][i] : fb[bbuf][j],
+                                                        Cfg::ROWS_IN_LANE ? fb[bbuf][j] : fa[abuf][i], acc[half * HA + i][j], 0, 0, 0);
     };
     // the reads of the four phases, in the order the MFMAs that follow need them
     auto reads0 = [&](const char *st, const char *, int q) {       // A half 1 of k-block 0, then B first half of k-block 1
@@ -414,11 +421,14 @@ struct NoSideJob {
     __device__ void run(int, char *) const {}
 };
 // row / column of accumulator element v of block (i, j) for lane l, relative to the sub-tile origin
-__device__ __forceinline__ int acc_row(int i, int v, int lane) { return i * 16 + 4 * (lane >> 4) + v; }
-__device__ __forceinline__ int acc_col(int j, int lane) { return j * 16 + (lane & 15); }
+__device__ __forceinline__ int acc_row(int i, int lane) { return i * 16 + (lane & 15); }
+__device__ __forceinline__ int acc_col(int j, int v, int lane) { return j * 16 + 4 * (lane >> 4) + v; }
+// the same for ROWS_IN_LANE
+__device__ __forceinline__ int acc_row_of_lane(int i, int v, int lane) { return i * 16 + 4 * (lane >> 4) + v; }
+__device__ __forceinline__ int acc_col_of_lane(int j, int lane) { return j * 16 + (lane & 15); }
 
 // Epilogues whose result is a plain function of the sum over K (kSplittable) may have the launch's last round split along
-// K (split_plan): put(row, col, value) stores one element.
+// K (split_plan): put(row, col, values) stores four consecutive columns.
 template <class Epi, class = void> struct IsSplittable { static constexpr bool value = false; };
 template <class Epi> struct IsSplittable<Epi, decltype((void)Epi::kSplittable)> { static constexpr bool value = true; };
 
@@ -464,7 +474,7 @@ __global__ void __launch_bounds__(Cfg::THREADS) k_gemm_nt_split(GemmOperands g, 
         split_item(split, item, (g.K + Cfg::BK - 1) / Cfg::BK, bid, part, k0, k1);
         // the operands from K-step k0 on
         g.A += Cfg::AKM ? (size_t)k0 * Cfg::BK * g.lda : (size_t)k0 * (Cfg::ABL ? Cfg::BM * Cfg::BK : Cfg::BK);
-        g.B += Cfg::BKM ? (size_t)k0 * Cfg::BK * g.ldb : (size_t)k0 * (Cfg::BBL ? Cfg::BN * Cfg::BK : Cfg::BK);
+        g.B += Cfg::BKM ? (size_t)k0 * Cfg::BK * g.ldb : (size_t)k0 * Cfg::BK;
         g.ka_rows = max(g.ka_rows - k0 * Cfg::BK, 0);
         g.kb_rows = max(g.kb_rows - k0 * Cfg::BK, 0);
         g.K = min(g.K, k1 * Cfg::BK) - k0 * Cfg::BK;
@@ -496,9 +506,10 @@ __global__ void __launch_bounds__(Cfg::THREADS) k_gemm_add_parts(GemmOperands g,
     int tm, tn;
     if (!tile_of_block(split.first + slot, g.tiles_m, g.tiles_n, g.gm, tm, tn)) return;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int row = tm * Cfg::BM + (wave / Cfg::WN) * Cfg::WTM + acc_row(i, 0, lane);
-    const int col = tn * Cfg::BN + (wave % Cfg::WN) * Cfg::WTN + acc_col(0, lane);
-    if (row - 4 * (lane >> 4) >= g.M) return;
+    static_assert(!Cfg::ROWS_IN_LANE, "four columns per lane");
+    const int row = tm * Cfg::BM + (wave / Cfg::WN) * Cfg::WTM + acc_row(i, lane);
+    const int col = tn * Cfg::BN + (wave % Cfg::WN) * Cfg::WTN + acc_col(0, 0, lane);
+    if (row - (lane & 15) >= g.M) return;
     f32x4_t sum[Cfg::TN16];
 #pragma unroll
     for (int j = 0; j < Cfg::TN16; ++j) sum[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -508,9 +519,7 @@ __global__ void __launch_bounds__(Cfg::THREADS) k_gemm_add_parts(GemmOperands g,
         for (int j = 0; j < Cfg::TN16; ++j) sum[j] += partial[partial_index<Cfg>(p * split.tail + slot, i, j, threadIdx.x)];
 #pragma unroll
     for (int j = 0; j < Cfg::TN16; ++j)
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-            if (row + v < g.M && col + j * 16 < g.N) epi.put(row + v, col + j * 16, sum[j][v]);
+        if (row < g.M && col + j * 16 < g.N) epi.put(row, col + j * 16, sum[j]);
 }
 
 // Scratch for the partial tiles of a split round; none: launches are never split.
@@ -562,7 +571,121 @@ inline void launch_gemm_nt(const char *name, const bf16_t *A, long lda, int M, c
 }
 
 // ---------------------------------------------------------------------------------------------
-// Coalesced output of a wavefront's sub-tile.  The MFMA result layout gives each lane single
+// Output of a wavefront's sub-tile straight from the accumulators (four columns of a row per lane), no LDS and no barrier:
+// a wavefront that is done leaves, whatever the others do.  (Through LDS, as store_tile_bf16 below still does for the other
+// layout, a tile of 256 x 256 cost 64 16-bit LDS writes and three barriers per 32 rows.)
+// ---------------------------------------------------------------------------------------------
+
+// 16 lanes of x change places with 16 lanes of y: x = {x0, y0, x2, y2}, y = {x1, y1, x3, y3} by groups of 16 lanes
+__device__ __forceinline__ void swap_groups16(uint32_t &x, uint32_t &y)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    const auto p = __builtin_amdgcn_permlane16_swap(x, y, false, false);
+    x = p[0];
+    y = p[1];
+#endif
+}
+// largest value / sum over the four lanes l % 16 + 16 k
+__device__ __forceinline__ float groups_max(float v)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
+    const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fmaxf(__uint_as_float(q[0]), __uint_as_float(q[1]));
+#endif
+    return v;
+}
+__device__ __forceinline__ float groups_sum(float v)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+    const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(q[0]) + __uint_as_float(q[1]);
+#endif
+    return v;
+}
+
+// Rows of 16-bit elements.  A lane's two words (four columns) of block j and of block j + 1 are exchanged between
+// neighbouring groups of 16 lanes so that it ends up with eight consecutive columns of one of the two: stores of 16 bytes,
+// 64 consecutive bytes per row, the other half of the cache line with the next store.
+// ld and col_limit are multiples of 8.  BLOCKED: dst is stored block by block (blocked64_index).
+template <class Cfg, bool BLOCKED>
+struct RowsOut16 {
+    static_assert(!Cfg::ROWS_IN_LANE && Cfg::TN16 % 2 == 0 && (!BLOCKED || Cfg::WTN % 64 == 0), "layout");
+    static_assert(Cfg::WTM <= 256 && 256 % Cfg::WTM == 0, "a wavefront's rows stay inside a block of 256");
+    uint16_t *out;          // of the lane's first row
+    size_t step;            // to the row 16 further on
+    int row, col, row_limit, col_limit;
+    bool whole;             // the sub-tile lies inside the matrix
+    __device__ __forceinline__ RowsOut16(int lane, int row0, int col0, int rows, int cols, uint16_t *dst, long ld)
+    {
+        const int q = lane >> 4;
+        row = row0 + (lane & 15);
+        col = col0 + (q & 1) * 16 + (q >> 1) * 8;
+        out = dst + (BLOCKED ? blocked64_index((size_t)row, col, ld) : (size_t)row * ld + col);
+        step = BLOCKED ? (size_t)16 * 64 : (size_t)16 * ld;
+        row_limit = rows;
+        col_limit = cols;
+        whole = row0 + Cfg::WTM <= rows && col0 + Cfg::WTN <= cols;
+    }
+    // block row i: words[j] are the lane's two words of block (i, j)
+    __device__ __forceinline__ void put(int i, uint2 (&words)[Cfg::TN16]) const
+    {
+        u32x4_t val[Cfg::TN16 / 2];
+#pragma unroll
+        for (int p = 0; p < Cfg::TN16 / 2; ++p) {
+            uint2 a = words[2 * p], b = words[2 * p + 1];
+            swap_groups16(a.x, b.x);
+            swap_groups16(a.y, b.y);
+            val[p] = u32x4_t{a.x, a.y, b.x, b.y};
+        }
+        uint16_t *o = out + i * step;
+        if (whole) {
+#pragma unroll
+            for (int p = 0; p < Cfg::TN16 / 2; ++p) *reinterpret_cast<u32x4_t *>(o + place(p)) = val[p];
+        } else if (row + 16 * i < row_limit) {
+#pragma unroll
+            for (int p = 0; p < Cfg::TN16 / 2; ++p)
+                if (col + 32 * p < col_limit) *reinterpret_cast<u32x4_t *>(o + place(p)) = val[p];
+        }
+    }
+    static __device__ __forceinline__ constexpr int place(int p) { return BLOCKED ? (p >> 1) * 16384 + (p & 1) * 32 : 32 * p; }
+};
+
+// Rows of fp32: dst = acc, or dst += acc when `accumulate` is set; 16-byte accesses, 64 consecutive bytes per row.
+// ld and col_limit are multiples of 4.
+template <class Cfg>
+__device__ __forceinline__ void store_rows_f32(const f32x4_t (&acc)[Cfg::TM16][Cfg::TN16], int lane, int row0, int col0, int row_limit,
+                                               int col_limit, float *__restrict__ dst, long ld, bool accumulate)
+{
+    static_assert(!Cfg::ROWS_IN_LANE, "four columns per lane");
+    const int row = row0 + acc_row(0, lane), col = col0 + acc_col(0, 0, lane);
+    float *out = dst + (size_t)row * ld + col;
+    const bool whole = row0 + Cfg::WTM <= row_limit && col0 + Cfg::WTN <= col_limit;
+#pragma unroll
+    for (int i = 0; i < Cfg::TM16; ++i) {
+        float *o = out + (size_t)(16 * i) * ld;
+        const bool in = row + 16 * i < row_limit;
+        if (accumulate) {
+            f32x4_t old[Cfg::TN16];
+#pragma unroll
+            for (int j = 0; j < Cfg::TN16; ++j)
+                old[j] = whole || (in && col + 16 * j < col_limit) ? *reinterpret_cast<const f32x4_t *>(o + 16 * j) : f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int j = 0; j < Cfg::TN16; ++j)
+                if (whole || (in && col + 16 * j < col_limit)) *reinterpret_cast<f32x4_t *>(o + 16 * j) = acc[i][j] + old[j];
+        } else {
+#pragma unroll
+            for (int j = 0; j < Cfg::TN16; ++j)
+                if (whole || (in && col + 16 * j < col_limit)) *reinterpret_cast<f32x4_t *>(o + 16 * j) = acc[i][j];
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
+// Coalesced output of a wavefront's sub-tile for ROWS_IN_LANE.  There the result layout gives each lane single
 // elements of 16-column blocks, so values are first laid out row-major in a wave-private
 // LDS area (32 rows at a time, the operand stages are free by then) and then written with
 // 16-byte stores: a wavefront store covers whole 256-byte row segments.
@@ -623,57 +746,6 @@ __device__ __forceinline__ void store_tile_bf16(char *smem, int wave, int lane, 
     }
 }
 
-// Two bf16 outputs of the same shape from one pass over the accumulators: pair(i, j, v) yields both values
-// (first in the low half); one set of barriers and one staging round serve both.
-template <class Cfg, class F>
-__device__ __forceinline__ void store_tile_bf16_pair(char *smem, int wave, int lane, int row0, int col0, int row_limit,
-                                                     int col_limit /* multiple of 8 */, bf16_t *__restrict__ dst0,
-                                                     bf16_t *__restrict__ dst1, long ld, F pair)
-{
-    constexpr int RS = Cfg::WTN * 2 + 16;
-    constexpr int CPR = Cfg::WTN / 8;
-    constexpr int RPP = kWave / CPR;
-    constexpr int REGION = Cfg::WM * Cfg::WN * 32 * RS;  // staging of one output
-    static_assert(2 * REGION <= Cfg::LDS_BYTES, "staging fits");
-    char *stage = smem + wave * (32 * RS);
-    size_t off = (size_t)(row0 + lane / CPR) * ld + (col0 + (lane % CPR) * 8);            // as in store_tile_bf16
-    const size_t step = (size_t)RPP * ld;
-    __syncthreads();
-#pragma unroll
-    for (int p = 0; p < Cfg::WTM / 32; ++p) {
-#pragma unroll
-        for (int ii = 0; ii < 2; ++ii) {
-            const int i = 2 * p + ii;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int r = 16 * ii + 4 * (lane >> 4) + v;
-#pragma unroll
-                for (int j = 0; j < Cfg::TN16; ++j) {
-                    const int c = j * 16 + (lane & 15);
-                    const uint32_t both = pair(i, j, v);
-                    *reinterpret_cast<bf16_t *>(stage + r * RS + c * 2) = (bf16_t)(both & 0xFFFFu);
-                    *reinterpret_cast<bf16_t *>(stage + REGION + r * RS + c * 2) = (bf16_t)(both >> 16);
-                }
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < 32 / RPP; ++q) {
-            const int r = q * RPP + lane / CPR, ch = lane % CPR;
-            const u32x4_t v0 = *reinterpret_cast<const u32x4_t *>(stage + r * RS + ch * 16);
-            const u32x4_t v1 = *reinterpret_cast<const u32x4_t *>(stage + REGION + r * RS + ch * 16);
-            const int grow = row0 + p * 32 + r, gcol = col0 + ch * 8;
-            if (grow < row_limit && gcol < col_limit) {
-                *reinterpret_cast<u32x4_t *>(dst0 + off) = v0;
-                *reinterpret_cast<u32x4_t *>(dst1 + off) = v1;
-            }
-            off += step;
-        }
-        __syncthreads();
-        __builtin_amdgcn_sched_barrier(0);
-    }
-}
-
 // Transposed bf16 output: dst[col * ld + row] = value(i, j, v, row, col).  A lane owns four consecutive
 // rows of one column per accumulator block, so the sub-tile is laid out column-major in LDS (64 rows at
 // a time, 8-byte writes) and leaves as 16-byte pieces of 128-byte column segments.
@@ -725,53 +797,6 @@ __device__ __forceinline__ void store_tile_bf16_transposed(char *smem, int wave,
             const int grow = row0 + ip * 64 + ch * 8, gcol = col0 + c;
             if (grow < row_limit && gcol < col_limit)
                 *reinterpret_cast<u32x4_t *>(out) = val;
-            out += step;
-        }
-        __syncthreads();
-        __builtin_amdgcn_sched_barrier(0);
-    }
-}
-
-// fp32 variant: dst = value, or dst += value when `accumulate` is set (16-byte loads and stores).
-template <class Cfg, class F>
-__device__ __forceinline__ void store_tile_f32(char *smem, int wave, int lane, int row0, int col0, int row_limit,
-                                               int col_limit /* multiple of 4 */, float *__restrict__ dst, long ld,
-                                               bool accumulate, F value)
-{
-    constexpr int RS = Cfg::WTN * 4 + 16;
-    constexpr int CPR = Cfg::WTN / 4;
-    constexpr int RPP = kWave / CPR;
-    static_assert(Cfg::WM * Cfg::WN * 32 * RS <= Cfg::LDS_BYTES, "staging fits");
-    char *stage = smem + wave * (32 * RS);
-    float *out = dst + (size_t)(row0 + lane / CPR) * ld + (col0 + (lane % CPR) * 4);          // as in store_tile_bf16
-    const size_t step = (size_t)RPP * ld;
-    __syncthreads();
-#pragma unroll
-    for (int p = 0; p < Cfg::WTM / 32; ++p) {
-#pragma unroll
-        for (int ii = 0; ii < 2; ++ii) {
-            const int i = 2 * p + ii;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int r = 16 * ii + 4 * (lane >> 4) + v;
-#pragma unroll
-                for (int j = 0; j < Cfg::TN16; ++j) {
-                    const int c = j * 16 + (lane & 15);
-                    *reinterpret_cast<float *>(stage + r * RS + c * 4) = value(i, j, v, row0 + p * 32 + r, col0 + c);
-                }
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < 32 / RPP; ++q) {
-            const int r = q * RPP + lane / CPR, ch = lane % CPR;
-            f32x4_t val = *reinterpret_cast<const f32x4_t *>(stage + r * RS + ch * 16);
-            const int grow = row0 + p * 32 + r, gcol = col0 + ch * 4;
-            if (grow < row_limit && gcol < col_limit) {
-                f32x4_t *o = reinterpret_cast<f32x4_t *>(out);
-                if (accumulate) val += *o;
-                *o = val;
-            }
             out += step;
         }
         __syncthreads();

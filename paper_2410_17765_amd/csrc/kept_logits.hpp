@@ -22,6 +22,15 @@ constexpr int kKeptBlock = 256;
 // 16-bit float (IEEE binary16) bit patterns, round to nearest even
 __device__ __forceinline__ uint16_t f32_to_f16_bits(float f) { return __builtin_bit_cast(uint16_t, (_Float16)f); }
 
+// two fp32 values -> two 16-bit floats in one register (a in the low half)
+__device__ __forceinline__ uint32_t f32x2_to_f16x2(float a, float b)
+{
+    typedef _Float16 f16x2_t __attribute__((ext_vector_type(2)));
+    typedef float f32x2_t __attribute__((ext_vector_type(2)));
+    const f32x2_t v = {a, b};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, f16x2_t));
+}
+
 typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
 
 struct KeptLogits {
