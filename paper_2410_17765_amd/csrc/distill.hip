@@ -280,18 +280,15 @@ struct EpiDistillStats {
     }
 };
 
-// Third product (backward): dz = c1 P - c3 p^c rho + c2 1[v = x] in bf16, row-major and transposed.
+// Third product (backward): dz = c1 P - c3 p^c rho + c2 1[v = x] in bf16, stored block by block (blocked64_index).
 template <int R>
 struct EpiDzDistill {
     bf16_t *dZ;
     long ldz;
-    bf16_t *dZt;             // or null
-    long ldzt;
     const float4 *rowinfo;   // chunk-relative [Mc] {lse, log qhat, c1, c2} (upstream gradient folded in)
     const float4 *grp;       // chunk-relative [Mc / R] {tlse, c3, target as int bits, -}
     const bf16_t *TZ;        // chunk-relative [Mc / R, V]; Mc / R * V < 2^31
-    int Mc, Mcp, V, Vp;
-    int blocked;             // dZ is stored block by block (blocked64_index)
+    int Mc, Mcp, V, Vp;      // the rows from Mc up to Mcp are zeroed
     template <class C>
     __device__ void run(f32x4_t (&acc)[C::TM16][C::TN16], int row0, int col0, int lane, int wave, int, char *smem) const
     {
@@ -303,7 +300,7 @@ struct EpiDzDistill {
         // load each, one row per thread, and are parked in the last BM * 32 bytes of the LDS buffer, beyond every
         // staging area of the stores below: loaded where they are used, they were a chain of exposed cache misses.
         static_assert(C::THREADS >= C::BM, "one row per thread");
-        static_assert(C::WM * C::WN * C::WTN * (64 * 2 + 16) <= C::LDS_BYTES - C::BM * 32, "row values beyond the staging areas");
+        static_assert(C::WM * C::WN * 32 * (C::WTN * 2 + 16) <= C::LDS_BYTES - C::BM * 32, "row values beyond the staging areas");
         float4 *linfo = reinterpret_cast<float4 *>(smem + C::LDS_BYTES - C::BM * 32), *lgrp = linfo + C::BM;
         {
             const int trow = row0 - (wave / C::WN) * C::WTM + (int)threadIdx.x;   // this thread's row of the tile
@@ -320,12 +317,10 @@ struct EpiDzDistill {
         // 64 rows at a time: turn their logits into gradients and write them out at once, so that the
         // finished values do not stay in registers
         convert<C, RG, NG, 0>(acc, row0, col0, lane, winfo, wgrp);
-        store_tile_bf16<C, decltype(dz), 0, 2>(smem, wave, lane, row0, col0, Mc, Vp, dZ, ldz, dz, blocked != 0);
-        if (dZt) store_tile_bf16_transposed<C, decltype(dz), 0, 1>(smem, wave, lane, row0, col0, Mcp, V, dZt, ldzt, dz);
+        store_tile_bf16<C, decltype(dz), 0, 2>(smem, wave, lane, row0, col0, Mcp, Vp, dZ, ldz, dz);
         if (C::WTM > 64) {
             convert<C, RG, NG, 1>(acc, row0, col0, lane, winfo, wgrp);
-            store_tile_bf16<C, decltype(dz), 2, 4>(smem, wave, lane, row0, col0, Mc, Vp, dZ, ldz, dz, blocked != 0);
-            if (dZt) store_tile_bf16_transposed<C, decltype(dz), 1, 2>(smem, wave, lane, row0, col0, Mcp, V, dZt, ldzt, dz);
+            store_tile_bf16<C, decltype(dz), 2, 4>(smem, wave, lane, row0, col0, Mcp, Vp, dZ, ldz, dz);
         }
     }
 
@@ -601,13 +596,11 @@ struct DistillDzArgs {
     int d, V, r;
 };
 template <int R>
-void distill_dz_launch(void *user, const bf16_t *Yc, int Mc, int Mcp, size_t m0, bf16_t *dZ, long ldz, bool dz_blocked,
-                       bf16_t *dZt, long ldzt, hipStream_t st)
+void distill_dz_launch(void *user, const bf16_t *Yc, int Mc, int Mcp, size_t m0, bf16_t *dZ, int Vp, hipStream_t st)
 {
     const DistillDzArgs *a = static_cast<const DistillDzArgs *>(user);
     launch_gemm_nt<Cfg>("distill_gemm_z_dz", Yc, a->d, Mc, a->U, a->d, a->V, a->d,
-                        EpiDzDistill<R>{dZ, ldz, dZt, ldzt, a->rowinfo + m0, a->grp + m0 / R, a->TZ + (m0 / R) * a->V, Mc, Mcp,
-                                        a->V, (int)ldz, dz_blocked ? 1 : 0},
+                        EpiDzDistill<R>{dZ, (long)Vp, a->rowinfo + m0, a->grp + m0 / R, a->TZ + (m0 / R) * a->V, Mc, Mcp, a->V, Vp},
                         st);
 }
 
@@ -628,12 +621,11 @@ struct DistillKeptArgs {
     int V;
 };
 template <int R>
-void distill_kept_dz_launch(void *user, const bf16_t *, int Mc, int Mcp, size_t m0, bf16_t *dZ, long ldz, bool dz_blocked,
-                            bf16_t *dZt, long ldzt, hipStream_t st)
+void distill_kept_dz_launch(void *user, const bf16_t *, int Mc, int Mcp, size_t m0, bf16_t *dZ, int Vp, hipStream_t st)
 {
     const DistillKeptArgs *a = static_cast<const DistillKeptArgs *>(user);
     launch_dz_from_kept(a->kept, m0, a->rowinfo + m0, DistillDzRule<R>{a->grp + m0 / R, a->TZ + (m0 / R) * a->V}, Mc, Mcp,
-                        a->V, dZ, ldz, dz_blocked, dZt, ldzt, st);
+                        a->V, dZ, Vp, st);
 }
 
 int mfma_distill_fwd(const cp_head_desc &ds, const void *H, const void *W, const void *Uv, const void *G,

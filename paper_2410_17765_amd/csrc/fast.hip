@@ -19,13 +19,14 @@ namespace cph {
 namespace {
 
 typedef TileCfg<256, 256, 2, 2> Cfg;
-// the same tile with the second, or both, operands K-major (the contraction index is their slow one)
-typedef TileCfg<256, 256, 2, 2, false, true> CfgNN;
+// the same tile with both operands K-major (the contraction index is their slow one)
 typedef TileCfg<256, 256, 2, 2, true, true> CfgTN;
 // A stored in blocks of 256 rows x 64 columns (the chunk's logit gradients as the dY product reads them)
 typedef TileCfg<256, 256, 2, 2, false, false, true> CfgBlockedA;
-// four rows of a column per lane
-typedef TileCfg<256, 256, 2, 2, false, false, false, true> CfgRows;
+// the same operand beside a K-major one (full heads: dH = dz F_sa)
+typedef TileCfg<256, 256, 2, 2, false, true, true> CfgBlockedANN;
+// and as the dU product reads it, K-major: the rows of dz are what it contracts over
+typedef TileCfg<256, 256, 2, 2, true, false, true> CfgBlockedTN;
 constexpr int kBlock = 256;
 
 
@@ -162,6 +163,7 @@ struct EpiRowStatsKeep {
     uint16_t *zs;   // [M, ldzs]
     long ldzs;
     int Vp;         // columns of zs that are written (V rounded up to 64; those from V on hold junk)
+    int streamed;   // written past the caches
     template <class C>
     __device__ void run(f32x4_t (&acc)[C::TM16][C::TN16], int row0, int col0, int lane, int wave, int tn, char *) const
     {
@@ -184,7 +186,7 @@ struct EpiRowStatsKeep {
                 }
                 w[j] = make_uint2(f32x2_to_f16x2(z[0], z[1]), f32x2_to_f16x2(z[2], z[3]));
             }
-            out.put(i, w);
+            out.put(i, w, streamed != 0);
             const float sum = groups_sum((s[0] + s[1]) + (s[2] + s[3]));
             const int r = row0 + acc_row(i, lane);
             if (lane < 16 && r < M) part[(size_t)r * parts + slot] = make_float2(mx, (mx == -INFINITY) ? 0.f : sum);
@@ -193,99 +195,59 @@ struct EpiRowStatsKeep {
     }
 };
 
-// Softmax gradient (derivative of eq. 8/9 with respect to the logits), written in bf16:
-//   dz[m, v] = coef[m] * (exp(z - lse[m]) - 1[v = x_m]),  zero in the padding columns V..Vp-1;
-// optionally also transposed (dzT[v, m], rows of the chunk padded with zeros up to Mcp), which is the
-// operand layout of the dU product.
+// Softmax gradient (derivative of eq. 8/9 with respect to the logits), written in bf16, block by block (blocked64_index):
+//   dz[m, v] = coef[m] * (exp(z - lse[m]) - 1[v = x_m]),  zero in the padding columns V..Vp-1 and the rows Mc..Mcp-1.
+// One copy serves both products that read it: dY takes it as it lies and dU K-major (a second, transposed copy for dU
+// was a third of this kernel's epilogue and of the HBM traffic of k_dz_from_kept, and more than the K-major loop costs).
 struct EpiDz {
-    bf16_t *dZ;          // [Mc, Vp] for the chunk
+    bf16_t *dZ;
     long ldz;
-    bf16_t *dZt;         // [V, Mcp] or null
-    long ldzt;
     const float4 *rowinfo;   // chunk-relative: {lse, coef (zero for dropped factors), target as int bits, -}
     int Mc, Mcp, V, Vp;
-    int blocked;             // dZ is stored block by block (blocked64_index)
+    int streamed;            // written past the caches
     template <class C>
-    __device__ void run(f32x4_t (&acc)[C::TM16][C::TN16], int row0, int col0, int lane, int wave, int, char *smem) const
+    __device__ void run(f32x4_t (&acc)[C::TM16][C::TN16], int row0, int col0, int lane, int, int, char *) const
     {
-        static_assert(C::WTM == 64 || C::WTM == 128, "sub-tiles of 64 or 128 rows");
-        static_assert(C::WM * C::WN * C::WTN * (64 * 2 + 16) <= C::LDS_BYTES - C::BM * 16, "row values beyond the staging areas");
-        // The row values of the tile's BM rows come in with one coalesced load, one row per thread, and are parked
-        // in the last BM * 16 bytes of the LDS buffer, beyond every staging area of the stores below: loaded where
-        // they are used, they were a chain of sixteen exposed cache misses per tile.
-        static_assert(C::THREADS >= C::BM, "one row per thread");
-        float4 *linfo = reinterpret_cast<float4 *>(smem + C::LDS_BYTES - C::BM * 16);
-        const int trow = row0 - (wave / C::WN) * C::WTM + (int)threadIdx.x;       // this thread's row of the tile
-        const float4 mine = rowinfo[trow < Mc ? trow : Mc - 1];
-        __syncthreads();                                    // every wavefront is done reading operand tiles
-        if ((int)threadIdx.x < C::BM) linfo[threadIdx.x] = mine;
-        __syncthreads();
-        const float4 *winfo = linfo + (wave / C::WN) * C::WTM;     // the rows of this wavefront's sub-tile
-        // after convert() the even accumulator of a pair of rows holds both gradients as two bf16
-        auto dz = [&](int i, int j, int v, int, int) {
-            const uint32_t pk = __float_as_uint(acc[i][j][v & ~1]);
-            return (bf16_t)((v & 1) ? (pk >> 16) : (pk & 0xFFFFu));
-        };
-        // 64 rows at a time: turn their logits into gradients in place and write them out at once, so that
-        // the finished values do not stay in registers
-        convert<C, 0>(acc, row0, col0, lane, winfo);
-        store_tile_bf16<C, decltype(dz), 0, 2>(smem, wave, lane, row0, col0, Mc, Vp, dZ, ldz, dz, blocked != 0);
-        if (dZt) store_tile_bf16_transposed<C, decltype(dz), 0, 1>(smem, wave, lane, row0, col0, Mcp, V, dZt, ldzt, dz);
-        if (C::WTM > 64) {
-            convert<C, 1>(acc, row0, col0, lane, winfo);
-            store_tile_bf16<C, decltype(dz), 2, 4>(smem, wave, lane, row0, col0, Mc, Vp, dZ, ldz, dz, blocked != 0);
-            if (dZt) store_tile_bf16_transposed<C, decltype(dz), 1, 2>(smem, wave, lane, row0, col0, Mcp, V, dZt, ldzt, dz);
-        }
-    }
-
-    // Logits -> gradients for the 16-row blocks 4 IP .. 4 IP + 3, two consecutive rows at a time; the pair
-    // is rounded to bf16 by one conversion and kept in the even row's accumulator.  The one-hot term touches
-    // one element of a row, so it is a branch that a wavefront takes only where a target falls into its
-    // columns.
-    template <class C, int IP>
-    __device__ __forceinline__ void convert(f32x4_t (&acc)[C::TM16][C::TN16], int row0, int col0, int lane,
-                                            const float4 *winfo) const
-    {
-        const int lcol = col0 + (lane & 15);
-        const bool ragged = col0 + 16 * C::TN16 > V;     // the same for the whole wavefront
+        // the values of the lane's eight rows in one go: loaded where they are used they were a chain of exposed cache misses
+        float4 info[C::TM16];
 #pragma unroll
-        for (int i = 4 * IP; i < 4 * IP + 4; ++i) {
+        for (int i = 0; i < C::TM16; ++i) info[i] = rowinfo[min(row0 + acc_row(i, lane), Mc - 1)];
 #pragma unroll
-            for (int v = 0; v < 4; v += 2) {
-                const int lrow = acc_row_of_lane(i, v, lane);                // rows lrow and lrow + 1 of the sub-tile
-                const int row = row0 + lrow;
-                const float4 ra = winfo[lrow];                       // rows past the chunk hold the last row's values
-                const float4 rb = winfo[lrow + 1];
-                // rows past the chunk hold zero logits: coefficient 0 and offset 0 keep their product finite
-                const float cfa = row < Mc ? ra.y : 0.f, cfb = row + 1 < Mc ? rb.y : 0.f;
-                const float la = row < Mc ? ra.x : 0.f, lb = row + 1 < Mc ? rb.x : 0.f;
-                float ga[C::TN16], gb[C::TN16];
+        for (int i = 0; i < C::TM16; ++i) asm volatile("" : "+v"(info[i].x), "+v"(info[i].y), "+v"(info[i].z));
+        const RowsOut16<C, true> out(lane, row0, col0, Mcp, Vp, dZ, ldz);
+        const int lcol = col0 + acc_col(0, 0, lane);
+        const bool ragged = col0 + C::WTN > V;           // the same for the whole wavefront
 #pragma unroll
-                for (int j = 0; j < C::TN16; ++j) {
-                    // z - lse first: exact where the logit is close to the log-normaliser (p close to 1)
-                    ga[j] = cfa * __builtin_amdgcn_exp2f((acc[i][j][v] - la) * kLog2e);
-                    gb[j] = cfb * __builtin_amdgcn_exp2f((acc[i][j][v + 1] - lb) * kLog2e);
-                }
-                const int xa = __float_as_int(ra.z) - lcol, xb = __float_as_int(rb.z) - lcol;   // 16 j at the target
-                const bool ha = (xa & 15) == 0 && (unsigned)xa < 16u * C::TN16;
-                const bool hb = (xb & 15) == 0 && (unsigned)xb < 16u * C::TN16;
-                if (ha || hb) {
+        for (int i = 0; i < C::TM16; ++i) {
+            // rows past the chunk hold zero logits: coefficient 0 and offset 0 keep their product finite
+            const bool in = row0 + acc_row(i, lane) < Mc;
+            const float cf = in ? info[i].y : 0.f, lse = in ? info[i].x : 0.f;
+            float g[C::TN16][4];
 #pragma unroll
-                    for (int j = 0; j < C::TN16; ++j) {
-                        if (ha && xa == 16 * j) ga[j] -= cfa;
-                        if (hb && xb == 16 * j) gb[j] -= cfb;
-                    }
-                }
-                if (ragged) {
+            for (int j = 0; j < C::TN16; ++j)
 #pragma unroll
-                    for (int j = 0; j < C::TN16; ++j)
-                        if (lcol + 16 * j >= V) { ga[j] = 0.f; gb[j] = 0.f; }
-                }
+                for (int v = 0; v < 4; ++v)     // z - lse first: exact where the logit is close to the log-normaliser (p close to 1)
+                    g[j][v] = cf * __builtin_amdgcn_exp2f((acc[i][j][v] - lse) * kLog2e);
+            // the one-hot term touches one element of a row: a branch that a wavefront takes only where a target falls into
+            // its columns
+            const int x = __float_as_int(info[i].z) - lcol;             // 16 j + v at the target
+            if ((unsigned)x < 16u * C::TN16 && (x & 15) < 4) {
 #pragma unroll
-                for (int j = 0; j < C::TN16; ++j) acc[i][j][v] = __uint_as_float(f32x2_to_bf16x2(ga[j], gb[j]));
+                for (int j = 0; j < C::TN16; ++j)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) g[j][v] -= x == 16 * j + v ? cf : 0.f;
             }
-            // keeps the per-row loads of the next block from being hoisted (they would spill registers)
-            asm volatile("" ::: "memory");
+            if (ragged) {
+#pragma unroll
+                for (int j = 0; j < C::TN16; ++j)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) g[j][v] = lcol + 16 * j + v < V ? g[j][v] : 0.f;
+            }
+            uint2 w[C::TN16];
+#pragma unroll
+            for (int j = 0; j < C::TN16; ++j) w[j] = make_uint2(f32x2_to_bf16x2(g[j][0], g[j][1]), f32x2_to_bf16x2(g[j][2], g[j][3]));
+            out.put(i, w, streamed != 0);
+            __builtin_amdgcn_sched_barrier(0);
         }
     }
 };
@@ -1075,14 +1037,14 @@ inline void need_below_dz(const cp_head_desc &ds, size_t chunk, SplitNeed &need)
     const size_t T = (size_t)ds.T, d = (size_t)ds.d, V = (size_t)ds.V, nrd = (size_t)ds.n * ds.r * d;
     SplitNeed::chunks(T * ds.n * ds.r, chunk, [&](size_t Mc) {
         if (split_dy(ds)) need.product<CfgBlockedA>(Mc, d, round_up(V, 64));         // dY
-        need.product<Cfg>(V, d, round_up(Mc, 64));                                   // dU
+        need.product<CfgBlockedTN>(V, d, round_up(Mc, 64));                          // dU
     });
     need.product<Cfg>(T, d, nrd);                                                    // dH
     need.product<CfgTN>(nrd, d, T);                                                  // dW
 }
 
 struct BwdWs {
-    size_t coef, dg, dGpart, Ut, Wt, dY, dZ, dZt, Yt, split, split_bytes, total;
+    size_t coef, dg, dGpart, Ut, Wt, dY, dZ, Yt, split, split_bytes, total;
     size_t Vp, chunk, chunk_p;
     size_t ldV, ldM, ldN;   // leading dimensions of the transposed operands (K padded to 64, plus 64)
 };
@@ -1103,7 +1065,6 @@ inline BwdWs bwd_ws(const cp_head_desc &ds)
     b.Wt = take((size_t)ds.d * b.ldN * 2);
     b.dY = take(M * ds.d * 2);
     b.dZ = take(round_up(b.chunk, 256) * b.Vp * 2);   // stored in blocks of 256 rows x 64 columns
-    b.dZt = take((size_t)ds.V * b.ldM * 2);
     b.Yt = take((size_t)ds.d * b.ldM * 2);
     SplitNeed need(ds);
     need_below_dz(ds, b.chunk, need);
@@ -1171,9 +1132,9 @@ inline size_t full_chunk_rows(const cp_head_desc &ds)
 }
 
 struct FullBwdWs {
-    size_t coef, dg, dGpart, Ht, dZ, dZt, split, split_bytes, total;
-    size_t Vp, Tp, chunk, chunk_p;
-    size_t ldT, ldM;
+    size_t coef, dg, dGpart, Ht, dZ, split, split_bytes, total;
+    size_t Vp, Tp, chunk;
+    size_t ldT;
 };
 inline FullBwdWs full_bwd_ws(const cp_head_desc &ds)
 {
@@ -1182,20 +1143,18 @@ inline FullBwdWs full_bwd_ws(const cp_head_desc &ds)
     b.Vp = round_up((size_t)ds.V, 64);
     b.Tp = round_up(T, 64);
     b.chunk = full_chunk_rows(ds);
-    b.chunk_p = round_up(b.chunk, 64);
-    b.ldT = b.Tp + 64; b.ldM = b.chunk_p + 64;
+    b.ldT = b.Tp + 64;
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes); return o; };
     b.coef = take(M * 16);
     b.dg = take(T * ds.r * 4);
     b.dGpart = take(gate_chunks(T) * ds.r * ds.d * 4);
     b.Ht = take((size_t)ds.d * b.ldT * 2);
-    b.dZ = take(b.chunk * b.Vp * 2);
-    b.dZt = take((size_t)ds.V * b.ldM * 2);
+    b.dZ = take(round_up(b.chunk, 256) * b.Vp * 2);   // stored in blocks of 256 rows x 64 columns
     SplitNeed need(ds);
     SplitNeed::chunks(T, b.chunk, [&](size_t Tc) {
-        need.product<CfgNN>(Tc, (size_t)ds.d, b.Vp);                                 // dH
-        need.product<Cfg>((size_t)ds.V, (size_t)ds.d, round_up(Tc, 64));             // dF
+        need.product<CfgBlockedANN>(Tc, (size_t)ds.d, b.Vp);                         // dH
+        need.product<CfgBlockedTN>((size_t)ds.V, (size_t)ds.d, round_up(Tc, 64));    // dF
     });
     b.split_bytes = need.bytes;
     b.split = take(need.bytes);
@@ -1391,7 +1350,8 @@ int fast_fwd_rows(const cp_head_desc &ds, const void *Hv, const void *Wv, const 
                         NoSideJob{0}, -1, -1, split_scratch(ws, f.split, f.split_bytes));                       // y = W_sa h
     if (cl.keep)                                                                               // z = U y, statistics, z kept
         launch_gemm_nt<Cfg>("gemm_z_stats_keep", Y, d, (int)M, U, d, V, d,
-                            EpiRowStatsKeep{part, f.parts, (int)M, V, at<uint16_t>(ctx, cl.zs), (long)cl.Vp, (int)cl.Vp}, st);
+                            EpiRowStatsKeep{part, f.parts, (int)M, V, at<uint16_t>(ctx, cl.zs), (long)cl.Vp, (int)cl.Vp,
+                                            streamed_store(M * cl.Vp * 2)}, st);
     else
         launch_gemm_nt<Cfg>("gemm_z_stats", Y, d, (int)M, U, d, V, d, EpiRowStats{part, f.parts, (int)M, V}, st);  // z = U y, statistics
     k_row_finish<<<blocks_for(M, kBlock / kWave), kBlock, 0, st>>>(M, d, ds.r, f.parts, part, Y, Ylo, U, X, lse, C);
@@ -1414,11 +1374,9 @@ int fast_loss_fwd(const cp_head_desc &ds, const void *Hv, const void *Wv, const 
 // contraction index is its slow one) with gfx950's transposing LDS read, which needs no transposed copy of anything
 // but costs the loop 4-5 % per K-major operand (two 64-bit reads per fragment instead of one 128-bit read: twice the
 // LDS instructions and LDS busy time for the same bytes; measured at the headline size: dY 97.3 -> 101.2 ms per step
-// with U K-major, dU 99.6 -> 109.9 with dz and Y K-major, dH 12.5 -> 13.0, dW 12.7 -> 13.7).  A transposed copy is
-// an HBM-bound pass that costs less than that wherever the product is vocabulary-sized (dz^T from the dz epilogue 5.3
-// ms per step, Y^T 2.7, U^T 0.1, W^T 0.5), so those products keep the K-contiguous form; dW = dY^T H is the one
-// whose transposed copies (4.3 GB of dY: 1.8 ms) cost more than its K-major loop (1.0 ms), and they were 4.3 GB of
-// workspace.
+// with U K-major, dH 12.5 -> 13.0, dW 12.7 -> 13.7).  U^T, W^T and Y^T are copies: those cost less than the loop does
+// (0.1, 0.5 and 1.6 ms).  dz, which dY reads as rows and dU as columns, is read K-major by dU, and so are both operands of
+// dW = dY^T H: a transposed copy of a logit-sized or row-sized buffer costs more than the loop.
 
 // The backward pass below dY: dH = dY W + G^T dg, dW = dY^T H, dG = dg^T H.  Wt: scratch for W^T [d, n r d + 64];
 // dGpart: the partial sums of the two-stage gate gradient.
@@ -1442,12 +1400,11 @@ static int bwd_below_dy(const cp_head_desc &ds, const bf16_t *H, const bf16_t *W
     return hipGetLastError() == hipSuccess ? CP_HEAD_OK : CP_HEAD_ERR_LAUNCH;
 }
 
-// dY = dz U and dU (+)= dz^T Y for one chunk of head rows whose dz (and, if dU is wanted, dz^T) is in place.
+// dY = dz U and dU (+)= dz^T Y for one chunk of head rows whose dz is in place.
 // dZ is stored block by block (blocked64_index, ld = Vp): its rows are 2 Vp bytes apart otherwise, a tile's K-step
 // touches 256 separate cache lines of it, and the product, which streams the chunk's 4 GiB of it from HBM, runs 4 %
 // slower.  Ut: U^T [d, Vp + 64]; Yt: scratch for the chunk's Y^T [d, Mcp + 64].
-static void bwd_chunk_products(const cp_head_desc &ds, const bf16_t *dZ, const bf16_t *dZt, long ldM, const bf16_t *Yc,
-                               int Mc, const bf16_t *Ut, bf16_t *Yt, bf16_t *dYc, float *dU, bool accumulate,
+static void bwd_chunk_products(const cp_head_desc &ds, const bf16_t *dZ, long ldM, const bf16_t *Yc, int Mc, const bf16_t *Ut, bf16_t *Yt, bf16_t *dYc, float *dU, bool accumulate,
                                const SplitScratch &split, hipStream_t st)
 {
     const int d = ds.d, V = ds.V;
@@ -1459,13 +1416,13 @@ static void bwd_chunk_products(const cp_head_desc &ds, const bf16_t *dZ, const b
     if (dU) {
         // dU += dz^T Y   (contraction over the rows of the chunk)
         transpose_bf16(Yc, d, Mc, d, Yt, ldM, Mcp, st);               // Yt[d, Mcp]
-        launch_gemm_nt<Cfg>("gemm_du", dZt, ldM, V, Yt, ldM, d, Mcp, EpiStoreF32{dU, (long)d, V, d, accumulate ? 1 : 0}, st,
+        launch_gemm_nt<CfgBlockedTN>("gemm_du", dZ, Vp, V, Yt, ldM, d, Mcp, EpiStoreF32{dU, (long)d, V, d, accumulate ? 1 : 0}, st,
                             kGroupRowsNarrow, NoSideJob{0}, -1, -1, split);
     }
 }
 
 // The backward pass below the logit gradients: per bounded chunk of head rows `dz_launch` writes dz
-// (bf16, row-major and, if dU is wanted, transposed), then dY = dz U and dU += dz^T Y; afterwards
+// (bf16), then dY = dz U and dU += dz^T Y; afterwards
 // dW = dY^T H, dH = dY W + G^T dg and dG = dg^T H.  dg[T,r] must already hold the gate gradients.
 int fast_bwd_from_dz(const cp_head_desc &ds, const void *Hv, const void *Wv, const void *Uv, const void *Gv,
                      const void *Yv, const float *dg, float *dH, float *dW, float *dU, float *dG, void *ws,
@@ -1477,7 +1434,7 @@ int fast_bwd_from_dz(const cp_head_desc &ds, const void *Hv, const void *Wv, con
     const BwdWs b = bwd_ws(ds);
     const size_t T = (size_t)ds.T, M = T * n * r;
     bf16_t *Ut = at<bf16_t>(ws, b.Ut), *Wt = at<bf16_t>(ws, b.Wt), *dY = at<bf16_t>(ws, b.dY);
-    bf16_t *dZ = at<bf16_t>(ws, b.dZ), *dZt = at<bf16_t>(ws, b.dZt), *Yt = at<bf16_t>(ws, b.Yt);
+    bf16_t *dZ = at<bf16_t>(ws, b.dZ), *Yt = at<bf16_t>(ws, b.Yt);
     const int Vp = (int)b.Vp;
     const SplitScratch split = split_scratch(ws, b.split, b.split_bytes);
 
@@ -1489,8 +1446,8 @@ int fast_bwd_from_dz(const cp_head_desc &ds, const void *Hv, const void *Wv, con
         const bf16_t *Yc = Y + m0 * d;
         // recompute z for the chunk; the epilogue turns it into dz (bf16); the tiles over V also
         // cover the padding columns V..Vp-1, which the epilogue zero-fills
-        dz_launch(user, Yc, Mc, Mcp, m0, dZ, (long)Vp, true, dU ? dZt : nullptr, (long)b.ldM, st);
-        bwd_chunk_products(ds, dZ, dZt, (long)b.ldM, Yc, Mc, Ut, Yt, dY + m0 * d, dU, !first, split, st);
+        dz_launch(user, Yc, Mc, Mcp, m0, dZ, Vp, st);
+        bwd_chunk_products(ds, dZ, (long)b.ldM, Yc, Mc, Ut, Yt, dY + m0 * d, dU, !first, split, st);
         first = 0;
     }
     return bwd_below_dy(ds, H, W, G, dY, dg, dH, dW, dG, Wt, at<float>(ws, b.dGpart), split, st);
@@ -1505,12 +1462,11 @@ struct LossDzArgs {
     int d, V;
 };
 // dz of the training loss: dz[m, v] = coef[m] (exp(z - lse[m]) - 1[v = x_m])
-void loss_dz_launch(void *user, const bf16_t *Yc, int Mc, int Mcp, size_t m0, bf16_t *dZ, long ldz, bool dz_blocked,
-                    bf16_t *dZt, long ldzt, hipStream_t st)
+void loss_dz_launch(void *user, const bf16_t *Yc, int Mc, int Mcp, size_t m0, bf16_t *dZ, int Vp, hipStream_t st)
 {
     const LossDzArgs *a = static_cast<const LossDzArgs *>(user);
-    launch_gemm_nt<CfgRows>("gemm_z_dz", Yc, a->d, Mc, a->U, a->d, a->V, a->d,
-                        EpiDz{dZ, ldz, dZt, ldzt, a->rowinfo + m0, Mc, Mcp, a->V, (int)ldz, dz_blocked ? 1 : 0}, st);
+    launch_gemm_nt<Cfg>("gemm_z_dz", Yc, a->d, Mc, a->U, a->d, a->V, a->d,
+                        EpiDz{dZ, (long)Vp, a->rowinfo + m0, Mc, Mcp, a->V, Vp, streamed_store((size_t)Mc * Vp * 2)}, st);
 }
 
 struct KeptDzArgs {
@@ -1519,11 +1475,10 @@ struct KeptDzArgs {
     int V;
 };
 // the same dz from the logits kept by the forward pass
-void kept_dz_launch(void *user, const bf16_t *, int Mc, int Mcp, size_t m0, bf16_t *dZ, long ldz, bool dz_blocked,
-                    bf16_t *dZt, long ldzt, hipStream_t st)
+void kept_dz_launch(void *user, const bf16_t *, int Mc, int Mcp, size_t m0, bf16_t *dZ, int Vp, hipStream_t st)
 {
     const KeptDzArgs *a = static_cast<const KeptDzArgs *>(user);
-    launch_dz_from_kept(a->kept, m0, a->rowinfo + m0, LossDzRule{}, Mc, Mcp, a->V, dZ, ldz, dz_blocked, dZt, ldzt, st);
+    launch_dz_from_kept(a->kept, m0, a->rowinfo + m0, LossDzRule{}, Mc, Mcp, a->V, dZ, Vp, st);
 }
 }  // namespace
 
@@ -1561,7 +1516,7 @@ int fast_loss_bwd(const cp_head_desc &ds, const void *Hv, const void *Wv, const 
 
 // Positions per chunk: whole positions whose head rows fit the backward pass's bound on logit-sized buffers.
 struct StepWs {
-    size_t logw, w, gamma, dg, dGpart, Ut, Wt, dY, C, lse, coef, Yc, Ylo, part, zs, dZ, dZt, Yt, split, split_bytes, total;
+    size_t logw, w, gamma, dg, dGpart, Ut, Wt, dY, C, lse, coef, Yc, Ylo, part, zs, dZ, Yt, split, split_bytes, total;
     size_t Vp, pos, rows, ldM;
     int parts;
 };
@@ -1594,7 +1549,6 @@ inline StepWs step_ws(const cp_head_desc &ds)
     f.part = take(f.rows * f.parts * sizeof(float2));
     f.zs = take(f.rows * f.Vp * 2);
     f.dZ = take(round_up(f.rows, 256) * f.Vp * 2);   // stored in blocks of 256 rows x 64 columns
-    f.dZt = take((size_t)ds.V * f.ldM * 2);
     f.Yt = take((size_t)ds.d * f.ldM * 2);
     SplitNeed need(ds);
     if (split_y(ds)) need.product<Cfg>(T, nrd, (size_t)ds.d);                        // y
@@ -1633,7 +1587,7 @@ int fast_loss_step(const cp_head_desc &ds, const void *Hv, const void *Wv, const
     const int Vp = (int)f.Vp;
     const SplitScratch split = split_scratch(ws, f.split, f.split_bytes);
 
-    bf16_t *Ut = at<bf16_t>(ws, f.Ut), *dZt = at<bf16_t>(ws, f.dZt), *Yt = at<bf16_t>(ws, f.Yt);
+    bf16_t *Ut = at<bf16_t>(ws, f.Ut), *Yt = at<bf16_t>(ws, f.Yt);
     launch_gate_bf16(ds, (const bf16_t *)Hv, (const bf16_t *)Gv, logw, w, st);                                                             // eq. 7, all positions
     transpose_bf16(U, d, V, d, Ut, (long)f.Vp + 64, Vp, st);                                          // Ut[d, Vp]
     int first = 1;
@@ -1647,16 +1601,16 @@ int fast_loss_step(const cp_head_desc &ds, const void *Hv, const void *Wv, const
         // forward of the chunk: y, statistics of z with the logits kept, log-normalisers and C (eq. 5, 8), mixture (eq. 9)
         launch_gemm_nt<Cfg>("gemm_y", H + t0 * d, d, (int)P, W, d, (int)nrd, d, EpiStoreBf16{Yc, Ylo, (long)nrd, (int)P, (int)nrd}, st,
                             kGroupRowsNarrow, NoSideJob{0}, -1, -1, split_y(ds) ? split : SplitScratch());
-        launch_gemm_nt<Cfg>("gemm_z_stats_keep", Yc, d, Mc, U, d, V, d, EpiRowStatsKeep{part, f.parts, Mc, V, zs, (long)Vp, Vp}, st);
+        launch_gemm_nt<Cfg>("gemm_z_stats_keep", Yc, d, Mc, U, d, V, d, EpiRowStatsKeep{part, f.parts, Mc, V, zs, (long)Vp, Vp, streamed_store((size_t)Mc * Vp * 2)},
+                            st);
         k_row_finish<<<blocks_for((size_t)Mc, kBlock / kWave), kBlock, 0, st>>>((size_t)Mc, d, r, f.parts, part, Yc, Ylo, U, Xc, lse, C);
         launch_mixture(sub, logw + t0 * r, C, loss + t0, gamma + t0 * r, -1.f, st);
         // backward of the chunk down to dY and dU
         k_bwd_coefficients<<<blocks_for((size_t)Mc, kBlock), kBlock, 0, st>>>((size_t)Mc, n, r, w + t0 * r, gamma + t0 * r, lse,
                                                                             dloss ? dloss + t0 : nullptr, scale, Xc, rowinfo,
                                                                             dg + t0 * r);
-        launch_dz_from_kept(KeptLogits{zs, part, (long)Vp, f.parts}, 0, rowinfo, LossDzRule{}, Mc, Mcp, V, dZ, (long)Vp, true,
-                            dU ? dZt : nullptr, (long)f.ldM, st);
-        bwd_chunk_products(ds, dZ, dZt, (long)f.ldM, Yc, Mc, Ut, Yt, dY + m0 * d, dU, !first, split, st);
+        launch_dz_from_kept(KeptLogits{zs, part, (long)Vp, f.parts}, 0, rowinfo, LossDzRule{}, Mc, Mcp, V, dZ, Vp, st);
+        bwd_chunk_products(ds, dZ, (long)f.ldM, Yc, Mc, Ut, Yt, dY + m0 * d, dU, !first, split, st);
         first = 0;
     }
     return bwd_below_dy(ds, H, W, G, dY, dg, dH, dW, dG, at<bf16_t>(ws, f.Wt), at<float>(ws, f.dGpart), split, st);
@@ -1803,7 +1757,7 @@ int fast_full_loss_fwd(const cp_head_desc &ds, const void *Hv, const void *Fv, c
         if (cl.keep)
             launch_gemm_nt<Cfg>("full_gemm_z_stats_keep", H, d, T, F + (size_t)sa * V * d, d, V, d,
                                 EpiRowStatsKeep{part + (size_t)sa * T * f.parts, f.parts, T, V,
-                                                zs + (size_t)sa * T * cl.Vp, (long)cl.Vp, (int)cl.Vp}, st);
+                                                zs + (size_t)sa * T * cl.Vp, (long)cl.Vp, (int)cl.Vp, streamed_store(M * cl.Vp * 2)}, st);
         else
             launch_gemm_nt<Cfg>("full_gemm_z_stats", H, d, T, F + (size_t)sa * V * d, d, V, d,
                                 EpiRowStats{part + (size_t)sa * T * f.parts, f.parts, T, V}, st);
@@ -1833,9 +1787,9 @@ int fast_full_loss_bwd(const cp_head_desc &ds, const void *Hv, const void *Fv, c
     float4 *rowinfo = at<float4>(ws, b.coef);
     float *dg = at<float>(ws, b.dg);
     bf16_t *Ht = at<bf16_t>(ws, b.Ht);
-    bf16_t *dZ = at<bf16_t>(ws, b.dZ), *dZt = at<bf16_t>(ws, b.dZt);
+    bf16_t *dZ = at<bf16_t>(ws, b.dZ);
     const int Vp = (int)b.Vp, Tp = (int)b.Tp;
-    const long ldT = (long)b.ldT, ldM = (long)b.ldM;
+    const long ldT = (long)b.ldT;
     const SplitScratch split = split_scratch(ws, b.split, b.split_bytes);
 
     k_full_bwd_coefficients<<<blocks_for(M, kBlock), kBlock, 0, st>>>(T, n, r, w, gamma, lse, dloss, scale, X, rowinfo, dg);
@@ -1847,21 +1801,21 @@ int fast_full_loss_bwd(const cp_head_desc &ds, const void *Hv, const void *Fv, c
         const bf16_t *Hc = H + t0 * d;
         for (int sa = 0; sa < nr; ++sa) {
             const bf16_t *Fsa = F + (size_t)sa * V * d;
-            // dz (bf16), also transposed, from the kept logits of these positions, or from z_sa recomputed
+            // dz (bf16) from the kept logits of these positions, or from z_sa recomputed
             if (cl.keep) {
                 KeptDzArgs kept{KeptLogits{at<uint16_t>(ctx, cl.zs), at<float2>(ctx, cl.zpart), (long)cl.Vp, cl.parts}, rowinfo, V};
-                kept_dz_launch(&kept, nullptr, Tc, Tcp, (size_t)sa * T + t0, dZ, (long)Vp, false, dF ? dZt : nullptr, ldM, st);
+                kept_dz_launch(&kept, nullptr, Tc, Tcp, (size_t)sa * T + t0, dZ, Vp, st);
             } else {
-                launch_gemm_nt<CfgRows>("full_gemm_z_dz", Hc, d, Tc, Fsa, d, V, d,
-                                    EpiDz{dZ, (long)Vp, dF ? dZt : nullptr, ldM, rowinfo + (size_t)sa * T + t0, Tc, Tcp, V, Vp, 0}, st);
+                launch_gemm_nt<Cfg>("full_gemm_z_dz", Hc, d, Tc, Fsa, d, V, d,
+                                    EpiDz{dZ, (long)Vp, rowinfo + (size_t)sa * T + t0, Tc, Tcp, V, Vp, streamed_store((size_t)Tc * Vp * 2)}, st);
             }
             // dH += dz F_sa   (contraction over the vocabulary; F_sa as it is stored is K-major for this product, and
             // a transposed copy of every head matrix per chunk would cost more than the K-major loop does)
-            launch_gemm_nt<CfgNN>("full_gemm_dh", dZ, Vp, Tc, Fsa, d, d, Vp,
+            launch_gemm_nt<CfgBlockedANN>("full_gemm_dh", dZ, Vp, Tc, Fsa, d, d, Vp,
                                   EpiStoreF32{dH + t0 * d, (long)d, Tc, d, sa ? 1 : 0}, st, kGroupRowsNarrow, NoSideJob{0}, -1, V, split);
             // dF_sa += dz^T H   (contraction over the positions of the chunk)
             if (dF)
-                launch_gemm_nt<Cfg>("full_gemm_df", dZt, ldM, V, Ht + t0, ldT, d, Tcp,
+                launch_gemm_nt<CfgBlockedTN>("full_gemm_df", dZ, Vp, V, Ht + t0, ldT, d, Tcp,
                                     EpiStoreF32{dF + (size_t)sa * V * d, (long)d, V, d, first_chunk ? 0 : 1}, st,
                                     kGroupRowsNarrow, NoSideJob{0}, -1, -1, split);
         }

@@ -41,7 +41,8 @@ struct GemmOperands {
     const bf16_t *B;   // [N, ldb]
     long lda, ldb;     // elements
     int M, N, K;       // K % 64 == 0 unless both operands are K-major
-    int ka_rows, kb_rows;   // K-major operands: rows that exist (<= K; the rest of K reads as zero)
+    int ka_rows, kb_rows;   // K-major operands: rows that exist (<= K; the rest of K reads as zero); not for a blocked one
+    int ka_tile;       // K-major A stored block by block: the K-tile (of 64 of its rows) that the contraction starts with
     int tiles_m, tiles_n;
     int gm;            // tile rows per group of the workgroup -> tile walk
 };
@@ -61,7 +62,9 @@ template <int BM_, int BN_, int WM_, int WN_, bool AKM_ = false, bool BKM_ = fal
 struct TileCfg {
     static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, BK = 64;
     static constexpr bool AKM = AKM_, BKM = BKM_;     // operand is K-major
-    static constexpr bool ABL = ABL_;                 // A is stored block by block: [rows/256][K/64][256][64]
+    // A is stored block by block, [rows/256][columns/64][256][64] (blocked64_index): its rows are the output's rows, or, if it
+    // is K-major as well, the contraction's
+    static constexpr bool ABL = ABL_;
     // which four neighbouring elements a lane holds of a 16x16 block of the result: one row's columns, or one column's rows
     static constexpr bool ROWS_IN_LANE = ROWS_IN_LANE_;
     static constexpr int THREADS = WM * WN * kWave;
@@ -72,7 +75,6 @@ struct TileCfg {
     static constexpr int A_BYTES = AKM_ ? kKmTileBytes : BM * BK * 2, B_BYTES = BKM_ ? kKmTileBytes : BN * BK * 2;
     static_assert(!(AKM_ || BKM_) || WM_ * WN_ == 4, "K-major operands: four wavefronts");
     static_assert((!AKM_ || BM_ == 256) && (!BKM_ || BN_ == 256), "a K-major tile has 256 columns");
-    static_assert(!(AKM_ && ABL_), "an operand is K-major or blocked, not both");
     static constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
     static constexpr int LDS_BYTES = 2 * STAGE_BYTES;
     static_assert(BM % (WM * 64) == 0 && BN % (WN * 32) == 0, "wave tile must be a multiple of 64 rows x 32 columns");
@@ -189,6 +191,7 @@ __device__ __forceinline__ void gemm_nt_mainloop_direct(const GemmOperands &g, i
         unsigned step;      // bytes from one K-tile to the next
         int full_tiles;     // tiles with all 64 rows
         unsigned full, tail;
+        unsigned step_row;  // blocked: bytes from a row of blocks' last K-tile to the next one's first
     };
     auto km_start = [&](const bf16_t *base, long ld, int col0, int krows) {
         KmWalk w;
@@ -201,6 +204,24 @@ __device__ __forceinline__ void gemm_nt_mainloop_direct(const GemmOperands &g, i
         w.d = make_rsrc_words(base + col0, w.full_tiles > 0 ? w.full : w.tail);
         return w;
     };
+    // A blocked operand: a row of blocks (256 k-rows, all columns) holds four K-tiles, 64 rows of every block each; the
+    // descriptor spans the row of blocks, and the producer of the operand has zeroed the rows up to the contraction's end.
+    auto km_start_blocked = [&](const bf16_t *base, long ld, int tile) {
+        KmWalk w;
+        w.tile = tile;
+        w.step = BK * 128;
+        w.step_row = (unsigned)(ld * 512) - 3 * BK * 128;
+        w.full_tiles = 0x7FFFFFFF;
+        w.full = w.tail = (unsigned)(ld * 512);
+        w.d = make_rsrc_words(base + (size_t)(tile >> 2) * 256 * ld + (size_t)(tile & 3) * BK * 64, w.full);
+        return w;
+    };
+    auto km_advance_blocked = [&](KmWalk &w) {
+        ++w.tile;
+        const unsigned long long at = (((unsigned long long)(unsigned)w.d[1] << 32) | (unsigned)w.d[0]) + ((w.tile & 3) ? w.step : w.step_row);
+        w.d[0] = (int)(unsigned)at;
+        w.d[1] = (int)(unsigned)(at >> 32);
+    };
     auto km_advance = [&](KmWalk &w) {
         const unsigned long long at = (((unsigned long long)(unsigned)w.d[1] << 32) | (unsigned)w.d[0]) + w.step;
         ++w.tile;
@@ -208,7 +229,10 @@ __device__ __forceinline__ void gemm_nt_mainloop_direct(const GemmOperands &g, i
         w.d[1] = (int)(unsigned)(at >> 32);
         w.d[2] = (int)(w.tile < w.full_tiles ? w.full : (w.tile == w.full_tiles ? w.tail : 0u));
     };
-    KmWalk walk_a = km_start(g.A, g.lda, m0, g.ka_rows), walk_b = km_start(g.B, g.ldb, n0, g.kb_rows);
+    constexpr bool kBlockedKm = Cfg::AKM && Cfg::ABL;
+    KmWalk walk_a = kBlockedKm ? km_start_blocked(g.A, g.lda, g.ka_tile) : km_start(g.A, g.lda, m0, g.ka_rows);
+    KmWalk walk_b = km_start(g.B, g.ldb, n0, g.kb_rows);
+    auto advance_a = [&]() { if (kBlockedKm) km_advance_blocked(walk_a); else km_advance(walk_a); };
     constexpr bool kSpelledOut = Cfg::AKM || Cfg::BKM;
     const i32x4_t wa = make_rsrc_words(g.A + (size_t)m0 * g.lda, span_a);
     const i32x4_t wb = make_rsrc_words(g.B + (size_t)n0 * g.ldb, span_b);
@@ -219,11 +243,13 @@ __device__ __forceinline__ void gemm_nt_mainloop_direct(const GemmOperands &g, i
     // K-major: k-row of the pass and first column that this thread fetches (see the layout above)
     const int km_row = (wave >> 1) * 4 + ((lane & 7) >> 1);
     const int km_col = ((wave & 1) * 8 + (lane >> 3)) * 16 + (lane & 1) * 8;
-    const unsigned voff_a = Cfg::AKM ? (unsigned)km_row * (unsigned)g.lda * 2u + km_col * 2u
+    // (blocked: columns past the last block read the last one again, they only reach accumulators that are never stored)
+    const unsigned voff_a = kBlockedKm ? (unsigned)min((m0 + km_col) >> 6, (int)(g.lda >> 6) - 1) * 32768u + (unsigned)km_row * 128u + (km_col & 63) * 2u
+                          : Cfg::AKM ? (unsigned)km_row * (unsigned)g.lda * 2u + km_col * 2u
                                      : (unsigned)lrow * rsa + gchunk * 16u;
     const unsigned voff_b = Cfg::BKM ? (unsigned)km_row * (unsigned)g.ldb * 2u + km_col * 2u
                                      : (unsigned)lrow * rsb + gchunk * 16u;
-    const unsigned pass_a = (unsigned)(Cfg::AKM ? 8 : Cfg::ROWS_PER_PASS) * rsa;
+    const unsigned pass_a = kBlockedKm ? 8u * 128u : (unsigned)(Cfg::AKM ? 8 : Cfg::ROWS_PER_PASS) * rsa;
     const unsigned pass_b = (unsigned)(Cfg::BKM ? 8 : Cfg::ROWS_PER_PASS) * rsb;
     constexpr int lds_pass_a = Cfg::AKM ? kKmPassBytes : Cfg::ROWS_PER_PASS * 128;
     constexpr int lds_pass_b = Cfg::BKM ? kKmPassBytes : Cfg::ROWS_PER_PASS * 128;
@@ -348,7 +374,7 @@ __device__ __forceinline__ void gemm_nt_mainloop_direct(const GemmOperands &g, i
 #pragma unroll
     for (int q = 0; q < NLOAD; ++q) load_one(0, 0, q);
     if (KT > 1) {
-        if (Cfg::AKM) km_advance(walk_a);
+        if (Cfg::AKM) advance_a();
         if (Cfg::BKM) km_advance(walk_b);
 #pragma unroll
         for (int q = 0; q < NEARLY; ++q) load_one(1, 1, q);
@@ -375,7 +401,7 @@ __device__ __forceinline__ void gemm_nt_mainloop_direct(const GemmOperands &g, i
         __builtin_amdgcn_s_waitcnt(0x0F70); /* vmcnt(0): tile kt+1 is complete in the other stage */ \
         __syncthreads();                                                                           \
         if (LOAD_AFTER) { /* the loads from here on are tile kt+2's */                             \
-            if (Cfg::AKM) km_advance(walk_a);                                                      \
+            if (Cfg::AKM) advance_a();                                                      \
             if (Cfg::BKM) km_advance(walk_b);                                                      \
         }                                                                                          \
         CPH_PHASE16(1, 1, 1, reads3, TN + HA, NM, LOAD_AFTER, (KT_) + 2, cur, 0, NEARLY)           \
@@ -473,7 +499,8 @@ __global__ void __launch_bounds__(Cfg::THREADS) k_gemm_nt_split(GemmOperands g, 
         item = bid - split.first;
         split_item(split, item, (g.K + Cfg::BK - 1) / Cfg::BK, bid, part, k0, k1);
         // the operands from K-step k0 on
-        g.A += Cfg::AKM ? (size_t)k0 * Cfg::BK * g.lda : (size_t)k0 * (Cfg::ABL ? Cfg::BM * Cfg::BK : Cfg::BK);
+        if (Cfg::AKM && Cfg::ABL) g.ka_tile += k0;
+        else g.A += Cfg::AKM ? (size_t)k0 * Cfg::BK * g.lda : (size_t)k0 * (Cfg::ABL ? Cfg::BM * Cfg::BK : Cfg::BK);
         g.B += Cfg::BKM ? (size_t)k0 * Cfg::BK * g.ldb : (size_t)k0 * Cfg::BK;
         g.ka_rows = max(g.ka_rows - k0 * Cfg::BK, 0);
         g.kb_rows = max(g.kb_rows - k0 * Cfg::BK, 0);
@@ -553,7 +580,7 @@ inline void launch_gemm_nt(const char *name, const bf16_t *A, long lda, int M, c
     ProfileScope prof(name, 2.0 * (double)M * (double)N * (double)K, st);
     GemmOperands g;
     g.A = A; g.B = B; g.lda = lda; g.ldb = ldb; g.M = M; g.N = N; g.K = K;
-    g.ka_rows = ka_rows < 0 ? K : ka_rows; g.kb_rows = kb_rows < 0 ? K : kb_rows;
+    g.ka_rows = ka_rows < 0 ? K : ka_rows; g.kb_rows = kb_rows < 0 ? K : kb_rows; g.ka_tile = 0;
     g.tiles_m = (M + Cfg::BM - 1) / Cfg::BM;
     g.tiles_n = (N + Cfg::BN - 1) / Cfg::BN;
     g.gm = gm;
@@ -630,8 +657,10 @@ struct RowsOut16 {
         col_limit = cols;
         whole = row0 + Cfg::WTM <= rows && col0 + Cfg::WTN <= cols;
     }
-    // block row i: words[j] are the lane's two words of block (i, j)
-    __device__ __forceinline__ void put(int i, uint2 (&words)[Cfg::TN16]) const
+    // block row i: words[j] are the lane's two words of block (i, j).  streamed (uniform): past the caches, for buffers that
+    // are larger than those: the panels that the tiles in flight share stay in L2 (keep the logits of 22500 x 50257, d = 768:
+    // 2204 -> 2115 us)
+    __device__ __forceinline__ void put(int i, uint2 (&words)[Cfg::TN16], bool streamed = false) const
     {
         u32x4_t val[Cfg::TN16 / 2];
 #pragma unroll
@@ -642,7 +671,10 @@ struct RowsOut16 {
             val[p] = u32x4_t{a.x, a.y, b.x, b.y};
         }
         uint16_t *o = out + i * step;
-        if (whole) {
+        if (whole && streamed) {
+#pragma unroll
+            for (int p = 0; p < Cfg::TN16 / 2; ++p) __builtin_nontemporal_store(val[p], reinterpret_cast<u32x4_t *>(o + place(p)));
+        } else if (whole) {
 #pragma unroll
             for (int p = 0; p < Cfg::TN16 / 2; ++p) *reinterpret_cast<u32x4_t *>(o + place(p)) = val[p];
         } else if (row + 16 * i < row_limit) {
@@ -653,6 +685,9 @@ struct RowsOut16 {
     }
     static __device__ __forceinline__ constexpr int place(int p) { return BLOCKED ? (p >> 1) * 16384 + (p & 1) * 32 : 32 * p; }
 };
+
+// Buffers of this size and more are written past the caches (the last level holds 256 MB)
+inline bool streamed_store(size_t bytes) { return bytes >= ((size_t)256 << 20); }
 
 // Rows of fp32: dst = acc, or dst += acc when `accumulate` is set; 16-byte accesses, 64 consecutive bytes per row.
 // ld and col_limit are multiples of 4.
@@ -695,26 +730,24 @@ __device__ __forceinline__ void store_rows_f32(const f32x4_t (&acc)[Cfg::TM16][C
 // ---------------------------------------------------------------------------------------------
 
 
-// P0, P1 restrict the call to the 32-row passes P0 .. P1-1 (default: all of them).  blocked: dst is stored block by
-// block (blocked64_index) instead of row-major.
+// P0, P1 restrict the call to the 32-row passes P0 .. P1-1 (default: all of them).  dst is stored block by block
+// (blocked64_index).
 template <class Cfg, class F, int P0 = 0, int P1 = Cfg::WTM / 32>
 __device__ __forceinline__ void store_tile_bf16(char *smem, int wave, int lane, int row0, int col0, int row_limit,
-                                                int col_limit /* multiple of 8 */, bf16_t *__restrict__ dst, long ld,
-                                                F value, bool blocked = false)
+                                                int col_limit /* multiple of 8 */, bf16_t *__restrict__ dst, long ld, F value)
 {
     constexpr int RS = Cfg::WTN * 2 + 16;              // padded row stride in bytes
     constexpr int CPR = Cfg::WTN / 8;                   // 16-byte chunks per row
     constexpr int RPP = kWave / CPR;                    // rows per store pass
     static_assert(Cfg::WM * Cfg::WN * 32 * RS <= Cfg::LDS_BYTES, "staging fits");
     char *stage = smem + wave * (32 * RS);
-    // a lane's first output address; every later one is a compile-time multiple of the (uniform) row stride away,
-    // which keeps 64-bit multiplies per store out of the vector unit
-    // (blocked: the rows of one call lie in one block of 256 and an 8-column piece in one block of 64 columns)
+    // a lane's first output address; every later one is a constant number of rows away
+    // (the rows of one call lie in one block of 256 and an 8-column piece in one block of 64 columns)
     static_assert(Cfg::WTM <= 256 && 256 % Cfg::WTM == 0, "a wavefront's rows stay inside a block of 256");
     const size_t first_row = (size_t)(row0 + P0 * 32 + lane / CPR);
     const int first_col = col0 + (lane % CPR) * 8;
-    bf16_t *out = dst + (blocked ? blocked64_index(first_row, first_col, ld) : first_row * ld + first_col);
-    const size_t step = blocked ? (size_t)RPP * 64 : (size_t)RPP * ld;
+    bf16_t *out = dst + blocked64_index(first_row, first_col, ld);
+    constexpr size_t step = (size_t)RPP * 64;
     __syncthreads();                                    // every wavefront is done reading operand tiles
 #pragma unroll
     for (int p = P0; p < P1; ++p) {
@@ -743,64 +776,6 @@ __device__ __forceinline__ void store_tile_bf16(char *smem, int wave, int lane, 
         }
         __syncthreads();
         __builtin_amdgcn_sched_barrier(0);              // conversions of the next pass stay behind this one's stores
-    }
-}
-
-// Transposed bf16 output: dst[col * ld + row] = value(i, j, v, row, col).  A lane owns four consecutive
-// rows of one column per accumulator block, so the sub-tile is laid out column-major in LDS (64 rows at
-// a time, 8-byte writes) and leaves as 16-byte pieces of 128-byte column segments.
-// row_limit and ld are multiples of 8; rows are written up to row_limit, columns up to col_limit.
-// IP0, IP1 restrict the call to the 64-row passes IP0 .. IP1-1 (default: all of them).
-template <class Cfg, class F, int IP0 = 0, int IP1 = Cfg::WTM / 64>
-__device__ __forceinline__ void store_tile_bf16_transposed(char *smem, int wave, int lane, int row0, int col0,
-                                                           int row_limit, int col_limit, bf16_t *__restrict__ dst,
-                                                           long ld, F value)
-{
-    static_assert(Cfg::WTM % 64 == 0, "four 16-row blocks per pass");
-    constexpr int CS = 64 * 2 + 16;                     // padded column stride in bytes (64 rows)
-    static_assert(Cfg::WM * Cfg::WN * Cfg::WTN * CS <= Cfg::LDS_BYTES, "staging fits");
-    char *stage = smem + wave * (Cfg::WTN * CS);
-    bf16_t *const out0 = dst + (size_t)(col0 + (lane >> 3)) * ld + (row0 + (lane & 7) * 8);         // as in store_tile_bf16
-    const size_t step = (size_t)8 * ld;
-    __syncthreads();
-#pragma unroll
-    for (int ip = IP0; ip < IP1; ++ip) {
-#pragma unroll
-        for (int ii = 0; ii < 4; ++ii) {
-            const int i = ip * 4 + ii;
-            const int r = 16 * ii + 4 * (lane >> 4);                 // first of four consecutive rows
-#pragma unroll
-            for (int j = 0; j < Cfg::TN16; ++j) {
-                const int c = j * 16 + (lane & 15);
-                unsigned lo, hi;
-                {
-                    const bf16_t a = value(i, j, 0, row0 + ip * 64 + r + 0, col0 + c);
-                    const bf16_t b = value(i, j, 1, row0 + ip * 64 + r + 1, col0 + c);
-                    lo = (unsigned)a | ((unsigned)b << 16);
-                }
-                {
-                    const bf16_t a = value(i, j, 2, row0 + ip * 64 + r + 2, col0 + c);
-                    const bf16_t b = value(i, j, 3, row0 + ip * 64 + r + 3, col0 + c);
-                    hi = (unsigned)a | ((unsigned)b << 16);
-                }
-                typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));
-                u32x2_t pk = {lo, hi};
-                *reinterpret_cast<u32x2_t *>(stage + c * CS + r * 2) = pk;
-            }
-        }
-        __syncthreads();
-        bf16_t *out = out0 + ip * 64;
-#pragma unroll
-        for (int p = 0; p < Cfg::WTN / 8; ++p) {
-            const int c = p * 8 + (lane >> 3), ch = lane & 7;
-            const u32x4_t val = *reinterpret_cast<const u32x4_t *>(stage + c * CS + ch * 16);
-            const int grow = row0 + ip * 64 + ch * 8, gcol = col0 + c;
-            if (grow < row_limit && gcol < col_limit)
-                *reinterpret_cast<u32x4_t *>(out) = val;
-            out += step;
-        }
-        __syncthreads();
-        __builtin_amdgcn_sched_barrier(0);
     }
 }
 
