@@ -56,10 +56,12 @@ enum {
     CP_HEAD_MIN_WORKSPACE = 2,  /* flags bit 1: the backward pass holds logit gradients for one
                                    tile of 256 head rows at a time (least workspace, slower)
                                    instead of its default of 32768 rows or 4 GiB worth of them,
-                                   whichever is more, up to 8 GiB (0.5 GiB on the plain path), and
-                                   the plain path's forward pass the row statistics of about 256
-                                   rows instead of 64 MiB of them */
-    CP_HEAD_KEEP_LOGITS = 4     /* flags bit 2, off by default (by default no logit is ever stored).
+                                   whichever is more, up to 8 GiB (0.5 GiB on the plain path), the
+                                   plain path's forward pass the row statistics of about 256
+                                   rows instead of 64 MiB of them, and the fine-tuning loss's
+                                   forward pass no logits instead of 3 GiB of them */
+    CP_HEAD_KEEP_LOGITS = 4     /* flags bit 2, off by default (by default no logit outlives its call, and
+                                   the pair of training loss calls stores none).
                                    Matrix-core path of the three loss call pairs only (cp_head_loss_,
                                    cp_head_full_loss_, cp_head_distill_loss_ fwd / bwd; ignored on the
                                    plain path and by the other calls): the forward pass keeps every logit
@@ -302,10 +304,12 @@ int cp_head_full_loss_bwd(const cp_head_desc *desc,
  * cp_head_workspace_bytes with CP_HEAD_OP_DISTILL_FWD / _BWD.  Backward: gradients of
  * sum_t dloss[t] * loss[t] with TZ constant; dloss/scale and the outputs as in cp_head_loss_bwd
  * (dU = NULL for the frozen unembedding of fine tuning).  Every entry of TZ must be finite, also in the
- * rows of dropped tokens.  For bf16 storage with d a multiple of 64 and r in {1, 2, 4, 8} no logits are
- * stored: the mixture over the experts is formed inside the tiles of two further vocabulary-sized
- * products on the matrix cores (with CP_HEAD_KEEP_LOGITS: the first product keeps its logits in ctx
- * and the two further ones become memory-bound passes over them).  Every other shape and fp32 storage
+ * rows of dropped tokens.  For bf16 storage with d a multiple of 64 and r in {1, 2, 4, 8} the forward call
+ * passes over the fp32 logits of a chunk of positions (at most 3 GiB of them, or one tile of 256 rows, in the
+ * workspace; none with CP_HEAD_MIN_WORKSPACE: then the mixture over the experts is formed inside the tiles of a
+ * second vocabulary-sized product), and the backward call forms the mixture inside the tiles of its product
+ * (with CP_HEAD_KEEP_LOGITS the product of the forward call keeps its logits in ctx and both calls pass over
+ * those).  Every other shape and fp32 storage
  * run on the plain fp32 path, which keeps the fp32 logits of one chunk of rows at a time in the workspace.
  */
 int cp_head_distill_ctx_bytes(const cp_head_desc *desc, size_t *bytes);

@@ -218,6 +218,12 @@ struct FastFwdBuffers {
 };
 int fast_fwd_rows(const cp_head_desc &ds, const void *H, const void *W, const void *U, const void *G,
                   const int32_t *X, void *ctx, void *ws, FastFwdBuffers *out, hipStream_t st);
+// The same, the fp32 logits of whole positions (fast_stored_positions of them at a time) left in z[rows, ldz] for `fn`, which
+// finds the results of the positions t0 .. t0 + P - 1 in place; ldz = V rounded up to 64.
+typedef void (*FastStoredRows)(void *user, const FastFwdBuffers &b, size_t t0, size_t P, const float *z, long ldz, hipStream_t st);
+size_t fast_stored_positions(const cp_head_desc &ds);
+int fast_fwd_rows_stored(const cp_head_desc &ds, const void *H, const void *W, const void *U, const void *G, const int32_t *X,
+                         void *ctx, void *ws, float *z, long ldz, FastStoredRows fn, void *user, FastFwdBuffers *out, hipStream_t st);
 // writes dz for rows m0 .. m0+Mc-1 of the chunk whose y is Yc to dZ, rows of Vp stored in blocks of 256 rows x 64 columns
 // (blocked64_index); the rows from Mc up to Mcp and the columns from V on are zeroed
 typedef void (*FastDzLaunch)(void *user, const bf16_t *Yc, int Mc, int Mcp, size_t m0, bf16_t *dZ, int Vp, hipStream_t st);

@@ -10,20 +10,21 @@
 // of one (t, k).  Those rows are adjacent (m = (t n + k) r + a) and, for r in {1, 2, 4, 8}, sit in the four
 // accumulator registers a lane holds of one 16x16 block of the MFMA result (and, for r = 8, in two neighbouring
 // 16-lane groups):
-// the epilogues below form log p^d_k[v] inside the tile, with no logits stored.
+// the epilogues below form log p^d_k[v] inside the tile.
 //
-// Forward:  the per-row part of the training loss (gate, y, statistics of z, lse, C) -> teacher log-normalisers
-//           -> expert weights qhat per token -> a second product z = Y U^T whose epilogue accumulates, per row,
-//           S_a = sum_v p^c[v] rho_a[v] and, per token, KL(p^c || p^d) -> per-position loss and the row
-//           coefficients of the backward pass.
-// Backward: a third product whose epilogue writes dz = c1 P - c3 p^c rho + c2 1[v = x] in bf16; everything
+// Forward:  per chunk of positions: the per-row part of the training loss (gate, y, z with its statistics, lse, C), z left in
+//           memory in fp32 -> expert weights qhat per token -> a pass over z that accumulates, per row,
+//           S_a = sum_v p^c[v] rho_a[v] and, per token, KL(p^c || p^d); then the per-position loss and the row
+//           coefficients of the backward pass.  With CP_HEAD_MIN_WORKSPACE that pass is a second product z = Y U^T.
+// Backward: another product whose epilogue writes dz = c1 P - c3 p^c rho + c2 1[v = x] in bf16; everything
 //           below dz is the training loss's backward pass.
-// With CP_HEAD_KEEP_LOGITS the first product keeps its logits (kept_logits.hpp) and the second and third
-// products become HBM-bound passes over them: k_distill_kl_kept and k_dz_from_kept<DistillDzRule>.
+// With CP_HEAD_KEEP_LOGITS the product of the forward pass keeps its logits (kept_logits.hpp) and both passes read those:
+// k_distill_kl and k_dz_from_kept<DistillDzRule>.
 #include "gemm_nt.hpp"
 #include "kept_logits.hpp"
 
 #include <math.h>
+#include <algorithm>
 
 namespace cph {
 
@@ -36,33 +37,128 @@ constexpr int kBlock = 256;
 // small kernels
 // ------------------------------------------------------------------------------------------
 
-// log-normaliser of every teacher row TZ[g, :], one block per row
-template <typename TT>
-__global__ void __launch_bounds__(kBlock) k_teacher_lse(int V, const TT *__restrict__ TZ, float *__restrict__ tlse)
+// Eight consecutive elements at any element address (one or two load instructions all the same)
+typedef uint32_t u32x4_any2_t __attribute__((ext_vector_type(4), aligned(2)));
+typedef float f32x4_any_t __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ void load8(const bf16_t *p, float (&x)[8])
 {
-    __shared__ float red[kBlock / kWave];
-    const size_t g = blockIdx.x;
-    const TT *row = TZ + g * V;
+    const u32x4_t raw = *reinterpret_cast<const u32x4_any2_t *>(p);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        x[2 * k] = __uint_as_float(raw[k] << 16);
+        x[2 * k + 1] = __uint_as_float(raw[k] & 0xFFFF0000u);
+    }
+}
+__device__ __forceinline__ void load8(const float *p, float (&x)[8])
+{
+    const f32x4_t a = *reinterpret_cast<const f32x4_any_t *>(p), b = *reinterpret_cast<const f32x4_any_t *>(p + 4);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        x[k] = a[k];
+        x[4 + k] = b[k];
+    }
+}
+
+// log-normaliser of every teacher row TZ[g, :], one block per row, its first kTeacherHeld columns held in registers between
+// the maximum and the sum.  HBM bound with eight elements per load; an element at a time the loads themselves were the bound
+// (16384 rows of 32000 bf16: 925 -> 353 us).
+constexpr int kTeacherBlock = 512, kTeacherSteps = 8, kTeacherHeld = kTeacherBlock * 8 * kTeacherSteps;
+template <typename TT>
+__global__ void __launch_bounds__(kTeacherBlock) k_teacher_lse(int V, const TT *__restrict__ TZ, float *__restrict__ tlse)
+{
+    __shared__ float red[kTeacherBlock / kWave];
+    const TT *row = TZ + (size_t)blockIdx.x * V;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const auto load = [&](int c, float (&x)[8]) {       // columns past the last one as -inf
+        if (c + 8 <= V) {
+            load8(row + c, x);
+        } else {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) x[k] = c + k < V ? ld_f32(row, (size_t)(c + k)) : -INFINITY;
+        }
+    };
+    const auto largest = [](const float (&x)[8], float mx) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) mx = fmaxf(mx, x[k]);
+        return mx;
+    };
+    float held[kTeacherSteps][8], x[8];
     float mx = -INFINITY;
-    for (int v = threadIdx.x; v < V; v += kBlock) mx = fmaxf(mx, ld_f32(row, v));
+#pragma unroll
+    for (int s = 0; s < kTeacherSteps; ++s) load((s * kTeacherBlock + (int)threadIdx.x) * 8, held[s]);
+#pragma unroll
+    for (int s = 0; s < kTeacherSteps; ++s) mx = largest(held[s], mx);
+    for (int c = kTeacherHeld + (int)threadIdx.x * 8; c < V; c += kTeacherBlock * 8) {
+        load(c, x);
+        mx = largest(x, mx);
+    }
     mx = wave_max(mx);
     if (lane == 0) red[wave] = mx;
     __syncthreads();
     float Mx = red[0];
 #pragma unroll
-    for (int w = 1; w < kBlock / kWave; ++w) Mx = fmaxf(Mx, red[w]);
+    for (int w = 1; w < kTeacherBlock / kWave; ++w) Mx = fmaxf(Mx, red[w]);
     __syncthreads();
     float l = 0.f;
-    for (int v = threadIdx.x; v < V; v += kBlock) l += expf(ld_f32(row, v) - Mx);
+    const auto add = [&](int c, const float (&x)[8]) {
+        if (c >= V) return;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) l += c + k < V ? expf(x[k] - Mx) : 0.f;
+    };
+#pragma unroll
+    for (int s = 0; s < kTeacherSteps; ++s) add((s * kTeacherBlock + (int)threadIdx.x) * 8, held[s]);
+    for (int c = kTeacherHeld + (int)threadIdx.x * 8; c < V; c += kTeacherBlock * 8) {
+        load(c, x);
+        add(c, x);
+    }
     l = wave_sum(l);
     if (lane == 0) red[wave] = l;
     __syncthreads();
     if (threadIdx.x == 0) {
         float L = 0.f;
 #pragma unroll
-        for (int w = 0; w < kBlock / kWave; ++w) L += red[w];
-        tlse[g] = Mx + logf(L);
+        for (int w = 0; w < kTeacherBlock / kWave; ++w) L += red[w];
+        tlse[blockIdx.x] = Mx + logf(L);
+    }
+}
+
+// k_distill_weights for R experts, a lane per (position, expert): the sums over the experts are R neighbouring lanes
+// (4096 positions, n = 4, R = 8, where a thread walked a position's experts one after the other: 37 -> 7 us).
+template <int R, class F>
+__device__ __forceinline__ float expert_lanes(float v, F f)
+{
+#pragma unroll
+    for (int off = 1; off < R; off <<= 1) v = f(v, __shfl_xor(v, off, kWave));
+    return v;
+}
+template <int R>
+__global__ void __launch_bounds__(kBlock) k_distill_weights_lanes(size_t Tr, int n, const float *__restrict__ logw, const float *__restrict__ C,
+                                                                  const float *__restrict__ lse, const int32_t *__restrict__ X,
+                                                                  float2 *__restrict__ rowa, float *__restrict__ rhox, float *__restrict__ ce)
+{
+    const size_t id = (size_t)blockIdx.x * kBlock + threadIdx.x;        // t R + a; whole groups of R lanes leave together
+    if (id >= Tr) return;
+    const size_t t = id / R;
+    const int a = (int)(id % R);
+    const auto larger = [](float x, float y) { return fmaxf(x, y); };
+    const auto add = [](float x, float y) { return x + y; };
+    float q = logw[id];
+    for (int k = 0; k < n; ++k) {
+        const size_t g = t * n + k, m = g * R + a;
+        const float c = C[m], l = lse[m];
+        if (X[g] < 0) {
+            rowa[m] = make_float2(l, 0.f);
+            rhox[m] = 0.f;
+            if (a == 0) ce[g] = 0.f;
+            continue;
+        }
+        const float mx = expert_lanes<R>(q, larger);
+        const float qn = mx + logf(expert_lanes<R>(expf(q - mx), add));
+        const float p = expf(q - qn + c), px = expert_lanes<R>(p, add);
+        rowa[m] = make_float2(l, q - qn);
+        rhox[m] = p / px;
+        if (a == 0) ce[g] = -logf(px);
+        q += c;
     }
 }
 
@@ -384,20 +480,14 @@ struct EpiDzDistill {
 };
 
 // ------------------------------------------------------------------------------------------
-// the same two passes over kept logits
+// the same two passes over logits in memory: kept ones, or (the first) a chunk's fp32 ones
 // ------------------------------------------------------------------------------------------
 
 // teacher logits of 8 consecutive columns; columns from V on read as the last valid one (and are not used)
 __device__ __forceinline__ void load_teacher8(const bf16_t *__restrict__ trow, int col, int V, float (&tz)[8])
 {
-    const bf16_t *p = trow + col;
-    if (col + 8 <= V && (reinterpret_cast<uintptr_t>(p) & 15u) == 0) {
-        const u32x4_t raw = *reinterpret_cast<const u32x4_t *>(p);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            tz[2 * k] = __uint_as_float(raw[k] << 16);
-            tz[2 * k + 1] = __uint_as_float(raw[k] & 0xFFFF0000u);
-        }
+    if (col + 8 <= V) {
+        load8(trow + col, tz);
     } else {
 #pragma unroll
         for (int k = 0; k < 8; ++k) tz[k] = bf16_to_f32(trow[col + k < V ? col + k : V - 1]);
@@ -416,12 +506,30 @@ __device__ __forceinline__ float log_mixture(const float (&l)[R])
     return mx + __logf(s);
 }
 
-// What EpiDistillStats accumulates, from the kept logits: one workgroup per token g, a thread takes 8 columns
-// of the token's R rows at a time; SK[g R + a] = {S_a, KL}.
-template <int R>
-__global__ void __launch_bounds__(kBlock) k_distill_kl_kept(KeptLogits kept, int V, int Vp, const float2 *__restrict__ rowa,
-                                                            const bf16_t *__restrict__ TZ, const float *__restrict__ tlse,
-                                                            float2 *__restrict__ SK)
+// fp32 logits of a chunk of rows
+struct StoredLogits {
+    const float *z;     // [rows, ld]
+    long ld;            // a multiple of 8
+};
+__device__ __forceinline__ void row_log_probs(const StoredLogits &k, size_t m, int col, float lse, float (&lp)[8])
+{
+    load8(k.z + m * k.ld + col, lp);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) lp[j] -= lse;
+}
+__device__ __forceinline__ void row_log_probs(const KeptLogits &k, size_t m, int col, float lse, float (&lp)[8])
+{
+    kept_log_probs(k, m, col, lse, lp);
+}
+
+// What EpiDistillStats accumulates, from logits in memory: one workgroup per token g, a thread takes 8 columns
+// of the token's R rows at a time; SK[g R + a] = {S_a, KL}.  With the fp32 logits of a chunk it is HBM bound (4 bytes per logit) and,
+// with the store, cheaper than multiplying U y again (the call's second product took 25.2 ms at T = 4096, d = 4096, V = 32000,
+// n = 4, r = 8).
+template <int R, class Logits>
+__global__ void __launch_bounds__(kBlock) k_distill_kl(Logits logits, int V, const float2 *__restrict__ rowa,
+                                                       const bf16_t *__restrict__ TZ, const float *__restrict__ tlse,
+                                                       float2 *__restrict__ SK)
 {
     __shared__ float red[kBlock / kWave][R + 1];
     const size_t g = blockIdx.x;
@@ -436,10 +544,10 @@ __global__ void __launch_bounds__(kBlock) k_distill_kl_kept(KeptLogits kept, int
     const float tl = tlse[g];
     const bf16_t *trow = TZ + g * (size_t)V;
     float kl = 0.f;
-    for (int col = (int)threadIdx.x * 8; col < Vp && col < V; col += kBlock * 8) {
+    for (int col = (int)threadIdx.x * 8; col < V; col += kBlock * 8) {
         float lp[R][8], tz[8];
 #pragma unroll
-        for (int a = 0; a < R; ++a) kept_log_probs(kept, g * R + a, col, lse_[a], lp[a]);
+        for (int a = 0; a < R; ++a) row_log_probs(logits, g * R + a, col, lse_[a], lp[a]);
         load_teacher8(trow, col, V, tz);
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
@@ -447,12 +555,21 @@ __global__ void __launch_bounds__(kBlock) k_distill_kl_kept(KeptLogits kept, int
             float l[R];
 #pragma unroll
             for (int a = 0; a < R; ++a) l[a] = lp[a][k] + lq_[a];
-            const float lm = log_mixture<R>(l);
+            float mx = l[0];
+#pragma unroll
+            for (int a = 1; a < R; ++a) mx = fmaxf(mx, l[a]);
+            float sum = 0.f;
+#pragma unroll
+            for (int a = 0; a < R; ++a) {
+                l[a] = __expf(l[a] - mx);
+                sum += l[a];
+            }
             const float lpc = tz[k] - tl;
             const float pc = __expf(lpc);
-            kl += pc * (lpc - lm);
+            kl += pc * (lpc - (mx + __logf(sum)));
+            const float share = pc / sum;
 #pragma unroll
-            for (int a = 0; a < R; ++a) S[a] += pc * __expf(l[a] - lm);
+            for (int a = 0; a < R; ++a) S[a] += share * l[a];
         }
     }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -544,10 +661,19 @@ DistillCtx distill_ctx(const cp_head_desc &ds)
     return c;
 }
 
-// forward workspace: the training loss's, then {rhox [M], ce [T n], SK [M] float2, part [M, parts] float2}
+// Whether the forward call leaves the fp32 logits of a chunk of positions in memory for the mixture, instead of multiplying
+// U y again once the log-normalisers are known: always, unless the caller asks for the least workspace or keeps 16-bit ones
+// anyway.  The store and the pass over it cost 8 bytes per logit, the product 2 d operations and the heavier epilogue.  Forward call,
+// us, product / stored: T = 4096, V = 32000, n = 4, r = 8: d = 4096 53.4 / 35.6 ms, 1024 18.1 / 13.6 ms, 512 12.4 / 10.8 ms; T = 2048, r = 4:
+// d = 256 2752 / 2527; T = 2048, n = 2, d = 128 2243 / 2247; T = 1000, V = 128000, n = 2, r = 4, d = 512 3488 / 3042.
+bool stores_logits(const cp_head_desc &ds) { return !(ds.flags & (CP_HEAD_KEEP_LOGITS | CP_HEAD_MIN_WORKSPACE)); }
+
+// forward workspace: the training loss's, then {rhox [M], ce [T n], SK [M] float2} and z [rows of a chunk, Vp] fp32 or
+// part [M, parts] float2 (second product)
 struct DistillFwdWs {
-    size_t rhox, ce, SK, part, total;
+    size_t rhox, ce, SK, part, z, total;
     int parts;
+    long ldz;
 };
 DistillFwdWs distill_fwd_ws(const cp_head_desc &ds)
 {
@@ -559,7 +685,10 @@ DistillFwdWs distill_fwd_ws(const cp_head_desc &ds)
     f.rhox = take(M * 4);
     f.ce = take(Tn * 4);
     f.SK = take(M * 8);
-    f.part = (ds.flags & CP_HEAD_KEEP_LOGITS) ? off : take(M * f.parts * sizeof(float2));   // no second product then
+    f.part = f.z = off;
+    f.ldz = (long)round_up((size_t)ds.V, 64);
+    if (stores_logits(ds)) f.z = take(std::min(fast_stored_positions(ds) * ds.n * ds.r, M) * f.ldz * 4);
+    else if (!(ds.flags & CP_HEAD_KEEP_LOGITS)) f.part = take(M * f.parts * sizeof(float2));
     f.total = off;
     return f;
 }
@@ -611,7 +740,28 @@ void launch_kl_kept(const cp_head_desc &ds, const KeptLogits &kept, const float2
     const size_t Tn = (size_t)ds.T * ds.n;
     // algorithmic traffic: kept logits and teacher logits read once
     ProfileScope scope("distill_kl_kept", ((double)Tn * R * kept.ld + (double)Tn * ds.V) * 2.0, st);
-    k_distill_kl_kept<R><<<(unsigned)Tn, kBlock, 0, st>>>(kept, ds.V, (int)kept.ld, rowa, TZ, tlse, SK);
+    k_distill_kl<R><<<(unsigned)Tn, kBlock, 0, st>>>(kept, ds.V, rowa, TZ, tlse, SK);
+}
+
+struct StoredKlArgs {
+    const cp_head_desc *ds;
+    const int32_t *X;
+    const bf16_t *TZ;
+    const float *tlse;
+    float2 *rowa, *SK;
+    float *rhox, *ce;
+};
+// a chunk of positions: the expert weights of its tokens, then S and KL from its logits
+template <int R>
+void stored_kl(void *user, const FastFwdBuffers &b, size_t t0, size_t P, const float *z, long ldz, hipStream_t st)
+{
+    const StoredKlArgs *a = static_cast<const StoredKlArgs *>(user);
+    const int n = a->ds->n, V = a->ds->V;
+    const size_t g0 = t0 * n, m0 = g0 * R, tokens = P * n;
+    k_distill_weights_lanes<R><<<blocks_for(P * R, kBlock), kBlock, 0, st>>>(P * R, n, b.logw + t0 * R, b.C + m0, b.lse + m0, a->X + g0,
+                                                                             a->rowa + m0, a->rhox + m0, a->ce + g0);
+    ProfileScope scope("distill_kl_stored", (double)tokens * (R * ldz * 4.0 + V * 2.0), st);
+    k_distill_kl<R><<<(unsigned)tokens, kBlock, 0, st>>>(StoredLogits{z, ldz}, V, a->rowa + m0, a->TZ + g0 * V, a->tlse + g0, a->SK + m0);
 }
 
 struct DistillKeptArgs {
@@ -633,9 +783,6 @@ int mfma_distill_fwd(const cp_head_desc &ds, const void *H, const void *W, const
                      hipStream_t st)
 {
     if (ds.T == 0) return CP_HEAD_OK;
-    FastFwdBuffers fb;
-    const int rc = fast_fwd_rows(ds, H, W, Uv, G, X, ctx, ws, &fb, st);      // gate, y, statistics, lse, C (eq. 5-8)
-    if (rc != CP_HEAD_OK) return rc;
     const bf16_t *U = (const bf16_t *)Uv, *TZ = (const bf16_t *)TZv;
     const DistillCtx dc = distill_ctx(ds);
     const DistillFwdWs f = distill_fwd_ws(ds);
@@ -645,8 +792,20 @@ int mfma_distill_fwd(const cp_head_desc &ds, const void *H, const void *W, const
     float *tlse = at<float>(ctx, dc.tlse), *dgsum = at<float>(ctx, dc.dgsum);
     float *rhox = at<float>(ws, f.rhox), *ce = at<float>(ws, f.ce);
     float2 *SK = at<float2>(ws, f.SK), *part = at<float2>(ws, f.part);
+    FastFwdBuffers fb;
 
-    k_teacher_lse<bf16_t><<<(unsigned)Tn, kBlock, 0, st>>>(ds.V, TZ, tlse);
+    k_teacher_lse<bf16_t><<<(unsigned)Tn, kTeacherBlock, 0, st>>>(ds.V, TZ, tlse);
+    if (stores_logits(ds)) {
+        StoredKlArgs args{&ds, X, TZ, tlse, rowa, SK, rhox, ce};
+        FastStoredRows fn = ds.r == 1 ? stored_kl<1> : ds.r == 2 ? stored_kl<2> : ds.r == 4 ? stored_kl<4> : stored_kl<8>;
+        const int rc = fast_fwd_rows_stored(ds, H, W, Uv, G, X, ctx, ws, at<float>(ws, f.z), f.ldz, fn, &args, &fb, st);
+        if (rc != CP_HEAD_OK) return rc;
+        k_distill_finish<8><<<blocks_for(T, kBlock), kBlock, 0, st>>>(T, ds.n, ds.r, beta, disc, X, rowa, rhox, ce, SK, loss, c1, c2, c3,
+                                                                      dgsum);
+        return hipGetLastError() == hipSuccess ? CP_HEAD_OK : CP_HEAD_ERR_LAUNCH;
+    }
+    const int rc = fast_fwd_rows(ds, H, W, Uv, G, X, ctx, ws, &fb, st);      // gate, y, statistics, lse, C (eq. 5-8)
+    if (rc != CP_HEAD_OK) return rc;
     k_distill_weights<8><<<blocks_for(T, kBlock), kBlock, 0, st>>>(T, ds.n, ds.r, fb.logw, fb.C, fb.lse, X, rowa, rhox, ce);
     const CtxLayout cl = ctx_layout(ds, true);
     if (cl.keep) {
@@ -841,7 +1000,7 @@ int plain_distill_fwd(const cp_head_desc &ds, const void *H, const void *W, cons
     float *tlse = at<float>(ctx, dc.tlse), *dgsum = at<float>(ctx, dc.dgsum);
     float *rhox = at<float>(ws, f.rhox), *ce = at<float>(ws, f.ce), *zc = at<float>(ws, f.zc);
     float2 *SK = at<float2>(ws, f.SK);
-    k_teacher_lse<TT><<<(unsigned)Tn, kBlock, 0, st>>>(ds.V, TZ, tlse);
+    k_teacher_lse<TT><<<(unsigned)Tn, kTeacherBlock, 0, st>>>(ds.V, TZ, tlse);
     k_distill_weights<kMaxRank><<<blocks_for(T, kBlock), kBlock, 0, st>>>(T, ds.n, ds.r, fb.logw, fb.C, fb.lse, X, rowa,
                                                                           rhox, ce);
     const size_t chunk = generic_bwd_chunk_rows(ds);

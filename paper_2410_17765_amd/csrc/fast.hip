@@ -195,6 +195,37 @@ struct EpiRowStatsKeep {
     }
 };
 
+// The statistics of EpiRowStats, and the fp32 logits themselves: for a pass over them while they are still a bounded chunk.
+struct EpiRowStatsStore {
+    float2 *part;   // [M, parts]
+    int parts;
+    int M, V;
+    float *z;       // [M, ldz]
+    long ldz;       // a multiple of 4, and the columns that are written (those from V on hold -inf)
+    int streamed;   // written past the caches
+    template <class C>
+    __device__ void run(f32x4_t (&acc)[C::TM16][C::TN16], int row0, int col0, int lane, int wave, int tn, char *) const
+    {
+        const int slot = tn * C::WN + (wave % C::WN);
+        mask_columns_past_vocabulary<C>(acc, col0, lane, V);
+        store_lines_f32<C>(acc, lane, row0, col0, M, (int)ldz, z, ldz, streamed != 0);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < C::TM16; ++i) {
+            float mx, ref, s[4] = {0.f, 0.f, 0.f, 0.f};
+            row_max<C>(acc[i], mx, ref);
+#pragma unroll
+            for (int j = 0; j < C::TN16; ++j)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) s[v] += __expf(acc[i][j][v] - ref);
+            const float sum = groups_sum((s[0] + s[1]) + (s[2] + s[3]));
+            const int r = row0 + acc_row(i, lane);
+            if (lane < 16 && r < M) part[(size_t)r * parts + slot] = make_float2(mx, (mx == -INFINITY) ? 0.f : sum);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+};
+
 // Softmax gradient (derivative of eq. 8/9 with respect to the logits), written in bf16, block by block (blocked64_index):
 //   dz[m, v] = coef[m] * (exp(z - lse[m]) - 1[v = x_m]),  zero in the padding columns V..Vp-1 and the rows Mc..Mcp-1.
 // One copy serves both products that read it: dY takes it as it lies and dU K-major (a second, transposed copy for dU
@@ -1326,36 +1357,102 @@ size_t fast_workspace_bytes(const cp_head_desc &ds, int op)
     return draft_ws(ds, op == CP_HEAD_OP_DRAFT_SEQUENTIAL).total;
 }
 
+namespace {
+// Where the per-row part of a forward pass has its buffers, and its two steps before the logits.
+struct FwdRows {
+    FwdWs f;
+    CtxLayout cl;
+    FastFwdBuffers b;
+    bf16_t *Ylo;
+    float2 *part;
+    FwdRows(const cp_head_desc &ds, void *ctx, void *ws) : f(fwd_ws(ds)), cl(ctx_layout(ds, true))
+    {
+        b.lse = at<float>(ctx, cl.lse); b.w = at<float>(ctx, cl.w); b.gamma = at<float>(ctx, cl.gamma);
+        b.Y = at<bf16_t>(ctx, cl.Y);
+        b.logw = at<float>(ws, f.logw); b.C = at<float>(ws, f.C);
+        Ylo = at<bf16_t>(ws, f.Ylo);
+        part = cl.keep ? at<float2>(ctx, cl.zpart) : at<float2>(ws, f.part);
+    }
+    void gate_and_y(const cp_head_desc &ds, const bf16_t *H, const bf16_t *W, const bf16_t *G, void *ws, hipStream_t st) const
+    {
+        const int T = (int)ds.T, d = ds.d, nrd = ds.n * ds.r * d;
+        launch_gate_bf16(ds, H, G, b.logw, b.w, st);                                                            // eq. 7
+        launch_gemm_nt<Cfg>("gemm_y", H, d, T, W, d, nrd, d, EpiStoreBf16{b.Y, Ylo, (long)nrd, T, nrd}, st, kGroupRowsNarrow,
+                            NoSideJob{0}, -1, -1, split_scratch(ws, f.split, f.split_bytes));                   // y = W_sa h
+    }
+    // log-normalisers and C of the rows m0 .. m0 + Mc - 1 (whole positions) from their statistics
+    void finish(const cp_head_desc &ds, size_t m0, size_t Mc, const bf16_t *U, const int32_t *X, hipStream_t st) const
+    {
+        k_row_finish<<<blocks_for(Mc, kBlock / kWave), kBlock, 0, st>>>(Mc, ds.d, ds.r, f.parts, part + m0 * f.parts, b.Y + m0 * ds.d,
+                                                                        Ylo + m0 * ds.d, U, X + m0 / ds.r, b.lse + m0, b.C + m0);
+    }
+};
+}  // namespace
+
 // Everything of the forward pass that is per head row: gate (eq. 7), y, the statistics of z, the
 // log-normalisers (eq. 5) and C (eq. 8).  `out` receives where the results live in ctx and ws.
 int fast_fwd_rows(const cp_head_desc &ds, const void *Hv, const void *Wv, const void *Uv, const void *Gv,
                   const int32_t *X, void *ctx, void *ws, FastFwdBuffers *out, hipStream_t st)
 {
     if (!dims_fit(ds)) return CP_HEAD_ERR_UNSUPPORTED;
-    const bf16_t *H = (const bf16_t *)Hv, *W = (const bf16_t *)Wv, *U = (const bf16_t *)Uv;
-    const CtxLayout cl = ctx_layout(ds, true);
-    const FwdWs f = fwd_ws(ds);
-    const int T = (int)ds.T, d = ds.d, V = ds.V;
-    const size_t M = (size_t)T * ds.n * ds.r;
-    const int nrd = ds.n * ds.r * d;
-    float *lse = at<float>(ctx, cl.lse), *w = at<float>(ctx, cl.w), *gamma = at<float>(ctx, cl.gamma);
-    bf16_t *Y = at<bf16_t>(ctx, cl.Y);
-    float *logw = at<float>(ws, f.logw), *C = at<float>(ws, f.C);
-    bf16_t *Ylo = at<bf16_t>(ws, f.Ylo);
-    float2 *part = cl.keep ? at<float2>(ctx, cl.zpart) : at<float2>(ws, f.part);
+    const bf16_t *U = (const bf16_t *)Uv;
+    const FwdRows fr(ds, ctx, ws);
+    const FwdWs &f = fr.f;
+    const CtxLayout &cl = fr.cl;
+    const int d = ds.d, V = ds.V;
+    const size_t M = (size_t)ds.T * ds.n * ds.r;
     if (cl.keep && (cl.parts != f.parts || kKeptTile != Cfg::WTN)) return CP_HEAD_ERR_UNSUPPORTED;
-
-    launch_gate_bf16(ds, (const bf16_t *)Hv, (const bf16_t *)Gv, logw, w, st);                                                      // eq. 7
-    launch_gemm_nt<Cfg>("gemm_y", H, d, T, W, d, nrd, d, EpiStoreBf16{Y, Ylo, (long)nrd, T, nrd}, st, kGroupRowsNarrow,
-                        NoSideJob{0}, -1, -1, split_scratch(ws, f.split, f.split_bytes));                       // y = W_sa h
+    fr.gate_and_y(ds, (const bf16_t *)Hv, (const bf16_t *)Wv, (const bf16_t *)Gv, ws, st);
     if (cl.keep)                                                                               // z = U y, statistics, z kept
-        launch_gemm_nt<Cfg>("gemm_z_stats_keep", Y, d, (int)M, U, d, V, d,
-                            EpiRowStatsKeep{part, f.parts, (int)M, V, at<uint16_t>(ctx, cl.zs), (long)cl.Vp, (int)cl.Vp,
+        launch_gemm_nt<Cfg>("gemm_z_stats_keep", fr.b.Y, d, (int)M, U, d, V, d,
+                            EpiRowStatsKeep{fr.part, f.parts, (int)M, V, at<uint16_t>(ctx, cl.zs), (long)cl.Vp, (int)cl.Vp,
                                             streamed_store(M * cl.Vp * 2)}, st);
     else
-        launch_gemm_nt<Cfg>("gemm_z_stats", Y, d, (int)M, U, d, V, d, EpiRowStats{part, f.parts, (int)M, V}, st);  // z = U y, statistics
-    k_row_finish<<<blocks_for(M, kBlock / kWave), kBlock, 0, st>>>(M, d, ds.r, f.parts, part, Y, Ylo, U, X, lse, C);
-    out->lse = lse; out->w = w; out->gamma = gamma; out->logw = logw; out->C = C; out->Y = Y;
+        launch_gemm_nt<Cfg>("gemm_z_stats", fr.b.Y, d, (int)M, U, d, V, d, EpiRowStats{fr.part, f.parts, (int)M, V}, st);  // z = U y, statistics
+    fr.finish(ds, 0, M, U, X, st);
+    *out = fr.b;
+    return hipGetLastError() == hipSuccess ? CP_HEAD_OK : CP_HEAD_ERR_LAUNCH;
+}
+
+// The rounds of the z product's tiles leave the least of the chip idle in their last one at some number of tile rows: the
+// best one among those of at most kStoredLogitsBytes of fp32 logits (at least one tile row), as whole positions.  3 GiB, less
+// than the backward call's logit gradients: chunks that stay in the last-level cache (200 MB) save the pass nothing and the
+// product's rounds cost more (forward call at T = 4096, d = 1024, V = 32000, n = 4, r = 8: 200 MB 16.3 ms, 1.5 GiB 14.0, 3 GiB 13.6).
+constexpr size_t kStoredLogitsBytes = (size_t)3 << 30;
+size_t fast_stored_positions(const cp_head_desc &ds)
+{
+    const size_t nr = (size_t)ds.n * ds.r, row = round_up((size_t)ds.V, 64) * 4, T = (size_t)ds.T;
+    const size_t tiles_n = ((size_t)ds.V + Cfg::BN - 1) / Cfg::BN, most = std::max<size_t>(kStoredLogitsBytes / (row * Cfg::BM), 1);
+    if (T * nr <= most * Cfg::BM) return T ? T : 1;
+    size_t best = most;
+    double least = 1e30;
+    for (size_t m = most; m >= 1 && m * 2 >= most; --m) {
+        const double per_tile = (double)((m * tiles_n + 255) / 256) / (double)(m * tiles_n);
+        if (per_tile < least) { least = per_tile; best = m; }
+    }
+    const size_t pos = best * Cfg::BM / nr;
+    return pos < 1 ? 1 : pos;
+}
+
+// The same with the fp32 logits of a chunk of positions in z[rows of the chunk, ldz] for `fn` to pass over, chunk by chunk.
+int fast_fwd_rows_stored(const cp_head_desc &ds, const void *Hv, const void *Wv, const void *Uv, const void *Gv, const int32_t *X,
+                         void *ctx, void *ws, float *z, long ldz, FastStoredRows fn, void *user, FastFwdBuffers *out, hipStream_t st)
+{
+    if (!dims_fit(ds)) return CP_HEAD_ERR_UNSUPPORTED;
+    const bf16_t *U = (const bf16_t *)Uv;
+    const FwdRows fr(ds, ctx, ws);
+    const int d = ds.d, V = ds.V;
+    const size_t T = (size_t)ds.T, nr = (size_t)ds.n * ds.r, pos = fast_stored_positions(ds);
+    *out = fr.b;
+    fr.gate_and_y(ds, (const bf16_t *)Hv, (const bf16_t *)Wv, (const bf16_t *)Gv, ws, st);
+    for (size_t t0 = 0; t0 < T; t0 += pos) {
+        const size_t P = T - t0 < pos ? T - t0 : pos, m0 = t0 * nr;
+        const int Mc = (int)(P * nr);
+        launch_gemm_nt<Cfg>("gemm_z_stats_store", fr.b.Y + m0 * d, d, Mc, U, d, V, d,
+                            EpiRowStatsStore{fr.part + m0 * fr.f.parts, fr.f.parts, Mc, V, z, ldz, streamed_store((size_t)Mc * ldz * 4)}, st);
+        fr.finish(ds, m0, (size_t)Mc, U, X, st);
+        fn(user, fr.b, t0, P, z, ldz, st);
+    }
     return hipGetLastError() == hipSuccess ? CP_HEAD_OK : CP_HEAD_ERR_LAUNCH;
 }
 

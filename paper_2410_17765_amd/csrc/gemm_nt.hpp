@@ -719,6 +719,55 @@ __device__ __forceinline__ void store_rows_f32(const f32x4_t (&acc)[Cfg::TM16][C
     }
 }
 
+// A lane's 16 bytes of row l % 16 at one place, and at the place that follows where the four lanes of the row end, become the
+// lane's 16 bytes of row l % 8 and of row 8 + l % 8: eight lanes then write a whole cache line of a row.
+__device__ __forceinline__ void exchange_rows8(f32x4_t &a, f32x4_t &b, int lane)
+{
+    const bool low = (lane & 8) == 0;
+    f32x4_t a1, b1;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        const float take = dpp_move<0x128>(0.f, low ? b[w] : a[w]);     // rotated by eight of the 16 lanes
+        a1[w] = low ? a[w] : take;
+        b1[w] = low ? take : b[w];
+    }
+    a = a1;
+    b = b1;
+}
+
+// The same without accumulation, 128 consecutive bytes per row: for a buffer that is written past the caches (`streamed`), where
+// half lines cost (fp32 logits of 131072 x 32000, d = 4096: 29.3 -> 27.9 ms), and not where the caches join them (16-bit logits
+// of 65536 x 32000, d = 2048, the same way: 7.05 -> 7.23 ms).
+template <class Cfg>
+__device__ __forceinline__ void store_lines_f32(const f32x4_t (&acc)[Cfg::TM16][Cfg::TN16], int lane, int row0, int col0, int row_limit,
+                                                int col_limit, float *__restrict__ dst, long ld, bool streamed)
+{
+    static_assert(!Cfg::ROWS_IN_LANE && Cfg::TN16 % 2 == 0, "four columns per lane");
+    const int row = row0 + (lane & 7), col = col0 + (lane & 8) * 2 + 4 * (lane >> 4);
+    float *out = dst + (size_t)row * ld + col;
+    const size_t step = (size_t)8 * ld;
+    const bool whole = row0 + Cfg::WTM <= row_limit && col0 + Cfg::WTN <= col_limit;
+#pragma unroll
+    for (int i = 0; i < Cfg::TM16; ++i) {
+        f32x4_t val[Cfg::TN16];         // [2 p] of rows 0..7 of the block row, [2 p + 1] of rows 8..15; 32 columns each
+#pragma unroll
+        for (int j = 0; j < Cfg::TN16; ++j) val[j] = acc[i][j];
+#pragma unroll
+        for (int p = 0; p < Cfg::TN16 / 2; ++p) exchange_rows8(val[2 * p], val[2 * p + 1], lane);
+        float *o = out + 2 * i * step;
+        auto place = [&](int j) { return reinterpret_cast<f32x4_t *>(o + (j & 1) * step + 32 * (j >> 1)); };
+        if (whole && streamed) {
+#pragma unroll
+            for (int j = 0; j < Cfg::TN16; ++j) __builtin_nontemporal_store(val[j], place(j));
+        } else {
+#pragma unroll
+            for (int j = 0; j < Cfg::TN16; ++j)
+                if (row + 16 * i + 8 * (j & 1) < row_limit && col + 32 * (j >> 1) < col_limit) *place(j) = val[j];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
 // ---------------------------------------------------------------------------------------------
 // Coalesced output of a wavefront's sub-tile for ROWS_IN_LANE.  There the result layout gives each lane single
 // elements of 16-column blocks, so values are first laid out row-major in a wave-private
