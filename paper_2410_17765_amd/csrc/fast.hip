@@ -13,6 +13,7 @@
 #include "kept_logits.hpp"
 
 #include <math.h>
+#include <type_traits>
 
 namespace cph {
 
@@ -508,24 +509,31 @@ struct GatePickSide {
 // Log-normaliser (eq. 5) of one row from its per-segment statistics, by one wavefront.
 __device__ __forceinline__ float row_lse_from_parts(const float2 *__restrict__ pm, int parts, int lane)
 {
-    // four independent loads per lane and step: the chain of rescalings is short, the loads overlap
+    // many independent loads per lane and step: a step is a memory latency and a link of the chain of rescalings (32 rows of
+    // 2004 segments, the draft call's at V = 128256: four loads a step 10.5 us for k_draft_lse_segment, sixteen 9.2)
     float mx = -INFINITY, l = 0.f;
-    for (int p0 = 0; p0 < parts; p0 += 4 * kWave) {
-        float2 qv[4];
+    auto step = [&](int p0, auto loads) {
+        constexpr int N = decltype(loads)::value;
+        float2 qv[N];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < N; ++i) {
             const int p = p0 + i * kWave + lane;
             qv[i] = p < parts ? pm[p] : make_float2(-INFINITY, 0.f);
         }
-        const float m4 = fmaxf(fmaxf(qv[0].x, qv[1].x), fmaxf(qv[2].x, qv[3].x));
-        if (m4 == -INFINITY) continue;
-        const float mn = fmaxf(mx, m4);
+        float most = qv[0].x;
+#pragma unroll
+        for (int i = 1; i < N; ++i) most = fmaxf(most, qv[i].x);
+        if (most == -INFINITY) return;
+        const float mn = fmaxf(mx, most);
         float add = 0.f;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) add += qv[i].y * __expf(qv[i].x - mn);     // exp(-inf) = 0 for empty segments
+        for (int i = 0; i < N; ++i) add += qv[i].y * __expf(qv[i].x - mn);     // exp(-inf) = 0 for empty segments
         l = l * __expf(mx - mn) + add;
         mx = mn;
-    }
+    };
+    int p0 = 0;
+    for (; parts - p0 > 4 * kWave; p0 += 16 * kWave) step(p0, std::integral_constant<int, 16>());
+    if (p0 < parts) step(p0, std::integral_constant<int, 4>());
     const float Mx = wave_max(mx);
     const float L = wave_sum(mx == -INFINITY ? 0.f : l * __expf(mx - Mx));
     return Mx + logf(L);
@@ -777,52 +785,38 @@ __global__ void __launch_bounds__(kBlock) k_lse_from_parts(size_t rows, int part
     if (lane == 0) lse[row] = v;
 }
 
-// (max, sum of exp(z - max)) of one chunk of kStatCols columns of one row of stored fp32 logits
-// (row stride ld, a multiple of 4): the per-segment statistics of eq. 5 for logits that are kept.
-constexpr int kStatCols = 4096;
-__global__ void __launch_bounds__(kBlock) k_row_stats_f32(int V, size_t ld, int parts, const float *__restrict__ z,
-                                                          float2 *__restrict__ part)
+// logp[b, v] = logsumexp_a(log w_a + z[(b, a), v] - lse[(b, a)]) (eq. 11) for 256 tokens of one b, from the stored first-head logits and
+// the per-segment statistics of their rows: every workgroup forms the r log-normalisers by itself, which takes kMixPairs pairs
+// of them at most and saves the call a launch.
+constexpr int kMixPairs = 4096;
+__global__ void __launch_bounds__(kBlock) k_first_token_from_parts(int V, int r, int parts, size_t ld, const float *__restrict__ z,
+                                                                   const float2 *__restrict__ part, const float *__restrict__ logw,
+                                                                   float *__restrict__ logp)
 {
-    __shared__ float red_m[kBlock / kWave], red_l[kBlock / kWave];
-    const size_t row = blockIdx.x;
-    const int c0 = blockIdx.y * kStatCols;
-    const float *zr = z + row * ld;
-    float4 x[kStatCols / 4 / kBlock];
-    float mx = -INFINITY;
-#pragma unroll
-    for (int i = 0; i < kStatCols / 4 / kBlock; ++i) {
-        const int c = c0 + (i * kBlock + threadIdx.x) * 4;
-        x[i] = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-        if (c + 3 < V) {
-            x[i] = *reinterpret_cast<const float4 *>(zr + c);
-        } else if (c < V) {
-            x[i].x = zr[c];
-            if (c + 1 < V) x[i].y = zr[c + 1];
-            if (c + 2 < V) x[i].z = zr[c + 2];
-        }
-        mx = fmaxf(fmaxf(mx, fmaxf(x[i].x, x[i].y)), fmaxf(x[i].z, x[i].w));
-    }
+    __shared__ float off_s[64];                   // log w - lse per expert
+    const size_t b = blockIdx.x;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    mx = wave_max(mx);
-    if (lane == 0) red_m[wave] = mx;
-    __syncthreads();
-    float Mx = red_m[0];
+    const int v = blockIdx.y * kBlock + threadIdx.x;
+    const float *zv = z + b * r * ld + min(v, V - 1);
+    float first[8];
 #pragma unroll
-    for (int w = 1; w < kBlock / kWave; ++w) Mx = fmaxf(Mx, red_m[w]);
-    const float ref = (Mx == -INFINITY) ? 0.f : Mx;
-    float l = 0.f;
-#pragma unroll
-    for (int i = 0; i < kStatCols / 4 / kBlock; ++i)
-        l += __expf(x[i].x - ref) + __expf(x[i].y - ref) + __expf(x[i].z - ref) + __expf(x[i].w - ref);
-    l = wave_sum(l);
-    if (lane == 0) red_l[wave] = l;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        float L = 0.f;
-#pragma unroll
-        for (int w = 0; w < kBlock / kWave; ++w) L += red_l[w];
-        part[row * parts + blockIdx.y] = make_float2(Mx, (Mx == -INFINITY) ? 0.f : L);
+    for (int a = 0; a < 8; ++a) first[a] = zv[min(a, r - 1) * ld];
+    for (int a = wave; a < r; a += kBlock / kWave) {
+        const float lse = row_lse_from_parts(part + (b * r + a) * parts, parts, lane);
+        if (lane == 0) off_s[a] = logw[b * r + a] - lse;
     }
+    __syncthreads();
+    if (v >= V) return;
+    float mx = -INFINITY, l = 0.f;
+    auto add = [&](float x) {
+        if (x > mx) { l = l * expf(mx - x) + 1.f; mx = x; }
+        else l += expf(x - mx);
+    };
+#pragma unroll
+    for (int a = 0; a < 8; ++a)
+        if (a < r) add(first[a] + off_s[a]);
+    for (int a = 8; a < r; ++a) add(zv[a * ld] + off_s[a]);
+    logp[b * (size_t)V + v] = mx + logf(l);
 }
 
 // The paper's sequential scheme (eq. 11-13), one workgroup per row b of the batch.
@@ -903,6 +897,113 @@ __global__ void __launch_bounds__(kWideBlock) k_sequential_step(int step, int V,
                      return m;
                  },
                  seg + b, base + b);
+}
+
+// The same for at most eight experts and PER segments per thread: a launch is a chain of memory latencies, so everything that
+// does not hang on the token drawn last (the masses of the next draw's segments, the logits of the present one's) is
+// requested at the start, and the logits stay in LDS for the update of the weights (11.6 -> 8.6 us a launch at B = 8, V = 128256, r = 8).
+template <bool ALONE, int PER>
+__global__ void __launch_bounds__(kWideBlock) k_sequential_step8(int step, int V, int n, int r, int parts, int seg_cols,
+                                                                 const float2 *__restrict__ part, const float *__restrict__ z,
+                                                                 const float *__restrict__ lse, float *__restrict__ q,
+                                                                 const float *__restrict__ uniforms, int32_t *__restrict__ seg,
+                                                                 double *__restrict__ base, int32_t *__restrict__ tokens,
+                                                                 float *__restrict__ logq)
+{
+    __shared__ float lse_s[8], qh_s[8], lp_s[8][kMaxSegCols];
+    __shared__ double p_s[kMaxSegCols];
+    const size_t b = blockIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const bool find = step < n;
+    float2 qv[PER][8];
+    if (find && (!ALONE || wave == 0)) {
+        const float2 *pm = part + (b * n + step) * r * parts;
+#pragma unroll
+        for (int i = 0; i < PER; ++i)
+#pragma unroll
+            for (int a = 0; a < 8; ++a) {
+                const int j = tid * PER + i;
+                qv[i][a] = a < r && j < parts ? pm[(size_t)a * parts + j] : make_float2(-INFINITY, 0.f);
+            }
+    }
+    int code = 0, v0 = 0, cols = 0;
+    float zv[8];
+    if (step > 0) {
+        code = seg[b];
+        v0 = (code < 0 ? ~code : code) * seg_cols;
+        cols = min(seg_cols, V - v0);
+        if (tid < cols) {
+#pragma unroll
+            for (int a = 0; a < 8; ++a) zv[a] = z[(b * r + min(a, r - 1)) * seg_cols + tid];
+        }
+        if (tid < r) lse_s[tid] = lse[(b * n + step - 1) * r + tid];
+    }
+    float qa = wave == 0 && lane < r ? q[b * r + lane] : -INFINITY;         // expert log-weights, lane a of wavefront 0
+    auto weights = [&]() {
+        if (wave != 0) return;
+        const float mx = wave_max(qa);
+        const float qn = mx + logf(wave_sum(lane < r ? expf(qa - mx) : 0.f));
+        if (lane < r) qh_s[lane] = expf(qa - qn);
+    };
+    if (step > 0) {
+        weights();
+        __syncthreads();
+        if (tid < cols) {
+            double p = 0.0;
+#pragma unroll
+            for (int a = 0; a < 8; ++a)
+                if (a < r) {
+                    const float lp = zv[a] - lse_s[a];
+                    lp_s[a][tid] = lp;
+                    p += (double)(qh_s[a] * expf(lp));
+                }
+            p_s[tid] = p;
+        }
+        __syncthreads();
+        if (wave == 0) {
+            // the running sum over the whole vocabulary never passes u: the last token
+            const int at = code < 0 ? cols - 1
+                                    : wave_pick_token(seg_cols, cols, base[b], (double)uniforms[b * n + step - 1], lane,
+                                                      [&](int i) { return p_s[i]; });
+            if (lane == 0) tokens[b * n + step - 1] = v0 + at;
+            // expert log-weights take the log-probability of the drawn token (text under eq. 12)
+            if (lane < r) {
+                qa += lp_s[lane][at];
+                q[b * r + lane] = qa;
+            }
+        }
+    }
+    if (!find) {
+        if (logq && wave == 0) {
+            const float mx = wave_max(qa);
+            const float sum = wave_sum(lane < r ? expf(qa - mx) : 0.f);
+            if (lane == 0) logq[b] = mx + logf(sum);
+        }
+        return;
+    }
+    weights();
+    float e[PER][8];
+    if (!ALONE || wave == 0) {
+#pragma unroll
+        for (int a = 0; a < 8; ++a) {
+            const float la = lse[(b * n + step) * r + min(a, r - 1)];
+#pragma unroll
+            for (int i = 0; i < PER; ++i) e[i][a] = qv[i][a].y * expf(qv[i][a].x - la);       // empty segments: 0 exp(-inf)
+        }
+    }
+    __syncthreads();
+    double mass[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        mass[i] = 0.0;
+        if (!ALONE || wave == 0) {
+#pragma unroll
+            for (int a = 0; a < 8; ++a)
+                if (a < r) mass[i] += (double)(qh_s[a] * e[i][a]);
+        }
+    }
+    find_segment<ALONE>(parts, (V - 1) / seg_cols, (double)uniforms[b * n + step],
+                        [&](int j) { return PER == 1 || j == tid * PER ? mass[0] : mass[PER - 1]; }, seg + b, base + b);
 }
 
 // Per head row {lse, coef = up_t * gamma[t, a] (zero for dropped factors), target}; dg[t, a] = up_t (w - gamma)
@@ -1225,7 +1326,8 @@ inline void launch_z_streamed(const char *name, const bf16_t *Y, int d, int rows
 // reads.  The tiled main loop waits for a stage of LDS at every K-step, d / 64 times a memory latency, which the other
 // workgroups of a compute unit hide only where there are two on each (512 tiles of 256 columns); here a workgroup has
 // 16 columns of y, and eight or more workgroups, whose loads overlap, share a compute unit.
-// The four wavefronts share the contraction and their partial products meet in LDS.
+// The four wavefronts share the contraction, two blocks of 64 columns in flight each (whole first-token calls on cold weights at
+// V = 32000, r = 8, one / two: T = 1, d = 4096 117.8 / 112.7 us, T = 4, d = 2048 55.8 / 54.8), and their partial products meet in LDS.
 constexpr int kStreamRows = 16, kStreamWaves = 4, kStreamBlock = kStreamWaves * kWave;
 __global__ void __launch_bounds__(kStreamBlock) k_stream_y(const bf16_t *__restrict__ H, int B, int d,
                                                            const bf16_t *__restrict__ W, int cols, bf16_t *__restrict__ Y,
@@ -1242,7 +1344,7 @@ __global__ void __launch_bounds__(kStreamBlock) k_stream_y(const bf16_t *__restr
     const bf16_t *const ph[1] = {H + (size_t)min(row, B - 1) * d + q * 16};     // rows past the last one repeat it, not stored
     const bf16_t *pw = W + (size_t)(col0 + row) * d + q * 16;
     f32x4_t acc[1] = {{0.f, 0.f, 0.f, 0.f}};
-    tile16_products<kStreamWaves, 1>(pw, ph, d, wave, acc);
+    tile16_products<kStreamWaves, 2>(pw, ph, d, wave, acc);
 #pragma unroll
     for (int v = 0; v < 4; ++v) sums[wave][tile16_row(v, lane)][row] = acc[0][v];
     __syncthreads();
@@ -1271,6 +1373,68 @@ inline void launch_y_with_gate(const char *name, const cp_head_desc &ds, const b
     } else if (B <= CfgSkinny::BM) launch_gemm_nt<CfgSkinny>(name, H, d, B, W, d, cols, d, epi, st, kGroupRowsWide, side);
     else launch_gemm_nt<Cfg>(name, H, d, B, W, d, cols, d, epi, st, kGroupRowsWide, side);
 }
+// z = U y for at most 32 head rows, stored in fp32 with the statistics of EpiRowStats per 64 columns: U goes from memory straight
+// into the registers of the matrix instruction, as W does in k_stream_y.  A workgroup has 64 columns, so that there are four
+// times as many as tiles of 256 (128 beyond 16 rows, since every workgroup reads all of Y from L2); its wavefronts share the contraction and their partial products meet in LDS.
+constexpr int kStreamZSeg = 64, kStreamZWaves = 8, kStreamZBlock = kStreamZWaves * kWave;
+template <int NG>
+struct StreamZ {
+    static constexpr int CG = NG == 1 ? 4 : 8, COLS = 16 * CG, AHEAD = NG == 1 ? 2 : 1, WAVES_PER_SIMD = NG == 1 ? 4 : 2;
+};
+template <int NG>
+__global__ void __launch_bounds__(kStreamZBlock, StreamZ<NG>::WAVES_PER_SIMD) k_stream_z(const bf16_t *__restrict__ Y, int rows, int d,
+                                                                                         const bf16_t *__restrict__ U, int V,
+                                                                                         float *__restrict__ z, long ldz,
+                                                                                         float2 *__restrict__ part, int parts)
+{
+    constexpr int CG = StreamZ<NG>::CG, COLS = StreamZ<NG>::COLS;
+    __shared__ __attribute__((aligned(16))) float sums[kStreamZWaves][NG * 16][COLS + 4];
+    const int col0 = (int)blockIdx.x * COLS;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int row = lane & 15, q = lane >> 4;
+    const bf16_t *pu[CG], *py[NG];                // rows past the last one repeat it; they are masked or not stored
+#pragma unroll
+    for (int c = 0; c < CG; ++c) pu[c] = U + (size_t)min(col0 + 16 * c + row, V - 1) * d + q * 16;
+#pragma unroll
+    for (int g = 0; g < NG; ++g) py[g] = Y + (size_t)min(16 * g + row, rows - 1) * d + q * 16;
+    f32x4_t acc[CG][NG];
+#pragma unroll
+    for (int c = 0; c < CG; ++c)
+#pragma unroll
+        for (int g = 0; g < NG; ++g) acc[c][g] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    tile16_products_2d<kStreamZWaves, StreamZ<NG>::AHEAD>(pu, py, d, wave, acc);
+#pragma unroll
+    for (int c = 0; c < CG; ++c)
+#pragma unroll
+        for (int g = 0; g < NG; ++g) *reinterpret_cast<f32x4_t *>(&sums[wave][16 * g + row][16 * c + 4 * q]) = acc[c][g];
+    __syncthreads();
+    const int r = threadIdx.x >> 4;               // a row, and four columns of each segment, per thread; 16 threads per row
+    if (r >= NG * 16 || r >= rows) return;        // whole groups of 16 lanes
+#pragma unroll
+    for (int s = 0; s < COLS / kStreamZSeg; ++s) {
+        const int c4 = s * kStreamZSeg + (threadIdx.x & 15) * 4, seg = (int)blockIdx.x * (COLS / kStreamZSeg) + s;
+        f32x4_t v = *reinterpret_cast<const f32x4_t *>(&sums[0][r][c4]);
+#pragma unroll
+        for (int w = 1; w < kStreamZWaves; ++w) v += *reinterpret_cast<const f32x4_t *>(&sums[w][r][c4]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = col0 + c4 + e < V ? v[e] : -INFINITY;
+        if (col0 + c4 < ldz) *reinterpret_cast<f32x4_t *>(z + (size_t)r * ldz + col0 + c4) = v;
+        const float mx = row16_max(fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])));
+        const float ref = mx == -INFINITY ? 0.f : mx;
+        const float sum = row16_sum((__expf(v[0] - ref) + __expf(v[1] - ref)) + (__expf(v[2] - ref) + __expf(v[3] - ref)));
+        if ((threadIdx.x & 15) == 0 && seg < parts) part[(size_t)r * parts + seg] = make_float2(mx, mx == -INFINITY ? 0.f : sum);
+    }
+}
+// Where it is the faster one (whole first-token calls on cold weights, us, tiles / this, r = 8 unless given):
+//   up to 16 rows: T = 1: d 2048 V 32000 69.6 / 52.7; d 4096 V 32000 147 / 118; d 4096 V 128256 264 / 270; d 1024 V 128256 r 2 62.6 / 57.4
+//                  T = 4: d 1536 V 128000 r 4 96.9 / 100.5          T = 2: d 1024 V 16000 37.5 / 21.3; d 2048 V 64000 94 / 80
+//   up to 32 rows: T = 4: d 2048 V 32000 69.5 / 55.8; d 4096 V 32000 152 / 124; d 4096 V 128256 274 / 289
+//                  T = 8: d 2048 V 50000 r 4 78 / 73
+// (Tiles with EpiStoreF32 and a pass over the logits for their statistics.)  From about 300 tiles of 256 columns on the tiles
+// have the loads in flight that the stream has, and read Y less often.
+constexpr int kStreamZRows = 32, kStreamZMost = 65536;
+inline bool stream_z(int rows, int V) { return rows <= kStreamZRows && V <= kStreamZMost; }
+
 // statistics segments (pairs per row, columns per segment) of that choice
 inline void z_segments(int rows, int V, int &parts, int &seg_cols)
 {
@@ -1328,7 +1492,7 @@ inline DraftWs draft_ws(const cp_head_desc &ds, bool sequential)
 struct FirstTokenWs {
     size_t logw, Y, z, lse, part, total;
     size_t V4;
-    int parts;
+    int parts, seg_cols;
 };
 inline FirstTokenWs first_token_ws(const cp_head_desc &ds)
 {
@@ -1341,7 +1505,8 @@ inline FirstTokenWs first_token_ws(const cp_head_desc &ds)
     f.Y = take(rows * ds.d * 2);
     f.z = take(rows * f.V4 * 4);
     f.lse = take(rows * 4);
-    f.parts = (ds.V + kStatCols - 1) / kStatCols;
+    z_segments((int)rows, ds.V, f.parts, f.seg_cols);
+    if (stream_z((int)rows, ds.V)) f.parts = (ds.V + kStreamZSeg - 1) / kStreamZSeg;
     f.part = take(rows * f.parts * sizeof(float2));
     f.total = off;
     return f;
@@ -1782,14 +1947,23 @@ int fast_first_token(const cp_head_desc &ds, const void *Hv, const void *Wv, con
     bf16_t *Y = at<bf16_t>(ws, f.Y);
     // first head only: its matrices are the first r blocks of W, so y has rows (b, a); the gate (eq. 7) rides along
     launch_y_with_gate("first_gemm_y", ds, H, W, G, nullptr, Y, logw, nullptr, r, st);
-    // the r rows of logits per b are the output's own size: they are stored once (fp32), read once for
-    // their log-normalisers and once for the mixture
-    launch_z_streamed("first_gemm_z", Y, d, rows, U, V, EpiStoreF32{z, (long)V4, rows, V4, 0}, st);
-    ProfileScope prof("first_mix", (double)rows * V * 8 + (double)B * V * 4, st);
+    // the r rows of logits per b are the output's own size: they are stored once (fp32), with their statistics, and read once
     float2 *part = at<float2>(ws, f.part);
-    k_row_stats_f32<<<dim3((unsigned)rows, (unsigned)f.parts), kBlock, 0, st>>>(V, (size_t)V4, f.parts, z, part);
-    k_lse_from_parts<<<blocks_for((size_t)rows, kBlock / kWave), kBlock, 0, st>>>((size_t)rows, f.parts, part, lse);
-    launch_first_token_mix(ds, z, (size_t)V4, lse, logw, logp, st);                         // eq. 11
+    if (stream_z(rows, V)) {
+        ProfileScope prof("first_gemm_z", 2.0 * (double)rows * V * d, st);
+        if (rows <= 16) k_stream_z<1><<<blocks_for(V, StreamZ<1>::COLS), kStreamZBlock, 0, st>>>(Y, rows, d, U, V, z, (long)V4, part, f.parts);
+        else k_stream_z<2><<<blocks_for(V, StreamZ<2>::COLS), kStreamZBlock, 0, st>>>(Y, rows, d, U, V, z, (long)V4, part, f.parts);
+    } else {
+        launch_z_streamed("first_gemm_z", Y, d, rows, U, V, EpiRowStatsStore{part, f.parts, rows, V, z, (long)V4, 0}, st);
+    }
+    ProfileScope prof("first_mix", (double)rows * V * 4 + (double)B * V * 4, st);
+    if (r * f.parts <= kMixPairs) {
+        k_first_token_from_parts<<<dim3((unsigned)B, blocks_for((size_t)V, kBlock)), kBlock, 0, st>>>(V, r, f.parts, (size_t)V4, z, part, logw,
+                                                                                                     logp);
+    } else {
+        k_lse_from_parts<<<blocks_for((size_t)rows, kBlock / kWave), kBlock, 0, st>>>((size_t)rows, f.parts, part, lse);
+        launch_first_token_mix(ds, z, (size_t)V4, lse, logw, logp, st);                     // eq. 11
+    }
     return hipGetLastError() == hipSuccess ? CP_HEAD_OK : CP_HEAD_ERR_LAUNCH;
 }
 
@@ -1818,8 +1992,10 @@ int fast_draft_sequential(const cp_head_desc &ds, const void *Hv, const void *Wv
     double *base = at<double>(ws, f.base);
     k_lse_from_parts<<<blocks_for(M, kBlock / kWave), kBlock, 0, st>>>(M, parts, part, lse);
     for (int step = 0; step <= n; ++step) {
-        // one wavefront up to a segment a lane, whose mass is a sum over r experts
-        auto kernel = parts <= kWave ? k_sequential_step<true> : k_sequential_step<false>;
+        // one wavefront up to a segment a lane, whose mass is a sum over r experts; find_segment's segments per thread
+        auto kernel = parts <= kWave ? (r <= 8 ? k_sequential_step8<true, 1> : k_sequential_step<true>)
+                    : r > 8 || parts > 2 * kWideBlock ? k_sequential_step<false>
+                    : parts <= kWideBlock ? k_sequential_step8<false, 1> : k_sequential_step8<false, 2>;
         kernel<<<(unsigned)B, kWideBlock, 0, st>>>(step, V, n, r, parts, seg_cols, part, zseg, lse, logw, uniforms, seg, base, tokens,
                                                    logq);                                                      // eq. 11-13
         if (step < n)

@@ -5,6 +5,8 @@
 
 #include "cp_internal.hpp"
 
+#include <type_traits>
+
 namespace cph {
 
 typedef __bf16 tile16_bf16x8_t __attribute__((ext_vector_type(8)));
@@ -58,6 +60,40 @@ __device__ __forceinline__ void tile16_products(const bf16_t *a, const bf16_t *c
     if (AHEAD > 3 && left == 3) tile16_blocks<3>(a, b, k, kStride, acc);
     else if (AHEAD > 2 && left == 2) tile16_blocks<2>(a, b, k, kStride, acc);
     else if (AHEAD > 1 && left == 1) tile16_blocks<1>(a, b, k, kStride, acc);
+}
+// The same for NA x NB tiles: acc[c][g] += a[c] b[g]^T, AHEAD blocks of every row in flight.
+template <int WAVES, int AHEAD, int NA, int NB>
+__device__ __forceinline__ void tile16_products_2d(const bf16_t *(&a)[NA], const bf16_t *(&b)[NB], int d, int wave,
+                                                   tile16_acc_t (&acc)[NA][NB])
+{
+    constexpr int kStride = WAVES * 64;
+    auto blocks = [&](int k0, auto count) {
+        constexpr int N = decltype(count)::value;
+        tile16_u32x4_t av[N][NA][2], bv[N][NB][2];
+#pragma unroll
+        for (int u = 0; u < N; ++u)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+#pragma unroll
+                for (int e = 0; e < NA; ++e) av[u][e][c] = load16(a[e] + k0 + u * kStride + 8 * c);
+#pragma unroll
+                for (int e = 0; e < NB; ++e) bv[u][e][c] = load16(b[e] + k0 + u * kStride + 8 * c);
+            }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < N; ++u)
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+#pragma unroll
+                for (int e = 0; e < NA; ++e)
+#pragma unroll
+                    for (int f = 0; f < NB; ++f)
+                        acc[e][f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(tile16_bf16x8_t, av[u][e][c]),
+                                                                            __builtin_bit_cast(tile16_bf16x8_t, bv[u][f][c]), acc[e][f], 0, 0, 0);
+    };
+    int k = wave * 64, left = (d / 64 - wave + WAVES - 1) / WAVES;      // blocks of this wavefront
+    for (; left >= AHEAD; left -= AHEAD, k += AHEAD * kStride) blocks(k, std::integral_constant<int, AHEAD>());
+    for (; left > 0; --left, k += kStride) blocks(k, std::integral_constant<int, 1>());
 }
 // row (of a) of element v of the result in a lane; the column (of b) is l % 16
 __device__ __forceinline__ int tile16_row(int v, int lane) { return 4 * (lane >> 4) + v; }
