@@ -1314,14 +1314,6 @@ typedef TileCfg<64, 256, 1, 4> CfgSkinny;
 #define CPH_SKINNY_ROWS 64
 #endif
 constexpr int kSkinnyRows = CPH_SKINNY_ROWS;
-// z = U y for the few rows of a draft-type call: picks the tile by the number of rows
-template <class Epi>
-inline void launch_z_streamed(const char *name, const bf16_t *Y, int d, int rows, const bf16_t *U, int V, const Epi &epi,
-                              hipStream_t st)
-{
-    if (rows <= kSkinnyRows) launch_gemm_nt<CfgSkinny>(name, Y, d, rows, U, d, V, d, epi, st, kSkinnyRows / CfgSkinny::BM);
-    else launch_gemm_nt<Cfg>(name, Y, d, rows, U, d, V, d, epi, st);
-}
 // y = W_sa h for at most 16 positions: W goes from memory straight into the registers that the matrix instruction
 // reads.  The tiled main loop waits for a stage of LDS at every K-step, d / 64 times a memory latency, which the other
 // workgroups of a compute unit hide only where there are two on each (512 tiles of 256 columns); here a workgroup has
@@ -1373,7 +1365,7 @@ inline void launch_y_with_gate(const char *name, const cp_head_desc &ds, const b
     } else if (B <= CfgSkinny::BM) launch_gemm_nt<CfgSkinny>(name, H, d, B, W, d, cols, d, epi, st, kGroupRowsWide, side);
     else launch_gemm_nt<Cfg>(name, H, d, B, W, d, cols, d, epi, st, kGroupRowsWide, side);
 }
-// z = U y for at most 32 head rows, stored in fp32 with the statistics of EpiRowStats per 64 columns: U goes from memory straight
+// z = U y for at most 32 head rows, the statistics of EpiRowStats per 64 columns and, unless z is null, the fp32 logits: U goes from memory straight
 // into the registers of the matrix instruction, as W does in k_stream_y.  A workgroup has 64 columns, so that there are four
 // times as many as tiles of 256 (128 beyond 16 rows, since every workgroup reads all of Y from L2); its wavefronts share the contraction and their partial products meet in LDS.
 constexpr int kStreamZSeg = 64, kStreamZWaves = 8, kStreamZBlock = kStreamZWaves * kWave;
@@ -1418,7 +1410,7 @@ __global__ void __launch_bounds__(kStreamZBlock, StreamZ<NG>::WAVES_PER_SIMD) k_
         for (int w = 1; w < kStreamZWaves; ++w) v += *reinterpret_cast<const f32x4_t *>(&sums[w][r][c4]);
 #pragma unroll
         for (int e = 0; e < 4; ++e) v[e] = col0 + c4 + e < V ? v[e] : -INFINITY;
-        if (col0 + c4 < ldz) *reinterpret_cast<f32x4_t *>(z + (size_t)r * ldz + col0 + c4) = v;
+        if (z && col0 + c4 < ldz) *reinterpret_cast<f32x4_t *>(z + (size_t)r * ldz + col0 + c4) = v;
         const float mx = row16_max(fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])));
         const float ref = mx == -INFINITY ? 0.f : mx;
         const float sum = row16_sum((__expf(v[0] - ref) + __expf(v[1] - ref)) + (__expf(v[2] - ref) + __expf(v[3] - ref)));
@@ -1430,20 +1422,43 @@ __global__ void __launch_bounds__(kStreamZBlock, StreamZ<NG>::WAVES_PER_SIMD) k_
 //                  T = 4: d 1536 V 128000 r 4 96.9 / 100.5          T = 2: d 1024 V 16000 37.5 / 21.3; d 2048 V 64000 94 / 80
 //   up to 32 rows: T = 4: d 2048 V 32000 69.5 / 55.8; d 4096 V 32000 152 / 124; d 4096 V 128256 274 / 289
 //                  T = 8: d 2048 V 50000 r 4 78 / 73
-// (Tiles with EpiStoreF32 and a pass over the logits for their statistics.)  From about 300 tiles of 256 columns on the tiles
+// (Tiles with EpiStoreF32 and a pass over the logits for their statistics.)  Draft calls (tiles with EpiRowStats): T = 1, n = 4, r = 8: d 2048
+// V 32000 110 / 99.6; T = 1, n = 4, r = 4: d 1024 V 16000 42.4 / 30.1; T = 16, n = r = 1: d 2048 V 32000 68.6 / 50.8; T = 4, n = 2, r = 4: d 2048
+// V 50000 86 / 84.5.  From about 300 tiles of 256 columns on the tiles
 // have the loads in flight that the stream has, and read Y less often.
 constexpr int kStreamZRows = 32, kStreamZMost = 65536;
 inline bool stream_z(int rows, int V) { return rows <= kStreamZRows && V <= kStreamZMost; }
 
-// statistics segments (pairs per row, columns per segment) of that choice
+// statistics segments (pairs per row, columns per segment) of the z product of a draft-type call
 inline void z_segments(int rows, int V, int &parts, int &seg_cols)
 {
-    if (rows <= kSkinnyRows) {
+    if (stream_z(rows, V)) {
+        parts = (V + kStreamZSeg - 1) / kStreamZSeg;
+        seg_cols = kStreamZSeg;
+    } else if (rows <= kSkinnyRows) {
         parts = ((V + CfgSkinny::BN - 1) / CfgSkinny::BN) * CfgSkinny::WN;
         seg_cols = CfgSkinny::WTN;
     } else {
         parts = ((V + Cfg::BN - 1) / Cfg::BN) * Cfg::WN;
         seg_cols = Cfg::WTN;
+    }
+}
+// z = U y for the few rows of a draft-type call with its statistics, and the logits themselves unless z is null; streams U once
+inline void launch_z_stats(const char *name, const bf16_t *Y, int d, int rows, const bf16_t *U, int V, float2 *part, int parts, float *z,
+                           long ldz, hipStream_t st)
+{
+    auto tiles = [&](auto epi) {
+        if (rows <= kSkinnyRows) launch_gemm_nt<CfgSkinny>(name, Y, d, rows, U, d, V, d, epi, st, kSkinnyRows / CfgSkinny::BM);
+        else launch_gemm_nt<Cfg>(name, Y, d, rows, U, d, V, d, epi, st);
+    };
+    if (stream_z(rows, V)) {
+        ProfileScope prof(name, 2.0 * (double)rows * V * d, st);
+        if (rows <= 16) k_stream_z<1><<<blocks_for(V, StreamZ<1>::COLS), kStreamZBlock, 0, st>>>(Y, rows, d, U, V, z, ldz, part, parts);
+        else k_stream_z<2><<<blocks_for(V, StreamZ<2>::COLS), kStreamZBlock, 0, st>>>(Y, rows, d, U, V, z, ldz, part, parts);
+    } else if (z) {
+        tiles(EpiRowStatsStore{part, parts, rows, V, z, ldz, 0});
+    } else {
+        tiles(EpiRowStats{part, parts, rows, V});
     }
 }
 
@@ -1506,7 +1521,6 @@ inline FirstTokenWs first_token_ws(const cp_head_desc &ds)
     f.z = take(rows * f.V4 * 4);
     f.lse = take(rows * 4);
     z_segments((int)rows, ds.V, f.parts, f.seg_cols);
-    if (stream_z((int)rows, ds.V)) f.parts = (ds.V + kStreamZSeg - 1) / kStreamZSeg;
     f.part = take(rows * f.parts * sizeof(float2));
     f.total = off;
     return f;
@@ -1902,7 +1916,7 @@ int fast_draft(const cp_head_desc &ds, const void *Hv, const void *Wv, const voi
     // z = U y for all B*n*r rows with running statistics; streams U once, logits are not stored
     int parts, seg_cols;
     z_segments((int)M, V, parts, seg_cols);
-    launch_z_streamed("draft_gemm_z", Y, d, (int)M, U, V, EpiRowStats{part, parts, (int)M, V}, st);
+    launch_z_stats("draft_gemm_z", Y, d, (int)M, U, V, part, parts, nullptr, 0, st);
     {
         ProfileScope prof("draft_lse_segment", (double)M * parts * 8, st);
         // one wavefront up to four segments a lane
@@ -1949,13 +1963,7 @@ int fast_first_token(const cp_head_desc &ds, const void *Hv, const void *Wv, con
     launch_y_with_gate("first_gemm_y", ds, H, W, G, nullptr, Y, logw, nullptr, r, st);
     // the r rows of logits per b are the output's own size: they are stored once (fp32), with their statistics, and read once
     float2 *part = at<float2>(ws, f.part);
-    if (stream_z(rows, V)) {
-        ProfileScope prof("first_gemm_z", 2.0 * (double)rows * V * d, st);
-        if (rows <= 16) k_stream_z<1><<<blocks_for(V, StreamZ<1>::COLS), kStreamZBlock, 0, st>>>(Y, rows, d, U, V, z, (long)V4, part, f.parts);
-        else k_stream_z<2><<<blocks_for(V, StreamZ<2>::COLS), kStreamZBlock, 0, st>>>(Y, rows, d, U, V, z, (long)V4, part, f.parts);
-    } else {
-        launch_z_streamed("first_gemm_z", Y, d, rows, U, V, EpiRowStatsStore{part, f.parts, rows, V, z, (long)V4, 0}, st);
-    }
+    launch_z_stats("first_gemm_z", Y, d, rows, U, V, part, f.parts, z, (long)V4, st);
     ProfileScope prof("first_mix", (double)rows * V * 4 + (double)B * V * 4, st);
     if (r * f.parts <= kMixPairs) {
         k_first_token_from_parts<<<dim3((unsigned)B, blocks_for((size_t)V, kBlock)), kBlock, 0, st>>>(V, r, f.parts, (size_t)V4, z, part, logw,
@@ -1982,7 +1990,7 @@ int fast_draft_sequential(const cp_head_desc &ds, const void *Hv, const void *Wv
     launch_y_with_gate("seq_gemm_y", ds, H, W, G, nullptr, Y, logw, nullptr, n * r, st);          // y and the gate (eq. 7)
     int parts, seg_cols;
     z_segments((int)M, V, parts, seg_cols);
-    launch_z_streamed("seq_gemm_z", Y, d, (int)M, U, V, EpiRowStats{part, parts, (int)M, V}, st);
+    launch_z_stats("seq_gemm_z", Y, d, (int)M, U, V, part, parts, nullptr, 0, st);
     // A draw is two launches: a workgroup per row for everything but the logits of the segment, which many share.
     // (One launch with a workgroup per row for all draws fetched them on one
     // compute unit: the call took 691 us at B = 8, d = 4096, V = 128256, n = 4, r = 8 and takes 534 us this way.)
