@@ -31,6 +31,10 @@ struct F32Tile {
     static_assert(WM * WN * WK == 4 && BM % (16 * WM) == 0 && BN % (16 * WN) == 0 && CHUNKS % WK == 0, "four wavefronts");
 };
 typedef F32Tile<128, 128, 2, 2, 1, 32> F32Large;
+// Both operands K-contiguous: a K-step of 16 lets a third workgroup share the compute unit, whose products fill more of the
+// others' gaps (z, dz and y of T = 500, d = 512, V = 8191, n = r = 4: 1474 -> 1371 us).  A K-major operand's fragments are four reads
+// each, so that the shorter K-step gains nothing there (dY and dU: 1132 -> 1147 us), nor in the 64-wide tile (125 -> 166 us).
+typedef F32Tile<128, 128, 2, 2, 1, 16> F32LargeContiguous;
 typedef F32Tile<64, 64, 2, 2, 1, 32> F32Mid;
 typedef F32Tile<32, 32, 1, 1, 4, 64> F32Small;
 constexpr int kF32Threads = 256;
@@ -146,6 +150,7 @@ struct F32Gemm {
     typedef F32Loader<TB, BKM, Tile::BN, Tile::BK> LoadB;
     static constexpr int STAGE = LoadA::FLOATS + LoadB::FLOATS;
     static constexpr int LDS_FLOATS = 2 * STAGE;
+    static constexpr int PER_CU = Tile::BM == 128 && Tile::BK == 16 ? 3 : 2;      // workgroups that the register limit allows for
 
     // Tile `index` of the problem.  The epilogue is called by the wavefronts that hold results, with the origin of their
     // sub-tile, the split, and the sub-tile's column slot (tile column times WN plus wavefront column).
@@ -305,7 +310,7 @@ inline F32Problem f32_batch(F32Problem p, int batch, long stride)
 // Up to three problems in one launch (their tiles share the compute units: two workgroups of 59 % of the matrix cores'
 // rate each fill one another's gaps to 80 %); a problem with zero tiles is absent.
 template <class G1, class E1, class G2, class E2, class G3, class E3>
-__global__ void __launch_bounds__(kF32Threads, 2)       // at most 256 registers: two workgroups per compute unit
+__global__ void __launch_bounds__(kF32Threads, G1::PER_CU)
      k_gemm_f32(F32Problem p1, E1 e1, F32Problem p2, E2 e2, F32Problem p3, E3 e3)
 {
     constexpr int L12 = G1::LDS_FLOATS > G2::LDS_FLOATS ? G1::LDS_FLOATS : G2::LDS_FLOATS;
