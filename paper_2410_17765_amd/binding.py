@@ -132,7 +132,8 @@ def _nbytes(t) -> int:
 def _stream(stream) -> Optional[int]:
     if stream is None:
         import torch
-        return torch.cuda.current_stream().cuda_stream
+        # the handle itself: a Stream object takes 3 us to make, a fifth of a small call
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     return int(stream)
 
 
