@@ -81,18 +81,13 @@ struct TileCfg {
     static_assert(BM % ROWS_PER_PASS == 0 && BN % ROWS_PER_PASS == 0, "tile rows must divide into load passes");
 };
 
-// Raw buffer descriptor for `bytes` bytes at `base` (no stride, range-checked).
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *base, unsigned bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00020000);
-}
-
-// The same descriptor as four scalar words, and a direct global->LDS load of 16 bytes per lane spelled out, for the
-// kernels with K-major operands.  Their fragments come from gfx950's transposing LDS read, and before every such
-// read the compiler waits for all outstanding loads once it knows that loads into LDS are in flight (it cannot tell
+// Raw buffer descriptor for `bytes` bytes at `base` (no stride, range-checked) as four scalar words, and a direct global->LDS load
+// of 16 bytes per lane spelled out.  Fragments of K-major operands come from gfx950's transposing LDS read, and before
+// every such read the compiler waits for all outstanding loads once it knows that loads into LDS are in flight (it cannot tell
 // that they go to the other stage), which serialises the whole pipeline (measured: 3-5 times slower).  Loads
 // issued this way are invisible to that bookkeeping; the main loop's own explicit waits (before the barrier that
-// publishes a stage) are what orders them, exactly as for the other kernels.
+// publishes a stage) are what orders them.  The kernels without a K-major operand issue theirs the same way: the
+// builtin's address arithmetic between the products cost the kept-logits product 2 % (d = 2048: 7.07 -> 6.94 ms).
 typedef int i32x4_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ i32x4_t make_rsrc_words(const void *base, unsigned bytes)
 {
@@ -179,8 +174,6 @@ __device__ __forceinline__ void gemm_nt_mainloop_direct(const GemmOperands &g, i
     // (a blocked operand's descriptor spans the whole panel of its tile row: all 256 rows of every block exist)
     const unsigned span_a = Cfg::ABL ? (unsigned)((size_t)BM * g.K * 2) : (unsigned)((size_t)rows_a * g.lda * 2);
     const unsigned span_b = (unsigned)((size_t)rows_b * g.ldb * 2);
-    const __amdgpu_buffer_rsrc_t ra = make_rsrc(g.A + (size_t)m0 * g.lda, span_a);
-    const __amdgpu_buffer_rsrc_t rb = make_rsrc(g.B + (size_t)n0 * g.ldb, span_b);
     // A K-major operand's descriptor is kept for the K-tile whose loads are being issued and moved on by one tile
     // (64 k-rows) at a time: a 64-bit add on the base and a choice among three sizes (a full tile, the operand's
     // last, partial one, nothing past its end).  Rebuilding it from the tile index cost a dozen scalar instructions
@@ -233,7 +226,6 @@ __device__ __forceinline__ void gemm_nt_mainloop_direct(const GemmOperands &g, i
     KmWalk walk_a = kBlockedKm ? km_start_blocked(g.A, g.lda, g.ka_tile) : km_start(g.A, g.lda, m0, g.ka_rows);
     KmWalk walk_b = km_start(g.B, g.ldb, n0, g.kb_rows);
     auto advance_a = [&]() { if (kBlockedKm) km_advance_blocked(walk_a); else km_advance(walk_a); };
-    constexpr bool kSpelledOut = Cfg::AKM || Cfg::BKM;
     const i32x4_t wa = make_rsrc_words(g.A + (size_t)m0 * g.lda, span_a);
     const i32x4_t wb = make_rsrc_words(g.B + (size_t)n0 * g.ldb, span_b);
     const unsigned lds_smem = __builtin_amdgcn_readfirstlane((unsigned)reinterpret_cast<unsigned long long>((lds_void *)smem));
@@ -270,30 +262,22 @@ __device__ __forceinline__ void gemm_nt_mainloop_direct(const GemmOperands &g, i
 
     // Everything that the descriptor's range check must see is in the vector offset (the scalar offset is added to
     // the address but not checked): the pass for both layouts.  The K-step is the scalar offset of a K-contiguous
-    // operand and part of the descriptor's base for a K-major one.  Kernels with a K-major operand issue all their
-    // loads spelled out (see load_lds_16_spelled_out).
+    // operand and part of the descriptor's base for a K-major one.
     auto load_one = [&](int kt, int stage, int q) {
         // the K-step: 128 bytes along the row, or one block of BM rows x 128 bytes of a blocked operand
         const int soff = q < Cfg::A_PASSES ? kt * (Cfg::ABL ? BM * 128 : BK * 2) : kt * (BK * 2);
-        char *base = smem + stage * Cfg::STAGE_BYTES + lds_wave;
         const unsigned lbase = lds_smem + stage * Cfg::STAGE_BYTES + lds_wave;
         if (q < Cfg::A_PASSES) {
             if (Cfg::AKM)
                 load_lds_16_spelled_out(walk_a.d, lbase + q * lds_pass_a, voff_a + q * pass_a, 0);       // tile kt == walk_a.tile
-            else if (kSpelledOut)
-                load_lds_16_spelled_out(wa, lbase + q * lds_pass_a, voff_a + q * pass_a, soff);
             else
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_void *)(base + q * lds_pass_a), 16,
-                                                         (int)(voff_a + q * pass_a), soff, 0, 0);
+                load_lds_16_spelled_out(wa, lbase + q * lds_pass_a, voff_a + q * pass_a, soff);
         } else {
             const int qb = q - Cfg::A_PASSES;
             if (Cfg::BKM)
                 load_lds_16_spelled_out(walk_b.d, lbase + Cfg::A_BYTES + qb * lds_pass_b, voff_b + qb * pass_b, 0);
-            else if (kSpelledOut)
-                load_lds_16_spelled_out(wb, lbase + Cfg::A_BYTES + qb * lds_pass_b, voff_b + qb * pass_b, soff);
             else
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_void *)(base + Cfg::A_BYTES + qb * lds_pass_b), 16,
-                                                         (int)(voff_b + qb * pass_b), soff, 0, 0);
+                load_lds_16_spelled_out(wb, lbase + Cfg::A_BYTES + qb * lds_pass_b, voff_b + qb * pass_b, soff);
         }
     };
     // a fragment of a K-major tile: 16-column block `blk` of the wavefront, k-block kb: two transposing reads
@@ -317,23 +301,20 @@ __device__ __forceinline__ void gemm_nt_mainloop_direct(const GemmOperands &g, i
         else fb[buf][q] = *reinterpret_cast<const bf16x8_t *>(st + lds_rb + q * 16 * 128 + coff[kb]);
     };
     auto mfma_one = [&](int abuf, int bbuf, int half, int idx) {
-        const int i = idx / TN, j = idx % TN;
-        // With K-major operands (fragments assembled from two 64-bit reads) the register allocator no longer keeps
-        // the accumulators in place: it rotates them through copies between the two register files, several hundred
-        // per K-step.  Spelling the instruction out with the accumulator tied to itself in the accumulation
-        // registers and the fragments in vector registers gives the allocation the other kernels get by themselves.
+        // The columns are walked there and back: every product shares a fragment with the one before it, which on these
+        // power-limited matrix cores is worth 0.4-0.5 % of every large product.
+        const int i = idx / TN, j = (i & 1) ? TN - 1 - idx % TN : idx % TN;
+        // The instruction is spelled out with the accumulator tied to itself in the accumulation registers and the
+        // fragments in vector registers.  Left to itself the register allocator rotates accumulators through copies between
+        // the two register files: several hundred per K-step where fragments are assembled from two 64-bit reads (K-major
+        // operands) or the columns are walked in another order (z at d = 4096 93.5 -> 106 ms), and dozens in the 64-row tile.
         // The compiler still inserts the waits for the fragments' LDS reads (it sees the operands); what it cannot see
         // is that the instruction is a matrix instruction: uses of one accumulator are 64 instructions apart here, and
         // the wait states before the accumulators are read back are added after the loop (without them the epilogue
         // read accumulators that lacked the last K-block's contribution).
-        if (Cfg::AKM || Cfg::BKM)
-            asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0"
-                         : "+a"(acc[half * HA + i][j])
-                         : "v"(Cfg::ROWS_IN_LANE ? fa[abuf][i] : fb[bbuf][j]), "v"(Cfg::ROWS_IN_LANE ? fb[bbuf][j] : fa[abuf][i]));
-        else
-            acc[half * HA + i][j] =
-                __builtin_amdgcn_mfma_f32_16x16x32_bf16(Cfg::ROWS_IN_LANE ? fa[abuf][i] : fb[bbuf][j],
-                                                        Cfg::ROWS_IN_LANE ? fb[bbuf][j] : fa[abuf][i], acc[half * HA + i][j], 0, 0, 0);
+        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0"
+                     : "+a"(acc[half * HA + i][j])
+                     : "v"(Cfg::ROWS_IN_LANE ? fa[abuf][i] : fb[bbuf][j]), "v"(Cfg::ROWS_IN_LANE ? fb[bbuf][j] : fa[abuf][i]));
     };
     // the reads of the four phases, in the order the MFMAs that follow need them
     auto reads0 = [&](const char *st, const char *, int q) {       // A half 1 of k-block 0, then B first half of k-block 1
@@ -417,13 +398,11 @@ __device__ __forceinline__ void gemm_nt_mainloop_direct(const GemmOperands &g, i
     // compiler does not know that they are matrix instructions: wait out their latency here, and pass every
     // accumulator through an (empty) volatile statement, which the compiler keeps behind that wait and ahead of
     // every later use of the accumulator.
-    if (Cfg::AKM || Cfg::BKM) {
-        asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
+    asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int j = 0; j < TN; ++j) asm volatile("" : "+a"(acc[i][j]));
-    }
+        for (int j = 0; j < TN; ++j) asm volatile("" : "+a"(acc[i][j]));
 #undef CPH_K_STEP_DIRECT16
 #undef CPH_PHASE16
 #undef CPH_PIN
