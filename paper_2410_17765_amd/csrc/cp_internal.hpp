@@ -48,6 +48,14 @@ __device__ __forceinline__ float wave_max(float v)
     return v;
 }
 
+// eq. 10 by one wavefront: L_aux = sum_a (n_a / N - 1/r)^2, n_a in lane a
+__device__ __forceinline__ float balance_statistic(size_t T, int r, unsigned long long count, int lane)
+{
+    float dev = 0.f;
+    if (lane < r) dev = (T ? (float)((double)count / (double)T) : 0.f) - 1.f / (float)r;
+    return wave_sum(dev * dev);
+}
+
 // Cross-lane steps of the row statistics, as data-parallel-primitive moves (no LDS traffic):
 // quad swaps, mirror inside 8 and inside 16 lanes give every lane of a 16-lane row the row's value.
 template <int CTRL, int ROW_MASK = 0xF>
@@ -165,10 +173,12 @@ void launch_first_token_mix(const cp_head_desc &ds, const float *z, size_t ld, c
                             float *logp, hipStream_t st);
 
 // Kernels of the generic path that the matrix-core path reuses (fp32 bookkeeping per position).
-// The gate of the matrix-core path (gate.hip): log-softmax, the arg-max counts of eq. 10 (added to `counts`), and the
+// The gate of the matrix-core path (gate.hip): log-softmax, the arg-max counts of eq. 10 (added to `counts`; returns whether the
+// statistic has been formed from them too: T > 0, laux zero before), and the
 // gate gradient dG = dg^T H, whose partial sums take gate_chunks(T) r d floats of `partial`.
 void launch_gate_bf16(const cp_head_desc &ds, const bf16_t *H, const bf16_t *G, float *logw, float *w, hipStream_t st);
-void launch_aux_argmax_bf16(const cp_head_desc &ds, const bf16_t *H, const bf16_t *G, unsigned long long *counts, hipStream_t st);
+bool launch_aux_argmax_bf16(const cp_head_desc &ds, const bf16_t *H, const bf16_t *G, unsigned long long *counts, float *laux,
+                            hipStream_t st);
 constexpr int kGateChunk = 512;     // positions per partial sum
 inline size_t gate_chunks(size_t T) { return (T + kGateChunk - 1) / kGateChunk; }
 void launch_gate_gradient_bf16(const cp_head_desc &ds, const bf16_t *H, const float *dg, float *partial, float *dG, hipStream_t st);

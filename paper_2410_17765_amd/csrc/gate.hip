@@ -142,11 +142,15 @@ __global__ void __launch_bounds__(kBlock) k_gate_bf16(size_t T, int d, int r, co
     }
 }
 
-// counts[a] += positions whose largest gate is expert a, the first index on ties (eq. 10)
+// counts[a] += positions whose largest gate is expert a, the first index on ties (eq. 10).  Unless laux is null the workgroup that
+// adds its counts last also forms the statistic from the sums, which saves a launch; until then the four bytes of laux count
+// the workgroups that have added theirs, and both start at zero.
 template <int NG>
 __global__ void __launch_bounds__(kBlock) k_aux_argmax_bf16(size_t T, int d, int r, const bf16_t *__restrict__ H,
-                                                            const bf16_t *__restrict__ G, unsigned long long *__restrict__ counts)
+                                                            const bf16_t *__restrict__ G, unsigned long long *__restrict__ counts,
+                                                            float *__restrict__ laux)
 {
+    __shared__ bool last;
     __shared__ float red[kWaves][kRows][NG * 16 + 1];
     __shared__ unsigned int hist[64];
     if (threadIdx.x < 64) hist[threadIdx.x] = 0;
@@ -165,7 +169,21 @@ __global__ void __launch_bounds__(kBlock) k_aux_argmax_bf16(size_t T, int d, int
         }
         __syncthreads();
     }
-    if ((int)threadIdx.x < r && hist[threadIdx.x]) atomicAdd(&counts[threadIdx.x], (unsigned long long)hist[threadIdx.x]);
+    if ((int)threadIdx.x < r && hist[threadIdx.x]) {
+        atomicAdd(&counts[threadIdx.x], (unsigned long long)hist[threadIdx.x]);
+        if (laux) __threadfence();                        // before the workgroup counts as done
+    }
+    if (!laux) return;
+    __syncthreads();
+    if (threadIdx.x == 0)
+        last = __hip_atomic_fetch_add(reinterpret_cast<unsigned *>(laux), 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+    __syncthreads();
+    if (!last || threadIdx.x >= kWave) return;
+    __threadfence();
+    const int lane = threadIdx.x;
+    const unsigned long long count = lane < r ? __hip_atomic_load(&counts[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
+    const float s = balance_statistic(T, r, count, lane);
+    if (lane == 0) *laux = s;
 }
 
 // dG[a, j] = sum_t dg[t, a] H[t, j] in two deterministic stages: partial sums over chunks of kGateChunk positions in turn,
@@ -250,13 +268,19 @@ void launch_gate_bf16(const cp_head_desc &ds, const bf16_t *H, const bf16_t *G, 
     else k_gate_bf16<8, 4><<<blocks, kBlock, 0, st>>>(T, ds.d, ds.r, H, G, logw, w);
 }
 
-void launch_aux_argmax_bf16(const cp_head_desc &ds, const bf16_t *H, const bf16_t *G, unsigned long long *counts, hipStream_t st)
+// The statistic in the same launch: each workgroup orders its caches before it counts as done, one after the other, so for few
+// workgroups only.  Whole calls, us, two launches / three: T = 300 (19 workgroups) 7.3 / 13.0, T = 2048 (128) 9.5 / 13.1, T = 4096 (256)
+// 20.4 / 16.1, T = 16384 (512) 75 / 34.7.
+constexpr unsigned kAuxAlone = 128;
+bool launch_aux_argmax_bf16(const cp_head_desc &ds, const bf16_t *H, const bf16_t *G, unsigned long long *counts, float *laux, hipStream_t st)
 {
     const size_t T = (size_t)ds.T;
     // at most two workgroups per compute unit: each ends with up to r atomic additions to the same few counters
     const unsigned tiles = blocks_for(T, kRows), blocks = tiles < 512 ? tiles : 512;
-    if (ds.r <= 16) k_aux_argmax_bf16<1><<<blocks, kBlock, 0, st>>>(T, ds.d, ds.r, H, G, counts);
-    else k_aux_argmax_bf16<4><<<blocks, kBlock, 0, st>>>(T, ds.d, ds.r, H, G, counts);
+    const bool whole = blocks <= kAuxAlone;
+    auto kernel = ds.r <= 16 ? k_aux_argmax_bf16<1> : k_aux_argmax_bf16<4>;
+    kernel<<<blocks, kBlock, 0, st>>>(T, ds.d, ds.r, H, G, counts, whole ? laux : nullptr);
+    return whole;
 }
 
 void launch_gate_gradient_bf16(const cp_head_desc &ds, const bf16_t *H, const float *dg, float *partial, float *dG, hipStream_t st)

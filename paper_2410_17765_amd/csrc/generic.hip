@@ -666,10 +666,11 @@ __global__ void __launch_bounds__(kBlock) k_aux_argmax(size_t T, int d, int r, c
     if ((int)threadIdx.x < r && hist[threadIdx.x]) atomicAdd(&counts[threadIdx.x], (unsigned long long)hist[threadIdx.x]);
 }
 
-__global__ void k_fill_zero_u64(int count, unsigned long long *__restrict__ p)
+__global__ void k_aux_begin(int r, unsigned long long *__restrict__ counts, float *__restrict__ laux)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < count) p[i] = 0ull;
+    const int i = threadIdx.x;
+    if (i < r) counts[i] = 0ull;
+    if (i == 0) *laux = 0.f;
 }
 
 // eq. 10, second stage: L_aux = sum_a (n_a / N - 1/r)^2
@@ -677,9 +678,7 @@ __global__ void __launch_bounds__(kWave) k_aux_finish(size_t T, int r, const uns
                                                       float *__restrict__ laux)
 {
     const int lane = threadIdx.x;
-    float dev = 0.f;
-    if (lane < r) dev = (T ? (float)((double)counts[lane] / (double)T) : 0.f) - 1.f / (float)r;
-    const float s = wave_sum(dev * dev);
+    const float s = balance_statistic(T, r, lane < r ? counts[lane] : 0ull, lane);
     if (lane == 0) *laux = s;
 }
 
@@ -1120,18 +1119,19 @@ int generic_first_token(const cp_head_desc &ds, const void *H, const void *W, co
 int aux_balance(const cp_head_desc &ds, const void *H, const void *G, int64_t *counts, float *laux, hipStream_t st)
 {
     unsigned long long *c = reinterpret_cast<unsigned long long *>(counts);
-    k_fill_zero_u64<<<1, 64, 0, st>>>(ds.r, c);
+    k_aux_begin<<<1, 64, 0, st>>>(ds.r, c, laux);
+    bool finished = false;
     if (ds.T > 0) {
         const unsigned blocks = (unsigned)std::min<size_t>(((size_t)ds.T + kWavesPerBlock - 1) / kWavesPerBlock, 4096);
         if (use_fast_path(ds))
-            launch_aux_argmax_bf16(ds, (const bf16_t *)H, (const bf16_t *)G, c, st);
+            finished = launch_aux_argmax_bf16(ds, (const bf16_t *)H, (const bf16_t *)G, c, laux, st);
         else if (ds.dtype == CP_HEAD_FP32)
             k_aux_argmax<float><<<blocks, kBlock, 0, st>>>((size_t)ds.T, ds.d, ds.r, (const float *)H, (const float *)G, c);
         else
             k_aux_argmax<bf16_t><<<blocks, kBlock, 0, st>>>((size_t)ds.T, ds.d, ds.r, (const bf16_t *)H,
                                                             (const bf16_t *)G, c);
     }
-    k_aux_finish<<<1, kWave, 0, st>>>((size_t)ds.T, ds.r, c, laux);
+    if (!finished) k_aux_finish<<<1, kWave, 0, st>>>((size_t)ds.T, ds.r, c, laux);
     return hipGetLastError() == hipSuccess ? CP_HEAD_OK : CP_HEAD_ERR_LAUNCH;
 }
 
