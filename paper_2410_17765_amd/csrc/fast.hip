@@ -1022,17 +1022,28 @@ __global__ void k_bwd_coefficients(size_t M, int n, int r, const float *__restri
     if ((m / r) % n == 0) dg[t * r + a] = up * (w[t * r + a] - gm);
 }
 
-// dH[t, j] += sum_a dg[t, a] G[a, j]
-__global__ void k_add_gate_to_dh(size_t T, int d, int r, const bf16_t *__restrict__ G, const float *__restrict__ dg,
-                                 float *__restrict__ dH)
+// dH[t, j] += sum_a dg[t, a] G[a, j], four columns a thread (T = 16384, d = 4096, r = 8: one a
+// thread 374 us, four 153 = 3.5 TB/s)
+typedef uint32_t u32x2_any_t __attribute__((ext_vector_type(2), aligned(2)));
+typedef float f32x4_any_t __attribute__((ext_vector_type(4), aligned(4)));
+__global__ void __launch_bounds__(kBlock) k_add_gate_to_dh(size_t T, int d, int r, const bf16_t *__restrict__ G, const float *__restrict__ dg,
+                                                           float *__restrict__ dH)
 {
-    const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= T * d) return;
-    const size_t t = idx / d;
-    const int j = (int)(idx % d);
-    float acc = dH[idx];
-    for (int a = 0; a < r; ++a) acc += dg[t * r + a] * bf16_to_f32(G[(size_t)a * d + j]);
-    dH[idx] = acc;
+    const size_t idx = (size_t)blockIdx.x * kBlock + threadIdx.x, quads = (size_t)d / 4;       // d is a multiple of 64
+    if (idx >= T * quads) return;
+    const size_t t = idx / quads;
+    const int j = (int)(idx % quads) * 4;
+    f32x4_any_t *out = reinterpret_cast<f32x4_any_t *>(dH + t * d + j);
+    f32x4_t acc = *out;
+    for (int a = 0; a < r; ++a) {
+        const float c = dg[t * r + a];
+        const u32x2_any_t g = *reinterpret_cast<const u32x2_any_t *>(G + (size_t)a * d + j);
+        acc[0] += c * __uint_as_float(g[0] << 16);
+        acc[1] += c * __uint_as_float(g[0] & 0xFFFF0000u);
+        acc[2] += c * __uint_as_float(g[1] << 16);
+        acc[3] += c * __uint_as_float(g[1] & 0xFFFF0000u);
+    }
+    *out = acc;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1667,7 +1678,7 @@ static int bwd_below_dy(const cp_head_desc &ds, const bf16_t *H, const bf16_t *W
     transpose_bf16(W, d, (int)nrd, d, Wt, ldN, (int)nrd, st);         // Wt[d, nrd]
     launch_gemm_nt<Cfg>("gemm_dh", dY, (long)nrd, (int)T, Wt, ldN, d, (int)nrd, EpiStoreF32{dH, (long)d, (int)T, d, 0}, st,
                         kGroupRowsNarrow, NoSideJob{0}, -1, -1, split);
-    k_add_gate_to_dh<<<blocks_for(T * d, kBlock), kBlock, 0, st>>>(T, d, r, G, dg, dH);
+    k_add_gate_to_dh<<<blocks_for(T * d / 4, kBlock), kBlock, 0, st>>>(T, d, r, G, dg, dH);
     if (dW)
         // dW_sa = dY_sa^T H   (contraction over positions: both operands K-major, any number of positions)
         launch_gemm_nt<CfgTN>("gemm_dw", dY, (long)nrd, (int)nrd, H, d, d, (int)T, EpiStoreF32{dW, (long)d, (int)nrd, d, 0}, st,
@@ -2102,7 +2113,7 @@ int fast_full_loss_bwd(const cp_head_desc &ds, const void *Hv, const void *Fv, c
         }
         first_chunk = 0;
     }
-    k_add_gate_to_dh<<<blocks_for(T * d, kBlock), kBlock, 0, st>>>(T, d, r, G, dg, dH);       // + G^T dg
+    k_add_gate_to_dh<<<blocks_for(T * d / 4, kBlock), kBlock, 0, st>>>(T, d, r, G, dg, dH);       // + G^T dg
     if (dG) launch_gate_gradient_bf16(ds, H, dg, at<float>(ws, b.dGpart), dG, st);
     return hipGetLastError() == hipSuccess ? CP_HEAD_OK : CP_HEAD_ERR_LAUNCH;
 }
