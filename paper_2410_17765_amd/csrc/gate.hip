@@ -142,10 +142,10 @@ __global__ void __launch_bounds__(kBlock) k_gate_bf16(size_t T, int d, int r, co
     }
 }
 
-// counts[a] += positions whose largest gate is expert a, the first index on ties (eq. 10).  Unless laux is null the workgroup that
+// counts[a] += positions whose largest gate is expert a, the first index on ties (eq. 10).  STATISTIC: the workgroup that
 // adds its counts last also forms the statistic from the sums, which saves a launch; until then the four bytes of laux count
 // the workgroups that have added theirs, and both start at zero.
-template <int NG>
+template <int NG, bool STATISTIC>
 __global__ void __launch_bounds__(kBlock) k_aux_argmax_bf16(size_t T, int d, int r, const bf16_t *__restrict__ H,
                                                             const bf16_t *__restrict__ G, unsigned long long *__restrict__ counts,
                                                             float *__restrict__ laux)
@@ -171,9 +171,9 @@ __global__ void __launch_bounds__(kBlock) k_aux_argmax_bf16(size_t T, int d, int
     }
     if ((int)threadIdx.x < r && hist[threadIdx.x]) {
         atomicAdd(&counts[threadIdx.x], (unsigned long long)hist[threadIdx.x]);
-        if (laux) __threadfence();                        // before the workgroup counts as done
+        if (STATISTIC) __threadfence();                   // before the workgroup counts as done
     }
-    if (!laux) return;
+    if (!STATISTIC) return;
     __syncthreads();
     if (threadIdx.x == 0)
         last = __hip_atomic_fetch_add(reinterpret_cast<unsigned *>(laux), 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
@@ -278,8 +278,9 @@ bool launch_aux_argmax_bf16(const cp_head_desc &ds, const bf16_t *H, const bf16_
     // at most two workgroups per compute unit: each ends with up to r atomic additions to the same few counters
     const unsigned tiles = blocks_for(T, kRows), blocks = tiles < 512 ? tiles : 512;
     const bool whole = blocks <= kAuxAlone;
-    auto kernel = ds.r <= 16 ? k_aux_argmax_bf16<1> : k_aux_argmax_bf16<4>;
-    kernel<<<blocks, kBlock, 0, st>>>(T, ds.d, ds.r, H, G, counts, whole ? laux : nullptr);
+    auto kernel = ds.r <= 16 ? (whole ? k_aux_argmax_bf16<1, true> : k_aux_argmax_bf16<1, false>)
+                             : (whole ? k_aux_argmax_bf16<4, true> : k_aux_argmax_bf16<4, false>);
+    kernel<<<blocks, kBlock, 0, st>>>(T, ds.d, ds.r, H, G, counts, laux);
     return whole;
 }
 
