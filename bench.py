@@ -28,13 +28,13 @@ PEAK_FP32_TFLOPS = 157.3   # 256 compute units x 128 fp32 multiply-adds a cycle 
 GIB = float(1 << 30)
 TRAFFIC_BYTES = {
     # (workload, launch name, launches per step): L2 fills + writes per launch
-    ("head_7b", "gemm_z_stats_keep", 1): (203.536 + 32.510) * GIB,       # loss_head_7b_kept_logits_kernel_stats.md
-    ("head_7b", "gemm_z_stats_keep", 8): (26.849 + 4.066) * GIB,         # loss_head_7b_single_call_kernel_stats.md
-    ("head_7b", "gemm_z_stats", 1): (210.580 + 1.294) * GIB,             # loss_head_7b_kernel_stats.md
-    ("head_7b", "gemm_z_dz", 8): (25.455 + 7.813) * GIB,                 # loss_head_7b_kernel_stats.md
+    ("head_7b", "gemm_z_stats_keep", 1): (211.104 + 33.282) * GIB,       # loss_head_7b_kept_logits_kernel_stats.md
+    ("head_7b", "gemm_z_stats_keep", 8): (28.775 + 4.162) * GIB,         # loss_head_7b_single_call_kernel_stats.md
+    ("head_7b", "gemm_z_stats", 1): (221.220 + 2.338) * GIB,             # loss_head_7b_kernel_stats.md
+    ("head_7b", "gemm_z_dz", 8): (28.460 + 3.906) * GIB,                 # loss_head_7b_kernel_stats.md
     # draft step: L2 fills of its kernels per step at B = 1, 8, 64 (profiles/draft_b8_kernel_stats.md)
-    ("draft", 1): 1.986 * GIB,
-    ("draft", 8): (1.0018 + 1.0105 + 0.0020 + 0.0332 + 0.0001) * GIB,
+    ("draft", 1): 1.985 * GIB,
+    ("draft", 8): (1.0019 + 1.0105 + 0.0020 + 0.0332 + 0.0001) * GIB,
     ("draft", 64): 5.103 * GIB,
 }
 
@@ -252,7 +252,8 @@ def bench_distill(args):
         "data": "synthetic (teacher logits drawn on the device)",
         "config": {"workload": "distill_7b", "T": cfg.T, "d": cfg.d, "V": cfg.V, "n": cfg.n, "r": cfg.r,
                    "beta": 0.9, "discount": 0.8, "frozen_u": True, "token": "one position (n future tokens each)",
-                   "logits": "kept in HBM between forward and backward" if keep else "never stored (recomputed twice)",
+                   "logits": "kept in HBM between forward and backward" if keep else
+                             "one chunk of positions at a time stored for the mixture, recomputed for the gradients",
                    "ctx_gib": ctx.numel() / GIB},
         "model_tflops": model_flops / (ms_per_step * 1e-3) / 1e12,
         "model_flop_frac_of_bf16_peak": model_flops / (ms_per_step * 1e-3) / 1e12 / PEAK_BF16_TFLOPS,
