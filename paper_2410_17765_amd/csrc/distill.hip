@@ -19,7 +19,7 @@
 // Backward: another product whose epilogue writes dz = c1 P - c3 p^c rho + c2 1[v = x] in bf16; everything
 //           below dz is the training loss's backward pass.
 // With CP_HEAD_KEEP_LOGITS the product of the forward pass keeps its logits (kept_logits.hpp) and both passes read those:
-// k_distill_kl and k_dz_from_kept<DistillDzRule>.
+// k_distill_kl_kept and k_dz_from_kept<DistillDzRule>.
 #include "gemm_nt.hpp"
 #include "kept_logits.hpp"
 
@@ -59,16 +59,20 @@ __device__ __forceinline__ void load8(const float *p, float (&x)[8])
     }
 }
 
-// log-normaliser of every teacher row TZ[g, :], one block per row, its first kTeacherHeld columns held in registers between
-// the maximum and the sum.  HBM bound with eight elements per load; an element at a time the loads themselves were the bound
-// (16384 rows of 32000 bf16: 925 -> 353 us).
-constexpr int kTeacherBlock = 512, kTeacherSteps = 8, kTeacherHeld = kTeacherBlock * 8 * kTeacherSteps;
-template <typename TT>
-__global__ void __launch_bounds__(kTeacherBlock) k_teacher_lse(int V, const TT *__restrict__ TZ, float *__restrict__ tlse)
+// log-normaliser of every teacher row TZ[g, :], one block per row, its first THREADS * 8 * STEPS columns held in registers
+// between the maximum and the sum.  HBM bound with eight elements per load (one element a load: the loads themselves were the bound).
+// The exponentials are added up as 256 threads that walk the row together would add them, column v by thread v % 256,
+// whatever the loads are: the sum is the same fp32 number for every block size.  They meet in LDS for that.
+constexpr int kSumLanes = 256;
+template <typename TT, int THREADS, int STEPS>
+__global__ void __launch_bounds__(THREADS) k_teacher_lse(int V, const TT *__restrict__ TZ, float *__restrict__ tlse)
 {
-    __shared__ float red[kTeacherBlock / kWave];
+    constexpr int CHUNK = THREADS * 8;
+    static_assert(CHUNK % kSumLanes == 0 && THREADS >= kSumLanes, "whole rounds of the summing threads");
+    __shared__ float red[THREADS / kWave];
+    __shared__ __attribute__((aligned(16))) float terms[2][CHUNK];
     const TT *row = TZ + (size_t)blockIdx.x * V;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const auto load = [&](int c, float (&x)[8]) {       // columns past the last one as -inf
         if (c + 8 <= V) {
             load8(row + c, x);
@@ -82,14 +86,16 @@ __global__ void __launch_bounds__(kTeacherBlock) k_teacher_lse(int V, const TT *
         for (int k = 0; k < 8; ++k) mx = fmaxf(mx, x[k]);
         return mx;
     };
-    float held[kTeacherSteps][8], x[8];
+    float held[STEPS][8], x[8];
     float mx = -INFINITY;
 #pragma unroll
-    for (int s = 0; s < kTeacherSteps; ++s) load((s * kTeacherBlock + (int)threadIdx.x) * 8, held[s]);
+    for (int s = 0; s < STEPS; ++s)
+        if (s * CHUNK < V) load(s * CHUNK + tid * 8, held[s]);
 #pragma unroll
-    for (int s = 0; s < kTeacherSteps; ++s) mx = largest(held[s], mx);
-    for (int c = kTeacherHeld + (int)threadIdx.x * 8; c < V; c += kTeacherBlock * 8) {
-        load(c, x);
+    for (int s = 0; s < STEPS; ++s)
+        if (s * CHUNK < V) mx = largest(held[s], mx);
+    for (int c0 = STEPS * CHUNK; c0 < V; c0 += CHUNK) {
+        load(c0 + tid * 8, x);
         mx = largest(x, mx);
     }
     mx = wave_max(mx);
@@ -97,39 +103,96 @@ __global__ void __launch_bounds__(kTeacherBlock) k_teacher_lse(int V, const TT *
     __syncthreads();
     float Mx = red[0];
 #pragma unroll
-    for (int w = 1; w < kTeacherBlock / kWave; ++w) Mx = fmaxf(Mx, red[w]);
-    __syncthreads();
+    for (int w = 1; w < THREADS / kWave; ++w) Mx = fmaxf(Mx, red[w]);
     float l = 0.f;
-    const auto add = [&](int c, const float (&x)[8]) {
-        if (c >= V) return;
+    // two buffers: the terms of the next chunk may be written while these are added up
+    const auto add = [&](int c0, int buffer, const float (&x)[8]) {
+        const int c = c0 + tid * 8;
+        f32x4_t e[2];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) l += c + k < V ? expf(x[k] - Mx) : 0.f;
+        for (int k = 0; k < 8; ++k) e[k >> 2][k & 3] = c + k < V ? expf(x[k] - Mx) : 0.f;
+        *reinterpret_cast<f32x4_t *>(&terms[buffer][tid * 8]) = e[0];
+        *reinterpret_cast<f32x4_t *>(&terms[buffer][tid * 8 + 4]) = e[1];
+        __syncthreads();
+        if (tid >= kSumLanes) return;
+#pragma unroll
+        for (int i = 0; i < CHUNK / kSumLanes; ++i) l += terms[buffer][i * kSumLanes + tid];
     };
 #pragma unroll
-    for (int s = 0; s < kTeacherSteps; ++s) add((s * kTeacherBlock + (int)threadIdx.x) * 8, held[s]);
-    for (int c = kTeacherHeld + (int)threadIdx.x * 8; c < V; c += kTeacherBlock * 8) {
-        load(c, x);
-        add(c, x);
+    for (int s = 0; s < STEPS; ++s)
+        if (s * CHUNK < V) add(s * CHUNK, s & 1, held[s]);
+    int buffer = STEPS & 1;
+    for (int c0 = STEPS * CHUNK; c0 < V; c0 += CHUNK, buffer ^= 1) {
+        load(c0 + tid * 8, x);
+        add(c0, buffer, x);
     }
+    l = wave_sum(l);
+    __syncthreads();                                    // everyone has read the maxima
+    if (lane == 0 && tid < kSumLanes) red[wave] = l;
+    __syncthreads();
+    if (tid == 0) {
+        float L = 0.f;
+#pragma unroll
+        for (int w = 0; w < kSumLanes / kWave; ++w) L += red[w];
+        tlse[blockIdx.x] = Mx + logf(L);
+    }
+}
+// The same for short rows: the 256 threads take an element each, which is the order above by itself.
+template <typename TT>
+__global__ void __launch_bounds__(kSumLanes) k_teacher_lse_short(int V, const TT *__restrict__ TZ, float *__restrict__ tlse)
+{
+    __shared__ float red[kSumLanes / kWave];
+    const TT *row = TZ + (size_t)blockIdx.x * V;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    float mx = -INFINITY;
+    for (int v = threadIdx.x; v < V; v += kSumLanes) mx = fmaxf(mx, ld_f32(row, (size_t)v));
+    mx = wave_max(mx);
+    if (lane == 0) red[wave] = mx;
+    __syncthreads();
+    float Mx = red[0];
+#pragma unroll
+    for (int w = 1; w < kSumLanes / kWave; ++w) Mx = fmaxf(Mx, red[w]);
+    __syncthreads();
+    float l = 0.f;
+    for (int v = threadIdx.x; v < V; v += kSumLanes) l += expf(ld_f32(row, (size_t)v) - Mx);
     l = wave_sum(l);
     if (lane == 0) red[wave] = l;
     __syncthreads();
     if (threadIdx.x == 0) {
         float L = 0.f;
 #pragma unroll
-        for (int w = 0; w < kTeacherBlock / kWave; ++w) L += red[w];
+        for (int w = 0; w < kSumLanes / kWave; ++w) L += red[w];
         tlse[blockIdx.x] = Mx + logf(L);
     }
 }
+// us for an element a load, <256, 4> and <512, 8>:
+//   bf16: 16384 rows of 100 12.2 / 26 / 81, 500 15.1 / 26 / 81, 1000 27.7 / 25.6 / 80, 8000 189 / 69 / 120, 32000 933 / 291 / 364
+//         2000 rows of 500 3.9 / 5.5 / 12.1, 8000 24 / 13 / 17, 16000 46 / 27 / 27, 32000 89 / 51 / 46;  64 rows of 32000 35 / 15 / 9
+//   fp32: 16384 rows of 100 12.2 / 26 / 75, 8000 250 / 90 / 125, 16000 504 / 219 / 194, 32000 1050 / 505 / 339
+template <typename TT>
+void launch_teacher_lse(const cp_head_desc &ds, size_t rows, const TT *TZ, float *tlse, hipStream_t st)
+{
+    if (ds.V <= 512) k_teacher_lse_short<TT><<<(unsigned)rows, kSumLanes, 0, st>>>(ds.V, TZ, tlse);
+    else if (ds.V <= 8192) k_teacher_lse<TT, 256, 4><<<(unsigned)rows, 256, 0, st>>>(ds.V, TZ, tlse);
+    else k_teacher_lse<TT, 512, 8><<<(unsigned)rows, 512, 0, st>>>(ds.V, TZ, tlse);
+}
 
-// k_distill_weights for R experts, a lane per (position, expert): the sums over the experts are R neighbouring lanes
-// (4096 positions, n = 4, R = 8, where a thread walked a position's experts one after the other: 37 -> 7 us).
-template <int R, class F>
-__device__ __forceinline__ float expert_lanes(float v, F f)
+// k_distill_weights for R experts, a lane per (position, expert): the sums over the experts take them from the R neighbouring
+// lanes, first to last as a thread that walks them would (4096 positions, n = 4, R = 8, with such a thread: 37 us).
+template <int R>
+__device__ __forceinline__ float expert_max(float v)
 {
 #pragma unroll
-    for (int off = 1; off < R; off <<= 1) v = f(v, __shfl_xor(v, off, kWave));
+    for (int off = 1; off < R; off <<= 1) v = fmaxf(v, __shfl_xor(v, off, kWave));
     return v;
+}
+template <int R>
+__device__ __forceinline__ float expert_sum(float v)
+{
+    float s = 0.f;
+#pragma unroll
+    for (int a = 0; a < R; ++a) s += __shfl(v, a, R);
+    return s;
 }
 template <int R>
 __global__ void __launch_bounds__(kBlock) k_distill_weights_lanes(size_t Tr, int n, const float *__restrict__ logw, const float *__restrict__ C,
@@ -140,8 +203,6 @@ __global__ void __launch_bounds__(kBlock) k_distill_weights_lanes(size_t Tr, int
     if (id >= Tr) return;
     const size_t t = id / R;
     const int a = (int)(id % R);
-    const auto larger = [](float x, float y) { return fmaxf(x, y); };
-    const auto add = [](float x, float y) { return x + y; };
     float q = logw[id];
     for (int k = 0; k < n; ++k) {
         const size_t g = t * n + k, m = g * R + a;
@@ -152,9 +213,9 @@ __global__ void __launch_bounds__(kBlock) k_distill_weights_lanes(size_t Tr, int
             if (a == 0) ce[g] = 0.f;
             continue;
         }
-        const float mx = expert_lanes<R>(q, larger);
-        const float qn = mx + logf(expert_lanes<R>(expf(q - mx), add));
-        const float p = expf(q - qn + c), px = expert_lanes<R>(p, add);
+        const float mx = expert_max<R>(q);
+        const float qn = mx + logf(expert_sum<R>(expf(q - mx)));
+        const float p = expf(q - qn + c), px = expert_sum<R>(p);
         rowa[m] = make_float2(l, q - qn);
         rhox[m] = p / px;
         if (a == 0) ce[g] = -logf(px);
@@ -506,30 +567,12 @@ __device__ __forceinline__ float log_mixture(const float (&l)[R])
     return mx + __logf(s);
 }
 
-// fp32 logits of a chunk of rows
-struct StoredLogits {
-    const float *z;     // [rows, ld]
-    long ld;            // a multiple of 8
-};
-__device__ __forceinline__ void row_log_probs(const StoredLogits &k, size_t m, int col, float lse, float (&lp)[8])
-{
-    load8(k.z + m * k.ld + col, lp);
-#pragma unroll
-    for (int j = 0; j < 8; ++j) lp[j] -= lse;
-}
-__device__ __forceinline__ void row_log_probs(const KeptLogits &k, size_t m, int col, float lse, float (&lp)[8])
-{
-    kept_log_probs(k, m, col, lse, lp);
-}
-
-// What EpiDistillStats accumulates, from logits in memory: one workgroup per token g, a thread takes 8 columns
-// of the token's R rows at a time; SK[g R + a] = {S_a, KL}.  With the fp32 logits of a chunk it is HBM bound (4 bytes per logit) and,
-// with the store, cheaper than multiplying U y again (the call's second product took 25.2 ms at T = 4096, d = 4096, V = 32000,
-// n = 4, r = 8).
-template <int R, class Logits>
-__global__ void __launch_bounds__(kBlock) k_distill_kl(Logits logits, int V, const float2 *__restrict__ rowa,
-                                                       const bf16_t *__restrict__ TZ, const float *__restrict__ tlse,
-                                                       float2 *__restrict__ SK)
+// What EpiDistillStats accumulates, from the kept logits: one workgroup per token g, a thread takes 8 columns
+// of the token's R rows at a time; SK[g R + a] = {S_a, KL}.
+template <int R>
+__global__ void __launch_bounds__(kBlock) k_distill_kl_kept(KeptLogits kept, int V, const float2 *__restrict__ rowa,
+                                                            const bf16_t *__restrict__ TZ, const float *__restrict__ tlse,
+                                                            float2 *__restrict__ SK)
 {
     __shared__ float red[kBlock / kWave][R + 1];
     const size_t g = blockIdx.x;
@@ -547,7 +590,7 @@ __global__ void __launch_bounds__(kBlock) k_distill_kl(Logits logits, int V, con
     for (int col = (int)threadIdx.x * 8; col < V; col += kBlock * 8) {
         float lp[R][8], tz[8];
 #pragma unroll
-        for (int a = 0; a < R; ++a) row_log_probs(logits, g * R + a, col, lse_[a], lp[a]);
+        for (int a = 0; a < R; ++a) kept_log_probs(kept, g * R + a, col, lse_[a], lp[a]);
         load_teacher8(trow, col, V, tz);
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
@@ -555,21 +598,12 @@ __global__ void __launch_bounds__(kBlock) k_distill_kl(Logits logits, int V, con
             float l[R];
 #pragma unroll
             for (int a = 0; a < R; ++a) l[a] = lp[a][k] + lq_[a];
-            float mx = l[0];
-#pragma unroll
-            for (int a = 1; a < R; ++a) mx = fmaxf(mx, l[a]);
-            float sum = 0.f;
-#pragma unroll
-            for (int a = 0; a < R; ++a) {
-                l[a] = __expf(l[a] - mx);
-                sum += l[a];
-            }
+            const float lm = log_mixture<R>(l);
             const float lpc = tz[k] - tl;
             const float pc = __expf(lpc);
-            kl += pc * (lpc - (mx + __logf(sum)));
-            const float share = pc / sum;
+            kl += pc * (lpc - lm);
 #pragma unroll
-            for (int a = 0; a < R; ++a) S[a] += share * l[a];
+            for (int a = 0; a < R; ++a) S[a] += pc * __expf(l[a] - lm);
         }
     }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -589,6 +623,102 @@ __global__ void __launch_bounds__(kBlock) k_distill_kl(Logits logits, int V, con
             k += red[w][R];
         }
         SK[g * R + threadIdx.x] = make_float2(s, k);
+    }
+}
+
+// What EpiDistillStats and k_sum_parts leave, from a chunk's fp32 logits z[rows, ld] in memory, bit for bit: the same terms, added up
+// in the same order.  A workgroup per token; 16 lanes take a sub-tile of 128 columns as the epilogue's lanes do (lane c the columns
+// 16 j + c), and the sub-tiles p, p + 64, ... of a row are added in order before the 64 sums meet.
+template <int R>
+__device__ __forceinline__ float sum_of_experts(const float (&e)[R])     // as the accumulator registers of a lane are added
+{
+    if (R < 4) return R == 1 ? e[0] : e[0] + e[R - 1];
+    const float s = e[0] + e[1 % R] + e[2 % R] + e[3 % R];
+    return R == 8 ? s + (e[4 % R] + e[5 % R] + e[6 % R] + e[7 % R]) : s;
+}
+// THREADS: 1024, a group of 16 lanes for each of the 64 sums, where a row has sub-tiles for half of them; 256 below.  Whole forward calls, d = 512,
+// us, 256 / 1024: V = 2000, r = 2: 2048 tokens 82 / 87, 8192 141 / 164;  V = 8000, r = 8: 64 tokens 89 / 85, 8192 1365 / 1365;  V = 32000,
+// r = 4: 64 tokens 120 / 96, 1024 418 / 406, 8192 2841 / 2777.
+template <int R, int THREADS>
+__global__ void __launch_bounds__(THREADS) k_distill_kl_stored(const float *__restrict__ z, long ld, int V, const float2 *__restrict__ rowa,
+                                                               const bf16_t *__restrict__ TZ, const float *__restrict__ tlse,
+                                                               float2 *__restrict__ SK)
+{
+    constexpr int kCols = Cfg::WTN, kGroups = THREADS / 16, kRounds = kWave / kGroups;
+    __shared__ float sums[R + 1][kWave];
+    const size_t g = blockIdx.x;
+    const int c16 = threadIdx.x & 15, group = threadIdx.x >> 4;
+    float lse_[R], lq_[R], tot[kRounds][R + 1];
+#pragma unroll
+    for (int a = 0; a < R; ++a) {
+        const float2 ra = rowa[g * R + a];
+        lse_[a] = ra.x;
+        lq_[a] = ra.y;
+    }
+#pragma unroll
+    for (int u = 0; u < kRounds; ++u)
+#pragma unroll
+        for (int a = 0; a <= R; ++a) tot[u][a] = 0.f;
+    const float tl = tlse[g];
+    const bf16_t *trow = TZ + g * (size_t)V;
+    const float *zrow = z + g * R * (size_t)ld;
+    for (int p0 = group; p0 * kCols < V; p0 += kWave) {
+#pragma unroll
+        for (int u = 0; u < kRounds; ++u) {
+            const int col0 = (p0 + u * kGroups) * kCols;
+            if (col0 >= V) continue;                     // whole groups of 16 lanes
+            float zv[R][kCols / 16], tz[kCols / 16];
+            const auto read = [&](auto column) {
+#pragma unroll
+                for (int j = 0; j < kCols / 16; ++j) {
+                    const int col = column(col0 + 16 * j + c16);
+#pragma unroll
+                    for (int a = 0; a < R; ++a) zv[a][j] = zrow[a * (size_t)ld + col];
+                    tz[j] = bf16_to_f32(trow[col]);
+                }
+            };
+            if (col0 + kCols <= V) read([](int col) { return col; });
+            else read([&](int col) { return min(col, V - 1); });
+            float S[R], kl = 0.f;
+#pragma unroll
+            for (int a = 0; a < R; ++a) S[a] = 0.f;
+#pragma unroll
+            for (int j = 0; j < kCols / 16; ++j) {
+                float l[R], e[R], lm;
+#pragma unroll
+                for (int a = 0; a < R; ++a) l[a] = zv[a][j] - lse_[a] + lq_[a];
+                if (R == 1) {
+                    lm = l[0];
+                } else {
+                    float mx = l[0];
+#pragma unroll
+                    for (int a = 1; a < R; ++a) mx = fmaxf(mx, l[a]);
+#pragma unroll
+                    for (int a = 0; a < R; ++a) e[a] = __expf(l[a] - mx);
+                    lm = mx + __logf(sum_of_experts<R>(e));
+                }
+                const float lpc = tz[j] - tl;
+                const float pc = col0 + 16 * j + c16 < V ? __expf(lpc) : 0.f;
+#pragma unroll
+                for (int a = 0; a < R; ++a) S[a] += pc * __expf(l[a] - lm);
+                kl += pc * (lpc - lm);
+            }
+#pragma unroll
+            for (int a = 0; a < R; ++a) tot[u][a] += row16_sum(S[a]);
+            tot[u][R] += row16_sum(kl);
+        }
+    }
+    if (c16 == 0) {
+#pragma unroll
+        for (int u = 0; u < kRounds; ++u)
+#pragma unroll
+            for (int a = 0; a <= R; ++a) sums[a][group + u * kGroups] = tot[u][a];
+    }
+    __syncthreads();
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int a = wave; a < R; a += THREADS / kWave) {
+        const float s = wave_sum(sums[a][lane]), k = wave_sum(sums[R][lane]);
+        if (lane == 0) SK[g * R + a] = make_float2(s, k);
     }
 }
 
@@ -740,7 +870,7 @@ void launch_kl_kept(const cp_head_desc &ds, const KeptLogits &kept, const float2
     const size_t Tn = (size_t)ds.T * ds.n;
     // algorithmic traffic: kept logits and teacher logits read once
     ProfileScope scope("distill_kl_kept", ((double)Tn * R * kept.ld + (double)Tn * ds.V) * 2.0, st);
-    k_distill_kl<R><<<(unsigned)Tn, kBlock, 0, st>>>(kept, ds.V, rowa, TZ, tlse, SK);
+    k_distill_kl_kept<R><<<(unsigned)Tn, kBlock, 0, st>>>(kept, ds.V, rowa, TZ, tlse, SK);
 }
 
 struct StoredKlArgs {
@@ -761,7 +891,9 @@ void stored_kl(void *user, const FastFwdBuffers &b, size_t t0, size_t P, const f
     k_distill_weights_lanes<R><<<blocks_for(P * R, kBlock), kBlock, 0, st>>>(P * R, n, b.logw + t0 * R, b.C + m0, b.lse + m0, a->X + g0,
                                                                              a->rowa + m0, a->rhox + m0, a->ce + g0);
     ProfileScope scope("distill_kl_stored", (double)tokens * (R * ldz * 4.0 + V * 2.0), st);
-    k_distill_kl<R><<<(unsigned)tokens, kBlock, 0, st>>>(StoredLogits{z, ldz}, V, a->rowa + m0, a->TZ + g0 * V, a->tlse + g0, a->SK + m0);
+    const bool wide = V > kWave * Cfg::WTN / 2;
+    auto kernel = wide ? k_distill_kl_stored<R, 1024> : k_distill_kl_stored<R, 256>;
+    kernel<<<(unsigned)tokens, wide ? 1024 : 256, 0, st>>>(z, ldz, V, a->rowa + m0, a->TZ + g0 * V, a->tlse + g0, a->SK + m0);
 }
 
 struct DistillKeptArgs {
@@ -794,7 +926,7 @@ int mfma_distill_fwd(const cp_head_desc &ds, const void *H, const void *W, const
     float2 *SK = at<float2>(ws, f.SK), *part = at<float2>(ws, f.part);
     FastFwdBuffers fb;
 
-    k_teacher_lse<bf16_t><<<(unsigned)Tn, kTeacherBlock, 0, st>>>(ds.V, TZ, tlse);
+    launch_teacher_lse(ds, Tn, TZ, tlse, st);
     if (stores_logits(ds)) {
         StoredKlArgs args{&ds, X, TZ, tlse, rowa, SK, rhox, ce};
         FastStoredRows fn = ds.r == 1 ? stored_kl<1> : ds.r == 2 ? stored_kl<2> : ds.r == 4 ? stored_kl<4> : stored_kl<8>;
@@ -1000,7 +1132,7 @@ int plain_distill_fwd(const cp_head_desc &ds, const void *H, const void *W, cons
     float *tlse = at<float>(ctx, dc.tlse), *dgsum = at<float>(ctx, dc.dgsum);
     float *rhox = at<float>(ws, f.rhox), *ce = at<float>(ws, f.ce), *zc = at<float>(ws, f.zc);
     float2 *SK = at<float2>(ws, f.SK);
-    k_teacher_lse<TT><<<(unsigned)Tn, kTeacherBlock, 0, st>>>(ds.V, TZ, tlse);
+    launch_teacher_lse(ds, Tn, TZ, tlse, st);
     k_distill_weights<kMaxRank><<<blocks_for(T, kBlock), kBlock, 0, st>>>(T, ds.n, ds.r, fb.logw, fb.C, fb.lse, X, rowa,
                                                                           rhox, ce);
     const size_t chunk = generic_bwd_chunk_rows(ds);
