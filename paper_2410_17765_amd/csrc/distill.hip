@@ -401,7 +401,7 @@ struct EpiDistillStats {
                 lse_[jj] = ri.x;
                 lq_[jj] = ri.y;
                 tl_[jj] = ri.z;
-                trow_[jj] = (size_t)(rc / R) * V;
+                trow_[jj] = teacher_row_start(rc / R, V);
             }
             float S[4] = {0.f, 0.f, 0.f, 0.f}, KL[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -444,7 +444,7 @@ struct EpiDzDistill {
     long ldz;
     const float4 *rowinfo;   // chunk-relative [Mc] {lse, log qhat, c1, c2} (upstream gradient folded in)
     const float4 *grp;       // chunk-relative [Mc / R] {tlse, c3, target as int bits, -}
-    const bf16_t *TZ;        // chunk-relative [Mc / R, V]; Mc / R * V < 2^31
+    const bf16_t *TZ;        // chunk-relative [Mc / R, V], which may hold 2^31 elements and more
     int Mc, Mcp, V, Vp;      // the rows from Mc up to Mcp are zeroed
     template <class C>
     __device__ void run(f32x4_t (&acc)[C::TM16][C::TN16], int row0, int col0, int lane, int wave, int, char *smem) const
@@ -486,7 +486,6 @@ struct EpiDzDistill {
     __device__ __forceinline__ void convert(f32x4_t (&acc)[C::TM16][C::TN16], int row0, int col0, int lane,
                                             const float4 *winfo, const float4 *wgrp) const
     {
-        const bf16_t *__restrict__ tz = TZ;
 #pragma unroll
         for (int i = 4 * IP; i < 4 * IP + 4; ++i) {
             const int lbase = 16 * i + 4 * (lane >> 4);      // first of the lane's four rows, in the sub-tile
@@ -502,7 +501,8 @@ struct EpiDzDistill {
                 c2_[jj] = row < Mc ? ri.w : 0.f;
             }
             float tl_[NG], c3_[NG];
-            int x_[NG], toff_[NG];
+            int x_[NG];
+            const bf16_t *__restrict__ trow_[NG];
 #pragma unroll
             for (int gi = 0; gi < NG; ++gi) {
                 const int row = rbase + gi * RG;
@@ -511,7 +511,7 @@ struct EpiDzDistill {
                 tl_[gi] = gv.x;
                 c3_[gi] = row < Mc ? gv.y : 0.f;
                 x_[gi] = __float_as_int(gv.z);
-                toff_[gi] = g * V;
+                trow_[gi] = TZ + teacher_row_start(g, V);
             }
 #pragma unroll
             for (int j = 0; j < C::TN16; ++j) {
@@ -524,7 +524,7 @@ struct EpiDzDistill {
                 group_log_mixture<R>(l, lm);
 #pragma unroll
                 for (int gi = 0; gi < NG; ++gi) {
-                    const float lpc = bf16_to_f32(tz[toff_[gi] + cc]) - tl_[gi];
+                    const float lpc = bf16_to_f32(trow_[gi][cc]) - tl_[gi];
 #pragma unroll
                     for (int e = 0; e < RG; ++e) {
                         const int jj = gi * RG + e;
@@ -735,12 +735,12 @@ struct DistillDzRule {
 #pragma unroll
         for (int gi = 0; gi < RT / R; ++gi) {
             if (gi * R >= nrows) continue;
-            const size_t tok = (size_t)(row / R + gi);
+            const int tok = row / R + gi;
             const float4 gv = grp[tok];
             const float tl = gv.x, c3 = gv.y;
             const int x = __float_as_int(gv.z) - col;
             float tz[8];
-            load_teacher8(TZ + tok * (size_t)V, col, V, tz);
+            load_teacher8(TZ + teacher_row_start(tok, V), col, V, tz);
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
                 if (col + k >= V) continue;

@@ -1122,26 +1122,10 @@ inline SplitScratch split_scratch(void *ws, size_t off, size_t bytes)
     return s;
 }
 
-// Rows of logit gradients held at a time: about 4 GiB of bf16 at V = 32000, i.e. 65536 rows.  Measured on the
-// headline step: 2 GiB 450.4 ms, 4 GiB 447.9, 8 GiB 448.3 (the dU product gains from fewer accumulation passes
-// over its fp32 output, the dz product loses about half of that).  A larger vocabulary keeps at least 32768
-// rows, up to 8 GiB of them: the rows of a chunk are the contraction length of its dU product, and at 8192 rows
-// (2 GiB at V = 128256) that product ran at 1.08 PFLOP/s against 1.25 at 32768.  The count is a multiple of 16
-// tiles of 256 rows where possible, so that the d-wide products of a chunk (16 tile columns at d = 4096) fill
-// all 256 compute units in whole rounds.
 inline size_t bwd_chunk_rows(const cp_head_desc &ds)
 {
-    const size_t M = (size_t)ds.T * ds.n * ds.r;
-    const size_t Vp = round_up((size_t)ds.V, 64);
-    size_t rows = ((size_t)1 << 32) / (Vp * 2);
-    if (rows < 32768) {
-        const size_t cap = ((size_t)1 << 33) / (Vp * 2);
-        rows = cap < 32768 ? cap : 32768;
-    }
-    if (rows >= 16 * (size_t)Cfg::BM) rows = rows / (16 * Cfg::BM) * (16 * Cfg::BM);
-    else rows = rows / Cfg::BM * Cfg::BM;
-    if (rows < (size_t)Cfg::BM || (ds.flags & CP_HEAD_MIN_WORKSPACE)) rows = Cfg::BM;
-    return rows < M ? rows : (M ? M : 1);
+    static_assert(Cfg::BM == 256, "the tile of backward_chunk_rows");
+    return backward_chunk_rows((size_t)ds.T * ds.n * ds.r, round_up((size_t)ds.V, 64), (ds.flags & CP_HEAD_MIN_WORKSPACE) != 0);
 }
 
 // The pair of loss calls and the single call add up every row's y and dY in the same order, so these two are split along K

@@ -95,3 +95,28 @@ CPH_HD size_t blocked64_index(size_t row, int col, long ld)
 {
     return ((row >> 8) * (size_t)(ld >> 6) + (size_t)(col >> 6)) * 16384 + (row & 255) * 64 + (size_t)(col & 63);
 }
+
+// Rows of logit gradients held at a time: about 4 GiB of bf16 at V = 32000, i.e. 65536 rows.  Measured on the
+// headline step: 2 GiB 450.4 ms, 4 GiB 447.9, 8 GiB 448.3 (the dU product gains from fewer accumulation passes
+// over its fp32 output, the dz product loses about half of that).  A larger vocabulary keeps at least 32768
+// rows, up to 8 GiB of them: the rows of a chunk are the contraction length of its dU product, and at 8192 rows
+// (2 GiB at V = 128256) that product ran at 1.08 PFLOP/s against 1.25 at 32768.  The count is a multiple of 16
+// tiles of 256 rows where possible, so that the d-wide products of a chunk (16 tile columns at d = 4096) fill
+// all 256 compute units in whole rounds.  M: all rows; Vp: the vocabulary rounded up to 64; least: one tile of rows.
+inline size_t backward_chunk_rows(size_t M, size_t Vp, bool least)
+{
+    constexpr size_t kTile = 256;
+    size_t rows = ((size_t)1 << 32) / (Vp * 2);
+    if (rows < 32768) {
+        const size_t cap = ((size_t)1 << 33) / (Vp * 2);
+        rows = cap < 32768 ? cap : 32768;
+    }
+    if (rows >= 16 * kTile) rows = rows / (16 * kTile) * (16 * kTile);
+    else rows = rows / kTile * kTile;
+    if (rows < kTile || least) rows = kTile;
+    return rows < M ? rows : (M ? M : 1);
+}
+
+// First element of a token's row in the teacher logits [tokens, V] of a chunk: in 64 bits, because the tokens of a chunk are its
+// rows over r, and 32768 rows of one expert times V pass 2^31 from V = 65537 on.
+CPH_HD size_t teacher_row_start(int token, int V) { return (size_t)token * (size_t)V; }
