@@ -509,8 +509,8 @@ struct GatePickSide {
 // Log-normaliser (eq. 5) of one row from its per-segment statistics, by one wavefront.
 __device__ __forceinline__ float row_lse_from_parts(const float2 *__restrict__ pm, int parts, int lane)
 {
-    // many independent loads per lane and step: a step is a memory latency and a link of the chain of rescalings (32 rows of
-    // 2004 segments, the draft call's at V = 128256: four loads a step 10.5 us for k_draft_lse_segment, sixteen 9.2)
+    // many independent loads per lane and step, since a step is a memory latency (32 rows of 2004 segments, the draft call's at
+    // V = 128256: four loads a step 10.5 us for k_draft_lse_segment, sixteen 9.2); they are added up four at a time whatever the step is
     float mx = -INFINITY, l = 0.f;
     auto step = [&](int p0, auto loads) {
         constexpr int N = decltype(loads)::value;
@@ -520,16 +520,17 @@ __device__ __forceinline__ float row_lse_from_parts(const float2 *__restrict__ p
             const int p = p0 + i * kWave + lane;
             qv[i] = p < parts ? pm[p] : make_float2(-INFINITY, 0.f);
         }
-        float most = qv[0].x;
 #pragma unroll
-        for (int i = 1; i < N; ++i) most = fmaxf(most, qv[i].x);
-        if (most == -INFINITY) return;
-        const float mn = fmaxf(mx, most);
-        float add = 0.f;
+        for (int i = 0; i < N; i += 4) {
+            const float m4 = fmaxf(fmaxf(qv[i].x, qv[i + 1].x), fmaxf(qv[i + 2].x, qv[i + 3].x));
+            if (m4 == -INFINITY) continue;
+            const float mn = fmaxf(mx, m4);
+            float add = 0.f;
 #pragma unroll
-        for (int i = 0; i < N; ++i) add += qv[i].y * __expf(qv[i].x - mn);     // exp(-inf) = 0 for empty segments
-        l = l * __expf(mx - mn) + add;
-        mx = mn;
+            for (int e = i; e < i + 4; ++e) add += qv[e].y * __expf(qv[e].x - mn);     // exp(-inf) = 0 for empty segments
+            l = l * __expf(mx - mn) + add;
+            mx = mn;
+        }
     };
     int p0 = 0;
     for (; parts - p0 > 4 * kWave; p0 += 16 * kWave) step(p0, std::integral_constant<int, 16>());
