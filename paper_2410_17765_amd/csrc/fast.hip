@@ -127,7 +127,8 @@ __device__ __forceinline__ void row_max(const f32x4_t (&acc)[C::TN16], float &mx
 // Running statistics of the logits (eq. 5 in log space): for every row of the wavefront's
 // sub-tile the maximum and the sum of exp(z - max) over its columns.  One (max, sum) pair per
 // row and per (tile column, wavefront column) goes to `part`; the logits themselves are dropped.
-// A row of the sub-tile lives in the four lanes l % 16 + 16 k; the first of them writes the pair.
+// A row of the sub-tile lives in the four lanes l % 16 + 16 k; the first of them writes the pair.  Where no column counts the maximum is
+// -infinity and the sum 0; if the columns were NaN, which no maximum shows, it is NaN, and so is the row's log-normaliser.
 struct EpiRowStats {
     float2 *part;   // [M, parts]
     int parts;      // tiles_n * WN
@@ -147,7 +148,7 @@ struct EpiRowStats {
                 for (int v = 0; v < 4; ++v) s[v] += __expf(acc[i][j][v] - ref);
             const float sum = groups_sum((s[0] + s[1]) + (s[2] + s[3]));
             const int r = row0 + acc_row(i, lane);
-            if (lane < 16 && r < M) part[(size_t)r * parts + slot] = make_float2(mx, (mx == -INFINITY) ? 0.f : sum);
+            if (lane < 16 && r < M) part[(size_t)r * parts + slot] = make_float2(mx, sum);
             __builtin_amdgcn_sched_barrier(0);      // one block row at a time: more of them spill registers
         }
     }
@@ -190,7 +191,7 @@ struct EpiRowStatsKeep {
             out.put(i, w, streamed != 0);
             const float sum = groups_sum((s[0] + s[1]) + (s[2] + s[3]));
             const int r = row0 + acc_row(i, lane);
-            if (lane < 16 && r < M) part[(size_t)r * parts + slot] = make_float2(mx, (mx == -INFINITY) ? 0.f : sum);
+            if (lane < 16 && r < M) part[(size_t)r * parts + slot] = make_float2(mx, sum);
             __builtin_amdgcn_sched_barrier(0);      // one block row at a time: more of them spill registers
         }
     }
@@ -221,7 +222,7 @@ struct EpiRowStatsStore {
                 for (int v = 0; v < 4; ++v) s[v] += __expf(acc[i][j][v] - ref);
             const float sum = groups_sum((s[0] + s[1]) + (s[2] + s[3]));
             const int r = row0 + acc_row(i, lane);
-            if (lane < 16 && r < M) part[(size_t)r * parts + slot] = make_float2(mx, (mx == -INFINITY) ? 0.f : sum);
+            if (lane < 16 && r < M) part[(size_t)r * parts + slot] = make_float2(mx, sum);
             __builtin_amdgcn_sched_barrier(0);
         }
     }
@@ -402,9 +403,10 @@ __global__ void __launch_bounds__(kBlock) k_row_finish(size_t M, int d, int r, i
             const float2 q = part[m * parts + p];
             if (q.x > mx) { l = l * __expf(mx - q.x) + q.y; mx = q.x; }
             else if (q.x != -INFINITY) l += q.y * __expf(q.x - mx);
+            else l += q.y;                                   // no valid column: 0, or the NaN it had
         }
         const float Mx = wave_max(mx);
-        const float L = wave_sum(mx == -INFINITY ? 0.f : l * __expf(mx - Mx));
+        const float L = wave_sum(mx == -INFINITY ? l : l * __expf(mx - Mx));
         lse = Mx + logf(L);
         if (lane == 0) lse_io[m] = lse;
     } else {
@@ -523,7 +525,10 @@ __device__ __forceinline__ float row_lse_from_parts(const float2 *__restrict__ p
 #pragma unroll
         for (int i = 0; i < N; i += 4) {
             const float m4 = fmaxf(fmaxf(qv[i].x, qv[i + 1].x), fmaxf(qv[i + 2].x, qv[i + 3].x));
-            if (m4 == -INFINITY) continue;
+            if (m4 == -INFINITY) {                           // no valid columns: zeros, or the NaN they had
+                l += (qv[i].y + qv[i + 1].y) + (qv[i + 2].y + qv[i + 3].y);
+                continue;
+            }
             const float mn = fmaxf(mx, m4);
             float add = 0.f;
 #pragma unroll
@@ -536,7 +541,7 @@ __device__ __forceinline__ float row_lse_from_parts(const float2 *__restrict__ p
     for (; parts - p0 > 4 * kWave; p0 += 16 * kWave) step(p0, std::integral_constant<int, 16>());
     if (p0 < parts) step(p0, std::integral_constant<int, 4>());
     const float Mx = wave_max(mx);
-    const float L = wave_sum(mx == -INFINITY ? 0.f : l * __expf(mx - Mx));
+    const float L = wave_sum(mx == -INFINITY ? l : l * __expf(mx - Mx));
     return Mx + logf(L);
 }
 
@@ -1410,7 +1415,7 @@ __global__ void __launch_bounds__(kStreamZBlock, StreamZ<NG>::WAVES_PER_SIMD) k_
         const float mx = row16_max(fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])));
         const float ref = mx == -INFINITY ? 0.f : mx;
         const float sum = row16_sum((__expf(v[0] - ref) + __expf(v[1] - ref)) + (__expf(v[2] - ref) + __expf(v[3] - ref)));
-        if ((threadIdx.x & 15) == 0 && seg < parts) part[(size_t)r * parts + seg] = make_float2(mx, mx == -INFINITY ? 0.f : sum);
+        if ((threadIdx.x & 15) == 0 && seg < parts) part[(size_t)r * parts + seg] = make_float2(mx, sum);
     }
 }
 // Where it is the faster one (whole first-token calls on cold weights, us, tiles / this, r = 8 unless given):
