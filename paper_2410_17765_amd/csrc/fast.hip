@@ -792,9 +792,7 @@ __global__ void __launch_bounds__(kBlock) k_lse_from_parts(size_t rows, int part
 }
 
 // logp[b, v] = logsumexp_a(log w_a + z[(b, a), v] - lse[(b, a)]) (eq. 11) for 256 tokens of one b, from the stored first-head logits and
-// the per-segment statistics of their rows: every workgroup forms the r log-normalisers by itself, which takes kMixPairs pairs
-// of them at most and saves the call a launch.
-constexpr int kMixPairs = 4096;
+// the per-segment statistics of their rows: every workgroup forms the r log-normalisers by itself, which saves the call a launch.
 __global__ void __launch_bounds__(kBlock) k_first_token_from_parts(int V, int r, int parts, size_t ld, const float *__restrict__ z,
                                                                    const float2 *__restrict__ part, const float *__restrict__ logw,
                                                                    float *__restrict__ logp)
@@ -1505,6 +1503,28 @@ inline DraftWs draft_ws(const cp_head_desc &ds, bool sequential)
     return f;
 }
 
+// Whether the mixture forms the log-normalisers itself: all its workgroups read all pairs of a b's statistics, kMixPairs of them at most
+// (they are a chain in the workgroup) and kMixReads over the launch.  Whole calls on cold weights, us, a launch of their own / in the mixture:
+//   B = 1, d = 512, r = 8: V = 4000 23.3 / 21.4, 32000 (4000 pairs, 0.5 M reads) 27.2 / 25.7, 128256 (16032 pairs) 43.6 / 44.7; r = 64, V = 32000
+//   (32000 pairs) 86.8 / 101;  B = 4, d = 1024, r = 8, V = 32000 (2.0 M) 37.8 / 37.3;  B = 17, r = 1: V = 32000 (1.1 M) 48.3 / 48.3, 50000 (2.6 M)
+//   52.6 / 53.2, 65000 (4.4 M) 58.4 / 60.4;  B = 64, r = 1: d = 1024, V = 32000 (4.0 M) 53.7 / 57.9, d = 64, V = 128256 (64 M) 40.3 / 75.9
+constexpr long kMixPairs = 4096, kMixReads = 1 << 21;
+inline bool mix_from_parts(long B, long V, long r, long parts)
+{
+    return r * parts <= kMixPairs && B * (long)blocks_for((size_t)V, kBlock) * r * parts <= kMixReads;
+}
+
+// Whether the mixture forms the log-normalisers itself: all its workgroups read all pairs of a b's statistics, kMixPairs of them at most
+// (they are a chain in the workgroup) and kMixReads over the launch.  Whole calls on cold weights, us, a launch of their own / in the mixture:
+//   B = 1, d = 512, r = 8: V = 4000 23.3 / 21.4, 32000 (4000 pairs, 0.5 M reads) 27.2 / 25.7, 128256 (16032 pairs) 43.6 / 44.7; r = 64, V = 32000
+//   (32000 pairs) 86.8 / 101;  B = 4, d = 1024, r = 8, V = 32000 (2.0 M) 37.8 / 37.3;  B = 17, r = 1: V = 32000 (1.1 M) 48.3 / 48.3, 50000 (2.6 M)
+//   52.6 / 53.2, 65000 (4.4 M) 58.4 / 60.4;  B = 64, r = 1: d = 1024, V = 32000 (4.0 M) 53.7 / 57.9, d = 64, V = 128256 (64 M) 40.3 / 75.9
+constexpr long kMixPairs = 4096, kMixReads = 1 << 21;
+inline bool mix_from_parts(long B, long V, long r, long parts)
+{
+    return r * parts <= kMixPairs && B * (long)blocks_for((size_t)V, kBlock) * r * parts <= kMixReads;
+}
+
 struct FirstTokenWs {
     size_t logw, Y, z, lse, part, total;
     size_t V4;
@@ -1966,7 +1986,7 @@ int fast_first_token(const cp_head_desc &ds, const void *Hv, const void *Wv, con
     float2 *part = at<float2>(ws, f.part);
     launch_z_stats("first_gemm_z", Y, d, rows, U, V, part, f.parts, z, (long)V4, st);
     ProfileScope prof("first_mix", (double)rows * V * 4 + (double)B * V * 4, st);
-    if (r * f.parts <= kMixPairs) {
+    if (mix_from_parts(B, V, r, f.parts)) {
         k_first_token_from_parts<<<dim3((unsigned)B, blocks_for((size_t)V, kBlock)), kBlock, 0, st>>>(V, r, f.parts, (size_t)V4, z, part, logw,
                                                                                                      logp);
     } else {
