@@ -1514,17 +1514,6 @@ inline bool mix_from_parts(long B, long V, long r, long parts)
     return r * parts <= kMixPairs && B * (long)blocks_for((size_t)V, kBlock) * r * parts <= kMixReads;
 }
 
-// Whether the mixture forms the log-normalisers itself: all its workgroups read all pairs of a b's statistics, kMixPairs of them at most
-// (they are a chain in the workgroup) and kMixReads over the launch.  Whole calls on cold weights, us, a launch of their own / in the mixture:
-//   B = 1, d = 512, r = 8: V = 4000 23.3 / 21.4, 32000 (4000 pairs, 0.5 M reads) 27.2 / 25.7, 128256 (16032 pairs) 43.6 / 44.7; r = 64, V = 32000
-//   (32000 pairs) 86.8 / 101;  B = 4, d = 1024, r = 8, V = 32000 (2.0 M) 37.8 / 37.3;  B = 17, r = 1: V = 32000 (1.1 M) 48.3 / 48.3, 50000 (2.6 M)
-//   52.6 / 53.2, 65000 (4.4 M) 58.4 / 60.4;  B = 64, r = 1: d = 1024, V = 32000 (4.0 M) 53.7 / 57.9, d = 64, V = 128256 (64 M) 40.3 / 75.9
-constexpr long kMixPairs = 4096, kMixReads = 1 << 21;
-inline bool mix_from_parts(long B, long V, long r, long parts)
-{
-    return r * parts <= kMixPairs && B * (long)blocks_for((size_t)V, kBlock) * r * parts <= kMixReads;
-}
-
 struct FirstTokenWs {
     size_t logw, Y, z, lse, part, total;
     size_t V4;
