@@ -1416,22 +1416,28 @@ __global__ void __launch_bounds__(kStreamZBlock, StreamZ<NG>::WAVES_PER_SIMD) k_
         if ((threadIdx.x & 15) == 0 && seg < parts) part[(size_t)r * parts + seg] = make_float2(mx, sum);
     }
 }
-// Where it is the faster one (whole first-token calls on cold weights, us, tiles / this, r = 8 unless given):
-//   up to 16 rows: T = 1: d 2048 V 32000 69.6 / 52.7; d 4096 V 32000 147 / 118; d 4096 V 128256 264 / 270; d 1024 V 128256 r 2 62.6 / 57.4
-//                  T = 4: d 1536 V 128000 r 4 96.9 / 100.5          T = 2: d 1024 V 16000 37.5 / 21.3; d 2048 V 64000 94 / 80
-//   up to 32 rows: T = 4: d 2048 V 32000 69.5 / 55.8; d 4096 V 32000 152 / 124; d 4096 V 128256 274 / 289
-//                  T = 8: d 2048 V 50000 r 4 78 / 73
-// (Tiles with EpiStoreF32 and a pass over the logits for their statistics.)  Draft calls (tiles with EpiRowStats): T = 1, n = 4, r = 8: d 2048
-// V 32000 110 / 99.6; T = 1, n = 4, r = 4: d 1024 V 16000 42.4 / 30.1; T = 16, n = r = 1: d 2048 V 32000 68.6 / 50.8; T = 4, n = 2, r = 4: d 2048
-// V 50000 86 / 84.5.  From about 300 tiles of 256 columns on the tiles
-// have the loads in flight that the stream has, and read Y less often.
+// Where it is the faster one (whole calls on cold weights, us, tiles / this, first token with r = 8 unless given):
+//   up to 16 rows, two workgroups of 64 columns per compute unit: T = 1: d 512 V 32000 25.7 / 19.0; d 1024 V 33000 37.5 / 30.5, V 50000 39.8 / 36.4,
+//     V 65000 43.6 / 40.8; d 2048 V 16000 57 / 37, V 65000 94 / 79; d 4096 V 32000 138 / 114, V 65000 186 / 168; draft T = 2, d 1024, V 33000 40.9 / 38.0
+//   up to 32 rows, one workgroup of 128 columns per compute unit, so that 32768 columns are a round: T = 4: d 512 V 4000 22.0 / 17.6, V 32000 26.6 / 23.1,
+//     V 33000 27.3 / 29.3, V 65000 33.2 / 34.5; d 1024 V 32000 37.3 / 31.4, V 33000 38.4 / 42.0, V 50000 42.9 / 44.5, V 65000 47.3 / 49.2; d 2048 V 32000
+//     65.2 / 55.2, V 33000 65.1 / 72.8, V 50000 79.5 / 79.4, V 65000 97 / 89; d 4096 V 33000 144 / 155, V 50000 165 / 163, V 65000 193 / 179;
+//     draft T = 4: d 1024 V 16000 39 / 34, V 33000 43.9 / 47.5, V 65000 50 / 53; d 2048 V 65000 98 / 93; d 4096 V 65000 200 / 185
+// From about 65536 columns on the tiles have the loads in flight that the stream has, and read Y less often.  Beyond one round it needs wide
+// rows, and rounds that are seven eighths full (V 50000 on weights that the caches hold: d 2048 62.4 / 67.4).
 constexpr int kStreamZRows = 32, kStreamZMost = 65536;
-inline bool stream_z(int rows, int V) { return rows <= kStreamZRows && V <= kStreamZMost; }
+inline bool stream_z(int rows, int V, int d)
+{
+    if (rows > kStreamZRows || V > kStreamZMost) return false;
+    if (rows <= 16) return true;
+    const int groups = (V + StreamZ<2>::COLS - 1) / StreamZ<2>::COLS, rounds = (groups + 255) / 256;
+    return rounds == 1 || (d >= 2048 && groups * 8 >= rounds * 256 * 7);
+}
 
 // statistics segments (pairs per row, columns per segment) of the z product of a draft-type call
-inline void z_segments(int rows, int V, int &parts, int &seg_cols)
+inline void z_segments(int rows, int V, int d, int &parts, int &seg_cols)
 {
-    if (stream_z(rows, V)) {
+    if (stream_z(rows, V, d)) {
         parts = (V + kStreamZSeg - 1) / kStreamZSeg;
         seg_cols = kStreamZSeg;
     } else if (rows <= kSkinnyRows) {
@@ -1450,7 +1456,7 @@ inline void launch_z_stats(const char *name, const bf16_t *Y, int d, int rows, c
         if (rows <= kSkinnyRows) launch_gemm_nt<CfgSkinny>(name, Y, d, rows, U, d, V, d, epi, st, kSkinnyRows / CfgSkinny::BM);
         else launch_gemm_nt<Cfg>(name, Y, d, rows, U, d, V, d, epi, st);
     };
-    if (stream_z(rows, V)) {
+    if (stream_z(rows, V, d)) {
         ProfileScope prof(name, 2.0 * (double)rows * V * d, st);
         if (rows <= 16) k_stream_z<1><<<blocks_for(V, StreamZ<1>::COLS), kStreamZBlock, 0, st>>>(Y, rows, d, U, V, z, ldz, part, parts);
         else k_stream_z<2><<<blocks_for(V, StreamZ<2>::COLS), kStreamZBlock, 0, st>>>(Y, rows, d, U, V, z, ldz, part, parts);
@@ -1530,7 +1536,7 @@ inline FirstTokenWs first_token_ws(const cp_head_desc &ds)
     f.Y = take(rows * ds.d * 2);
     f.z = take(rows * f.V4 * 4);
     f.lse = take(rows * 4);
-    z_segments((int)rows, ds.V, f.parts, f.seg_cols);
+    z_segments((int)rows, ds.V, ds.d, f.parts, f.seg_cols);
     f.part = take(rows * f.parts * sizeof(float2));
     f.total = off;
     return f;
@@ -1925,7 +1931,7 @@ int fast_draft(const cp_head_desc &ds, const void *Hv, const void *Wv, const voi
     launch_y_with_gate("draft_gemm_y", ds, H, W, G, uniforms, Y, logw, alpha, n * r, st);
     // z = U y for all B*n*r rows with running statistics; streams U once, logits are not stored
     int parts, seg_cols;
-    z_segments((int)M, V, parts, seg_cols);
+    z_segments((int)M, V, d, parts, seg_cols);
     launch_z_stats("draft_gemm_z", Y, d, (int)M, U, V, part, parts, nullptr, 0, st);
     {
         ProfileScope prof("draft_lse_segment", (double)M * parts * 8, st);
@@ -1999,7 +2005,7 @@ int fast_draft_sequential(const cp_head_desc &ds, const void *Hv, const void *Wv
     float2 *part = at<float2>(ws, f.part);
     launch_y_with_gate("seq_gemm_y", ds, H, W, G, nullptr, Y, logw, nullptr, n * r, st);          // y and the gate (eq. 7)
     int parts, seg_cols;
-    z_segments((int)M, V, parts, seg_cols);
+    z_segments((int)M, V, d, parts, seg_cols);
     launch_z_stats("seq_gemm_z", Y, d, (int)M, U, V, part, parts, nullptr, 0, st);
     // A draw is two launches: a workgroup per row for everything but the logits of the segment, which many share.
     // (One launch with a workgroup per row for all draws fetched them on one
