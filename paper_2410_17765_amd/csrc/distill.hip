@@ -915,6 +915,7 @@ int mfma_distill_fwd(const cp_head_desc &ds, const void *H, const void *W, const
                      hipStream_t st)
 {
     if (ds.T == 0) return CP_HEAD_OK;
+    if (!fast_dims_fit(ds)) return CP_HEAD_ERR_UNSUPPORTED;         // before anything is launched
     const bf16_t *U = (const bf16_t *)Uv, *TZ = (const bf16_t *)TZv;
     const DistillCtx dc = distill_ctx(ds);
     const DistillFwdWs f = distill_fwd_ws(ds);
