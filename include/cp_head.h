@@ -306,8 +306,9 @@ int cp_head_full_loss_bwd(const cp_head_desc *desc,
  * (dU = NULL for the frozen unembedding of fine tuning).  Every entry of TZ must be finite, also in the
  * rows of dropped tokens.  For bf16 storage with d a multiple of 64 and r in {1, 2, 4, 8} the forward call
  * passes over the fp32 logits of a chunk of positions (at most 3 GiB of them, or one tile of 256 rows, in the
- * workspace; none with CP_HEAD_MIN_WORKSPACE: then the mixture over the experts is formed inside the tiles of a
- * second vocabulary-sized product), and the backward call forms the mixture inside the tiles of its product
+ * workspace; none with CP_HEAD_MIN_WORKSPACE, and none in a workspace that has no room for them but for the statistics of a
+ * second vocabulary-sized product, 8 bytes per row and 128 columns: then the mixture over the experts is formed inside
+ * the tiles of that product, with the same results bit for bit), and the backward call forms the mixture inside the tiles of its product
  * (with CP_HEAD_KEEP_LOGITS the product of the forward call keeps its logits in ctx and both calls pass over
  * those).  Every other shape and fp32 storage
  * run on the plain fp32 path, which keeps the fp32 logits of one chunk of rows at a time in the workspace.

@@ -397,8 +397,8 @@ int cp_head_distill_loss_fwd(const cp_head_desc *desc, const void *H, const void
     if (!(beta >= 0.f && beta <= 1.f) || !(discount >= 0.f)) return CP_HEAD_ERR_INVALID_ARG;
     if (!ctx || !workspace || misaligned(ctx) || misaligned(workspace)) return CP_HEAD_ERR_INVALID_ARG;
     if (!distill_shape_supported(*desc)) return CP_HEAD_ERR_UNSUPPORTED;
-    if (workspace_bytes < workspace_need(*desc, CP_HEAD_OP_DISTILL_FWD)) return CP_HEAD_ERR_WORKSPACE;
-    return distill_loss_fwd(*desc, H, W, U, G, X, TZ, beta, discount, loss, ctx, workspace,
+    if (!distill_fwd_fits(*desc, workspace_bytes)) return CP_HEAD_ERR_WORKSPACE;
+    return distill_loss_fwd(*desc, H, W, U, G, X, TZ, beta, discount, loss, ctx, workspace, workspace_bytes,
                             static_cast<hipStream_t>(stream));
 }
 

@@ -254,8 +254,9 @@ int fast_full_loss_bwd(const cp_head_desc &ds, const void *H, const void *F, con
 bool distill_on_matrix_cores(const cp_head_desc &ds);   // the fine-tuning loss's own path selector
 size_t distill_ctx_bytes(const cp_head_desc &ds);
 size_t distill_workspace_bytes(const cp_head_desc &ds, int op);
+bool distill_fwd_fits(const cp_head_desc &ds, size_t ws_bytes);     // whether the forward call takes a workspace of that size
 int distill_loss_fwd(const cp_head_desc &ds, const void *H, const void *W, const void *U, const void *G,
-                     const int32_t *X, const void *TZ, float beta, float disc, float *loss, void *ctx, void *ws,
+                     const int32_t *X, const void *TZ, float beta, float disc, float *loss, void *ctx, void *ws, size_t ws_bytes,
                      hipStream_t st);
 int distill_loss_bwd(const cp_head_desc &ds, const void *H, const void *W, const void *U, const void *G,
                      const int32_t *X, const void *TZ, const float *dloss, float scale, const void *ctx, float *dH,

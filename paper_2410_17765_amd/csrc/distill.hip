@@ -437,7 +437,7 @@ struct EpiDistillStats {
     }
 };
 
-// Third product (backward): dz = c1 P - c3 p^c rho + c2 1[v = x] in bf16, stored block by block (blocked64_index).
+// The product of the backward call: dz = c1 P - c3 p^c rho + c2 1[v = x] in bf16, stored block by block (blocked64_index).
 template <int R>
 struct EpiDzDistill {
     bf16_t *dZ;
@@ -798,14 +798,14 @@ DistillCtx distill_ctx(const cp_head_desc &ds)
 // d = 256 2752 / 2527; T = 2048, n = 2, d = 128 2243 / 2247; T = 1000, V = 128000, n = 2, r = 4, d = 512 3488 / 3042.
 bool stores_logits(const cp_head_desc &ds) { return !(ds.flags & (CP_HEAD_KEEP_LOGITS | CP_HEAD_MIN_WORKSPACE)); }
 
-// forward workspace: the training loss's, then {rhox [M], ce [T n], SK [M] float2} and z [rows of a chunk, Vp] fp32 or
+// forward workspace: the training loss's, then {rhox [M], ce [T n], SK [M] float2} and z [rows of a chunk, Vp] fp32 (store) or
 // part [M, parts] float2 (second product)
 struct DistillFwdWs {
     size_t rhox, ce, SK, part, z, total;
     int parts;
     long ldz;
 };
-DistillFwdWs distill_fwd_ws(const cp_head_desc &ds)
+DistillFwdWs distill_fwd_ws(const cp_head_desc &ds, bool store)
 {
     DistillFwdWs f;
     const size_t M = (size_t)ds.T * ds.n * ds.r, Tn = (size_t)ds.T * ds.n;
@@ -817,10 +817,16 @@ DistillFwdWs distill_fwd_ws(const cp_head_desc &ds)
     f.SK = take(M * 8);
     f.part = f.z = off;
     f.ldz = (long)round_up((size_t)ds.V, 64);
-    if (stores_logits(ds)) f.z = take(std::min(fast_stored_positions(ds) * ds.n * ds.r, M) * f.ldz * 4);
+    if (store) f.z = take(std::min(fast_stored_positions(ds) * ds.n * ds.r, M) * f.ldz * 4);
     else if (!(ds.flags & CP_HEAD_KEEP_LOGITS)) f.part = take(M * f.parts * sizeof(float2));
     f.total = off;
     return f;
+}
+// A workspace that the chunk does not fit but the second product does is taken too, as if no logits were to be stored: the
+// results are the same bits.
+bool distill_fwd_stores(const cp_head_desc &ds, size_t ws_bytes)
+{
+    return stores_logits(ds) && ws_bytes >= distill_fwd_ws(ds, true).total;
 }
 
 // backward workspace: the training loss's, then {rowinfo [M] float4, grp [T n] float4, dg [T r]}
@@ -911,14 +917,15 @@ void distill_kept_dz_launch(void *user, const bf16_t *, int Mc, int Mcp, size_t 
 }
 
 int mfma_distill_fwd(const cp_head_desc &ds, const void *H, const void *W, const void *Uv, const void *G,
-                     const int32_t *X, const void *TZv, float beta, float disc, float *loss, void *ctx, void *ws,
+                     const int32_t *X, const void *TZv, float beta, float disc, float *loss, void *ctx, void *ws, size_t ws_bytes,
                      hipStream_t st)
 {
     if (ds.T == 0) return CP_HEAD_OK;
     if (!fast_dims_fit(ds)) return CP_HEAD_ERR_UNSUPPORTED;         // before anything is launched
     const bf16_t *U = (const bf16_t *)Uv, *TZ = (const bf16_t *)TZv;
     const DistillCtx dc = distill_ctx(ds);
-    const DistillFwdWs f = distill_fwd_ws(ds);
+    const bool store = distill_fwd_stores(ds, ws_bytes);
+    const DistillFwdWs f = distill_fwd_ws(ds, store);
     const size_t T = (size_t)ds.T, M = T * ds.n * ds.r, Tn = T * ds.n;
     float2 *rowa = at<float2>(ctx, dc.rowa);
     float *c1 = at<float>(ctx, dc.c1), *c2 = at<float>(ctx, dc.c2), *c3 = at<float>(ctx, dc.c3);
@@ -928,7 +935,7 @@ int mfma_distill_fwd(const cp_head_desc &ds, const void *H, const void *W, const
     FastFwdBuffers fb;
 
     launch_teacher_lse(ds, Tn, TZ, tlse, st);
-    if (stores_logits(ds)) {
+    if (store) {
         StoredKlArgs args{&ds, X, TZ, tlse, rowa, SK, rhox, ce};
         FastStoredRows fn = ds.r == 1 ? stored_kl<1> : ds.r == 2 ? stored_kl<2> : ds.r == 4 ? stored_kl<4> : stored_kl<8>;
         const int rc = fast_fwd_rows_stored(ds, H, W, Uv, G, X, ctx, ws, at<float>(ws, f.z), f.ldz, fn, &args, &fb, st);
@@ -1198,17 +1205,24 @@ size_t distill_ctx_bytes(const cp_head_desc &ds) { return distill_ctx(without_ke
 size_t distill_workspace_bytes(const cp_head_desc &ds_in, int op)
 {
     const cp_head_desc ds = without_kept_logits(ds_in);
-    if (on_matrix_cores(ds)) return op == CP_HEAD_OP_DISTILL_FWD ? distill_fwd_ws(ds).total : distill_bwd_ws(ds).total;
+    if (on_matrix_cores(ds)) return op == CP_HEAD_OP_DISTILL_FWD ? distill_fwd_ws(ds, stores_logits(ds)).total : distill_bwd_ws(ds).total;
     return op == CP_HEAD_OP_DISTILL_FWD ? plain_fwd_ws(ds).total : plain_bwd_ws(ds).total;
 }
 
+bool distill_fwd_fits(const cp_head_desc &ds_in, size_t ws_bytes)
+{
+    const cp_head_desc ds = without_kept_logits(ds_in);
+    return ws_bytes >= distill_workspace_bytes(ds, CP_HEAD_OP_DISTILL_FWD) ||
+           (on_matrix_cores(ds) && ws_bytes >= distill_fwd_ws(ds, false).total);
+}
+
 int distill_loss_fwd(const cp_head_desc &ds_in, const void *H, const void *W, const void *U, const void *G,
-                     const int32_t *X, const void *TZ, float beta, float disc, float *loss, void *ctx, void *ws,
+                     const int32_t *X, const void *TZ, float beta, float disc, float *loss, void *ctx, void *ws, size_t ws_bytes,
                      hipStream_t st)
 {
     const cp_head_desc ds = without_kept_logits(ds_in);
     if (ds.T == 0) return CP_HEAD_OK;
-    if (on_matrix_cores(ds)) return mfma_distill_fwd(ds, H, W, U, G, X, TZ, beta, disc, loss, ctx, ws, st);
+    if (on_matrix_cores(ds)) return mfma_distill_fwd(ds, H, W, U, G, X, TZ, beta, disc, loss, ctx, ws, ws_bytes, st);
     if (ds.dtype == CP_HEAD_FP32)
         return plain_distill_fwd<float>(ds, H, W, U, G, X, (const float *)TZ, beta, disc, loss, ctx, ws, st);
     return plain_distill_fwd<bf16_t>(ds, H, W, U, G, X, (const bf16_t *)TZ, beta, disc, loss, ctx, ws, st);
