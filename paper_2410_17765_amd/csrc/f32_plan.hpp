@@ -23,7 +23,7 @@ struct F32Shape {
     long M, N, K;
     long batch = 1;
 };
-// The choice is the one with the least time in a model with measured constants: rounds of tiles over the compute units
+// The choice is the one with the least time in a model with measured constants (of K-steps of 32 for the 128-wide tile): rounds of tiles over the compute units
 // at the average cost of a tile, not less than the longest tile alone on its compute unit, plus, if a sum is split, the
 // pass that adds the parts.  Cycles per k-value of one tile, alone and with a second tile on the compute unit,
 // at 2.4 GHz: 128-wide 171 / 156, 64-wide 51 / 44, 32-wide 16 / 13.3 (at K = 4096, TFLOP/s on 128 and on 512 tiles: 59 / 125,
@@ -73,6 +73,25 @@ inline F32Plan f32_plan(long M, long N, long K, bool may_split, long batch = 1)
     F32Plan p;
     f32_plan(&q, 1, may_split, &p);
     return p;
+}
+
+// Whether a launch of 128-wide tiles whose operands are both K-contiguous takes K-steps of 16 instead of 32: three workgroups share a
+// compute unit then instead of two, so that a round is 768 tiles instead of 512.  `narrow` of the operands are bfloat16, whose rows
+// are then read 32 bytes at a time; `vec`: four elements per load.  Products of K = 512 (vec) and 511 or 445 (not), us, K-step 32 / 16:
+//   tiles           256        512        768       1024       1152       1280       1536       2048       2304       2560       3072       4032
+//   fp32        46 / 46    82 / 79  149 / 119  157 / 208  211 / 210  220 / 212  230 / 221  305 / 312  357 / 324  377 / 397  452 / 428  594 / 573
+//   not vec     47 / 46    88 / 80  158 / 122  167 / 213  201 / 216  231 / 219  243 / 230  323 / 320  375 / 335  405 / 390  482 / 443  632 / 587
+//   one bf16    49 / 52    79 / 82  147 / 119  153 / 215  217 / 217  218 / 220  223 / 227  295 / 320  359 / 334  365 / 413  438 / 443  580 / 604
+//   not vec     47 / 50    81 / 77  147 / 114  152 / 202  212 / 206  215 / 209  222 / 217  293 / 306  355 / 321  363 / 391  432 / 424  570 / 572
+//   both bf16   49 / 51    78 / 81  147 / 119  150 / 213  216 / 218  217 / 221  220 / 226  292 / 325  358 / 336  362 / 401  433 / 444  582 / 608
+// (K = 1024, fp32, 1088 to 1216 tiles: 359 to 367 / 394.)  Beyond a round the tiles that are left go to the compute units that are free
+// first, three or two at a time, so that a few of them cost as much as many; rounds have smeared out after five of 512.
+inline bool f32_short_steps(long tiles, int narrow, bool vec)
+{
+    const long by2 = 2 * ((tiles + 511) / 512), by3 = 3 * ((tiles + 767) / 768);        // rounds, in tiles of a compute unit
+    if (narrow == 2 || (narrow == 1 && vec)) return tiles > 512 && 21 * by3 < 20 * by2;
+    if (narrow == 0 && tiles > 2560) return true;
+    return by3 < by2 || (by3 == by2 && tiles > 1216) || (tiles <= 512 && (narrow == 0 || tiles > 256));
 }
 
 }  // namespace cph

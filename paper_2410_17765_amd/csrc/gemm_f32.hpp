@@ -32,8 +32,9 @@ struct F32Tile {
 };
 typedef F32Tile<128, 128, 2, 2, 1, 32> F32Large;
 // Both operands K-contiguous: a K-step of 16 lets a third workgroup share the compute unit, whose products fill more of the
-// others' gaps (z, dz and y of T = 500, d = 512, V = 8191, n = r = 4: 1474 -> 1371 us).  A K-major operand's fragments are four reads
-// each, so that the shorter K-step gains nothing there (dY and dU: 1132 -> 1147 us), nor in the 64-wide tile (125 -> 166 us).
+// others' gaps (z, dz and y of T = 500, d = 512, V = 8191, n = r = 4: 1474 -> 1371 us); where that pays: f32_short_steps.  A K-major
+// operand's fragments are four reads each, so that the shorter K-step gains nothing there (dY and dU: 1132 -> 1147 us), nor in
+// the 64-wide tile (125 -> 166 us).
 typedef F32Tile<128, 128, 2, 2, 1, 16> F32LargeContiguous;
 typedef F32Tile<64, 64, 2, 2, 1, 32> F32Mid;
 typedef F32Tile<32, 32, 1, 1, 4, 64> F32Small;
@@ -307,8 +308,8 @@ inline F32Problem f32_batch(F32Problem p, int batch, long stride)
     return p;
 }
 
-// Up to three problems in one launch (their tiles share the compute units: two workgroups of 59 % of the matrix cores'
-// rate each fill one another's gaps to 80 %); a problem with zero tiles is absent.
+// Up to three problems in one launch (their tiles share the compute units: two workgroups with K-steps of 32, each 59 % of the matrix
+// cores' rate alone, fill one another's gaps to 80 %, three with K-steps of 16 to 86 %); a problem with zero tiles is absent.
 template <class G1, class E1, class G2, class E2, class G3, class E3>
 __global__ void __launch_bounds__(kF32Threads, G1::PER_CU)
      k_gemm_f32(F32Problem p1, E1 e1, F32Problem p2, E2 e2, F32Problem p3, E3 e3)

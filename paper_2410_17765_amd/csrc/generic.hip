@@ -373,18 +373,20 @@ __global__ void __launch_bounds__(1024) k_lse_of_rows(size_t rows, int V, const 
     }
 }
 
-// ---- launches: the plan picks the tile
+// ---- launches: the plan picks the tile, and for two K-contiguous operands f32_short_steps its K-step
 template <bool CONTIGUOUS, typename F>
-void with_f32_tile(int kind, const F &f)
+void with_f32_tile(int kind, bool short_steps, const F &f)
 {
-    if (kind == kF32LargeTile) f(std::conditional_t<CONTIGUOUS, F32LargeContiguous, F32Large>{});
+    if (kind == kF32LargeTile && CONTIGUOUS && short_steps) f(std::conditional_t<CONTIGUOUS, F32LargeContiguous, F32Large>{});
+    else if (kind == kF32LargeTile) f(F32Large{});
     else if (kind == kF32MidTile) f(F32Mid{});
     else f(F32Small{});
 }
 template <typename TA, typename TB, bool AKM, bool BKM, class Epi>
 void launch_f32(const F32Problem &p, int kind, const Epi &e, hipStream_t st)
 {
-    with_f32_tile<!AKM && !BKM>(kind, [&](auto tile) {
+    const int narrow = (sizeof(TA) < 4) + (sizeof(TB) < 4);
+    with_f32_tile<!AKM && !BKM>(kind, f32_short_steps(p.tiles(), narrow, p.vec != 0), [&](auto tile) {
         k_gemm_f32<F32Gemm<decltype(tile), TA, TB, AKM, BKM>, Epi, NoF32Problem, NoEpi, NoF32Problem, NoEpi>
             <<<(unsigned)p.tiles(), kF32Threads, 0, st>>>(p, e, F32Problem{}, NoEpi{}, F32Problem{}, NoEpi{});
     });
@@ -403,7 +405,8 @@ void launch_f32_y(const cp_head_desc &ds, int heads, const TIn *H, const TIn *W,
     const F32Problem py = f32_problem<false, false>(H, d, W, d, T, cols, d, d, plan);
     F32Problem pg{};
     if (gate) pg = f32_problem<false, false>(H, d, G, d, T, ds.r, d, d, plan);
-    with_f32_tile<true>(plan.kind, [&](auto tile) {
+    const bool short_steps = f32_short_steps(py.tiles() + pg.tiles(), sizeof(TIn) < 4 ? 2 : 0, py.vec != 0);
+    with_f32_tile<true>(plan.kind, short_steps, [&](auto tile) {
         typedef F32Gemm<decltype(tile), TIn, TIn, false, false> Gm;
         // the few gate tiles first: they share the launch's first round
         k_gemm_f32<Gm, EpiF32Store, Gm, EpiF32Store, NoF32Problem, NoEpi><<<(unsigned)(py.tiles() + pg.tiles()), kF32Threads, 0, st>>>(
@@ -849,7 +852,7 @@ int bwd_from_dz_t(const cp_head_desc &ds, const TIn *H, const TIn *W, const TIn 
         const F32Problem py = f32_problem<false, true>((const float *)dZ, Vp, U, d, Mc, d, Vp, V, pl.chunk[0]);
         F32Problem pu{};
         if (dU) pu = f32_problem<true, true>((const float *)dZ, Vp, Y + m0 * d, d, V, d, Mc, Mc, pl.chunk[1]);
-        with_f32_tile<false>(pl.chunk[0].kind, [&](auto tile) {
+        with_f32_tile<false>(pl.chunk[0].kind, false, [&](auto tile) {
             typedef decltype(tile) Tile;
             k_gemm_f32<F32Gemm<Tile, float, TIn, false, true>, EpiF32Store, F32Gemm<Tile, float, float, true, true>, EpiF32Store,
                        NoF32Problem, NoEpi><<<(unsigned)(py.tiles() + pu.tiles()), kF32Threads, 0, st>>>(
@@ -867,7 +870,7 @@ int bwd_from_dz_t(const cp_head_desc &ds, const TIn *H, const TIn *W, const TIn 
     F32Problem pw{}, pg{};
     if (dW) pw = f32_problem<true, true>((const float *)dY, nrd, H, d, nrd, d, T, T, pl.weights[1]);
     if (dG) pg = f32_problem<true, true>(dg, ds.r, H, d, ds.r, d, T, T, pl.weights[2]);
-    with_f32_tile<false>(pl.weights[0].kind, [&](auto tile) {
+    with_f32_tile<false>(pl.weights[0].kind, false, [&](auto tile) {
         typedef decltype(tile) Tile;
         typedef F32Gemm<Tile, float, TIn, true, true> Gw;
         k_gemm_f32<F32Gemm<Tile, float, TIn, false, true>, EpiF32Dh<TIn>, Gw, EpiF32Store, Gw, EpiF32Store>
