@@ -1317,9 +1317,9 @@ constexpr int kSkinnyRows = CPH_SKINNY_ROWS;
 // reads.  The tiled main loop waits for a stage of LDS at every K-step, d / 64 times a memory latency, which the other
 // workgroups of a compute unit hide only where there are two on each (512 tiles of 256 columns); here a workgroup has
 // 16 columns of y, and eight or more workgroups, whose loads overlap, share a compute unit.
-// The four wavefronts share the contraction, two blocks of 64 columns in flight each (whole first-token calls on cold weights at
-// V = 32000, r = 8, one / two: T = 1, d = 4096 117.8 / 112.7 us, T = 4, d = 2048 55.8 / 54.8), and their partial products meet in LDS.
+// The four wavefronts share the contraction, AHEAD blocks of 64 columns in flight each, and their partial products meet in LDS.
 constexpr int kStreamRows = 16, kStreamWaves = 4, kStreamBlock = kStreamWaves * kWave;
+template <int AHEAD>
 __global__ void __launch_bounds__(kStreamBlock) k_stream_y(const bf16_t *__restrict__ H, int B, int d,
                                                            const bf16_t *__restrict__ W, int cols, bf16_t *__restrict__ Y,
                                                            GatePickSide side)
@@ -1335,7 +1335,7 @@ __global__ void __launch_bounds__(kStreamBlock) k_stream_y(const bf16_t *__restr
     const bf16_t *const ph[1] = {H + (size_t)min(row, B - 1) * d + q * 16};     // rows past the last one repeat it, not stored
     const bf16_t *pw = W + (size_t)(col0 + row) * d + q * 16;
     f32x4_t acc[1] = {{0.f, 0.f, 0.f, 0.f}};
-    tile16_products<kStreamWaves, 2>(pw, ph, d, wave, acc);
+    tile16_products<kStreamWaves, AHEAD>(pw, ph, d, wave, acc);
 #pragma unroll
     for (int v = 0; v < 4; ++v) sums[wave][tile16_row(v, lane)][row] = acc[0][v];
     __syncthreads();
@@ -1348,6 +1348,15 @@ __global__ void __launch_bounds__(kStreamBlock) k_stream_y(const bf16_t *__restr
 //   cols 65536 (d 4096): T = 1 182 / 211, T = 8 223 / 232, T = 16 256 / 238
 //   cols 98304 (d 4096): T = 1 228 / 246, T = 4 257 / 253, T = 16 323 / 261
 // The tiles catch up where they fill the chip and where the rows of H differ: each workgroup reads all of them from L2.
+// (Measured with one block in flight.)  Two in flight where fewer than two workgroups share a compute unit or the rows are long.  Draft calls at
+// V = 2000, us, one / two, on cold weights:
+//   T = 1: d 1536 cols 3072 26.3 / 25.2; d 4096 cols 4096 45.1 / 42.5; d 2560 cols 5120 36.1 / 35.1; d 2048 cols 8192 34.1 / 34.2, cols 32768 52.7 / 54.9;
+//     d 1024 cols 32768 37.6 / 37.6; d 1536 cols 24576 38.0 / 37.3; d 2560 cols 20480 49.9 / 48.2; d 3072 cols 24576 58.5 / 56.3; d 4096 cols 32768 87.1 / 83.0
+//   T = 4: d 4096 cols 4096 46.3 / 44.0; d 2048 cols 16384 50.0 / 51.1, cols 32768 76.3 / 78.1; d 4096 cols 32768 110.1 / 104.2
+//   T = 16: d 4096 cols 4096 49.0 / 47.1; d 1024 cols 32768 60.5 / 60.8; d 2048 cols 32768 97.7 / 101.8; d 3072 cols 24576 121.4 / 121.6
+// (the first-token call at T = 4, d 2048, cols 16384 by its vocabulary: V 2000 43.4 / 42.8 for two / one, V 32000 55.2 / 55.3) and on weights that the
+// caches hold: T = 1: d 2048 cols 32768 46.8 / 51.5; d 2560 cols 20480 42.8 / 42.0; d 4096 cols 32768 76.6 / 78.7.
+inline bool stream_y_two_ahead(int cols, int d) { return cols < 8192 || d > 2048; }
 inline bool stream_y(int B, int cols) { return B <= kStreamRows && (cols <= 32768 || (cols <= 65536 && B <= 8)); }
 
 // y = W_sa h for the first `heads` of the n r head matrices (bf16, rounded: part of the draft distribution's
@@ -1360,7 +1369,8 @@ inline void launch_y_with_gate(const char *name, const cp_head_desc &ds, const b
     const EpiStoreBf16 epi{Y, nullptr, (long)cols, B, cols};
     if (stream_y(B, cols)) {
         ProfileScope prof(name, 2.0 * (double)B * (double)cols * (double)d, st);
-        k_stream_y<<<side.blocks + cols / 16, kStreamBlock, 0, st>>>(H, B, d, W, cols, Y, side);
+        auto kernel = stream_y_two_ahead(cols, d) ? k_stream_y<2> : k_stream_y<1>;
+        kernel<<<side.blocks + cols / 16, kStreamBlock, 0, st>>>(H, B, d, W, cols, Y, side);
     } else if (B <= CfgSkinny::BM) launch_gemm_nt<CfgSkinny>(name, H, d, B, W, d, cols, d, epi, st, kGroupRowsWide, side);
     else launch_gemm_nt<Cfg>(name, H, d, B, W, d, cols, d, epi, st, kGroupRowsWide, side);
 }
