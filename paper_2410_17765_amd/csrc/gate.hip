@@ -269,15 +269,20 @@ void launch_gate_bf16(const cp_head_desc &ds, const bf16_t *H, const bf16_t *G, 
 }
 
 // The statistic in the same launch: each workgroup orders its caches before it counts as done, one after the other, so for few
-// workgroups only.  Whole calls, us, two launches / three: T = 300 (19 workgroups) 7.3 / 13.0, T = 2048 (128) 9.5 / 13.1, T = 4096 (256)
-// 20.4 / 16.1, T = 16384 (512) 75 / 34.7.
+// workgroups only.  Whole calls, us, two launches / three: T = 300 (19 workgroups) 7.3 / 13.0, T = 4096 (256) 20.4 / 16.1, T = 16384 (512) 75 / 34.7.
+// And only for calls that the host's launches bound, not the work of the counting kernel; calls after one another, by T d max(r, 8) / 2^20:
+//   r = 2: T 1024 d 2048 (16) 8.6 / 10.6, T 1024 d 3072 (24) 9.7 / 10.6, T 1536 d 4096 (48) 11.6 / 10.8, T 2048 d 4096 (64) 13.1 / 11.2
+//   r = 8: T 512 d 4096 (16) 11.1 / 11.2, T 1536 d 2048 (24) 9.8 / 10.5, T 1024 d 3072 (24) 10.5 / 10.5, T 2048 d 2048 (32) 10.7 / 10.5, T 2048 d 4096
+//   (64) 14.3 / 12.4;  r = 16: T 1024 d 2048 (32) 9.8 / 10.6, T 512 d 3072 (24) 10.9 / 10.9, T 2048 d 2048 (64) 11.7 / 10.5, T 2048 d 4096 (128) 15.2 / 13.6
+//   r = 17: T 512 d 4096 (34) 16.7 / 16.4, T 2048 d 2048 (68) 13.5 / 12.4;  r = 64: T 256 d 1024 (16) 11.5 / 11.6, T 2048 d 4096 (512) 27.6 / 26.7
 constexpr unsigned kAuxAlone = 128;
+constexpr size_t kAuxAloneWork = (size_t)24 << 20;
 bool launch_aux_argmax_bf16(const cp_head_desc &ds, const bf16_t *H, const bf16_t *G, unsigned long long *counts, float *laux, hipStream_t st)
 {
     const size_t T = (size_t)ds.T;
     // at most two workgroups per compute unit: each ends with up to r atomic additions to the same few counters
     const unsigned tiles = blocks_for(T, kRows), blocks = tiles < 512 ? tiles : 512;
-    const bool whole = blocks <= kAuxAlone;
+    const bool whole = blocks <= kAuxAlone && T * ds.d * (ds.r > 8 ? ds.r : 8) <= kAuxAloneWork;
     auto kernel = ds.r <= 16 ? (whole ? k_aux_argmax_bf16<1, true> : k_aux_argmax_bf16<1, false>)
                              : (whole ? k_aux_argmax_bf16<4, true> : k_aux_argmax_bf16<4, false>);
     kernel<<<blocks, kBlock, 0, st>>>(T, ds.d, ds.r, H, G, counts, laux);

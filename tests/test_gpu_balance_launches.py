@@ -1,11 +1,12 @@
-"""Counts and statistic of eq. 10 on both sides of the line at which the statistic gets a launch of its own (128 workgroups of
-16 positions), several calls on the same buffers: counts exactly those of the gate's arg-max, the statistic that of the counts."""
+"""Counts and statistic of eq. 10 on both sides of the lines at which the statistic gets a launch of its own (128 workgroups of
+16 positions; T d max(r, 8) = 24 * 2^20), several calls on the same buffers: counts exactly those of the gate's arg-max, the statistic that of the counts."""
 import pytest
 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("shape", [(1, 64, 3), (2048, 128, 8), (2049, 64, 8), (2050, 64, 17), (2000, 192, 64)], ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("shape", [(1, 64, 3), (2048, 128, 8), (2049, 64, 8), (2050, 64, 17), (2000, 192, 64), (1536, 2048, 8), (1537, 2048, 2), (1536, 1024, 16), (1537, 1024, 16),
+                                   (384, 1024, 64), (385, 1024, 64)], ids=lambda s: "x".join(map(str, s)))
 def test_counts_and_statistic(shape):
     import torch
     from paper_2410_17765_amd import binding
