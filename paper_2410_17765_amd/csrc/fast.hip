@@ -1524,10 +1524,15 @@ inline DraftWs draft_ws(const cp_head_desc &ds, bool sequential)
 //   B = 1, d = 512, r = 8: V = 4000 23.3 / 21.4, 32000 (4000 pairs, 0.5 M reads) 27.2 / 25.7, 128256 (16032 pairs) 43.6 / 44.7; r = 64, V = 32000
 //   (32000 pairs) 86.8 / 101;  B = 4, d = 1024, r = 8, V = 32000 (2.0 M) 37.8 / 37.3;  B = 17, r = 1: V = 32000 (1.1 M) 48.3 / 48.3, 50000 (2.6 M)
 //   52.6 / 53.2, 65000 (4.4 M) 58.4 / 60.4;  B = 64, r = 1: d = 1024, V = 32000 (4.0 M) 53.7 / 57.9, d = 64, V = 128256 (64 M) 40.3 / 75.9
-constexpr long kMixPairs = 4096, kMixReads = 1 << 21;
+// And the chain stands in front of every workgroup, so that there may not be many of them either, fewer with many experts.  d = 64, calls after one
+// another: r = 1: 2016 workgroups (B = 32, V = 16000) 14.2 / 12.7, 2048 (B = 256, V = 2000) 29.1 / 28.2, 4000 (B = 500, V = 2000) 31.1 / 31.7, 4032 (B = 64)
+//   17.7 / 18.3, 16000 (B = 500, V = 8000) 43.3 / 50.9, 32000 (B = 1000, V = 8000) 53.4 / 69.6;  r = 2: 2048 (B = 64, V = 8000) 24.9 / 24.0, 4032 28.2 / 28.5;
+//   r = 8: 1008 (B = 16, V = 16000) 28.5 / 27.2, 1024 (B = 128, V = 2000) 32.6 / 31.3, 2016 (B = 32, V = 16000) 36.2 / 36.7, 4096 (B = 128, V = 8000) 45.9 / 47.9
+constexpr long kMixPairs = 4096, kMixReads = 1 << 21, kMixGroups = 2048, kMixGroupsMany = 1024;
 inline bool mix_from_parts(long B, long V, long r, long parts)
 {
-    return r * parts <= kMixPairs && B * (long)blocks_for((size_t)V, kBlock) * r * parts <= kMixReads;
+    const long groups = B * (long)blocks_for((size_t)V, kBlock);
+    return r * parts <= kMixPairs && groups * r * parts <= kMixReads && groups <= (r <= 4 ? kMixGroups : kMixGroupsMany);
 }
 
 struct FirstTokenWs {
