@@ -791,6 +791,54 @@ __global__ void __launch_bounds__(kBlock) k_lse_from_parts(size_t rows, int part
     if (lane == 0) lse[row] = v;
 }
 
+// (max, sum of exp(z - max)) of one chunk of kStatCols columns of one row of stored fp32 logits
+// (row stride ld, a multiple of 4): the per-segment statistics of eq. 5 for logits that are stored.
+constexpr int kStatCols = 4096;
+__global__ void __launch_bounds__(kBlock) k_row_stats_f32(int V, size_t ld, int parts, const float *__restrict__ z,
+                                                          float2 *__restrict__ part)
+{
+    __shared__ float red_m[kBlock / kWave], red_l[kBlock / kWave];
+    const size_t row = blockIdx.x;
+    const int c0 = blockIdx.y * kStatCols;
+    const float *zr = z + row * ld;
+    float4 x[kStatCols / 4 / kBlock];
+    float mx = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < kStatCols / 4 / kBlock; ++i) {
+        const int c = c0 + (i * kBlock + threadIdx.x) * 4;
+        x[i] = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+        if (c + 3 < V) {
+            x[i] = *reinterpret_cast<const float4 *>(zr + c);
+        } else if (c < V) {
+            x[i].x = zr[c];
+            if (c + 1 < V) x[i].y = zr[c + 1];
+            if (c + 2 < V) x[i].z = zr[c + 2];
+        }
+        mx = fmaxf(fmaxf(mx, fmaxf(x[i].x, x[i].y)), fmaxf(x[i].z, x[i].w));
+    }
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    mx = wave_max(mx);
+    if (lane == 0) red_m[wave] = mx;
+    __syncthreads();
+    float Mx = red_m[0];
+#pragma unroll
+    for (int w = 1; w < kBlock / kWave; ++w) Mx = fmaxf(Mx, red_m[w]);
+    const float ref = (Mx == -INFINITY) ? 0.f : Mx;
+    float l = 0.f;
+#pragma unroll
+    for (int i = 0; i < kStatCols / 4 / kBlock; ++i)
+        l += __expf(x[i].x - ref) + __expf(x[i].y - ref) + __expf(x[i].z - ref) + __expf(x[i].w - ref);
+    l = wave_sum(l);
+    if (lane == 0) red_l[wave] = l;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        float L = 0.f;
+#pragma unroll
+        for (int w = 0; w < kBlock / kWave; ++w) L += red_l[w];
+        part[row * parts + blockIdx.y] = make_float2(Mx, L);        // as EpiRowStats leaves it: a NaN stays one
+    }
+}
+
 // logp[b, v] = logsumexp_a(log w_a + z[(b, a), v] - lse[(b, a)]) (eq. 11) for 256 tokens of one b, from the stored first-head logits and
 // the per-segment statistics of their rows: every workgroup forms the r log-normalisers by itself, which saves the call a launch.
 __global__ void __launch_bounds__(kBlock) k_first_token_from_parts(int V, int r, int parts, size_t ld, const float *__restrict__ z,
@@ -1535,6 +1583,20 @@ inline bool mix_from_parts(long B, long V, long r, long parts)
     return r * parts <= kMixPairs && groups * r * parts <= kMixReads && groups <= (r <= 4 ? kMixGroups : kMixGroupsMany);
 }
 
+// Whether the statistics of the stored logits come from a pass over them instead of from the epilogue of 256-row tiles.  The epilogue forms
+// them for all 256 rows of a tile, 7 us at the end of a launch of few tiles; the pass costs the logits' bytes once more.  Whole calls on cold weights, us,
+// epilogue / pass:
+//   72 rows (r = 8): d 64: V 8000 23.9 / 20.6, V 32000 27.8 / 25.9, V 128256 51.5 / 49.2; d 1024 V 128256 104.2 / 99.1; d 2048 V 128256 191.5 / 187.6
+//   128 rows (r = 8): d 512 V 8000 33.4 / 32.0, V 16000 35.5 / 33.9, V 128256 85.7 / 86.3;   256 rows: r = 1, d 512 V 8000 55.0 / 53.5;
+//     r = 8, d 64 V 8000 29.7 / 28.4, V 16000 33.6 / 34.2;   512 rows (r = 8): d 64 V 4000 30.6 / 29.0, V 8000 33.5 / 34.4
+//   1024 rows (r = 8): d 64 V 2000 31.2 / 29.5, V 16000 52.0 / 58.6;   2048 rows (r = 8): d 64 V 1000 35.5 / 33.8;   8000 rows (r = 8): d 64 V 300 42.3 / 46.2
+constexpr int kApartRows = 96, kApartMostRows = 2048;
+constexpr long kApartLogits = 5L << 19;
+inline bool stats_apart(int rows, int V)
+{
+    return rows > kSkinnyRows && (rows <= kApartRows || (rows <= kApartMostRows && (long)rows * V <= kApartLogits));
+}
+
 struct FirstTokenWs {
     size_t logw, Y, z, lse, part, total;
     size_t V4;
@@ -1992,15 +2054,22 @@ int fast_first_token(const cp_head_desc &ds, const void *Hv, const void *Wv, con
     bf16_t *Y = at<bf16_t>(ws, f.Y);
     // first head only: its matrices are the first r blocks of W, so y has rows (b, a); the gate (eq. 7) rides along
     launch_y_with_gate("first_gemm_y", ds, H, W, G, nullptr, Y, logw, nullptr, r, st);
-    // the r rows of logits per b are the output's own size: they are stored once (fp32), with their statistics, and read once
+    // the r rows of logits per b are the output's own size: they are stored once (fp32), with their statistics, and read once (twice: stats_apart)
     float2 *part = at<float2>(ws, f.part);
-    launch_z_stats("first_gemm_z", Y, d, rows, U, V, part, f.parts, z, (long)V4, st);
+    int parts = f.parts;
+    if (stats_apart(rows, V)) {
+        launch_gemm_nt<Cfg>("first_gemm_z", Y, d, rows, U, d, V, d, EpiStoreF32{z, (long)V4, rows, V4, 0}, st);
+        parts = (V + kStatCols - 1) / kStatCols;
+        k_row_stats_f32<<<dim3((unsigned)rows, (unsigned)parts), kBlock, 0, st>>>(V, (size_t)V4, parts, z, part);
+    } else {
+        launch_z_stats("first_gemm_z", Y, d, rows, U, V, part, parts, z, (long)V4, st);
+    }
     ProfileScope prof("first_mix", (double)rows * V * 4 + (double)B * V * 4, st);
-    if (mix_from_parts(B, V, r, f.parts)) {
-        k_first_token_from_parts<<<dim3((unsigned)B, blocks_for((size_t)V, kBlock)), kBlock, 0, st>>>(V, r, f.parts, (size_t)V4, z, part, logw,
+    if (mix_from_parts(B, V, r, parts)) {
+        k_first_token_from_parts<<<dim3((unsigned)B, blocks_for((size_t)V, kBlock)), kBlock, 0, st>>>(V, r, parts, (size_t)V4, z, part, logw,
                                                                                                      logp);
     } else {
-        k_lse_from_parts<<<blocks_for((size_t)rows, kBlock / kWave), kBlock, 0, st>>>((size_t)rows, f.parts, part, lse);
+        k_lse_from_parts<<<blocks_for((size_t)rows, kBlock / kWave), kBlock, 0, st>>>((size_t)rows, parts, part, lse);
         launch_first_token_mix(ds, z, (size_t)V4, lse, logw, logp, st);                     // eq. 11
     }
     return hipGetLastError() == hipSuccess ? CP_HEAD_OK : CP_HEAD_ERR_LAUNCH;
