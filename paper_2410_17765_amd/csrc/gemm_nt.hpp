@@ -309,9 +309,11 @@ __device__ __forceinline__ void gemm_nt_mainloop_direct(const GemmOperands &g, i
         // the two register files: several hundred per K-step where fragments are assembled from two 64-bit reads (K-major
         // operands) or the columns are walked in another order (z at d = 4096 93.5 -> 106 ms), and dozens in the 64-row tile.
         // The compiler still inserts the waits for the fragments' LDS reads (it sees the operands); what it cannot see
-        // is that the instruction is a matrix instruction: uses of one accumulator are 64 instructions apart here, and
-        // the wait states before the accumulators are read back are added after the loop (without them the epilogue
-        // read accumulators that lacked the last K-block's contribution).
+        // is that the instruction is a matrix instruction: uses of one accumulator are TM TN instructions apart here, 64 in
+        // the 256-row tile and 16 in the 64-row one, and the wait states before the accumulators are read back are added
+        // after the loop (without them the epilogue read accumulators that lacked the last K-block's contribution).
+        // This one takes four passes (16 cycles); even the result of one of eight may be read after 11 other instructions.
+        static_assert(TM * TN >= 12, "uses of an accumulator far enough apart for instructions without wait states");
         asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0"
                      : "+a"(acc[half * HA + i][j])
                      : "v"(Cfg::ROWS_IN_LANE ? fa[abuf][i] : fb[bbuf][j]), "v"(Cfg::ROWS_IN_LANE ? fb[bbuf][j] : fa[abuf][i]));
@@ -382,7 +384,7 @@ __device__ __forceinline__ void gemm_nt_mainloop_direct(const GemmOperands &g, i
         __builtin_amdgcn_s_waitcnt(0x0F70); /* vmcnt(0): tile kt+1 is complete in the other stage */ \
         __syncthreads();                                                                           \
         if (LOAD_AFTER) { /* the loads from here on are tile kt+2's */                             \
-            if (Cfg::AKM) advance_a();                                                      \
+            if (Cfg::AKM) advance_a();                                                             \
             if (Cfg::BKM) km_advance(walk_b);                                                      \
         }                                                                                          \
         CPH_PHASE16(1, 1, 1, reads3, TN + HA, NM, LOAD_AFTER, (KT_) + 2, cur, 0, NEARLY)           \
@@ -428,8 +430,7 @@ struct NoSideJob {
 // row / column of accumulator element v of block (i, j) for lane l, relative to the sub-tile origin
 __device__ __forceinline__ int acc_row(int i, int lane) { return i * 16 + (lane & 15); }
 __device__ __forceinline__ int acc_col(int j, int v, int lane) { return j * 16 + 4 * (lane >> 4) + v; }
-// the same for ROWS_IN_LANE
-__device__ __forceinline__ int acc_row_of_lane(int i, int v, int lane) { return i * 16 + 4 * (lane >> 4) + v; }
+// the column for ROWS_IN_LANE
 __device__ __forceinline__ int acc_col_of_lane(int j, int lane) { return j * 16 + (lane & 15); }
 
 // Epilogues whose result is a plain function of the sum over K (kSplittable) may have the launch's last round split along

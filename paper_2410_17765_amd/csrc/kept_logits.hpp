@@ -18,10 +18,7 @@ namespace cph {
 constexpr int kKeptTile = 128;      // rows and columns of a workgroup's tile; its columns are one block of `part`
 constexpr int kKeptBlock = 256;
 
-// 16-bit float (IEEE binary16) bit patterns, round to nearest even
-__device__ __forceinline__ uint16_t f32_to_f16_bits(float f) { return __builtin_bit_cast(uint16_t, (_Float16)f); }
-
-// two fp32 values -> two 16-bit floats in one register (a in the low half)
+// two fp32 values -> two 16-bit floats (IEEE binary16, round to nearest even) in one register (a in the low half)
 __device__ __forceinline__ uint32_t f32x2_to_f16x2(float a, float b)
 {
     typedef _Float16 f16x2_t __attribute__((ext_vector_type(2)));

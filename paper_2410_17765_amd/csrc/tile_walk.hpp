@@ -89,8 +89,9 @@ CPH_HD void split_item(const SplitPlan &p, int i, int k_steps, int &bid, int &pa
 }
 
 // Element (row, col) of a bf16 matrix stored block by block, [rows / 256][ld / 64][256][64] (ld a multiple of 64, the
-// rows allocated up to a multiple of 256): the layout in which the main loop reads an operand flagged ABL / BBL, one
-// K-step of a tile being 32 KB of consecutive memory.
+// rows allocated up to a multiple of 256): the layout of the chunk's logit gradients, which two products read as their first
+// operand.  Where its rows are the product's rows (ABL), a K-step of a tile is a block, 32 KB of consecutive memory; where they are
+// what the product contracts over (ABL and AKM), a K-step is 64 rows of the tile's four blocks, 8 KB of consecutive memory of each.
 CPH_HD size_t blocked64_index(size_t row, int col, long ld)
 {
     return ((row >> 8) * (size_t)(ld >> 6) + (size_t)(col >> 6)) * 16384 + (row & 255) * 64 + (size_t)(col & 63);
