@@ -66,9 +66,9 @@ def test_gate_gradient_workspace(lib):
     sizes = [binding.cp_head_workspace_bytes(binding.make_desc(16384, 4096, 512, 1, r, binding.BF16), binding.OP_LOSS_BWD) for r in (63, 64)]
     per_expert = sizes[1] - sizes[0]
     # the other buffers that grow with r, at their size per expert: {lse, coefficient, target}, dg, dY, W^T (and the dz rows of
-    # one chunk, which holds them all here: dz, its transpose, y^T)
+    # one chunk, which holds them all here: dz, y^T)
     T, d, V = 16384, 4096, 512
-    others = T * 16 + T * 4 + T * d * 2 + d * d * 2 + 2 * T * V * 2 + d * T * 2
+    others = T * 16 + T * 4 + T * d * 2 + d * d * 2 + T * V * 2 + d * T * 2
     assert per_expert - others <= T // 512 * d * 4 + 65536
 
 
